@@ -126,7 +126,7 @@ typedef struct {
  *                     below it is one fixed linear map of that level's right-hand side (Alg.
  *                     alg:tg applied recursively, starting from x = 0); it is computed at setup
  *                     by running that part of the V-cycle on the columns of the identity
- *                     (the batched V-cycle of eamg_solve_batch, 64 columns per pass) and
+ *                     (up to 8192 columns per pass, fewer where memory is short) and
  *                     applied as one dense product per V-cycle (an FP64 matrix with FP64
  *                     accumulation, in either V-cycle precision unless dense_tail_fp32).  The
  *                     operator is symmetric, so the product reads only the 128 x 128 tiles of
@@ -135,7 +135,8 @@ typedef struct {
  *                     tail when that level is the coarsest or no level qualifies.  Memory: about
  *                     1.5 ld^2 doubles (the full matrix, kept for the block panels, and the upper
  *                     tiles; + 0.5 ld^2 floats with dense_tail_fp32), ld = the tail's dofs
- *                     rounded up to 128.
+ *                     rounded up to 128; during setup also work panels of about 2 ld doubles per
+ *                     column of a pass.
  *  dense_tail_fp32    0: the FP32 V-cycle applies the dense tail, which holds the coarsest
  *                     level's inverse, from its FP64 matrix with FP64 accumulation (FP32 vectors
  *                     in and out), as it applies the coarsest inverse without a tail (default).

@@ -16,7 +16,7 @@ ARCH = "gfx950"
 HOST_SOURCES = ["coarsen.cpp", "structure.cpp", "api.cpp", "batch.cpp", "gnn_api.cpp",
                 "staging.cpp", "fused.cpp"]
 HIP_SOURCES = ["kernels.hip", "panel.hip", "gnn.hip", "coarse.hip", "criteria.hip", "noalloc.hip",
-               "fused.hip"]
+               "fused.hip", "wide.hip"]
 # the criteria must round like the host code (no fused multiply-add)
 FILE_FLAGS = {"criteria.hip": ["-ffp-contract=off"]}
 

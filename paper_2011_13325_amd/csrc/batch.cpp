@@ -11,6 +11,7 @@
 
 #include "hierarchy.hpp"
 #include "panel.hpp"
+#include "wide.hpp"
 
 namespace eamg {
 
@@ -361,44 +362,78 @@ double time_ms(hipStream_t s, int reps, F &&f) {
 
 }  // namespace
 
-// Panel launch shapes measured on the hierarchy's own matrices for K columns (FP64 V-cycle
-// kernels): per level, the sweep + upper-residual sequence and each transfer with one or four
-// wavefronts per row; the faster is kept in SolveMat::panel_waves.  Returns the summed time of the
-// tuned kernels before / after (ms).
+namespace {
+
+// Work panels of a level below the tail's first: right-hand side, solution and residual.
+struct WideLevel {
+  WidePanel b, x, r;
+};
+
+// x = V_l(b) for K columns on level l (b.p == nullptr: columns j0 .. j0 + K - 1 of the identity,
+// and x is zero on entry).  The forward sweep of an identity right-hand side stays at or below
+// the diagonal, so each colour takes only the columns that reach its rows; r is zeroed for the
+// rest.
+void wide_vcycle(eamg_hierarchy *h, std::vector<WideLevel> &w, size_t l, WidePanel b, int j0, WidePanel x,
+                 int K, hipStream_t s) {
+  Level &L = h->lv[l];
+  if (l + 1 == h->lv.size()) {
+    hip_check(launch_wide_dense(h->nL, h->ldL, h->Ainv, K, b, x, s), "wide coarsest");
+    return;
+  }
+  const WidePanel r = w[l].r;
+  if (!b.p) hip_check(launch_fill(level_dofs(L) * r.ld, 0.0, r.p, s), "fill");
+  for (int c = 0; c < L.ncolors; ++c) {
+    const int r0 = L.color_ptr[c], r1 = L.color_ptr[c + 1];
+    const int64_t reach = int64_t(r1) * L.bs - j0;
+    const int Kc = b.p ? K : int(std::max<int64_t>(0, std::min<int64_t>(K, (reach + 1) / 2 * 2)));
+    hip_check(launch_wide_fwd(L.Am, L.Dinv, r0, r1, Kc, b, j0, x, r, s), "wide fwd");
+  }
+  hip_check(launch_wide_resid(L.Am, K, x, r, s), "wide resid");
+  WideLevel &C = w[l + 1];
+  hip_check(launch_wide_rect(L.Rm, K, r, C.b, false, s), "wide restrict");
+  wide_vcycle(h, w, l + 1, C.b, 0, C.x, K, s);
+  hip_check(launch_wide_rect(L.Pm, K, C.x, x, true, s), "wide prolong");
+  for (int c = L.ncolors - 1; c >= 0; --c)
+    hip_check(launch_wide_bwd(L.Am, L.Dinv, L.color_ptr[c], L.color_ptr[c + 1], K, b, j0, x, s), "wide bwd");
+}
+
+}  // namespace
+
 DenseTail make_dense_tail(eamg_hierarchy *h, size_t t, DevArena &out, hipStream_t s) {
   if (t == 0 || t + 1 >= h->lv.size()) fail(EAMG_ERR_INVALID_ARG, "dense tail must start above the coarsest level, below the finest");
   const Level &Lt = h->lv[t];
   const int n = Lt.n * Lt.bs;
   if (n > kMaxCoarsestDofs) fail(EAMG_ERR_INVALID_ARG, "dense tail too large");
-  // a workspace of 64-column panels for levels t .. coarsest only (the batched solve's own is
-  // sized for level 0)
-  constexpr int K = 64;
-  BatchWork w;
-  w.K = K;
-  w.dense = w.arena.alloc<double>(std::max<size_t>(1, dense_panel_work_doubles(h->nL, K)));
-  const size_t nl = h->lv.size();
-  w.vx[0].assign(nl, nullptr);
-  w.vb[0].assign(nl, nullptr);
-  w.vr[0].assign(nl, nullptr);
-  for (size_t l = t; l < nl; ++l) {
-    const size_t nd = size_t(level_dofs(h->lv[l])) * K;
-    w.vx[0][l] = w.arena.alloc<double>(nd);
-    w.vb[0][l] = w.arena.alloc<double>(nd);
-    if (l + 1 < nl) w.vr[0][l] = w.arena.alloc<double>(nd);
-  }
-  w.have[0] = true;
+  // columns per pass: few, wide passes fill the chip on levels of a few dozen rows per colour;
+  // kWideCols bounds the residual panel to half of the largest tail matrix.  Each pass's solution
+  // panel is its columns of T itself.
+  constexpr int kWideCols = 8192;
   const int ld = dense_ld(n);
   double *T = out.alloc<double>(size_t(ld) * ld);
-  hip_check(launch_fill(int64_t(ld) * ld, 0.0, T, s), "fill");
-  double *B = vp<double>(w.vb[0][t]), *X = vp<double>(w.vx[0][t]);
-  const bool prof = h->prof_on;
-  h->prof_on = false;
-  for (int j0 = 0; j0 < n; j0 += K) {
-    hip_check(launch_identity_panel(n, K, j0, B, s), "identity panel");
-    pvcycle_t<double>(h, &w, t, B, X, s);
-    hip_check(launch_scatter_panel(n, K, j0, std::min(K, n - j0), X, ld, T, s), "scatter panel");
+  int K = std::min(ld, kWideCols);
+  std::unique_ptr<DevArena> work;
+  std::vector<WideLevel> w(h->lv.size());
+  for (;; K = (K / 2 + 1) / 2 * 2) {
+    // narrower passes where the panels do not fit in the free memory
+    work = std::make_unique<DevArena>();
+    try {
+      for (size_t l = t; l < h->lv.size(); ++l) {
+        auto panel = [&] { return WidePanel{work->alloc<double>(size_t(level_dofs(h->lv[l])) * K), K}; };
+        if (l > t) {
+          w[l].b = panel();
+          w[l].x = panel();
+        }
+        if (l + 1 < h->lv.size()) w[l].r = panel();
+      }
+      break;
+    } catch (const Failure &e) {
+      if (e.code != EAMG_ERR_OOM || K <= 128) throw;
+      (void)hipGetLastError();
+    }
   }
-  h->prof_on = prof;
+  hip_check(launch_fill(int64_t(ld) * ld, 0.0, T, s), "fill");
+  for (int j0 = 0; j0 < n; j0 += K)
+    wide_vcycle(h, w, t, WidePanel{}, j0, WidePanel{T + j0, ld}, std::min(K, (n - j0 + 1) / 2 * 2), s);
   DenseTail d;
   d.T = T;
   d.n = n;
@@ -423,6 +458,10 @@ void build_dense_tail(eamg_hierarchy *h, size_t t, hipStream_t s) {
   h->tail_level = int(t);
 }
 
+// Panel launch shapes measured on the hierarchy's own matrices for K columns (FP64 V-cycle
+// kernels): per level, the sweep + upper-residual sequence and each transfer with one or four
+// wavefronts per row; the faster is kept in SolveMat::panel_waves.  Returns the summed time of the
+// tuned kernels before / after (ms).
 std::pair<double, double> tune_panels(eamg_hierarchy *h, int K, hipStream_t s) {
   BatchWork *w = ensure_work(h, K, false);
   const int reps = 5;

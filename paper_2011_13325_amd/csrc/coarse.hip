@@ -393,25 +393,6 @@ __global__ void k_dense_symv_sum_multi(int nparts, const SymPart *__restrict__ p
   y[P.off + i] = TV(symv_row_sum(P.nb, i, W + P.woff));
 }
 
-// Panel of K columns (entry (dof, k) at dof * K + k) holding columns j0 .. j0 + K - 1 of the
-// n x n identity (zero where j0 + k >= n).
-__global__ void k_identity_panel(int n, int K, int j0, double *__restrict__ B) {
-  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= int64_t(n) * K) return;
-  const int d = int(t / K), k = int(t % K);
-  B[t] = (d == j0 + k) ? 1.0 : 0.0;
-}
-
-// Columns j0 .. j0 + ncols - 1 of the row-major matrix D (leading dimension ld, first n rows)
-// := the first ncols columns of the panel X (n x K).
-__global__ void k_scatter_panel(int n, int K, int j0, int ncols, const double *__restrict__ X, int ld,
-                                double *__restrict__ D) {
-  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= int64_t(n) * ncols) return;
-  const int d = int(t / ncols), k = int(t % ncols);
-  D[size_t(d) * ld + j0 + k] = X[size_t(d) * K + k];
-}
-
 // Y = D X for a panel of K columns on the matrix cores (v_mfma_f64_16x16x4): a dense FP64
 // contraction, n x n by n x K.  One wavefront per 16-row tile of D and slice of the inner
 // dimension (the slices give the chip enough wavefronts).  The inner indices go in blocks of 16:
@@ -522,23 +503,6 @@ hipError_t launch_dense_gemv(int n, int ld, const double *D, const T *x, T *y, h
   if (n == 0) return hipSuccess;
   if (ld < n || ld % 128 != 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_dense_gemv<T>, dim3(cdiv(n, kThreads / 64)), dim3(kThreads), 0, s, n, ld, D, x, y);
-  return hipGetLastError();
-}
-
-hipError_t launch_identity_panel(int n, int K, int j0, double *B, hipStream_t s) {
-  const int64_t nk = int64_t(n) * K;
-  if (nk == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_identity_panel, dim3(cdiv(nk, kThreads)), dim3(kThreads), 0, s, n, K, j0, B);
-  return hipGetLastError();
-}
-
-hipError_t launch_scatter_panel(int n, int K, int j0, int ncols, const double *X, int ld, double *D,
-                                hipStream_t s) {
-  if (ncols < 1 || ncols > K || j0 + ncols > ld) return hipErrorInvalidValue;
-  const int64_t nk = int64_t(n) * ncols;
-  if (nk == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_scatter_panel, dim3(cdiv(nk, kThreads)), dim3(kThreads), 0, s, n, K, j0, ncols,
-                     X, ld, D);
   return hipGetLastError();
 }
 

@@ -88,14 +88,6 @@ template <class TM, class TV>
 hipError_t launch_dense_symv_multi(int nparts, const SymPart *parts, int tiles, int rows,
                                    const double *active, const TV *x, TV *y, double *W, hipStream_t s);
 
-// B (n x K panel, entry (dof, k) at dof * K + k) := columns j0 .. j0 + K - 1 of the identity.
-hipError_t launch_identity_panel(int n, int K, int j0, double *B, hipStream_t s);
-
-// Columns j0 .. j0 + ncols - 1 (ncols <= K) of the row-major D (leading dimension ld) := the
-// first ncols columns of the n x K panel X.
-hipError_t launch_scatter_panel(int n, int K, int j0, int ncols, const double *X, int ld, double *D,
-                                hipStream_t s);
-
 // Y = D X for a panel of K columns (K a power of two in [1, 64]; entry (dof, k) at dof * K + k),
 // on the matrix cores in FP64, summed over dense_panel_splits(n) slices of the inner dimension
 // through `work` (device, dense_panel_work_doubles(n, K) doubles); deterministic.

@@ -259,7 +259,7 @@ std::pair<double, double> tune_panels(eamg_hierarchy *h, int K, hipStream_t s);
 void vcycle_staged(eamg_hierarchy *h, const double *r_dev, double *z_dev, bool f32, double *rp,
                    double *zp, hipStream_t s);
 // The V-cycle on levels t .. coarsest of h as a dense matrix in the colour-major numbering of
-// level t, from the batched V-cycle applied to the columns of the identity: FP64, row-major, ld a
+// level t, from the V-cycle applied to wide panels of the identity's columns: FP64, row-major, ld a
 // multiple of 128, zero padding, allocated in `out`.
 struct DenseTail {
   double *T = nullptr;
