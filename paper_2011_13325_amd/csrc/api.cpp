@@ -339,10 +339,112 @@ void level_shapes(Level &L, const Pattern &Ap, const std::vector<int> &dg) {
   }, 1);
 }
 
+void build_sweep_stages(DevArena &ar, Level &L, const Pattern &Ap, const std::vector<int> &dg, bool f32,
+                        hipStream_t s) {
+  PhaseTimer tp;
+  const SweepPlan pl = plan_sweeps(Ap, dg, L.color_ptr, L.ncolors, L.bs);
+  tp.mark("layout: sweep plan");
+  const int ns = int(pl.cut.size()) - 1, bs = L.bs;
+  L.cut = pl.cut;
+  for (auto *v : {&L.sh_rf, &L.sh_rb, &L.sh_sf, &L.sh_sb}) v->assign(size_t(ns), LaunchShape());
+  L.gs_f.assign(size_t(ns), 0);
+  L.gs_b.assign(size_t(ns), 0);
+  if (!pl.grouped()) return;
+  std::vector<int64_t> unused;
+  const Pattern Sb = transpose_pattern(pl.S, unused);
+  // lanes per row of each group's S, and what its launches stream
+  std::vector<int> mark(size_t(L.n), -1);
+  int stamp = 0;
+  auto shape = [&](int k, const Pattern &M, auto &&lo, auto &&hi) {
+    LaunchShape sh;
+    sh.rows = L.row1(k) - L.row0(k);
+    ++stamp;
+    for (int i = L.row0(k); i < L.row1(k); ++i) {
+      const int64_t a = lo(i), b = hi(i);
+      sh.blocks += double(b - a);
+      for (int64_t q = a; q < b; ++q)
+        if (mark[size_t(M.col[size_t(q)])] != stamp) {
+          mark[size_t(M.col[size_t(q)])] = stamp;
+          sh.uniq += 1.0;
+        }
+    }
+    return sh;
+  };
+  auto lanes = [](const LaunchShape &sh) {
+    return sh.blocks > kWideRowBlocks * sh.rows ? kBlock : std::max(8, pick_group(int64_t(sh.blocks), int(sh.rows)));
+  };
+  for (int k = 0; k < ns; ++k) {
+    if (!L.is_group(k)) continue;
+    L.sh_rf[size_t(k)] = shape(k, Ap, [&](int i) { return Ap.rp[size_t(i)]; }, [&](int i) { return pl.pre[size_t(i)]; });
+    L.sh_rb[size_t(k)] = shape(k, Ap, [&](int i) { return Ap.rp[size_t(i)]; }, [&](int i) { return Ap.rp[size_t(i) + 1]; });
+    L.sh_sf[size_t(k)] = shape(k, pl.S, [&](int i) { return pl.S.rp[size_t(i)]; }, [&](int i) { return pl.S.rp[size_t(i) + 1]; });
+    L.sh_sb[size_t(k)] = shape(k, Sb, [&](int i) { return Sb.rp[size_t(i)]; }, [&](int i) { return Sb.rp[size_t(i) + 1]; });
+    L.gs_f[size_t(k)] = lanes(L.sh_sf[size_t(k)]);
+    L.gs_b[size_t(k)] = lanes(L.sh_sb[size_t(k)]);
+  }
+  // positions of the rows' couplings inside their groups, in the whole matrix and in its lower part
+  std::vector<int> right(size_t(L.n)), lo_end(size_t(L.n));
+  int64_t lo = 0;
+  for (int i = 0; i < L.n; ++i) {
+    right[size_t(i)] = dg[size_t(i)] + 1;
+    lo_end[size_t(i)] = int(lo + (pl.pre[size_t(i)] - Ap.rp[size_t(i)]));
+    lo += dg[size_t(i)] - Ap.rp[size_t(i)];
+  }
+  L.lo_end = ar.upload(lo_end, s);
+  int *pre_d = ar.upload(pl.pre, s), *post_d = ar.upload(pl.post, s), *right_d = ar.upload(right, s);
+  std::vector<int> order, rank_ptr(size_t(pl.max_rank) + 2, 0);
+  for (int r : pl.rank)
+    if (r >= 0) ++rank_ptr[size_t(r) + 1];
+  for (int r = 0; r <= pl.max_rank; ++r) rank_ptr[size_t(r) + 1] += rank_ptr[size_t(r)];
+  order.resize(size_t(rank_ptr.back()));
+  std::vector<int> fill(rank_ptr.begin(), rank_ptr.end() - 1);
+  for (int i = 0; i < L.n; ++i)
+    if (pl.rank[size_t(i)] >= 0) order[size_t(fill[size_t(pl.rank[size_t(i)])]++)] = i;
+  int *order_d = ar.upload(order, s);
+  auto matrix = [&](const Pattern &P, bool fwd) {
+    SolveMat M;
+    M.n_rows = M.n_cols = L.n;
+    M.br = M.bc = bs;
+    M.nnz = P.nnz();
+    M.rp = ar.upload(to_i32(P.rp), s);
+    M.col = ar.upload(P.col, s);
+    double *v = ar.alloc<double>(size_t(M.nnz) * bs * bs);
+    // the rows of a rank need those of every rank nearer their group's first (last) colour
+    for (int t = 0; t <= pl.max_rank; ++t) {
+      const int r = fwd ? t : pl.max_rank - t;
+      hip_check(launch_group_fill(rank_ptr[size_t(r) + 1] - rank_ptr[size_t(r)], order_d + rank_ptr[size_t(r)], bs,
+                                  fwd ? pre_d : right_d, fwd ? L.Am.diag : post_d, L.Am.col, L.Am.val,
+                                  L.Dinv, M.rp, M.col, v, s),
+                "group fill");
+    }
+    M.val = v;
+    if (f32) {
+      float *v32 = ar.alloc<float>(size_t(M.nnz) * bs * bs);
+      hip_check(launch_convert<double, float>(M.nnz * bs * bs, v, v32, s), "convert");
+      M.val32 = v32;
+    }
+    return M;
+  };
+  L.Sf = matrix(pl.S, true);
+  L.Sb = matrix(Sb, false);
+  L.u = ar.alloc<double>(size_t(L.n) * bs);
+  if (f32) L.u32 = ar.alloc<float>(size_t(L.n) * bs);
+  hip_check(hipStreamSynchronize(s), "sync");
+  for (int *p : {pre_d, post_d, right_d, order_d}) ar.release(p);
+}
+
 namespace {
 
 static_assert(std::is_nothrow_move_constructible<Level>::value,
               "levels must move without copying their patterns");
+
+// Level the dense V-cycle tail starts on, 0 if there is none.
+size_t tail_start(const eamg_hierarchy *h) {
+  if (h->prm.dense_tail_dofs > 0)
+    for (size_t l = 1; l + 1 < h->lv.size(); ++l)
+      if (int64_t(h->lv[l].n) * h->lv[l].bs <= h->prm.dense_tail_dofs) return l;
+  return 0;
+}
 
 void build_level_layout(eamg_hierarchy *h, size_t l, hipStream_t s) {
   Level &L = h->lv[l];
@@ -410,6 +512,10 @@ void build_level_layout(eamg_hierarchy *h, size_t l, hipStream_t s) {
   }
   hip_check(hipStreamSynchronize(s), "sync");
   ar.release(Dn);
+  // no sweeps below the dense tail's first level
+  const size_t t = tail_start(h);
+  if (t == 0 || l < t) build_sweep_stages(ar, L, Ap, dg, f32, s);
+  tl.mark("layout: sweep stages");
   // transfers: fine rows colour-major, coarse columns in the coarse level's colour-major order
   const Level &C = h->lv[l + 1];
   std::vector<int64_t> srcP;
@@ -496,6 +602,47 @@ hipError_t resid_update(const Level &L, const T *x, T *r, hipStream_t s) {
   return hipSuccess;
 }
 
+// Stage k of the forward and of the backward sweep of level L.
+template <class T>
+hipError_t fwd_stage(Level &L, int k, const T *b, T *x, T *r, hipStream_t s) {
+  const LevelBufs<T> B = bufs<T>(L);
+  const SolveMat A = L.fwd_mat(k);
+  if (!L.is_group(k)) return launch_gs_fwd<T>(A, B.Dinv, L.row0(k), L.row1(k), b, x, r, s);
+  const T *u = b;   // the first group has nothing before it
+  if (k > 0) {
+    const hipError_t e = launch_group_rhs<T>(A, L.lo_end, L.row0(k), L.row1(k), b, x, B.u, s);
+    if (e != hipSuccess) return e;
+    u = B.u;
+  }
+  SolveMat S = L.Sf;
+  S.group = L.gs_f[size_t(k)];
+  return launch_group_fwd<T>(A, S, B.Dinv, L.row0(k), L.row1(k), u, x, r, s);
+}
+template <class T>
+hipError_t bwd_stage(Level &L, int k, const T *b, T *x, hipStream_t s) {
+  const LevelBufs<T> B = bufs<T>(L);
+  const SolveMat A = L.bwd_mat(k);
+  if (!L.is_group(k)) return launch_gs_bwd<T>(A, B.Dinv, L.row0(k), L.row1(k), b, x, s);
+  const hipError_t e = launch_group_rhs<T>(A, nullptr, L.row0(k), L.row1(k), b, x, B.u, s);
+  if (e != hipSuccess) return e;
+  SolveMat S = L.Sb;
+  S.group = L.gs_b[size_t(k)];
+  return launch_group_bwd<T>(S, B.Dinv, L.row0(k), L.row1(k), B.u, x, s);
+}
+
+// Launches and algorithmic bytes (values of vs bytes) of stage k.
+int stage_launches(const Level &L, int k, bool fwd) { return !L.is_group(k) || (fwd && k == 0) ? 1 : 2; }
+double stage_bytes(const Level &L, int k, bool fwd, double vs) {
+  const int bs = L.bs;
+  const LaunchKind kind = fwd ? LK_GS_FWD : LK_GS_BWD;
+  if (!L.is_group(k)) {
+    const int c = L.cut[size_t(k)];
+    return launch_bytes((fwd ? L.sh_fwd : L.sh_bwd)[size_t(c)], kind, bs, bs, vs, 1);
+  }
+  const double rhs = launch_bytes((fwd ? L.sh_rf : L.sh_rb)[size_t(k)], LK_RESID, bs, bs, vs, 1);
+  return (fwd && k == 0 ? 0.0 : rhs) + launch_bytes((fwd ? L.sh_sf : L.sh_sb)[size_t(k)], kind, bs, bs, vs, 1);
+}
+
 // Algorithmic bytes of one dense-tail apply: the packed upper tiles (FP32 or FP64), both passes
 // over the partial sums, and x and y.
 double tail_apply_bytes(const eamg_hierarchy *h, bool fp32_matrix, size_t vec_bytes) {
@@ -563,24 +710,27 @@ void vcycle_t(eamg_hierarchy *h, size_t l, const T *b, T *x, hipStream_t s) {
   const LevelBufs<T> B = bufs<T>(L);
   const int bs = L.bs;
   const double vs = sizeof(T);
+  const int ns = L.stages();
   double fwd_bytes = 0.0, bwd_bytes = 0.0;
-  for (int c = 0; c < L.ncolors; ++c) {
-    fwd_bytes += launch_bytes(L.sh_fwd[c], LK_GS_FWD, bs, bs, vs, 1);
-    bwd_bytes += launch_bytes(L.sh_bwd[c], LK_GS_BWD, bs, bs, vs, 1);
+  int fwd_n = 0, bwd_n = 0;
+  for (int k = 0; k < ns; ++k) {
+    fwd_bytes += stage_bytes(L, k, true, vs);
+    bwd_bytes += stage_bytes(L, k, false, vs);
+    fwd_n += stage_launches(L, k, true);
+    bwd_n += stage_launches(L, k, false);
   }
   const std::string gs = "k_gs_color<" + ty + ", " + std::to_string(bs);
-  // the colours of a sweep are back-to-back launches of one kernel: one profiler record (events
-  // per launch would add their own dispatch to every launch)
+  // the stages of a sweep are back-to-back launches: one profiler record (events per launch would
+  // add their own dispatch to every launch)
   if (h->prof_colours) {
-    for (int c = 0; c < L.ncolors; ++c)
-      timed(h, "gs_fwd", lvname(h, l, "c" + std::to_string(c) + " " + gs + ", true>"),
-            launch_bytes(L.sh_fwd[c], LK_GS_FWD, bs, bs, vs, 1), s, [&] {
-              return launch_gs_fwd<T>(L.fwd_mat(c), B.Dinv, L.color_ptr[c], L.color_ptr[c + 1], b, x, B.r, s);
-            });
+    for (int k = 0; k < ns; ++k)
+      timed_n(h, "gs_fwd", lvname(h, l, "c" + std::to_string(L.cut[size_t(k)]) + " " + gs + ", true>"),
+              stage_bytes(L, k, true, vs), stage_launches(L, k, true), s,
+              [&] { return fwd_stage<T>(L, k, b, x, B.r, s); });
   } else {
-    timed_n(h, "gs_fwd", lvname(h, l, gs + ", true>"), fwd_bytes, L.ncolors, s, [&] {
-      for (int c = 0; c < L.ncolors; ++c) {
-        const hipError_t e = launch_gs_fwd<T>(L.fwd_mat(c), B.Dinv, L.color_ptr[c], L.color_ptr[c + 1], b, x, B.r, s);
+    timed_n(h, "gs_fwd", lvname(h, l, gs + ", true>"), fwd_bytes, fwd_n, s, [&] {
+      for (int k = 0; k < ns; ++k) {
+        const hipError_t e = fwd_stage<T>(L, k, b, x, B.r, s);
         if (e != hipSuccess) return e;
       }
       return hipSuccess;
@@ -599,16 +749,15 @@ void vcycle_t(eamg_hierarchy *h, size_t l, const T *b, T *x, hipStream_t s) {
   timed(h, "prolong", lvname(h, l, "k_rect<" + ty + ", " + std::to_string(bs) + ", " + std::to_string(L.kc) + ">"),
         launch_bytes(L.sh_P, LK_RECT_ACC, bs, L.kc, vs, 1), s, [&] { return launch_rect<T>(L.Pm, CB.x, x, true, s); });
   if (h->prof_colours) {
-    for (int c = L.ncolors - 1; c >= 0; --c)
-      timed(h, "gs_bwd", lvname(h, l, "c" + std::to_string(c) + " " + gs + ", false>"),
-            launch_bytes(L.sh_bwd[c], LK_GS_BWD, bs, bs, vs, 1), s, [&] {
-              return launch_gs_bwd<T>(L.bwd_mat(c), B.Dinv, L.color_ptr[c], L.color_ptr[c + 1], b, x, s);
-            });
+    for (int k = ns - 1; k >= 0; --k)
+      timed_n(h, "gs_bwd", lvname(h, l, "c" + std::to_string(L.cut[size_t(k)]) + " " + gs + ", false>"),
+              stage_bytes(L, k, false, vs), stage_launches(L, k, false), s,
+              [&] { return bwd_stage<T>(L, k, b, x, s); });
     return;
   }
-  timed_n(h, "gs_bwd", lvname(h, l, gs + ", false>"), bwd_bytes, L.ncolors, s, [&] {
-    for (int c = L.ncolors - 1; c >= 0; --c) {
-      const hipError_t e = launch_gs_bwd<T>(L.bwd_mat(c), B.Dinv, L.color_ptr[c], L.color_ptr[c + 1], b, x, s);
+  timed_n(h, "gs_bwd", lvname(h, l, gs + ", false>"), bwd_bytes, bwd_n, s, [&] {
+    for (int k = ns - 1; k >= 0; --k) {
+      const hipError_t e = bwd_stage<T>(L, k, b, x, s);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -1211,11 +1360,7 @@ eamg_status eamg_setup(const eamg_problem *pb, const eamg_setup_params *params, 
     for (size_t l = h->lv.size(); l-- > 0;) build_level_layout(h.get(), l, s);
     tm.mark("setup: solve layout");
     if (prm.dense_tail_dofs > 0) {
-      for (size_t l = 1; l + 1 < h->lv.size(); ++l)
-        if (int64_t(h->lv[l].n) * h->lv[l].bs <= prm.dense_tail_dofs) {
-          build_dense_tail(h.get(), l, s);
-          break;
-        }
+      if (const size_t t = tail_start(h.get())) build_dense_tail(h.get(), t, s);
       tm.mark("setup: dense tail");
     }
     const int64_t N0 = int64_t(n) * dim;
@@ -1349,13 +1494,11 @@ eamg_status eamg_autotune(eamg_hierarchy *h, int32_t panel_width, void *stream, 
       double *b = l == 0 ? h->r : L.b, *x = l == 0 ? h->z : L.x;
       for (double *v : {b, x, L.r}) hip_check(launch_fill(nv, 0.0, v, s), "fill");
       auto fwd_part = [&] {
-        for (int c = 0; c < L.ncolors; ++c)
-          hip_check(launch_gs_fwd<double>(L.fwd_mat(c), L.Dinv, L.color_ptr[c], L.color_ptr[c + 1], b, x, L.r, s), "gs");
+        for (int k = 0; k < L.stages(); ++k) hip_check(fwd_stage<double>(L, k, b, x, L.r, s), "gs");
       };
       auto resid_part = [&] { hip_check(resid_update<double>(L, x, L.r, s), "resid"); };
       auto bwd_part = [&] {
-        for (int c = L.ncolors - 1; c >= 0; --c)
-          hip_check(launch_gs_bwd<double>(L.bwd_mat(c), L.Dinv, L.color_ptr[c], L.color_ptr[c + 1], b, x, s), "gs");
+        for (int k = L.stages() - 1; k >= 0; --k) hip_check(bwd_stage<double>(L, k, b, x, s), "gs");
       };
       L.g_fwd.clear();
       L.g_bwd.clear();
@@ -1370,6 +1513,8 @@ eamg_status eamg_autotune(eamg_hierarchy *h, int32_t panel_width, void *stream, 
         L.Am.group = g;
         L.Am.group_bwd = 0;
         L.group_resid = 0;
+        L.gs_f.assign(L.gs_f.size(), g);
+        L.gs_b.assign(L.gs_b.size(), g);
         continue;
       }
       // forward sweep, residual update and backward sweep: lanes per row chosen apart
@@ -1402,7 +1547,7 @@ eamg_status eamg_autotune(eamg_hierarchy *h, int32_t panel_width, void *stream, 
       L.Am.group = gf;
       L.Am.group_bwd = gb == gf ? 0 : gb;
       L.group_resid = gr == gf ? 0 : gr;
-      // then per colour (the sweeps) and per range of colours (the residual update): each part
+      // then per stage (the sweeps) and per range of colours (the residual update): each part
       // is timed inside whole sweeps, so its matrix streams from memory as in a V-cycle; a
       // refinement is kept only if the whole part gets faster
       const int nc = L.ncolors;
@@ -1421,16 +1566,17 @@ eamg_status eamg_autotune(eamg_hierarchy *h, int32_t panel_width, void *stream, 
         if (tsum >= level_best) choice.clear();
         return choice.empty() ? level_best : tsum;
       };
-      bf = refine(L.g_fwd, nc, [&](auto &&mark) {
-        for (int c = 0; c < nc; ++c) {
-          hip_check(launch_gs_fwd<double>(L.fwd_mat(c), L.Dinv, L.color_ptr[c], L.color_ptr[c + 1], b, x, L.r, s), "gs");
-          mark(c);
+      const int ns = L.stages();
+      bf = refine(L.g_fwd, ns, [&](auto &&mark) {
+        for (int k = 0; k < ns; ++k) {
+          hip_check(fwd_stage<double>(L, k, b, x, L.r, s), "gs");
+          mark(k);
         }
       }, bf);
-      bb = refine(L.g_bwd, nc, [&](auto &&mark) {
-        for (int c = nc - 1; c >= 0; --c) {
-          hip_check(launch_gs_bwd<double>(L.bwd_mat(c), L.Dinv, L.color_ptr[c], L.color_ptr[c + 1], b, x, s), "gs");
-          mark(nc - 1 - c);
+      bb = refine(L.g_bwd, ns, [&](auto &&mark) {
+        for (int k = ns - 1; k >= 0; --k) {
+          hip_check(bwd_stage<double>(L, k, b, x, s), "gs");
+          mark(ns - 1 - k);
         }
       }, bb);
       // residual update in up to four launches over colour ranges of about equal upper blocks
@@ -1552,7 +1698,7 @@ eamg_status eamg_solve_multi(int32_t nsys, eamg_hierarchy *const *hs, const doub
     for (int m = 0; m < nsys; ++m) {
       double launches = 8.0, bytes = 0.0;
       for (const Level &L : hs[m]->lv) {
-        launches += 2.0 * L.ncolors + 4.0;
+        launches += 4.0 * L.stages() + 4.0;
         bytes += double(L.A.nnz()) * L.bs * L.bs * (f32 ? 4.0 : 8.0) * 2.0;
       }
       cost[m] = launches * 6e-6 + bytes / 2e12;
@@ -1752,8 +1898,7 @@ eamg_status eamg_traffic_model(const eamg_hierarchy *h, int32_t precision, doubl
       }
       const double vs = f32 ? 4.0 : 8.0;
       const int bs = L.bs;
-      for (const LaunchShape &sh : L.sh_fwd) v += launch_bytes(sh, LK_GS_FWD, bs, bs, vs, 1);
-      for (const LaunchShape &sh : L.sh_bwd) v += launch_bytes(sh, LK_GS_BWD, bs, bs, vs, 1);
+      for (int k = 0; k < L.stages(); ++k) v += stage_bytes(L, k, true, vs) + stage_bytes(L, k, false, vs);
       v += launch_bytes(L.sh_resid, LK_RESID, bs, bs, vs, 1) +
            launch_bytes(L.sh_R, LK_RECT, L.kc, bs, vs, 1) +
            launch_bytes(L.sh_P, LK_RECT_ACC, bs, L.kc, vs, 1);

@@ -194,6 +194,7 @@ void build_fused_level(eamg_hierarchy *F, const std::vector<eamg_hierarchy *> &h
       L.Dinv32 = ar.alloc<float>(size_t(o.n_smooth) * bs * bs);
       hip_check(launch_convert(int64_t(o.n_smooth) * bs * bs, L.Dinv, L.Dinv32, s), "convert");
     }
+    build_sweep_stages(ar, L, Ap, dg, f32, s);
     // transfers: P of the smoothed systems, rows in the fused order of level l, columns in the
     // fused order of level l + 1
     const FusedOrder &oc = ord[size_t(l) + 1];

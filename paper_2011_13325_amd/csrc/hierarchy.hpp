@@ -157,18 +157,33 @@ struct Level {
     if (group_resid) m.group = group_resid;
     return m;
   }
-  // per colour: lanes per row of the forward / backward sweep, 0 (or empty) for the level's
+  // The sweeps run in stages: stage k covers the colours [cut[k], cut[k + 1]), one colour or a
+  // group of colours (SweepPlan).  A group has its matrices Sf / Sb (forward / backward, solve
+  // numbering), the ends of its rows' outer couplings left of the diagonal (lo_end), and u, its
+  // right-hand side.
+  std::vector<int> cut;
+  SolveMat Sf, Sb;
+  const int *lo_end = nullptr;
+  double *u = nullptr;
+  float *u32 = nullptr;
+  std::vector<int> gs_f, gs_b;               // per stage: lanes per row of S
+  std::vector<LaunchShape> sh_rf, sh_rb, sh_sf, sh_sb;   // per stage: group launches
+  int stages() const { return cut.empty() ? 0 : int(cut.size()) - 1; }
+  bool is_group(int k) const { return cut[size_t(k) + 1] > cut[size_t(k)] + 1; }
+  int row0(int k) const { return color_ptr[size_t(cut[size_t(k)])]; }
+  int row1(int k) const { return color_ptr[size_t(cut[size_t(k) + 1])]; }
+  // per stage: lanes per row of the forward / backward sweep, 0 (or empty) for the level's
   // choice; the first row of a colour's lower blocks grows from none (colour 0) to a whole row
   // (the last colour), so one choice per level fits neither end
   std::vector<int> g_fwd, g_bwd;
-  SolveMat fwd_mat(int c) const {
+  SolveMat fwd_mat(int k) const {
     SolveMat m = Am;
-    if (size_t(c) < g_fwd.size() && g_fwd[size_t(c)]) m.group = g_fwd[size_t(c)];
+    if (size_t(k) < g_fwd.size() && g_fwd[size_t(k)]) m.group = g_fwd[size_t(k)];
     return m;
   }
-  SolveMat bwd_mat(int c) const {
+  SolveMat bwd_mat(int k) const {
     SolveMat m = Am;
-    if (size_t(c) < g_bwd.size() && g_bwd[size_t(c)]) m.group_bwd = g_bwd[size_t(c)];
+    if (size_t(k) < g_bwd.size() && g_bwd[size_t(k)]) m.group_bwd = g_bwd[size_t(k)];
     return m;
   }
   // the residual update as launches over consecutive colour ranges [resid_cut[k],
@@ -198,17 +213,17 @@ struct Level {
 template <class T>
 struct LevelBufs {
   const T *Dinv;
-  T *x, *b, *r;
+  T *x, *b, *r, *u;
 };
 template <class T>
 LevelBufs<T> bufs(Level &L);
 template <>
 inline LevelBufs<double> bufs<double>(Level &L) {
-  return {L.Dinv, L.x, L.b, L.r};
+  return {L.Dinv, L.x, L.b, L.r, L.u};
 }
 template <>
 inline LevelBufs<float> bufs<float>(Level &L) {
-  return {L.Dinv32, L.x32, L.b32, L.r32};
+  return {L.Dinv32, L.x32, L.b32, L.r32, L.u32};
 }
 template <class T>
 const char *type_name();
@@ -248,6 +263,10 @@ LaunchShape range_shape(const Pattern &Ap, const std::vector<int> &dg, int r0, i
 LaunchShape matrix_shape(const Pattern &M);
 // Launch shapes of a smoothed level (colours, residual update over smooth_rows(), SpMV).
 void level_shapes(Level &L, const Pattern &Ap, const std::vector<int> &dg);
+// Sweep stages of a smoothed level whose matrix and D^+ are in place (Ap, dg: its colour-major pattern
+// and diagonal positions): the plan, the group matrices and u.
+void build_sweep_stages(DevArena &ar, Level &L, const Pattern &Ap, const std::vector<int> &dg, bool f32,
+                        hipStream_t s);
 // z = V(r) on level-0 vectors in the hierarchy's solve numbering (FP64, or the FP32 V-cycle
 // with conversions at the boundary).
 void vcycle_apply(eamg_hierarchy *h, const double *r, double *z, bool f32, hipStream_t s);

@@ -440,11 +440,13 @@ __device__ inline T pick(const T (&v)[B], int i) {
 // (BWD) x_i[q], together with the row's blocks, so a row costs one round of row loads plus the
 // x gathers; a butterfly all-reduce leaves the row sum on every lane.  No other row of the
 // colour writes x_i, so the prefetched x_i[q] is the value the gathers see.
+// y: the vector the blocks multiply, x itself for a colour.  For a group of colours b and
+// y are both its right-hand side u and (rp, col, val) the group's matrix S (SweepPlan).
 template <class T, int B, bool FWD, int W>
 __device__ inline void gs_row(int row, bool valid, int lane, int G, const int *__restrict__ rp,
                               const int *__restrict__ col, const T *__restrict__ val, int64_t nnz,
                               const T *__restrict__ dval, int64_t nd, const T *__restrict__ Dinv,
-                              const T *__restrict__ b, T *x, T *r, T *sh) {
+                              const T *__restrict__ b, const T *y, T *x, T *r, T *sh) {
   const bool own = valid && lane < B;
   int p0 = 0, p1 = 0;
   if (valid) {
@@ -469,7 +471,7 @@ __device__ inline void gs_row(int row, bool valid, int lane, int G, const int *_
   T acc[B];
 #pragma unroll
   for (int q = 0; q < B; ++q) acc[q] = T(0);
-  if (valid) row_accumulate<T, B, B>(p0, p1, lane, G, col, val, nnz, x, acc);
+  if (valid) row_accumulate<T, B, B>(p0, p1, lane, G, col, val, nnz, y, acc);
   if (W > 1)
     wide_reduce<T, B, W>(acc, sh);
   else
@@ -500,17 +502,18 @@ __device__ inline void gs_row(int row, bool valid, int lane, int G, const int *_
   }
 }
 
-// r_i -= sum_{j > i} A_ij x_j for one row (rp, col, val: the blocks right of the diagonal).
+// r_i = b_i - sum over the blocks [rp[i], re[i]) of A_ij x_j for one row (b may be r).
 template <class T, int B, int W>
 __device__ inline void resid_row(int row, bool valid, int lane, int G, const int *__restrict__ rp,
-                                 const int *__restrict__ col, const T *__restrict__ val,
-                                 int64_t nnz, const T *x, T *r, T *sh) {
+                                 const int *__restrict__ re, const int *__restrict__ col,
+                                 const T *__restrict__ val, int64_t nnz, const T *x, const T *b, T *r,
+                                 T *sh) {
   T rq = T(0);
   int p0 = 0, p1 = 0;
   if (valid) {
     p0 = rp[row];
-    p1 = rp[row + 1];
-    if (lane < B) rq = r[int64_t(row) * B + lane];
+    p1 = re[row];
+    if (lane < B) rq = b[int64_t(row) * B + lane];
   }
   T acc[B];
 #pragma unroll
@@ -536,7 +539,114 @@ __global__ __launch_bounds__(kBlock) void k_gs_color(int r0, int r1, int G, cons
   __shared__ T sh[W > 1 ? (kBlock / 64) * B : 1];
   const int lane = threadIdx.x & (G - 1);
   const int row = r0 + xcd_block() * (kBlock / G) + threadIdx.x / G;
-  gs_row<T, B, FWD, W>(row, row < r1, lane, G, rp, col, val, nnz, dval, nd, Dinv, b, x, r, sh);
+  gs_row<T, B, FWD, W>(row, row < r1, lane, G, rp, col, val, nnz, dval, nd, Dinv, b, x, x, r, sh);
+}
+
+// Groups of colours.  On the levels of a few hundred rows per colour a colour launch is a chain of
+// dependent steps (dispatch, row offsets, blocks, gathers, reduction, store) of 3.3 to 5 us that its
+// bytes hardly add to, and a sweep is 20 to 70 such launches.  A group runs any number of colours
+// in two: u = b - (couplings outside the group) x over all its rows, then its colours' recursion
+// multiplied out, t = u - S u.  Sweeps of the library's defaults (no dense tail), start to now: 17^3
+// FP64 solve 9.22 -> 2.25 ms (1536 colour launches -> 132 group launches), Poisson 65x57x71 15.1 ->
+// 7.9 ms; with the tail 64^3 FP32 25.9 -> 19.6 ms, FP64 35.9 -> 29.3 ms, 128^3 FP32 155 -> 143 ms.
+template <class T, int B, int W>
+__global__ __launch_bounds__(kBlock) void k_group_rhs(int r0, int r1, int G, const int *__restrict__ rp,
+                                                     const int *__restrict__ re,
+                                                     const int *__restrict__ col,
+                                                     const T *__restrict__ val, int64_t nnz,
+                                                     const T *__restrict__ b, const T *__restrict__ x,
+                                                     T *__restrict__ u) {
+  __shared__ T sh[W > 1 ? (kBlock / 64) * B : 1];
+  const int lane = threadIdx.x & (G - 1);
+  const int row = r0 + xcd_block() * (kBlock / G) + int(threadIdx.x) / G;
+  resid_row<T, B, W>(row, row < r1, lane, G, rp, re, col, val, nnz, x, b, u, sh);
+}
+
+template <class T, int B, bool FWD, int W>
+__global__ __launch_bounds__(kBlock) void k_gs_group(int r0, int r1, int G, const int *__restrict__ rp,
+                                                    const int *__restrict__ col,
+                                                    const T *__restrict__ val, int64_t nnz,
+                                                    const T *__restrict__ dval, int64_t nd,
+                                                    const T *__restrict__ Dinv,
+                                                    const T *__restrict__ u, T *__restrict__ x,
+                                                    T *__restrict__ r) {
+  __shared__ T sh[W > 1 ? (kBlock / 64) * B : 1];
+  const int lane = threadIdx.x & (G - 1);
+  const int row = r0 + xcd_block() * (kBlock / G) + threadIdx.x / G;
+  gs_row<T, B, FWD, W>(row, row < r1, lane, G, rp, col, val, nnz, dval, nd, Dinv, u, u, x, r, sh);
+}
+
+// One row of S per workgroup (launch_group_fill); thread e owns entry e, e + 256, ... of the row.
+// The products A_q Dinv_j of kFillChunk couplings at a time sit in LDS.  Setup only.
+constexpr int kFillChunk = 32;
+template <int B>
+__global__ __launch_bounds__(kBlock) void k_group_fill(const int *__restrict__ rows,
+                                                      const int *__restrict__ q0,
+                                                      const int *__restrict__ q1,
+                                                      const int *__restrict__ col,
+                                                      const double *__restrict__ val,
+                                                      const double *__restrict__ Dinv,
+                                                      const int *__restrict__ Srp,
+                                                      const int *__restrict__ Scol, double *Sval) {
+  constexpr int BB = B * B;
+  __shared__ double P[kFillChunk * BB];
+  __shared__ int J[kFillChunk];
+  const int i = rows[blockIdx.x];
+  const int a = q0[i], b = q1[i], s0 = Srp[i], s1 = Srp[i + 1];
+  for (int e0 = s0; e0 < s1; e0 += kBlock) {
+    const int e = e0 + int(threadIdx.x);
+    const int k = e < s1 ? Scol[e] : -1;
+    double acc[BB];
+#pragma unroll
+    for (int v = 0; v < BB; ++v) acc[v] = 0.0;
+    for (int qa = a; qa < b; qa += kFillChunk) {
+      const int m = min(kFillChunk, b - qa);
+      __syncthreads();
+      for (int t = threadIdx.x; t < m * BB; t += kBlock) {
+        const int q = t / BB, r = (t % BB) / B, c = t % B;
+        const int j = col[qa + q];
+        double v = 0.0;
+        for (int l = 0; l < B; ++l) v = fma(val[int64_t(qa + q) * BB + r * B + l], Dinv[int64_t(j) * BB + l * B + c], v);
+        P[t] = v;
+        if (r == 0 && c == 0) J[q] = j;
+      }
+      __syncthreads();
+      if (k < 0) continue;
+      for (int q = 0; q < m; ++q) {
+        const int j = J[q];
+        const double *Pq = P + q * BB;
+        if (j == k) {
+#pragma unroll
+          for (int v = 0; v < BB; ++v) acc[v] += Pq[v];
+          continue;
+        }
+        int lo = Srp[j], hi = Srp[j + 1];
+        const int end = hi;
+        while (lo < hi) {
+          const int mid = (lo + hi) >> 1;
+          if (Scol[mid] < k)
+            lo = mid + 1;
+          else
+            hi = mid;
+        }
+        if (lo == end || Scol[lo] != k) continue;
+        const double *Sj = Sval + int64_t(lo) * BB;
+#pragma unroll
+        for (int l = 0; l < B; ++l) {
+          double sj[B];
+#pragma unroll
+          for (int c = 0; c < B; ++c) sj[c] = Sj[l * B + c];
+#pragma unroll
+          for (int r = 0; r < B; ++r)
+#pragma unroll
+            for (int c = 0; c < B; ++c) acc[r * B + c] = fma(-Pq[r * B + l], sj[c], acc[r * B + c]);
+        }
+      }
+    }
+    if (k >= 0)
+#pragma unroll
+      for (int v = 0; v < BB; ++v) Sval[int64_t(e) * BB + v] = acc[v];
+  }
 }
 
 template <class T, int B, int W>
@@ -547,7 +657,7 @@ __global__ __launch_bounds__(kBlock) void k_resid_upper(int r0, int r1, int G, c
   __shared__ T sh[W > 1 ? (kBlock / 64) * B : 1];
   const int lane = threadIdx.x & (G - 1);
   const int row = r0 + int(blockIdx.x) * (kBlock / G) + int(threadIdx.x) / G;
-  resid_row<T, B, W>(row, row < r1, lane, G, rp, col, val, nnz, x, r, sh);
+  resid_row<T, B, W>(row, row < r1, lane, G, rp, rp + 1, col, val, nnz, x, r, r, sh);
 }
 
 template <class T, int BR, int BC>
@@ -852,6 +962,77 @@ hipError_t launch_resid_upper(const SolveMat &A, int r0, int r1, const T *x, T *
 }
 
 template <class T>
+hipError_t launch_group_rhs(const SolveMat &A, const int *lo_end, int r0, int r1, const T *b, const T *x,
+                            T *u, hipStream_t s) {
+  if (r0 < 0 || r1 > A.n_rows) return hipErrorInvalidValue;
+  if (r1 <= r0) return hipSuccess;
+  const bool f32 = sizeof(T) == 4;
+  const T *val = lo_end ? reinterpret_cast<const T *>(f32 ? (const void *)A.lo_val32 : (const void *)A.lo_val)
+                        : solve_vals<T>(A);
+  const int *rp = lo_end ? A.lo_rp : A.rp, *re = lo_end ? lo_end : A.rp + 1;
+  const int *col = lo_end ? A.lo_col : A.col;
+  const int64_t nnz = lo_end ? A.lo_nnz : A.nnz;
+  if (!val || !rp) return hipErrorInvalidValue;
+  const int G = !lo_end && A.group_bwd ? A.group_bwd : A.group;
+  const dim3 grid(cdiv64(r1 - r0, groups_for(G)));
+  switch (A.br) {
+    case 1: EAMG_GS_W(W_, hipLaunchKernelGGL((k_group_rhs<T, 1, W_>), grid, dim3(kBlock), 0, s, r0, r1, G, rp, re, col, val, nnz, b, x, u)); break;
+    case 3: EAMG_GS_W(W_, hipLaunchKernelGGL((k_group_rhs<T, 3, W_>), grid, dim3(kBlock), 0, s, r0, r1, G, rp, re, col, val, nnz, b, x, u)); break;
+    case 6: EAMG_GS_W(W_, hipLaunchKernelGGL((k_group_rhs<T, 6, W_>), grid, dim3(kBlock), 0, s, r0, r1, G, rp, re, col, val, nnz, b, x, u)); break;
+    default: return hipErrorInvalidValue;
+  }
+  EAMG_LAUNCH_CHECK();
+}
+
+namespace {
+template <class T, bool FWD>
+hipError_t launch_group(const SolveMat &S, const T *dg, const T *Dinv, int r0, int r1, const T *u, T *x,
+                        T *r, hipStream_t s) {
+  if (r0 < 0 || r1 > S.n_rows) return hipErrorInvalidValue;
+  if (r1 <= r0) return hipSuccess;
+  const T *val = solve_vals<T>(S);
+  if (!val || !S.rp || (FWD && !dg)) return hipErrorInvalidValue;
+  const int G = S.group;
+  const dim3 grid(cdiv64(r1 - r0, groups_for(G)));
+  const int64_t nd = S.n_rows;
+  switch (S.br) {
+    case 1: EAMG_GS_W(W_, hipLaunchKernelGGL((k_gs_group<T, 1, FWD, W_>), grid, dim3(kBlock), 0, s, r0, r1, G, S.rp, S.col, val, S.nnz, dg, nd, Dinv, u, x, r)); break;
+    case 3: EAMG_GS_W(W_, hipLaunchKernelGGL((k_gs_group<T, 3, FWD, W_>), grid, dim3(kBlock), 0, s, r0, r1, G, S.rp, S.col, val, S.nnz, dg, nd, Dinv, u, x, r)); break;
+    case 6: EAMG_GS_W(W_, hipLaunchKernelGGL((k_gs_group<T, 6, FWD, W_>), grid, dim3(kBlock), 0, s, r0, r1, G, S.rp, S.col, val, S.nnz, dg, nd, Dinv, u, x, r)); break;
+    default: return hipErrorInvalidValue;
+  }
+  EAMG_LAUNCH_CHECK();
+}
+}  // namespace
+
+template <class T>
+hipError_t launch_group_fwd(const SolveMat &A, const SolveMat &S, const T *Dinv, int r0, int r1,
+                            const T *u, T *x, T *r, hipStream_t s) {
+  const T *dg = sizeof(T) == 4 ? reinterpret_cast<const T *>(A.dg_val32) : reinterpret_cast<const T *>(A.dg_val);
+  return launch_group<T, true>(S, dg, Dinv, r0, r1, u, x, r, s);
+}
+
+template <class T>
+hipError_t launch_group_bwd(const SolveMat &S, const T *Dinv, int r0, int r1, const T *u, T *x,
+                            hipStream_t s) {
+  return launch_group<T, false>(S, nullptr, Dinv, r0, r1, u, x, nullptr, s);
+}
+
+hipError_t launch_group_fill(int nrows, const int *rows, int bs, const int *q0, const int *q1,
+                             const int *col, const double *val, const double *Dinv, const int *Srp,
+                             const int *Scol, double *Sval, hipStream_t s) {
+  if (nrows == 0) return hipSuccess;
+  const dim3 grid(static_cast<unsigned>(nrows));
+  switch (bs) {
+    case 1: hipLaunchKernelGGL(k_group_fill<1>, grid, dim3(kBlock), 0, s, rows, q0, q1, col, val, Dinv, Srp, Scol, Sval); break;
+    case 3: hipLaunchKernelGGL(k_group_fill<3>, grid, dim3(kBlock), 0, s, rows, q0, q1, col, val, Dinv, Srp, Scol, Sval); break;
+    case 6: hipLaunchKernelGGL(k_group_fill<6>, grid, dim3(kBlock), 0, s, rows, q0, q1, col, val, Dinv, Srp, Scol, Sval); break;
+    default: return hipErrorInvalidValue;
+  }
+  EAMG_LAUNCH_CHECK();
+}
+
+template <class T>
 hipError_t launch_rect(const SolveMat &M, const T *x, T *y, bool accumulate, hipStream_t s) {
   if (M.n_rows == 0) return hipSuccess;
   const T *val = solve_vals<T>(M);
@@ -891,6 +1072,12 @@ template hipError_t launch_gs_bwd<double>(const SolveMat &, const double *, int,
 template hipError_t launch_gs_bwd<float>(const SolveMat &, const float *, int, int, const float *, float *, hipStream_t);
 template hipError_t launch_resid_upper<double>(const SolveMat &, int, int, const double *, double *, hipStream_t);
 template hipError_t launch_resid_upper<float>(const SolveMat &, int, int, const float *, float *, hipStream_t);
+template hipError_t launch_group_rhs<double>(const SolveMat &, const int *, int, int, const double *, const double *, double *, hipStream_t);
+template hipError_t launch_group_rhs<float>(const SolveMat &, const int *, int, int, const float *, const float *, float *, hipStream_t);
+template hipError_t launch_group_fwd<double>(const SolveMat &, const SolveMat &, const double *, int, int, const double *, double *, double *, hipStream_t);
+template hipError_t launch_group_fwd<float>(const SolveMat &, const SolveMat &, const float *, int, int, const float *, float *, float *, hipStream_t);
+template hipError_t launch_group_bwd<double>(const SolveMat &, const double *, int, int, const double *, double *, hipStream_t);
+template hipError_t launch_group_bwd<float>(const SolveMat &, const float *, int, int, const float *, float *, hipStream_t);
 template hipError_t launch_rect<double>(const SolveMat &, const double *, double *, bool, hipStream_t);
 template hipError_t launch_rect<float>(const SolveMat &, const float *, float *, bool, hipStream_t);
 template hipError_t launch_convert<double, float>(int64_t, const double *, float *, hipStream_t);

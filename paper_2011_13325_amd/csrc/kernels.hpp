@@ -117,6 +117,27 @@ hipError_t launch_resid_upper(const SolveMat &A, int r0, int r1, const T *x, T *
 template <class T>
 hipError_t launch_gs_bwd(const SolveMat &A, const T *Dinv, int r0, int r1, const T *b, T *x,
                          hipStream_t s);
+// Grouped sweep stages (SweepPlan, structure.hpp) on rows [r0, r1):
+//   launch_group_rhs: u_i = b_i - sum over the row's couplings outside the group of A_ij x_j; forward:
+//     the blocks left of the diagonal up to lo_end[i] (those inside the group are left out, and
+//     the later rows' x is zero); backward (lo_end null): the whole row, so that u = b - A x.
+//   launch_group_fwd: t_i = u_i - sum_j S_ij u_j; x_i = Dinv_i t_i; r_i = t_i - A_ii x_i.
+//   launch_group_bwd: t_i = u_i - sum_j S_ij u_j; x_i += Dinv_i t_i.
+template <class T>
+hipError_t launch_group_rhs(const SolveMat &A, const int *lo_end, int r0, int r1, const T *b, const T *x,
+                            T *u, hipStream_t s);
+template <class T>
+hipError_t launch_group_fwd(const SolveMat &A, const SolveMat &S, const T *Dinv, int r0, int r1,
+                            const T *u, T *x, T *r, hipStream_t s);
+template <class T>
+hipError_t launch_group_bwd(const SolveMat &S, const T *Dinv, int r0, int r1, const T *u, T *x,
+                            hipStream_t s);
+// One rank of the group matrices, row rows[k] (k < nrows) each: its couplings inside the group
+// are the positions [q0[i], q1[i]) of A (col, val, natural FP64 blocks in the solve numbering), and
+//   S_ik = sum over those q, j = col[q], of A_q Dinv_j ([j == k] I - S_jk).
+hipError_t launch_group_fill(int nrows, const int *rows, int bs, const int *q0, const int *q1,
+                             const int *col, const double *val, const double *Dinv, const int *Srp,
+                             const int *Scol, double *Sval, hipStream_t s);
 // y = M x (rectangular, overwrite) or y += M x (accumulate = true).
 template <class T>
 hipError_t launch_rect(const SolveMat &M, const T *x, T *y, bool accumulate, hipStream_t s);

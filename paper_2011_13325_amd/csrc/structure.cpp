@@ -276,4 +276,101 @@ Pattern permute_rect(const Pattern &P, const std::vector<int> &perm_rows,
   return R;
 }
 
+// A colour launch costs kLaunch beyond its bytes (replayed graphs: launches of a few hundred
+// kilobytes take 3.3 to 4.6 us), and a group's S, at most a few tens of megabytes that stay in the
+// Infinity Cache, streams at kRate.  A group of g colours costs two launches and the bytes of S, g
+// colours cost g launches; the couplings outside the group are read once either way.  Groups grow
+// while a further colour's part of S costs less than the group's mean per colour (the mean falls until
+// then), and stay if they save at least half a launch.  A block of S counts its FP64 value and column
+// (both precisions share one plan) and a 32-byte sector of the scattered gather, which is most of a
+// scalar block's cost.  The optimum is flat: S allowed 0.4, 1, 2 and 4 times these bytes gave 2.41,
+// 2.29, 2.21, 3.07 ms per 17^3 FP64 solve, 19.8, 19.3, 18.8, 19.6 ms per 64^3 FP32 solve and 29.3,
+// 29.3, 30.3, 32.6 ms in FP64.
+SweepPlan plan_sweeps(const Pattern &Ap, const std::vector<int> &dg, const std::vector<int> &color_ptr,
+                      int ncolors, int bs) {
+  constexpr double kLaunch = 3.5e-6, kRate = 6e12;
+  const double blk = bs * bs * 8.0 + 4.0 + 32.0;
+  const int n = Ap.n_rows;
+  SweepPlan pl;
+  pl.pre = dg;
+  pl.post.resize(size_t(n));
+  for (int i = 0; i < n; ++i) pl.post[size_t(i)] = dg[size_t(i)] + 1;
+  pl.rank.assign(size_t(n), -1);
+  pl.S.n_rows = pl.S.n_cols = n;
+  pl.S.rp.assign(size_t(n) + 1, 0);
+  std::vector<std::vector<int>> rows;   // S rows of the groups tried
+  rows.resize(size_t(color_ptr[size_t(ncolors)]));
+  auto first_at = [&](int i, int r) {   // first position of row i at a column >= r
+    return int(std::lower_bound(Ap.col.begin() + Ap.rp[size_t(i)], Ap.col.begin() + Ap.rp[size_t(i) + 1], r) -
+               Ap.col.begin());
+  };
+  pl.cut.push_back(0);
+  int c0 = 0;
+  while (c0 < ncolors) {
+    const int r0 = color_ptr[size_t(c0)];
+    // a group that starts at the first colour has no earlier rows: one launch forward, two backward
+    const double launches = c0 == 0 ? 1.5 : 2.0;
+    double cost = launches * kLaunch, nnz = 0.0;
+    int c1 = c0 + 1;
+    for (int i = r0; i < color_ptr[size_t(c1)]; ++i) rows[size_t(i)].clear();
+    for (; c1 < ncolors; ++c1) {
+      const int a = color_ptr[size_t(c1)], b = color_ptr[size_t(c1) + 1];
+      const double mean = cost / double(c1 - c0);
+      // the direct couplings alone may already cost too much; a first-fit colouring gives every
+      // row at least one in each lower colour
+      if (double(b - a) * (c1 - c0) * blk / kRate >= mean) break;
+      double direct = 0.0;
+      for (int i = a; i < b; ++i) direct += double(dg[size_t(i)] - first_at(i, r0));
+      if (direct * blk / kRate >= mean) break;
+      // threads only where the merged rows repay starting them
+      const bool many = direct * (1.0 + nnz / double(a - r0)) > 3e5;
+      const int chunk = many ? 32 : b - a, nch = (b - a + chunk - 1) / std::max(1, chunk);
+      parallel_for_dynamic(nch, [&](int64_t ch) {
+        std::vector<char> seen(size_t(a - r0), 0);
+        for (int i = a + int(ch) * chunk; i < std::min(b, a + int(ch + 1) * chunk); ++i) {
+          std::vector<int> &R = rows[size_t(i)];
+          R.clear();
+          auto add = [&](int j) {
+            if (!seen[size_t(j - r0)]) {
+              seen[size_t(j - r0)] = 1;
+              R.push_back(j);
+            }
+          };
+          for (int q = first_at(i, r0); q < dg[size_t(i)]; ++q) {
+            const int j = Ap.col[size_t(q)];
+            add(j);
+            for (int k : rows[size_t(j)]) add(k);
+          }
+          for (int j : R) seen[size_t(j - r0)] = 0;
+          std::sort(R.begin(), R.end());
+        }
+      }, 1);
+      double add = 0.0;
+      for (int i = a; i < b; ++i) add += double(rows[size_t(i)].size());
+      if (add * blk / kRate >= mean) break;
+      nnz += add;
+      cost += add * blk / kRate;
+    }
+    if (cost > (double(c1 - c0) - 0.5) * kLaunch || nnz == 0.0) c1 = c0 + 1;
+    if (c1 > c0 + 1) {
+      const int r1 = color_ptr[size_t(c1)];
+      for (int c = c0; c < c1; ++c)
+        for (int i = color_ptr[size_t(c)]; i < color_ptr[size_t(c) + 1]; ++i) {
+          pl.pre[size_t(i)] = first_at(i, r0);
+          pl.post[size_t(i)] = first_at(i, r1);
+          pl.rank[size_t(i)] = c - c0;
+        }
+      pl.max_rank = std::max(pl.max_rank, c1 - c0 - 1);
+    }
+    pl.cut.push_back(c1);
+    c0 = c1;
+  }
+  for (int i = 0; i < n; ++i)
+    pl.S.rp[size_t(i) + 1] = pl.S.rp[size_t(i)] + (pl.rank[size_t(i)] > 0 ? int64_t(rows[size_t(i)].size()) : 0);
+  pl.S.col.reserve(size_t(pl.S.nnz()));
+  for (int i = 0; i < n; ++i)
+    if (pl.rank[size_t(i)] > 0) pl.S.col.insert(pl.S.col.end(), rows[size_t(i)].begin(), rows[size_t(i)].end());
+  return pl;
+}
+
 }  // namespace eamg

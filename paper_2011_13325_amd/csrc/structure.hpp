@@ -54,6 +54,29 @@ inline std::vector<int> greedy_coloring(const Pattern &A, int &n_colors) {
 Pattern permute_pattern(const Pattern &A, const std::vector<int> &perm, const std::vector<int> &inv,
                         std::vector<int64_t> &src);
 
+// Sweep stages of a colour-major level.  A stage covers the colours [cut[k], cut[k + 1]): one
+// colour, or a group of consecutive colours done in two launches instead of one per colour.  With
+// u_i = b_i - (couplings of row i to the rows outside the group), the forward sweep inside a group is
+//   t = (I + L D^+)^{-1} u,   x_i = D_i^+ t_i,
+// L the group's blocks left of the diagonal: t_i = u_i - sum_j S_ij u_j with a sparse S whose
+// pattern holds, for each row, every row of the group from which a chain of couplings through
+// ascending colours leads to it.  The backward sweep's matrix, of (I + L^T D^+)^{-1}, has the
+// transposed pattern.
+struct SweepPlan {
+  std::vector<int> cut;           // stage boundaries (colours), 0 .. ncolors
+  Pattern S;                      // forward matrix (rows of one-colour stages are empty)
+  // positions in the level's pattern of a row's couplings inside its group: left [pre, diag),
+  // right (diag, post)
+  std::vector<int> pre, post;
+  std::vector<int> rank;          // a row's colour counted from its group's first, -1 if none
+  int max_rank = 0;
+  bool grouped() const { return S.nnz() > 0; }
+};
+// Ap: the level's colour-major pattern, dg its diagonal positions, color_ptr the colours' first
+// rows, bs the block size.
+SweepPlan plan_sweeps(const Pattern &Ap, const std::vector<int> &dg, const std::vector<int> &color_ptr,
+                      int ncolors, int bs);
+
 // Rows permuted by the fine permutation, columns renumbered by the coarse one (re-sorted).
 Pattern permute_rect(const Pattern &P, const std::vector<int> &perm_rows,
                      const std::vector<int> &inv_cols, std::vector<int64_t> &src);
