@@ -65,14 +65,17 @@ __device__ inline float wave_sum(float v) {
   return v;
 }
 
-// a2 = W2a h1 + W2b (m_u + m_v) + b2 ; z = w3 . relu(a2) + b3.  W2a^T, W2b^T staged in LDS.
+// a2 = W2a h1 + W2b (m_u + m_v) + b2 ; z = w3 . relu(a2) + b3.  W2a^T, W2b^T staged in LDS; a
+// wavefront takes kL2Edges edges at a time, so a weight read from LDS serves four FMAs (one edge at a
+// time: two LDS reads per FMA, 111 us at 60,001 edges; now 60 us, the same sums).
+constexpr int kL2Edges = 4;
 __global__ __launch_bounds__(kT) void k_gnn_l2(int64_t m, const float *__restrict__ P,
                                                const int *__restrict__ eu, const int *__restrict__ ev,
                                                const float *__restrict__ a1,
                                                const float *__restrict__ node, float *__restrict__ a2,
                                                float *__restrict__ z) {
   __shared__ float Wa[kGnnH * kGnnH], Wb[kGnnH * kGnnH];
-  __shared__ float vin[kEdgesPW][2 * kGnnH];
+  __shared__ __align__(16) float vin[kEdgesPW][2 * kGnnH][kL2Edges];
   for (int j = threadIdx.x; j < kGnnH * kGnnH; j += kT) {
     const int h = j / kGnnH, k = j % kGnnH;   // element (h, k) of W2a / W2b
     Wa[k * kGnnH + h] = P[kGnnOffW2a + j];
@@ -82,23 +85,44 @@ __global__ __launch_bounds__(kT) void k_gnn_l2(int64_t m, const float *__restric
   const int h = threadIdx.x & (kGnnH - 1);
   const int wv = threadIdx.x / kGnnH;
   const float b2 = P[kGnnOffB2 + h], w3 = P[kGnnOffW3 + h], b3 = P[kGnnOffB3];
-  for (int64_t base = int64_t(blockIdx.x) * kEdgesPW; base < m; base += int64_t(gridDim.x) * kEdgesPW) {
-    const int64_t e = base + wv;
-    const bool valid = e < m;   // uniform per wavefront
-    if (valid) {
-      vin[wv][h] = relu(a1[e * kGnnH + h]);
-      vin[wv][kGnnH + h] = node[int64_t(eu[e]) * kGnnH + h] + node[int64_t(ev[e]) * kGnnH + h];
+  constexpr int kStep = kEdgesPW * kL2Edges;
+  for (int64_t base = int64_t(blockIdx.x) * kStep; base < m; base += int64_t(gridDim.x) * kStep) {
+    const int64_t e0 = base + wv * kL2Edges;
+#pragma unroll
+    for (int q = 0; q < kL2Edges; ++q) {
+      const int64_t e = e0 + q < m ? e0 + q : m - 1;
+      vin[wv][h][q] = relu(a1[e * kGnnH + h]);
+      vin[wv][kGnnH + h][q] = node[int64_t(eu[e]) * kGnnH + h] + node[int64_t(ev[e]) * kGnnH + h];
     }
     __syncthreads();
-    if (valid) {
-      float acc = b2;
+    float acc[kL2Edges];
+#pragma unroll
+    for (int q = 0; q < kL2Edges; ++q) acc[q] = b2;
 #pragma unroll 8
-      for (int k = 0; k < kGnnH; ++k) acc = fmaf(Wa[k * kGnnH + h], vin[wv][k], acc);
+    for (int k = 0; k < kGnnH; ++k) {
+      const float4 u = *reinterpret_cast<const float4 *>(vin[wv][k]);
+      const float c = Wa[k * kGnnH + h];
+      acc[0] = fmaf(c, u.x, acc[0]);
+      acc[1] = fmaf(c, u.y, acc[1]);
+      acc[2] = fmaf(c, u.z, acc[2]);
+      acc[3] = fmaf(c, u.w, acc[3]);
+    }
 #pragma unroll 8
-      for (int k = 0; k < kGnnH; ++k) acc = fmaf(Wb[k * kGnnH + h], vin[wv][kGnnH + k], acc);
-      a2[e * kGnnH + h] = acc;
-      const float t = wave_sum(w3 * relu(acc));
-      if (h == 0) z[e] = t + b3;
+    for (int k = 0; k < kGnnH; ++k) {
+      const float4 u = *reinterpret_cast<const float4 *>(vin[wv][kGnnH + k]);
+      const float c = Wb[k * kGnnH + h];
+      acc[0] = fmaf(c, u.x, acc[0]);
+      acc[1] = fmaf(c, u.y, acc[1]);
+      acc[2] = fmaf(c, u.z, acc[2]);
+      acc[3] = fmaf(c, u.w, acc[3]);
+    }
+#pragma unroll
+    for (int q = 0; q < kL2Edges; ++q) {
+      const float t = wave_sum(w3 * relu(acc[q]));
+      if (e0 + q < m) {   // uniform per wavefront
+        a2[(e0 + q) * kGnnH + h] = acc[q];
+        if (h == 0) z[e0 + q] = t + b3;
+      }
     }
     __syncthreads();
   }
@@ -191,8 +215,13 @@ __global__ __launch_bounds__(kT) void k_gnn_b1(int64_t m, const int *__restrict_
   d1[q] = a1[q] > 0.0f ? t : 0.0f;
 }
 
-// Weight-gradient partials of one chunk of edges: tiles of kTile edges staged in LDS, each
-// thread summing its parameters over the tile in edge order.
+// Weight-gradient partials of one chunk of edges (blockIdx.x) for kRows hidden units (blockIdx.y):
+// tiles of kTile edges staged in LDS, the next tile's loads in flight meanwhile, each thread summing
+// its parameters over the chunk in edge order (two of W2a and two of W2b, and a share of the rest).
+// A partial's sums keep one order, 2048 edges long, since training amplifies any change of rounding
+// into other decisions of the learned walk; so the chip is filled by splitting the units instead:
+// 240 workgroups at 60,001 edges, where one workgroup per chunk (30) took 1156 us; now 215 us.
+constexpr int kRows = 8, kSlices = kGnnH / kRows;
 __global__ __launch_bounds__(kT) void k_gnn_wgrad(int64_t m, const float *__restrict__ X,
                                                   const int *__restrict__ eu, const int *__restrict__ ev,
                                                   const float *__restrict__ a1, const float *__restrict__ a2,
@@ -200,68 +229,84 @@ __global__ __launch_bounds__(kT) void k_gnn_wgrad(int64_t m, const float *__rest
                                                   const float *__restrict__ da1,
                                                   const float *__restrict__ da2,
                                                   const float *__restrict__ dz, float *__restrict__ part) {
-  __shared__ float sx[kTile][kGnnF], sh1[kTile][kGnnH], ss[kTile][kGnnH], sh2[kTile][kGnnH];
-  __shared__ float sd1[kTile][kGnnH], sd2[kTile][kGnnH], sdz[kTile];
-  constexpr int kPer = (kGnnParams + kT - 1) / kT;
-  float acc[kPer];
-#pragma unroll
-  for (int q = 0; q < kPer; ++q) acc[q] = 0.0f;
+  __shared__ __align__(8) float sh1[kTile][kGnnH], ss[kTile][kGnnH];
+  __shared__ float sx[kTile][kGnnF], sd1[kTile][kRows], sd2[kTile][kRows], sh2[kTile][kRows], sdz[kTile];
+  static_assert(kT == 256 && kGnnH == 64 && kGnnF == 12 && kRows == 8 && kTile == 32, "the thread layout below");
+  const int t = threadIdx.x, h0 = int(blockIdx.y) * kRows;
+  const int row = t / 32, col = 2 * (t % 32);    // W2a, W2b: unit h0 + row, inputs col, col + 1
   const int64_t c0 = int64_t(blockIdx.x) * kChunk;
   const int64_t c1 = c0 + kChunk < m ? c0 + kChunk : m;
-  for (int64_t t0 = c0; t0 < c1; t0 += kTile) {
-    const int nt = int(c1 - t0 < kTile ? c1 - t0 : kTile);
-    for (int j = threadIdx.x; j < kTile * kGnnH; j += kT) {
-      const int r = j / kGnnH, k = j % kGnnH;
-      if (r < nt) {
-        const int64_t e = t0 + r, q = e * kGnnH + k;
-        sh1[r][k] = relu(a1[q]);
-        sh2[r][k] = relu(a2[q]);
-        ss[r][k] = node[int64_t(eu[e]) * kGnnH + k] + node[int64_t(ev[e]) * kGnnH + k];
-        sd1[r][k] = da1[q];
-        sd2[r][k] = da2[q];
-      }
-    }
-    for (int j = threadIdx.x; j < kTile * kGnnF; j += kT) {
-      const int r = j / kGnnF, f = j % kGnnF;
-      if (r < nt) sx[r][f] = X[(t0 + r) * kGnnF + f];
-    }
-    if (int(threadIdx.x) < kTile && int(threadIdx.x) < nt) sdz[threadIdx.x] = dz[t0 + threadIdx.x];
-    __syncthreads();
+  constexpr int kPer = kTile * kGnnH / kT;       // staged entries per thread of a 64-unit array
+  float pa[kPer], ps[kPer], px[2], pd1, pd2, p2, pz;
+  auto fetch = [&](int64_t t0) {                 // a tile's values into registers, clamped past the end
+    const int64_t last = c1 - 1;
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
-      const int j = int(threadIdx.x) + q * kT;
-      if (j >= kGnnParams) break;
-      float s = acc[q];
-      if (j < kGnnOffB1) {
-        const int h = (j - kGnnOffW1) / kGnnF, f = (j - kGnnOffW1) % kGnnF;
-        for (int r = 0; r < nt; ++r) s = fmaf(sd1[r][h], sx[r][f], s);
-      } else if (j < kGnnOffW2a) {
-        const int h = j - kGnnOffB1;
-        for (int r = 0; r < nt; ++r) s += sd1[r][h];
-      } else if (j < kGnnOffW2b) {
-        const int h = (j - kGnnOffW2a) / kGnnH, k = (j - kGnnOffW2a) % kGnnH;
-        for (int r = 0; r < nt; ++r) s = fmaf(sd2[r][h], sh1[r][k], s);
-      } else if (j < kGnnOffB2) {
-        const int h = (j - kGnnOffW2b) / kGnnH, k = (j - kGnnOffW2b) % kGnnH;
-        for (int r = 0; r < nt; ++r) s = fmaf(sd2[r][h], ss[r][k], s);
-      } else if (j < kGnnOffW3) {
-        const int h = j - kGnnOffB2;
-        for (int r = 0; r < nt; ++r) s += sd2[r][h];
-      } else if (j < kGnnOffB3) {
-        const int h = j - kGnnOffW3;
-        for (int r = 0; r < nt; ++r) s = fmaf(sdz[r], sh2[r][h], s);
-      } else {
-        for (int r = 0; r < nt; ++r) s += sdz[r];
-      }
-      acc[q] = s;
+      const int64_t e = min(t0 + (t / kGnnH) + q * (kT / kGnnH), last);
+      const int k = t % kGnnH;
+      pa[q] = a1[e * kGnnH + k];
+      ps[q] = node[int64_t(eu[e]) * kGnnH + k] + node[int64_t(ev[e]) * kGnnH + k];
+    }
+    const int64_t e = min(t0 + t / kRows, last) * kGnnH + h0 + t % kRows;
+    pd1 = da1[e];
+    pd2 = da2[e];
+    p2 = a2[e];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) px[q] = X[min(t0 * kGnnF + min(t + q * kT, kTile * kGnnF - 1), c1 * kGnnF - 1)];
+    pz = dz[min(t0 + t % kTile, last)];
+  };
+  float A0 = 0.0f, A1 = 0.0f, B0 = 0.0f, B1 = 0.0f, v = 0.0f;
+  fetch(c0);
+  for (int64_t t0 = c0; t0 < c1; t0 += kTile) {
+    const int nt = int(c1 - t0 < kTile ? c1 - t0 : kTile);
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      sh1[t / kGnnH + q * (kT / kGnnH)][t % kGnnH] = relu(pa[q]);
+      ss[t / kGnnH + q * (kT / kGnnH)][t % kGnnH] = ps[q];
+    }
+    sd1[t / kRows][t % kRows] = pd1;
+    sd2[t / kRows][t % kRows] = pd2;
+    sh2[t / kRows][t % kRows] = relu(p2);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (t + q * kT < kTile * kGnnF) sx[(t + q * kT) / kGnnF][(t + q * kT) % kGnnF] = px[q];
+    if (t < kTile) sdz[t] = pz;
+    __syncthreads();
+    if (t0 + kTile < c1) fetch(t0 + kTile);
+    for (int r = 0; r < nt; ++r) {
+      const float d = sd2[r][row];
+      const float2 a = *reinterpret_cast<const float2 *>(&sh1[r][col]);
+      const float2 b = *reinterpret_cast<const float2 *>(&ss[r][col]);
+      A0 = fmaf(d, a.x, A0);
+      A1 = fmaf(d, a.y, A1);
+      B0 = fmaf(d, b.x, B0);
+      B1 = fmaf(d, b.y, B1);
+    }
+    // the slice's W1 (96 threads), b1, b2, w3 (8 each) and, in the first slice, b3
+    if (t < 96) {
+      for (int r = 0; r < nt; ++r) v = fmaf(sd1[r][t / kGnnF], sx[r][t % kGnnF], v);
+    } else if (t < 104) {
+      for (int r = 0; r < nt; ++r) v += sd1[r][t - 96];
+    } else if (t < 112) {
+      for (int r = 0; r < nt; ++r) v += sd2[r][t - 104];
+    } else if (t < 120) {
+      for (int r = 0; r < nt; ++r) v = fmaf(sdz[r], sh2[r][t - 112], v);
+    } else if (t == 120) {
+      for (int r = 0; r < nt; ++r) v += sdz[r];
     }
     __syncthreads();
   }
-#pragma unroll
-  for (int q = 0; q < kPer; ++q) {
-    const int j = int(threadIdx.x) + q * kT;
-    if (j < kGnnParams) part[int64_t(blockIdx.x) * kGnnParams + j] = acc[q];
-  }
+  float *out = part + int64_t(blockIdx.x) * kGnnParams;
+  const int w2 = (h0 + row) * kGnnH + col;
+  out[kGnnOffW2a + w2] = A0;
+  out[kGnnOffW2a + w2 + 1] = A1;
+  out[kGnnOffW2b + w2] = B0;
+  out[kGnnOffW2b + w2 + 1] = B1;
+  if (t < 96) out[kGnnOffW1 + h0 * kGnnF + t] = v;
+  else if (t < 104) out[kGnnOffB1 + h0 + t - 96] = v;
+  else if (t < 112) out[kGnnOffB2 + h0 + t - 104] = v;
+  else if (t < 120) out[kGnnOffW3 + h0 + t - 112] = v;
+  else if (t == 120 && h0 == 0) out[kGnnOffB3] = v;
 }
 
 __global__ void k_gnn_wreduce(int chunks, const float *__restrict__ part, float *__restrict__ grad) {
@@ -306,7 +351,7 @@ hipError_t launch_gnn_forward(const float *used, const GnnGraph &g, GnnWork &wk,
   hipLaunchKernelGGL(k_gnn_l1, dim3(grid_of(g.m, kEdgesPW)), dim3(kT), 0, s, g.m, used, g.X, wk.a1);
   hipLaunchKernelGGL(k_gnn_agg, dim3(grid_of(g.n, kEdgesPW)), dim3(kT), 0, s, g.n, g.inc_ptr, g.inc,
                      wk.a1, wk.node);
-  const unsigned gl2 = grid_of(g.m, kEdgesPW) < 4096u ? grid_of(g.m, kEdgesPW) : 4096u;
+  const unsigned nl2 = grid_of(g.m, kEdgesPW * kL2Edges), gl2 = nl2 < 2048u ? nl2 : 2048u;
   hipLaunchKernelGGL(k_gnn_l2, dim3(gl2), dim3(kT), 0, s, g.m, used, g.eu, g.ev, wk.a1, wk.node,
                      wk.a2, wk.z);
   return hipGetLastError();
@@ -325,7 +370,7 @@ hipError_t launch_gnn_backward(const float *used, const GnnGraph &g, GnnWork &wk
   hipLaunchKernelGGL(k_gnn_b1, dim3(grid_of(g.m, kEdgesPW)), dim3(kT), 0, s, g.m, g.eu, g.ev, wk.a1,
                      wk.dnode, wk.d1);
   const int nc = gnn_chunks(g.m);
-  hipLaunchKernelGGL(k_gnn_wgrad, dim3(nc), dim3(kT), 0, s, g.m, g.X, g.eu, g.ev, wk.a1, wk.a2, wk.node,
+  hipLaunchKernelGGL(k_gnn_wgrad, dim3(nc, kSlices), dim3(kT), 0, s, g.m, g.X, g.eu, g.ev, wk.a1, wk.a2, wk.node,
                      wk.d1, wk.d2, dz, wk.part);
   hipLaunchKernelGGL(k_gnn_wreduce, dim3(grid_of(kGnnParams, kT)), dim3(kT), 0, s, nc, wk.part, grad);
   hipLaunchKernelGGL(k_gnn_lreduce, dim3(1), dim3(64), 0, s, int(gdz), wk.lpart, loss_dev);
