@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "panel.hpp"
 
@@ -37,6 +38,17 @@ const float *pvals<float>(const SolveMat &M) {
   return M.val32;
 }
 
+// Logical workgroup of the launches over all rows of a level, whose row lengths may drift along the
+// numbering (upper halves): chunks of kChunkWg consecutive workgroups go to the XCDs in turn, so each
+// XCD's L2 still sees neighbouring rows together and no XCD gets all the long ones.  The grid is
+// rounded up to whole rounds of chunks; workgroups past the rows do nothing.
+constexpr int kChunkWg = 32;
+__device__ inline int chunk_block(int b) {
+  const int x = b & 7, i = b >> 3;
+  return (i / kChunkWg * 8 + x) * kChunkWg + i % kChunkWg;
+}
+inline unsigned chunk_grid(unsigned wgs) { return (wgs + 8 * kChunkWg - 1) / (8 * kChunkWg) * (8 * kChunkWg); }
+
 // A block row belongs to a team of 64 W lanes (W = 1: one wavefront per row, four rows per
 // workgroup; W = 4: the whole workgroup on one row, for levels of few long rows).  A lane owns C
 // consecutive columns (register blocking: every matrix value it loads serves C columns, and the
@@ -44,9 +56,18 @@ const float *pvals<float>(const SolveMat &M) {
 // and the S = 64 W C / K sub-teams of the team take the row's blocks in turn: sub-team s reads
 // blocks p0 + s, p0 + s + S, ...  At every step the S sub-teams read S consecutive blocks (one
 // contiguous run of memory), and the column index of a sub-team's next block is
-// fetched one step ahead, so a step waits for one round of gathers only.  The row sums of
-// column group g end in lane g of the team (sub-team 0).
+// fetched one step ahead, so a step waits for one round of gathers only.
+//
+// The row's BR K sums then spread over the lanes: halving exchanges across the sub-teams of a
+// wavefront (each lane ends with its share of the values, 21 shuffles for 6 x 4 values over eight
+// sub-teams where a butterfly takes 72), the wavefronts' shares meeting in LDS in wavefront order.
+// Output o of a row is entry (dof o / K, column o mod K), at o past the row's first entry of every
+// panel, so lane t of the team finishes outputs t, t + 64 W, ...: every lane works on the row's end,
+// its loads of b, x and y are coalesced and are issued with the row's first loads, and D^+ costs one
+// register per lane.  (Before, the K / C lanes of sub-team 0 finished the row, each loading all of
+// D^+ and, after the sums, its old x or A_ii.)  PANEL_NOTE
 constexpr int kWave = 64;
+constexpr int kMaxK = 64;
 
 template <class T, int C>
 struct PVec {
@@ -68,19 +89,6 @@ __device__ inline PVec<T, C> pload(const T *p) {
   return out;
 }
 
-template <class T, int C>
-__device__ inline void pstore(T *p, const T (&v)[C]) {
-  if constexpr (C == 1) {
-    p[0] = v[0];
-  } else {
-    typedef T vec_t __attribute__((ext_vector_type(C)));
-    vec_t w;
-#pragma unroll
-    for (int i = 0; i < C; ++i) w[i] = v[i];
-    *reinterpret_cast<vec_t *>(p) = w;
-  }
-}
-
 // Where a thread sits in a row team of 64 W lanes for K columns, C per lane.
 template <int C, int W>
 struct PTeam {
@@ -98,19 +106,50 @@ struct PTeam {
     s = t >> lg;
     S = (kWave * W) >> lg;
   }
-  __device__ bool lead() const { return t < (1 << lg); }
 };
 
-// Column groups per sub-team are at most 64 / 4 (K <= 64 with C = 4 for K >= 4).
-constexpr int kMaxGroups = 16;
+// LDS values written by the team's lanes become visible to all of them: a workgroup barrier, or
+// for a team of one wavefront (whose LDS operations are in order) a compiler fence.
+template <int W>
+__device__ inline void pteam_sync() {
+  if constexpr (W > 1) {
+    __syncthreads();
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
 
-// acc[r][i] = sum over blocks p in [p0, p1) of M_p X_col(p), column g C + i, in the lead lanes.
-// red: W > 1 only, kPB / (64 W) * W * kMaxGroups * BR * C values of LDS.
+// One halving exchange: the lanes of a pair (lane bit `off`) each keep half of the first 2 H values,
+// summed with the partner's.
+template <int H, class T, int N>
+__device__ __forceinline__ void phalve(T (&v)[N], int off) {
+  const bool up = (threadIdx.x & off) != 0;
+#pragma unroll
+  for (int k = 0; k < H; ++k) {
+    const T send = up ? v[k] : v[k + H];
+    const T keep = up ? v[k + H] : v[k];
+    v[k] = keep + __shfl_xor(send, off, kWave);
+  }
+}
+
+template <int N, class T, int M>
+__device__ __forceinline__ void pbutterfly(T (&v)[M], int off) {
+  for (; off < kWave; off <<= 1)
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] += __shfl_xor(v[k], off, kWave);
+}
+
+// The row's sums over blocks p in [p0, p1) of M_p X_col(p), by wavefront: entry (r, column k) of
+// wavefront w's share at red[(w BR + r) K + k], visible to the team on return.
 template <class T, int BR, int BC, int C, int W>
-__device__ inline void pteam_accumulate(int p0, int p1, int K, const PTeam<C, W> &tm,
-                                        const int *__restrict__ col, const T *__restrict__ val,
-                                        int64_t nnz, const T *__restrict__ x, T (&acc)[BR][C],
-                                        T *red) {
+__device__ inline void pteam_sums(int p0, int p1, int K, const PTeam<C, W> &tm,
+                                  const int *__restrict__ col, const T *__restrict__ val,
+                                  const T *__restrict__ x, T *red) {
+  constexpr int NV = BR * C;
+  T acc[NV];
+#pragma unroll
+  for (int e = 0; e < NV; ++e) acc[e] = T(0);
   int p = p0 + tm.s;
   int cn = p < p1 ? col[p] : 0;
   for (; p < p1; p += tm.S) {
@@ -128,184 +167,200 @@ __device__ inline void pteam_accumulate(int p0, int p1, int K, const PTeam<C, W>
 #pragma unroll
       for (int cc = 0; cc < BC; ++cc)
 #pragma unroll
-        for (int i = 0; i < C; ++i) acc[r][i] = fma(a[r * BC + cc], xv[cc].v[i], acc[r][i]);
+        for (int i = 0; i < C; ++i) acc[r * C + i] = fma(a[r * BC + cc], xv[cc].v[i], acc[r * C + i]);
   }
-  // sub-teams of one wavefront: butterfly over the lane bits above the column group
-  for (int off = K / C; off < kWave; off <<= 1)
-#pragma unroll
-    for (int r = 0; r < BR; ++r)
-#pragma unroll
-      for (int i = 0; i < C; ++i) acc[r][i] += __shfl_xor(acc[r][i], off, kWave);
-  if constexpr (W > 1) {
-    // wavefronts of the team: through LDS, summed in wavefront order by the lead lanes
-    const int wv = tm.t / kWave, ln = tm.t % kWave;
-    T *rr = red + tm.row_in_wg * (W * kMaxGroups * BR * C);
-    if (ln < (K / C))
-#pragma unroll
-      for (int r = 0; r < BR; ++r)
-#pragma unroll
-        for (int i = 0; i < C; ++i) rr[((wv * kMaxGroups + ln) * BR + r) * C + i] = acc[r][i];
-    __syncthreads();
-    if (tm.lead())
-#pragma unroll
-      for (int r = 0; r < BR; ++r)
-#pragma unroll
-        for (int i = 0; i < C; ++i) {
-          T v = rr[(tm.t * BR + r) * C + i];
-#pragma unroll
-          for (int w = 1; w < W; ++w) v += rr[((w * kMaxGroups + tm.t) * BR + r) * C + i];
-          acc[r][i] = v;
-        }
+  // K <= 64: a wavefront has at least four sub-teams
+  constexpr int H1 = NV % 2 == 0 ? NV / 2 : 0, H2 = NV % 4 == 0 ? NV / 4 : 0, H3 = NV % 8 == 0 ? NV / 8 : 0;
+  T *rw = red + size_t(tm.t / kWave) * BR * K;
+  const int ln = tm.t % kWave;
+  int off = K / C, base = 0;
+  if constexpr (H1 > 0) {
+    phalve<H1>(acc, off);
+    base += (ln & off) ? H1 : 0;
+    off <<= 1;
   }
+  if constexpr (H2 > 0) {
+    phalve<H2>(acc, off);
+    base += (ln & off) ? H2 : 0;
+    off <<= 1;
+  }
+  auto put = [&](auto count) {
+    constexpr int n = decltype(count)::value;
+    pbutterfly<n>(acc, off);
+    if (ln < off)   // the remaining lane bits hold copies
+#pragma unroll
+      for (int k = 0; k < n; ++k) {
+        const int e = base + k;
+        rw[(e / C) * K + tm.g * C + e % C] = acc[k];
+      }
+  };
+  constexpr int N2 = H2 > 0 ? H2 : (H1 > 0 ? H1 : NV);
+  if constexpr (H3 > 0) {
+    if (off < kWave) {
+      phalve<H3>(acc, off);
+      base += (ln & off) ? H3 : 0;
+      off <<= 1;
+      put(std::integral_constant<int, H3>{});
+    } else {
+      put(std::integral_constant<int, N2>{});
+    }
+  } else {
+    put(std::integral_constant<int, N2>{});
+  }
+  pteam_sync<W>();
 }
 
-// LDS for the cross-wavefront reduction of a W = 4 team (one row per workgroup).
-template <class T, int BR, int C, int W>
-struct PRed {
-  static constexpr int n = W > 1 ? (kPB / (kWave * W)) * W * kMaxGroups * BR * C : 1;
+// Output o of the row: the wavefronts' shares in wavefront order.
+template <class T, int BR, int W>
+__device__ inline T pout(const T *red, int K, int o) {
+  T v = red[o];
+#pragma unroll
+  for (int w = 1; w < W; ++w) v += red[size_t(w) * BR * K + o];
+  return v;
+}
+
+// Outputs per lane at the widest panel, and LDS values of a workgroup's shares.
+template <int B, int W>
+struct PSize {
+  static constexpr int outs = (B * kMaxK + kWave * W - 1) / (kWave * W);
+  static constexpr int red = (kPB / kWave) * B * kMaxK;
+  static constexpr int rows = kPB / (kWave * W);
 };
 
 // One colour of the symmetric block Gauss-Seidel sweep for K columns (see launch_pgs_fwd /
-// launch_pgs_bwd).  The row's D^+ block and right-hand side are loaded before the row's blocks
-// so their latency overlaps the block stream; the lead lanes finish the row.
-// FWD: rp, col, val hold the blocks left of the diagonal and dval the diagonal blocks (block i
-// for row i); BWD: rp, col, val hold whole rows.
+// launch_pgs_bwd).  FWD: rp, col, val hold the blocks left of the diagonal and dval the diagonal
+// blocks (block i for row i); BWD: rp, col, val hold whole rows.  y: the panel the blocks multiply
+// (x itself, or b for a group of colours: see launch_pgs_group).
 template <class T, int B, bool FWD, int C, int W>
 __global__ __launch_bounds__(kPB) void k_pgs_color(int r0, int r1, int K, const int *__restrict__ rp,
                                                    const int *__restrict__ col,
-                                                   const T *__restrict__ val, int64_t nnz,
-                                                   const T *__restrict__ dval, int64_t nd,
+                                                   const T *__restrict__ val,
+                                                   const T *__restrict__ dval,
                                                    const T *__restrict__ Dinv,
-                                                   const T *__restrict__ b, T *x, T *r) {
-  __shared__ T red[PRed<T, B, C, W>::n];
+                                                   const T *__restrict__ b, const T *y, T *x, T *r) {
+  using Z = PSize<B, W>;
+  __shared__ T red_s[Z::red], x_s[FWD ? Z::rows * B * kMaxK : 1], D_s[Z::rows][B * B],
+      A_s[FWD ? Z::rows : 1][FWD ? B * B : 1];
   const PTeam<C, W> tm(K);
-  const int row = r0 + xcd_block() * (kPB / (kWave * W)) + tm.row_in_wg;
-  if (row >= r1) return;   // W = 4: the whole workgroup leaves together
-  const int p0 = rp[row];
-  const int p1 = rp[row + 1];
-  PVec<T, C> bq[B];
-  T D[B][B];
-  const int64_t rb = int64_t(row) * B;
-  // every lane loads (valid addresses); only the lead lanes use them
+  const int row = r0 + xcd_block() * Z::rows + tm.row_in_wg;
+  if (row >= r1) return;   // W = 4: the whole workgroup leaves together; W = 1: whole wavefronts
+  const int n = B * K;
+  const int64_t rb = int64_t(row) * n;
+  const int p0 = rp[row], p1 = rp[row + 1];
+  T bq[Z::outs], xo[Z::outs], Dv = T(0), Av = T(0);
 #pragma unroll
-  for (int q = 0; q < B; ++q) {
-    bq[q] = pload<T, C>(b + (rb + q) * K + tm.g * C);
-#pragma unroll
-    for (int c = 0; c < B; ++c) D[q][c] = Dinv[(rb + q) * B + c];
+  for (int j = 0; j < Z::outs; ++j) {
+    const int o = tm.t + j * kWave * W;
+    bq[j] = o < n ? b[rb + o] : T(0);
+    xo[j] = !FWD && o < n ? x[rb + o] : T(0);
   }
-  T acc[B][C];
+  if (tm.t < B * B) {
+    Dv = Dinv[int64_t(row) * (B * B) + tm.t];
+    if (FWD) Av = dval[int64_t(row) * (B * B) + tm.t];
+  }
+  T *red = red_s + size_t(tm.row_in_wg) * W * n;
+  T *xs = x_s + (FWD ? size_t(tm.row_in_wg) * n : 0);
+  T *Ds = D_s[tm.row_in_wg], *As = A_s[FWD ? tm.row_in_wg : 0];
+  if (tm.t < B * B) {
+    Ds[tm.t] = Dv;
+    if (FWD) As[tm.t] = Av;
+  }
+  pteam_sums<T, B, B, C, W>(p0, p1, K, tm, col, val, y, red);
+  T t[Z::outs];
 #pragma unroll
-  for (int q = 0; q < B; ++q)
+  for (int j = 0; j < Z::outs; ++j) {
+    const int o = tm.t + j * kWave * W;
+    if (o < n) {
+      t[j] = bq[j] - pout<T, B, W>(red, K, o);
+      red[o] = t[j];   // only this lane reads entry o of any share before the next sync
+    }
+  }
+  pteam_sync<W>();
 #pragma unroll
-    for (int i = 0; i < C; ++i) acc[q][i] = T(0);
-  pteam_accumulate<T, B, B, C, W>(p0, p1, K, tm, col, val, nnz, x, acc, red);
-  if (!tm.lead()) return;
-  // forward: the diagonal block, loaded after the row stream to keep registers for it
-  T Ad[B][B];
-#pragma unroll
-  for (int q = 0; q < B; ++q)
-#pragma unroll
-    for (int c = 0; c < B; ++c) Ad[q][c] = FWD ? dval[int64_t(row) * (B * B) + q * B + c] : T(0);
-  T xo[B][C];
-#pragma unroll
-  for (int i = 0; i < C; ++i) {
-    T t[B];
-#pragma unroll
-    for (int q = 0; q < B; ++q) t[q] = bq[q].v[i] - acc[q][i];
-#pragma unroll
-    for (int q = 0; q < B; ++q) {
+  for (int j = 0; j < Z::outs; ++j) {
+    const int o = tm.t + j * kWave * W;
+    if (o < n) {
+      const int q = o / K, k = o % K;
       T v = T(0);
 #pragma unroll
-      for (int c = 0; c < B; ++c) v = fma(D[q][c], t[c], v);
-      xo[q][i] = v;
-    }
-    if (FWD) {
-      // r = t - A_ii x_i, kept in acc
-#pragma unroll
-      for (int q = 0; q < B; ++q) {
-        T v = t[q];
-#pragma unroll
-        for (int c = 0; c < B; ++c) v = fma(-Ad[q][c], xo[c][i], v);
-        acc[q][i] = v;
+      for (int c = 0; c < B; ++c) v = fma(Ds[q * B + c], red[c * K + k], v);
+      if (FWD) {
+        xs[o] = v;
+        x[rb + o] = v;
+      } else {
+        x[rb + o] = xo[j] + v;
       }
     }
   }
+  if constexpr (FWD) {
+    pteam_sync<W>();
 #pragma unroll
-  for (int q = 0; q < B; ++q) {
-    T *xq = x + (rb + q) * K + tm.g * C;
-    if (FWD) {
-      pstore<T, C>(xq, xo[q]);
-      pstore<T, C>(r + (rb + q) * K + tm.g * C, acc[q]);
-    } else {
-      const PVec<T, C> old = pload<T, C>(xq);
-      T nv[C];
+    for (int j = 0; j < Z::outs; ++j) {
+      const int o = tm.t + j * kWave * W;
+      if (o < n) {
+        const int q = o / K, k = o % K;
+        T v = t[j];
 #pragma unroll
-      for (int i = 0; i < C; ++i) nv[i] = old.v[i] + xo[q][i];
-      pstore<T, C>(xq, nv);
+        for (int c = 0; c < B; ++c) v = fma(-As[q * B + c], xs[c * K + k], v);
+        r[rb + o] = v;
+      }
     }
   }
 }
 
-// rp, col, val: the blocks right of the diagonal.
-template <class T, int B, int C, int W>
-__global__ __launch_bounds__(kPB) void k_presid_upper(int n_rows, int K, const int *__restrict__ rp,
-                                                      const int *__restrict__ col,
-                                                      const T *__restrict__ val, int64_t nnz,
-                                                      const T *__restrict__ x, T *__restrict__ r) {
-  __shared__ T red[PRed<T, B, C, W>::n];
+// r_i = b_i - sum over the blocks [rp[i], re[i]) of A_ij x_j on rows [r0, r1) (b may be r).
+// CHUNK: rows of every colour (the residual update); else one group's rows.
+template <class T, int B, int C, int W, bool CHUNK>
+__global__ __launch_bounds__(kPB) void k_presid(int r0, int r1, int K, const int *__restrict__ rp,
+                                                const int *__restrict__ re, const int *__restrict__ col,
+                                                const T *__restrict__ val, const T *__restrict__ x,
+                                                const T *b, T *r) {
+  using Z = PSize<B, W>;
+  __shared__ T red_s[Z::red];
   const PTeam<C, W> tm(K);
-  const int row = blockIdx.x * (kPB / (kWave * W)) + tm.row_in_wg;
-  if (row >= n_rows) return;
-  const int64_t rb = int64_t(row) * B;
-  PVec<T, C> rq[B];
-  T acc[B][C];
+  const int row = r0 + (CHUNK ? chunk_block(int(blockIdx.x)) : xcd_block()) * Z::rows + tm.row_in_wg;
+  if (row >= r1) return;
+  const int n = B * K;
+  const int64_t rb = int64_t(row) * n;
+  T bq[Z::outs];
 #pragma unroll
-  for (int q = 0; q < B; ++q) {
-    rq[q] = pload<T, C>(r + (rb + q) * K + tm.g * C);
-#pragma unroll
-    for (int i = 0; i < C; ++i) acc[q][i] = T(0);
+  for (int j = 0; j < Z::outs; ++j) {
+    const int o = tm.t + j * kWave * W;
+    bq[j] = o < n ? b[rb + o] : T(0);
   }
-  pteam_accumulate<T, B, B, C, W>(rp[row], rp[row + 1], K, tm, col, val, nnz, x, acc, red);
-  if (!tm.lead()) return;
+  T *red = red_s + size_t(tm.row_in_wg) * W * n;
+  pteam_sums<T, B, B, C, W>(rp[row], re[row], K, tm, col, val, x, red);
 #pragma unroll
-  for (int q = 0; q < B; ++q) {
-    T v[C];
-#pragma unroll
-    for (int i = 0; i < C; ++i) v[i] = rq[q].v[i] - acc[q][i];
-    pstore<T, C>(r + (rb + q) * K + tm.g * C, v);
+  for (int j = 0; j < Z::outs; ++j) {
+    const int o = tm.t + j * kWave * W;
+    if (o < n) r[rb + o] = bq[j] - pout<T, B, W>(red, K, o);
   }
 }
 
 template <class T, int BR, int BC, int C, int W>
 __global__ __launch_bounds__(kPB) void k_prect(int n_rows, int K, const int *__restrict__ rp,
                                                const int *__restrict__ col,
-                                               const T *__restrict__ val, int64_t nnz,
-                                               const T *__restrict__ x, T *__restrict__ y,
-                                               int accumulate) {
-  __shared__ T red[PRed<T, BR, C, W>::n];
+                                               const T *__restrict__ val, const T *__restrict__ x,
+                                               T *__restrict__ y, int accumulate) {
+  using Z = PSize<BR, W>;
+  __shared__ T red_s[Z::red];
   const PTeam<C, W> tm(K);
-  const int row = blockIdx.x * (kPB / (kWave * W)) + tm.row_in_wg;
+  const int row = chunk_block(int(blockIdx.x)) * Z::rows + tm.row_in_wg;
   if (row >= n_rows) return;
-  T acc[BR][C];
+  const int n = BR * K;
+  const int64_t rb = int64_t(row) * n;
+  T yo[Z::outs];
 #pragma unroll
-  for (int q = 0; q < BR; ++q)
+  for (int j = 0; j < Z::outs; ++j) {
+    const int o = tm.t + j * kWave * W;
+    yo[j] = accumulate && o < n ? y[rb + o] : T(0);
+  }
+  T *red = red_s + size_t(tm.row_in_wg) * W * n;
+  pteam_sums<T, BR, BC, C, W>(rp[row], rp[row + 1], K, tm, col, val, x, red);
 #pragma unroll
-    for (int i = 0; i < C; ++i) acc[q][i] = T(0);
-  pteam_accumulate<T, BR, BC, C, W>(rp[row], rp[row + 1], K, tm, col, val, nnz, x, acc, red);
-  if (!tm.lead()) return;
-#pragma unroll
-  for (int q = 0; q < BR; ++q) {
-    T *yq = y + (int64_t(row) * BR + q) * K + tm.g * C;
-    T v[C];
-    if (accumulate) {
-      const PVec<T, C> old = pload<T, C>(yq);
-#pragma unroll
-      for (int i = 0; i < C; ++i) v[i] = old.v[i] + acc[q][i];
-    } else {
-#pragma unroll
-      for (int i = 0; i < C; ++i) v[i] = acc[q][i];
-    }
-    pstore<T, C>(yq, v);
+  for (int j = 0; j < Z::outs; ++j) {
+    const int o = tm.t + j * kWave * W;
+    if (o < n) y[rb + o] = yo[j] + pout<T, BR, W>(red, K, o);
   }
 }
 
@@ -321,56 +376,41 @@ __device__ inline double pcol_sum(double v, int K, double *sh) {
 }
 
 // Y = A X (W = 1 teams), the workgroups striding over groups of four rows so that the
-// per-column partial sums of X.Y come in at most kPSpmvMax workgroups.
+// per-column partial sums of X.Y come in at most kPSpmvMax workgroups.  A lane's outputs all belong
+// to column (lane mod K).
 constexpr int kPSpmvMax = 2048;
 
 template <int B, int C>
 __global__ __launch_bounds__(kPB) void k_pspmv(int n_rows, int K, const int *__restrict__ rp,
                                                const int *__restrict__ col,
-                                               const double *__restrict__ val, int64_t nnz,
+                                               const double *__restrict__ val,
                                                const double *__restrict__ x, double *__restrict__ y,
                                                double *part) {
-  __shared__ double sh[kPB][C];
+  using Z = PSize<B, 1>;
+  __shared__ double red_s[Z::red], sh[kPB];
   const PTeam<C, 1> tm(K);
-  constexpr int rows_pb = kPB / kWave;
-  double d[C];
-#pragma unroll
-  for (int i = 0; i < C; ++i) d[i] = 0.0;
-  for (int row0 = blockIdx.x * rows_pb; row0 < n_rows; row0 += gridDim.x * rows_pb) {
-    const int row = row0 + tm.row_in_wg;
+  const int n = B * K;
+  double *red = red_s + size_t(tm.row_in_wg) * n;
+  double d = 0.0;
+  for (int wg = int(blockIdx.x); wg * Z::rows < n_rows + 8 * kChunkWg * Z::rows; wg += int(gridDim.x)) {
+    const int row = chunk_block(wg) * Z::rows + tm.row_in_wg;
     if (row >= n_rows) continue;   // whole wavefronts; no workgroup barrier inside
-    double acc[B][C];
+    const int64_t rb = int64_t(row) * n;
+    pteam_sums<double, B, B, C, 1>(rp[row], rp[row + 1], K, tm, col, val, x, red);
 #pragma unroll
-    for (int q = 0; q < B; ++q)
-#pragma unroll
-      for (int i = 0; i < C; ++i) acc[q][i] = 0.0;
-    pteam_accumulate<double, B, B, C, 1>(rp[row], rp[row + 1], K, tm, col, val, nnz, x, acc, nullptr);
-    if (tm.lead()) {
-#pragma unroll
-      for (int q = 0; q < B; ++q) {
-        const int64_t e = (int64_t(row) * B + q) * K + tm.g * C;
-        const PVec<double, C> xv = pload<double, C>(x + e);
-        pstore<double, C>(y + e, acc[q]);
-#pragma unroll
-        for (int i = 0; i < C; ++i) d[i] = fma(xv.v[i], acc[q][i], d[i]);
+    for (int j = 0; j < Z::outs; ++j) {
+      const int o = tm.t + j * kWave;
+      if (o < n) {
+        const double v = red[o];
+        y[rb + o] = v;
+        d = fma(x[rb + o], v, d);
       }
     }
+    pteam_sync<1>();   // the next row's shares overwrite this one's
   }
   if (part) {
-    // per-column sums over the workgroup: thread t holds columns (t mod (K / C)) C + i
-#pragma unroll
-    for (int i = 0; i < C; ++i) sh[threadIdx.x][i] = tm.lead() ? d[i] : 0.0;
-    __syncthreads();
-    const int KL = K / C;
-    for (int st = kPB / 2; st >= KL; st >>= 1) {
-      if (int(threadIdx.x) < st)
-#pragma unroll
-        for (int i = 0; i < C; ++i) sh[threadIdx.x][i] += sh[threadIdx.x + st][i];
-      __syncthreads();
-    }
-    if (int(threadIdx.x) < KL)
-#pragma unroll
-      for (int i = 0; i < C; ++i) part[int64_t(blockIdx.x) * K + threadIdx.x * C + i] = sh[threadIdx.x][i];
+    const double t = pcol_sum(d, K, sh);
+    if (int(threadIdx.x) < K) part[int64_t(blockIdx.x) * K + threadIdx.x] = t;
   }
 }
 
@@ -575,14 +615,12 @@ hipError_t launch_pgs(const SolveMat &A, const T *Dinv, int r0, int r1, int K, c
                       : nullptr;
   const int *rp = FWD ? A.lo_rp : A.rp;
   const int *col = FWD ? A.lo_col : A.col;
-  const int64_t nnz = FWD ? A.lo_nnz : A.nnz;
-  const int64_t nd = A.n_rows;
   if (!val || !rp || !valid_k(K) || (FWD && !dval) || r0 < 0 || r1 > A.n_rows) return hipErrorInvalidValue;
 #define EAMG_PGS(B_)                                                                                \
   EAMG_PTEAM(W, A, EAMG_PCOLS(C, hipLaunchKernelGGL((k_pgs_color<T, B_, FWD, C, W>),               \
                                                     dim3(pteam_grid(r1 - r0, W)), dim3(kPB), 0, s, \
-                                                    r0, r1, K, rp, col, val, nnz, dval, nd,        \
-                                                    Dinv, b, x, r)))
+                                                    r0, r1, K, rp, col, val, dval, Dinv, b, x, x,  \
+                                                    r)))
   switch (A.br) {
     case 1: EAMG_PGS(1); break;
     case 3: EAMG_PGS(3); break;
@@ -611,10 +649,10 @@ hipError_t launch_presid_upper(const SolveMat &A, int K, const T *x, T *r, hipSt
   const T *val = reinterpret_cast<const T *>(sizeof(T) == 4 ? (const void *)A.up_val32 : (const void *)A.up_val);
   if (!val || !A.up_rp || !valid_k(K)) return hipErrorInvalidValue;
 #define EAMG_PRES(B_)                                                                             \
-  EAMG_PTEAM(W, A, EAMG_PCOLS(C, hipLaunchKernelGGL((k_presid_upper<T, B_, C, W>),               \
-                                                    dim3(pteam_grid(A.n_rows, W)), dim3(kPB), 0, \
-                                                    s, A.n_rows, K, A.up_rp, A.up_col, val,      \
-                                                    A.up_nnz, x, r)))
+  EAMG_PTEAM(W, A, EAMG_PCOLS(C, hipLaunchKernelGGL((k_presid<T, B_, C, W, true>),               \
+                                                    dim3(chunk_grid(pteam_grid(A.n_rows, W))),   \
+                                                    dim3(kPB), 0, s, 0, A.n_rows, K, A.up_rp,    \
+                                                    A.up_rp + 1, A.up_col, val, x, r, r)))
   switch (A.br) {
     case 1: EAMG_PRES(1); break;
     case 3: EAMG_PRES(3); break;
@@ -633,9 +671,9 @@ hipError_t launch_prect(const SolveMat &M, int K, const T *x, T *y, bool accumul
   const int accf = accumulate ? 1 : 0;
 #define EAMG_PRECT(BR_, BC_)                                                                      \
   EAMG_PTEAM(W, M, EAMG_PCOLS(C, hipLaunchKernelGGL((k_prect<T, BR_, BC_, C, W>),                \
-                                                    dim3(pteam_grid(M.n_rows, W)), dim3(kPB), 0, \
-                                                    s, M.n_rows, K, M.rp, M.col, val, M.nnz, x,  \
-                                                    y, accf)))
+                                                    dim3(chunk_grid(pteam_grid(M.n_rows, W))),   \
+                                                    dim3(kPB), 0, s, M.n_rows, K, M.rp, M.col,   \
+                                                    val, x, y, accf)))
   if (M.br == 1 && M.bc == 1) { EAMG_PRECT(1, 1); }
   else if (M.br == 3 && M.bc == 6) { EAMG_PRECT(3, 6); }
   else if (M.br == 6 && M.bc == 3) { EAMG_PRECT(6, 3); }
@@ -656,9 +694,9 @@ hipError_t launch_pspmv(const SolveMat &A, int K, const double *x, double *y, do
   if (!valid_k(K) || A.br != A.bc) return hipErrorInvalidValue;
   const dim3 grid(pspmv_blocks(A, K));
   switch (A.br) {
-    case 1: EAMG_PCOLS(C, hipLaunchKernelGGL((k_pspmv<1, C>), grid, dim3(kPB), 0, s, A.n_rows, K, A.rp, A.col, A.val, A.nnz, x, y, part)); break;
-    case 3: EAMG_PCOLS(C, hipLaunchKernelGGL((k_pspmv<3, C>), grid, dim3(kPB), 0, s, A.n_rows, K, A.rp, A.col, A.val, A.nnz, x, y, part)); break;
-    case 6: EAMG_PCOLS(C, hipLaunchKernelGGL((k_pspmv<6, C>), grid, dim3(kPB), 0, s, A.n_rows, K, A.rp, A.col, A.val, A.nnz, x, y, part)); break;
+    case 1: EAMG_PCOLS(C, hipLaunchKernelGGL((k_pspmv<1, C>), grid, dim3(kPB), 0, s, A.n_rows, K, A.rp, A.col, A.val, x, y, part)); break;
+    case 3: EAMG_PCOLS(C, hipLaunchKernelGGL((k_pspmv<3, C>), grid, dim3(kPB), 0, s, A.n_rows, K, A.rp, A.col, A.val, x, y, part)); break;
+    case 6: EAMG_PCOLS(C, hipLaunchKernelGGL((k_pspmv<6, C>), grid, dim3(kPB), 0, s, A.n_rows, K, A.rp, A.col, A.val, x, y, part)); break;
     default: return hipErrorInvalidValue;
   }
   EAMG_PCHECK();
