@@ -133,10 +133,9 @@ typedef struct {
  *                     its upper block triangle, symmetrized.  The hierarchy, and the V-cycle as
  *                     an operator, are those of the sparse path; only the rounding differs.  No
  *                     tail when that level is the coarsest or no level qualifies.  Memory: about
- *                     1.5 ld^2 doubles (the full matrix, kept for the block panels, and the upper
- *                     tiles; + 0.5 ld^2 floats with dense_tail_fp32), ld = the tail's dofs
- *                     rounded up to 128; during setup also work panels of about 2 ld doubles per
- *                     column of a pass.
+ *                     0.5 ld^2 doubles (the upper tiles; + 0.5 ld^2 floats with dense_tail_fp32),
+ *                     ld = the tail's dofs rounded up to 128; during setup also the full matrix
+ *                     (ld^2) and work panels of about 2 ld doubles per column of a pass.
  *  dense_tail_fp32    0: the FP32 V-cycle applies the dense tail, which holds the coarsest
  *                     level's inverse, from its FP64 matrix with FP64 accumulation (FP32 vectors
  *                     in and out), as it applies the coarsest inverse without a tail (default).

@@ -70,7 +70,7 @@ BatchWork *ensure_work(eamg_hierarchy *h, int K, bool f32) {
     w->part = w->arena.alloc<double>(size_t(nparts) * K);
     w->scal = w->arena.alloc<double>(size_t(PS_COUNT) * K);
     w->dense = w->arena.alloc<double>(std::max<size_t>(
-        1, std::max(dense_panel_work_doubles(h->nL, K), dense_panel_work_doubles(h->nT, K))));
+        1, h->tail_level >= 0 ? sym_panel_work_doubles(h->nT, K) : dense_panel_work_doubles(h->nL, K)));
     hip_check(hipHostMalloc(reinterpret_cast<void **>(&w->scal_h), sizeof(double) * PS_COUNT * K,
                             hipHostMallocDefault),
               "hipHostMalloc");
@@ -112,9 +112,10 @@ void pvcycle_t(eamg_hierarchy *h, BatchWork *w, size_t l, const T *b, T *x, hipS
   const double vs = sizeof(T);
   Level &L = h->lv[l];
   if (int(l) == h->tail_level) {
-    const double by = double(h->nT) * h->nT * 8.0 + 2.0 * h->nT * K * vs;
-    timed(h, "dense tail", lvname(h, l, "k_dense_panel_mfma<" + ty + ">"), by, s,
-          [&] { return launch_dense_panel<T>(h->nT, h->ldT, K, h->tail, b, x, w->dense, s); });
+    const double by = double(sym_entries(h->nT)) * 8.0 + 2.0 * 8.0 * double(sym_panel_work_doubles(h->nT, K)) +
+                      2.0 * h->nT * K * vs;
+    timed(h, "dense tail", lvname(h, l, "k_dense_panel_sym<" + ty + ">"), by, s,
+          [&] { return launch_dense_panel_sym<T>(h->nT, K, h->tailS, b, x, w->dense, s); });
     return;
   }
   if (l + 1 == h->lv.size()) {
@@ -443,10 +444,9 @@ DenseTail make_dense_tail(eamg_hierarchy *h, size_t t, DevArena &out, hipStream_
 }
 
 void build_dense_tail(eamg_hierarchy *h, size_t t, hipStream_t s) {
-  const DenseTail d = make_dense_tail(h, t, h->arena, s);
-  h->tail = d.T;
+  DevArena full;
+  const DenseTail d = make_dense_tail(h, t, full, s);
   h->nT = d.n;
-  h->ldT = d.ld;
   h->tailS = h->arena.alloc<double>(sym_entries(d.n));
   hip_check(launch_pack_sym<double>(d.n, d.ld, d.T, h->tailS, s), "pack tail");
   if (h->prm.vcycle_fp32 && h->prm.dense_tail_fp32) {

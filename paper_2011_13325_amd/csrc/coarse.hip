@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "coarse.hpp"
 
@@ -467,6 +468,156 @@ __global__ __launch_bounds__(kThreads) void k_dense_panel_sum(int64_t nk, int S,
   Y[i] = T(v);
 }
 
+// ---- symmetric packed panel product ----------------------------------------------------------
+// Y = S X for the packed upper tiles S of a symmetric matrix and up to 16 columns of a panel
+// (v_mfma_f64_16x16x4).  A workgroup takes a run of up to R tiles (i, j), (i, j + 1), .. of one block
+// row; wavefront w columns 32 w .. 32 w + 31 of each tile, all 128 rows, as 16 x 16 sub-blocks.  A
+// sub-block multiplies x_j into the wavefront's sums of y_i, kept in registers over the run and added
+// across the wavefronts at its end, and, off the diagonal, transposed, x_i (in LDS) into its sums of y_j,
+// complete within the wavefront.  Both operands of a sub-block are loaded in their own lane layout
+// (lane l: row l % 16, columns 4 (l / 16) + s in step s; transposed: rows 4 (l / 16) + s, column
+// l % 16), the second from L1.  y_i sums go to P[run], y_j sums to Q[tile]; k_dense_panel_sym_sum adds
+// each output's parts in ascending order, so the result is reproducible.
+// Bound: the stored half of the matrix from HBM.  Reading the whole matrix row by row (16 rows 100 KB
+// apart per wavefront) took 473 us for 13,416 dofs and 8 columns (3.0 TB/s of twice the bytes); now
+// 236 us and 26 us for the sums.
+constexpr int kSymCols = 16;
+
+inline int sym_run_len(int nb) {
+  const int64_t r = sym_tiles(nb) / 2048;   // about two thousand workgroups
+  return int(r < 1 ? 1 : (r > 8 ? 8 : r));
+}
+inline int64_t sym_runs(int nb, int R) {
+  int64_t t = 0;
+  for (int i = 0; i < nb; ++i) t += (nb - i + R - 1) / R;
+  return t;
+}
+
+template <class T>
+__global__ __launch_bounds__(256, 2) void k_dense_panel_sym(int n, int nb, int R, int K, int c0, int Kc,
+                                                         const double *__restrict__ S,
+                                                         const T *__restrict__ X, double *__restrict__ P,
+                                                         double *__restrict__ Q) {
+  constexpr int kPad = kSymCols;   // columns held, zero past Kc
+  constexpr int kBatch = 4;
+  __shared__ double xi[kSymTile * kPad];
+  // block row and first tile of this run
+  int i = 0, g = int(blockIdx.x);
+  for (int c = (nb + R - 1) / R; g >= c; c = (nb - i + R - 1) / R) {
+    g -= c;
+    ++i;
+  }
+  const int j0 = i + g * R, j1 = min(nb, j0 + R);
+  for (int e = threadIdx.x; e < kSymTile * kPad; e += 256) {
+    const int d = i * kSymTile + e / kPad, c = e % kPad;
+    xi[e] = (d < n && c < Kc) ? double(X[size_t(d) * K + c0 + c]) : 0.0;
+  }
+  __syncthreads();
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lo = l & 15, hi = l >> 4;
+  dbl4 yi[8];
+#pragma unroll
+  for (int rg = 0; rg < 8; ++rg) yi[rg] = dbl4{0.0, 0.0, 0.0, 0.0};
+  const size_t tile0 = size_t(i) * nb - size_t(i) * (i - 1) / 2 - i;   // packed index of (i, j) is tile0 + j
+  auto tile = [&](int j, auto offdiag) {
+    constexpr bool off = decltype(offdiag)::value;
+    const double *Tl = S + (tile0 + j) * (kSymTile * kSymTile);
+#pragma unroll
+    for (int cs = 0; cs < 2; ++cs) {
+      const int cb = 32 * w + 16 * cs;            // the sub-blocks' first column
+      double xj[4];
+#pragma unroll
+      for (int st = 0; st < 4; ++st) {
+        const int d = j * kSymTile + cb + 4 * hi + st;
+        const double v = double(X[size_t(min(d, n - 1)) * K + c0 + min(lo, Kc - 1)]);
+        xj[st] = (d < n && lo < Kc) ? v : 0.0;
+      }
+      dbl4 yj = dbl4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int r0 = 0; r0 < 8; r0 += kBatch) {
+        // kBatch sub-blocks in flight, both operand layouts
+        dbl4 a[kBatch];
+        double bt[kBatch][4];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {
+          const double *sb = Tl + size_t(16 * (r0 + q)) * kSymTile + cb;
+          a[q] = *reinterpret_cast<const dbl4 *>(sb + size_t(lo) * kSymTile + 4 * hi);
+          if constexpr (off)
+#pragma unroll
+            for (int st = 0; st < 4; ++st) bt[q][st] = sb[size_t(4 * hi + st) * kSymTile + lo];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {
+          const int rg = r0 + q;
+#pragma unroll
+          for (int st = 0; st < 4; ++st) {
+            yi[rg] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q][st], xj[st], yi[rg], 0, 0, 0);
+            if constexpr (off)
+              yj = __builtin_amdgcn_mfma_f64_16x16x4f64(bt[q][st], xi[(16 * rg + 4 * hi + st) * kPad + lo], yj, 0, 0, 0);
+          }
+        }
+      }
+      if constexpr (off) {
+        double *q = Q + (tile0 + j) * (size_t(kSymTile) * Kc);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (lo < Kc) q[size_t(cb + hi + 4 * v) * Kc + lo] = yj[v];
+      }
+    }
+  };
+  int j = j0;
+  if (j == i) {
+    tile(j, std::false_type{});
+    ++j;
+  }
+  for (; j < j1; ++j) tile(j, std::true_type{});
+  // y_i: the wavefronts' sums in wavefront order, through the x_i buffer
+  for (int s = 0; s < 4; ++s) {
+    __syncthreads();
+    if (w == s)
+#pragma unroll
+      for (int rg = 0; rg < 8; ++rg)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          double *o = xi + size_t(16 * rg + hi + 4 * v) * kPad + lo;
+          *o = s == 0 ? yi[rg][v] : *o + yi[rg][v];
+        }
+  }
+  __syncthreads();
+  double *p = P + size_t(blockIdx.x) * kSymTile * Kc;
+  for (int e = threadIdx.x; e < kSymTile * Kc; e += 256) p[e] = xi[size_t(e / Kc) * kPad + e % Kc];
+}
+
+// Entry (d, c) of Y: its block row's runs, then the mirrored tiles (i, block row), i ascending.
+template <class T>
+__global__ __launch_bounds__(kThreads) void k_dense_panel_sym_sum(int n, int nb, int R, int K, int c0,
+                                                                  int Kc, const double *__restrict__ P,
+                                                                  const double *__restrict__ Q,
+                                                                  T *__restrict__ Y) {
+  const int64_t e = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+  if (e >= int64_t(n) * Kc) return;
+  const int d = int(e / Kc), c = int(e % Kc);
+  const int b = d / kSymTile;
+  const size_t at = size_t(d % kSymTile) * Kc + c, len = size_t(kSymTile) * Kc;
+  int g0 = 0;
+  for (int i = 0; i < b; ++i) g0 += (nb - i + R - 1) / R;
+  const int runs = (nb - b + R - 1) / R;
+  double v = 0.0;
+  for (int g = 0; g < runs; ++g) v += P[size_t(g0 + g) * len + at];
+  double u0 = 0.0, u1 = 0.0, u2 = 0.0, u3 = 0.0;
+  int i = 0;
+  auto tile = [&](int a) { return size_t(a) * nb - size_t(a) * (a - 1) / 2 + (b - a); };
+  for (; i + 4 <= b; i += 4) {
+    u0 += Q[tile(i) * len + at];
+    u1 += Q[tile(i + 1) * len + at];
+    u2 += Q[tile(i + 2) * len + at];
+    u3 += Q[tile(i + 3) * len + at];
+  }
+  for (; i < b; ++i) u0 += Q[tile(i) * len + at];
+  Y[size_t(d) * K + c0 + c] = T(v + ((u0 + u1) + (u2 + u3)));
+}
+
 }  // namespace
 
 hipError_t launch_dense_assemble(int n, int bs, const int64_t *rp, const int *col,
@@ -534,6 +685,27 @@ hipError_t launch_dense_panel(int n, int ld, int K, const double *D, const T *X,
   return hipGetLastError();
 }
 
+size_t sym_panel_work_doubles(int n, int K) {
+  const int nb = sym_blocks(n);
+  return size_t(sym_runs(nb, sym_run_len(nb)) + sym_tiles(nb)) * kSymTile * (K < kSymCols ? K : kSymCols);
+}
+
+template <class T>
+hipError_t launch_dense_panel_sym(int n, int K, const double *S, const T *X, T *Y, double *work,
+                                  hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  if (!S || !work || K < 1 || K > 64 || (K & (K - 1))) return hipErrorInvalidValue;
+  const int nb = sym_blocks(n), R = sym_run_len(nb), Kc = K < kSymCols ? K : kSymCols;
+  const unsigned runs = unsigned(sym_runs(nb, R));
+  double *P = work, *Q = work + size_t(runs) * kSymTile * Kc;
+  for (int c0 = 0; c0 < K; c0 += Kc) {
+    hipLaunchKernelGGL(k_dense_panel_sym<T>, dim3(runs), dim3(256), 0, s, n, nb, R, K, c0, Kc, S, X, P, Q);
+    hipLaunchKernelGGL(k_dense_panel_sym_sum<T>, dim3(cdiv(int64_t(n) * Kc, kThreads)), dim3(kThreads), 0, s, n,
+                       nb, R, K, c0, Kc, P, Q, Y);
+  }
+  return hipGetLastError();
+}
+
 template <class TM>
 hipError_t launch_pack_sym(int n, int ld, const double *D, TM *S, hipStream_t s) {
   if (n == 0) return hipSuccess;
@@ -566,6 +738,8 @@ hipError_t launch_dense_symv_multi(int nparts, const SymPart *parts, int tiles, 
   return hipGetLastError();
 }
 
+template hipError_t launch_dense_panel_sym<double>(int, int, const double *, const double *, double *, double *, hipStream_t);
+template hipError_t launch_dense_panel_sym<float>(int, int, const double *, const float *, float *, double *, hipStream_t);
 template hipError_t launch_pack_sym<double>(int, int, const double *, double *, hipStream_t);
 template hipError_t launch_pack_sym<float>(int, int, const double *, float *, hipStream_t);
 template hipError_t launch_dense_symv<double, double>(int, const double *, const double *, double *, double *, hipStream_t);

@@ -71,6 +71,14 @@ hipError_t launch_pack_sym(int n, int ld, const double *D, TM *S, hipStream_t s)
 template <class TM, class TV>
 hipError_t launch_dense_symv(int n, const TM *S, const TV *x, TV *y, double *W, hipStream_t s);
 
+// Y = S X for the packed symmetric FP64 S and a panel of K columns (K a power of two in [1, 64];
+// entry (dof, k) at dof * K + k; FP64 sums): on the matrix cores, up to 16 columns per pass, the parts
+// of every output through `work` (sym_panel_work_doubles(n, K) doubles) in a fixed order.
+size_t sym_panel_work_doubles(int n, int K);
+template <class T>
+hipError_t launch_dense_panel_sym(int n, int K, const double *S, const T *X, T *Y, double *work,
+                                  hipStream_t s);
+
 // One matrix of a multi-part symmetric product: packed upper tiles S (TM values) of an n x n
 // matrix (nb = sym_blocks(n)) applied to x[off .. off + n) into y[off .. off + n).  Among all
 // parts of a launch it has tiles t0 .. t0 + sym_tiles(nb) - 1 and rows row0 .. row0 + n - 1, and

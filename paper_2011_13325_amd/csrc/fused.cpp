@@ -486,6 +486,11 @@ eamg_status eamg_fuse(int32_t nsys, eamg_hierarchy *const *hs, int32_t dense_tai
               make_dense_tail(H, size_t(d), F->arena, s);
       }
     for (int l = 0; l < U; ++l) build_fused_level(F.get(), sys, F->fused->depth, ord, l, s);
+    // packed by now
+    for (DenseTail &d : F->fused->own) {
+      F->arena.release(d.T);
+      d.T = nullptr;
+    }
     // level 0: natural -> fused maps, segments of the CG vectors, CG workspace
     FusedInfo &I = *F->fused;
     const FusedOrder &o0 = ord[0];

@@ -285,8 +285,8 @@ struct DenseTail {
   int n = 0, ld = 0;
 };
 DenseTail make_dense_tail(eamg_hierarchy *h, size_t t, DevArena &out, hipStream_t s);
-// make_dense_tail into h's own arena, kept as h->tail with its packed upper tiles (h->tailS, and
-// h->tailS32 with dense_tail_fp32); sets h->tail_level = t.
+// The packed upper tiles of make_dense_tail's matrix in h's own arena (h->tailS, and h->tailS32 with
+// dense_tail_fp32); sets h->tail_level = t.
 void build_dense_tail(eamg_hierarchy *h, size_t t, hipStream_t s);
 
 }  // namespace eamg
@@ -301,12 +301,12 @@ struct eamg_hierarchy {
   int nL = 0;                 // coarsest dofs
   int ldL = 0;                // leading dimension of Ainv (nL rounded up to 128)
   // dense V-cycle tail: the V-cycle on levels tail_level .. coarsest as one dense matrix in the
-  // colour-major numbering of tail_level (row-major, zero padding), or tail_level = -1
+  // colour-major numbering of tail_level, or tail_level = -1
   int tail_level = -1;
-  int nT = 0, ldT = 0;
-  double *tail = nullptr;
+  int nT = 0;
   // the tail's upper tiles, packed (the V-cycle operator is symmetric): FP64 and, with
-  // dense_tail_fp32, FP32; the single-vector V-cycle reads these, with tailW as its workspace
+  // dense_tail_fp32, FP32; the panels read the FP64 tiles, the single-vector V-cycle either, with
+  // tailW as its workspace
   double *tailS = nullptr;
   float *tailS32 = nullptr;
   double *tailW = nullptr;
