@@ -164,7 +164,7 @@ def _kappa(E, h):
 
 
 # CG kernels of the iteration (everything else the profiler records is the preconditioner)
-_CG_KERNELS = ("k_spmv", "k_dot", "k_reduce", "k_update_xr", "k_update_p")
+_CG_KERNELS = ("k_spmv", "k_dot", "k_reduce", "k_update_xr", "k_update_p", "k_publish")
 
 
 def _profiled(E, hier, b, x, steps, precond, stream):

@@ -779,35 +779,78 @@ void vcycle(eamg_hierarchy *h, const double *r, double *z, bool f32, hipStream_t
   }
 }
 
-// One PCG iteration after the stopping test: z = V(r), beta, p = z + beta p, q = A p, alpha,
-// x += alpha p, r -= alpha q, r.r, and the scalars copied to pinned host memory.
-void enqueue_iteration(eamg_hierarchy *h, bool f32, hipStream_t s) {
+// The second half of a PCG iteration, p set: q = A p, alpha, x += alpha p, r -= alpha q, r.r, and the
+// scalars published to the host.
+void pcg_step(eamg_hierarchy *h, bool f32, hipStream_t s) {
   const Level &L0 = h->lv[0];
   const SolveMat &A = L0.Am;
   const int64_t N = int64_t(L0.n) * L0.bs;
-  const int nd = dot_blocks(N);
-  const int ns = spmv_blocks(A);
+  const double vecb = 8.0 * N;
+  const int nd = dot_blocks(N), ns = spmv_blocks(A);
   if (nd > h->part_cap || ns > h->part_cap) fail(EAMG_ERR_INVALID_ARG, "partial-sum buffer too small");
+  timed(h, "spmv", tname("k_spmv", L0.bs, L0.bs), launch_bytes(L0.sh_spmv, LK_SPMV, L0.bs, L0.bs, 8.0, 1) + 8.0 * ns,
+        s, [&] { return launch_spmv(A, h->p, h->q, h->part, s); });
+  const bool inl = ns <= kInlineParts;
+  if (!inl)
+    timed(h, "reduce", "k_reduce", 8.0 * ns, s, [&] { return launch_reduce(ns, h->part, h->scal, SC_PQ, s); });
+  timed(h, "update_xr", "k_update_xr", 6.0 * vecb + (f32 ? 4.0 * N : 0.0) + 8.0 * nd, s, [&] {
+    return launch_update_xr(N, h->scal, h->x, h->r, h->p, h->q, h->part_rr, inl ? ns : 0, inl ? h->part : nullptr, s,
+                            f32 ? h->lv[0].b32 : nullptr);
+  });
+  timed(h, "publish", "k_publish", 8.0 * nd, s,
+        [&] { return launch_publish(nd, h->part_rr, h->scal, h->ring_d, s); });
+}
+
+// p = z + beta p, z the V-cycle's output (FP32: level 0's x32, else h->z).
+void pcg_direction(eamg_hierarchy *h, bool f32, hipStream_t s) {
+  const Level &L0 = h->lv[0];
+  const int64_t N = int64_t(L0.n) * L0.bs;
+  const double vecb = 8.0 * N;
+  const int nd = dot_blocks(N);
   if (f32) {
-    // the FP32 V-cycle reads r's FP32 copy (written with r by the previous update) and its output
-    // z is read in FP32 by the dot product and the p update
-    vcycle_t<float>(h, 0, L0.b32, L0.x32, s);
-    hip_check(launch_dot(N, h->r, L0.x32, h->part, s), "dot");
-    hip_check(launch_reduce(nd, h->part, h->scal, SC_RZ, RED_BETA, s), "reduce");
-    hip_check(launch_update_p(N, h->scal, L0.x32, h->p, s), "update_p");
+    timed(h, "dot", "k_dot<float>", vecb + 4.0 * N + 8.0 * nd, s,
+          [&] { return launch_dot(N, h->r, L0.x32, h->part, s); });
+    timed(h, "update_p", "k_update_p<float>", 2.0 * vecb + 4.0 * N, s,
+          [&] { return launch_update_p(N, h->scal, L0.x32, h->p, nd, h->part, s); });
   } else {
-    vcycle(h, h->r, h->z, false, s);
-    hip_check(launch_dot(N, h->r, h->z, h->part, s), "dot");
-    hip_check(launch_reduce(nd, h->part, h->scal, SC_RZ, RED_BETA, s), "reduce");
-    hip_check(launch_update_p(N, h->scal, h->z, h->p, s), "update_p");
+    timed(h, "dot", "k_dot", 2.0 * vecb + 8.0 * nd, s, [&] { return launch_dot(N, h->r, h->z, h->part, s); });
+    timed(h, "update_p", "k_update_p", 3.0 * vecb, s,
+          [&] { return launch_update_p(N, h->scal, h->z, h->p, nd, h->part, s); });
   }
-  hip_check(launch_spmv(A, h->p, h->q, h->part, s), "spmv");
-  hip_check(launch_reduce(ns, h->part, h->scal, SC_PQ, RED_ALPHA, s), "reduce");
-  hip_check(launch_update_xr(N, h->scal, h->x, h->r, h->p, h->q, h->part, s, f32 ? L0.b32 : nullptr),
-            "update_xr");
-  hip_check(launch_reduce(nd, h->part, h->scal, SC_RR, RED_STORE, s), "reduce");
-  hip_check(hipMemcpyAsync(h->scal_h, h->scal, sizeof(double) * SC_COUNT, hipMemcpyDeviceToHost, s),
-            "copy");
+}
+
+// One PCG iteration after the stopping test.  With the FP32 V-cycle, it reads r's FP32 copy (written
+// with r by the previous update) and its output z is read in FP32 by the dot product and the p update.
+void enqueue_iteration(eamg_hierarchy *h, bool f32, hipStream_t s) {
+  if (f32)
+    vcycle_t<float>(h, 0, h->lv[0].b32, h->lv[0].x32, s);
+  else
+    vcycle(h, h->r, h->z, false, s);
+  pcg_direction(h, f32, s);
+  pcg_step(h, f32, s);
+}
+
+// Estimated time of one iteration: its launches in a chain plus its bytes at the HBM rate.
+double iteration_seconds(const eamg_hierarchy *h, bool f32) {
+  const double vs = f32 ? 4.0 : 8.0;
+  const Level &L0 = h->lv[0];
+  double launches = 6.0, bytes = launch_bytes(L0.sh_spmv, LK_SPMV, L0.bs, L0.bs, 8.0, 1) + 11.0 * 8.0 * L0.n * L0.bs;
+  for (size_t l = 0; l < h->lv.size(); ++l) {
+    const Level &L = h->lv[l];
+    if (int(l) == h->tail_level || l + 1 == h->lv.size()) {
+      launches += 2.0;
+      bytes += double(int(l) == h->tail_level ? sym_entries(h->nT) : size_t(h->nL) * h->nL) * 8.0;
+      break;
+    }
+    launches += 3.0;
+    bytes += launch_bytes(L.sh_resid, LK_RESID, L.bs, L.bs, vs, 1) + launch_bytes(L.sh_R, LK_RECT, L.kc, L.bs, vs, 1) +
+             launch_bytes(L.sh_P, LK_RECT_ACC, L.bs, L.kc, vs, 1);
+    for (int k = 0; k < L.stages(); ++k) {
+      launches += stage_launches(L, k, true) + stage_launches(L, k, false);
+      bytes += stage_bytes(L, k, true, vs) + stage_bytes(L, k, false, vs);
+    }
+  }
+  return launches * 3.5e-6 + bytes / 4.5e12;
 }
 
 // Capture enqueue_iteration once; on any failure fall back to eager launches.
@@ -853,8 +896,8 @@ struct SolveRun {
   bool f32 = false;
   hipStream_t s = nullptr;
   int64_t N = 0;
-  int nd = 0, ns = 0;
-  double vecb = 0.0, bnorm = 0.0;
+  int nd = 0;
+  double bnorm = 0.0;
   int iters = 0;
   double rel = 0.0, rel_true = 0.0, ms = 0.0;
   bool converged = false;
@@ -879,9 +922,7 @@ struct SolveRun {
     const Level &L0 = h->lv[0];
     N = int64_t(L0.n) * L0.bs;
     nd = dot_blocks(N);
-    ns = spmv_blocks(L0.Am);
-    if (nd > h->part_cap || ns > h->part_cap) fail(EAMG_ERR_INVALID_ARG, "partial-sum buffer too small");
-    vecb = double(N) * 8.0;
+    if (nd > h->part_cap) fail(EAMG_ERR_INVALID_ARG, "partial-sum buffer too small");
     hip_check(hipEventCreate(&e0), "event");
     hip_check(hipEventCreate(&e1), "event");
   }
@@ -899,38 +940,37 @@ struct SolveRun {
       hip_check(launch_copy(N, h->r, h->z, s), "copy");
   }
   float *r32() const { return f32 ? h->lv[0].b32 : nullptr; }
-  // r.z (partials into part) and p = z + beta p, z in FP64 or the FP32 V-cycle's output
-  void dot_rz() {
-    if (f32)
-      timed(h, "dot", "k_dot<float>", vecb + 4.0 * N + 8.0 * nd, s,
-            [&] { return launch_dot(N, h->r, h->lv[0].x32, h->part, s); });
-    else
-      timed(h, "dot", "k_dot", 2.0 * vecb + 8.0 * nd, s,
-            [&] { return launch_dot(N, h->r, h->z, h->part, s); });
-  }
-  void update_p() {
-    if (f32)
-      timed(h, "update_p", "k_update_p<float>", 2.0 * vecb + 4.0 * N, s,
-            [&] { return launch_update_p(N, h->scal, h->lv[0].x32, h->p, s); });
-    else
-      timed(h, "update_p", "k_update_p", 3.0 * vecb, s,
-            [&] { return launch_update_p(N, h->scal, h->z, h->p, s); });
-  }
-  void update_xr() {
-    timed(h, "update_xr", "k_update_xr", 6.0 * vecb + (f32 ? 4.0 * N : 0.0) + 8.0 * nd, s,
-          [&] { return launch_update_xr(N, h->scal, h->x, h->r, h->p, h->q, h->part, s, r32()); });
-  }
-
-  double spmv_bytes() const {
-    const Level &L0 = h->lv[0];
-    return launch_bytes(L0.sh_spmv, LK_SPMV, L0.bs, L0.bs, 8.0, 1) + 8.0 * ns;
-  }
-
   void copy_scalars() {
     hip_check(hipMemcpyAsync(h->scal_h, h->scal, sizeof(double) * SC_COUNT, hipMemcpyDeviceToHost, s),
               "copy");
   }
   void wait() { hip_check(hipStreamSynchronize(s), "sync"); }
+
+  // The published record of iteration k (1, 2, ..), once the device has written it.
+  const double *record(int k) const { return h->scal_h + SC_COUNT + 1 + size_t(k % kRing) * kRecord; }
+  bool published(int k) const {
+    return __atomic_load_n(reinterpret_cast<const int64_t *>(record(k) + kRecord - 1), __ATOMIC_ACQUIRE) ==
+           bits_of(double(k));
+  }
+  static int64_t bits_of(double v) {
+    int64_t b;
+    std::memcpy(&b, &v, sizeof(b));
+    return b;
+  }
+  // Wait for it in host memory: the stream itself may already hold the next iteration.  The stream is
+  // asked now and then, so that an error there ends the wait.
+  void await(int k) const {
+    for (int spins = 0;; ++spins) {
+      if (published(k)) return;
+      if (spins % 4096 == 4095) {
+        const hipError_t e = hipStreamQuery(s);
+        if (e == hipErrorNotReady) continue;
+        hip_check(e, "iteration");
+        if (published(k)) return;
+        fail(EAMG_ERR_HIP, "an iteration ended without its scalars");
+      }
+    }
+  }
 
   // start() in phases: each enqueue_* ends with the scalars copied to the host, each complete_*
   // (after the stream has been synchronised) reads them.  Interleaving the phases of several
@@ -943,11 +983,12 @@ struct SolveRun {
     h->cg_alpha.clear();
     h->cg_beta.clear();
     hip_check(hipEventRecord(e0, s), "event");
-    hip_check(launch_fill(SC_COUNT, 0.0, h->scal, s), "fill");
+    for (int k = 0; k < kRing; ++k) h->scal_h[SC_COUNT + 1 + size_t(k) * kRecord + kRecord - 1] = 0.0;
+    hip_check(launch_init_scal(sp.rtol, h->scal, s), "init");
     hip_check(launch_perm_in(L0.n, L0.bs, L0.perm_d, h->dir, b_dev, h->bp, s), "perm_in");
     hip_check(launch_finite_check(N, h->bp, h->scal, SC_NONFINITE, s), "finite");
     hip_check(launch_dot(N, h->bp, h->bp, h->part, s), "dot");
-    hip_check(launch_reduce(nd, h->part, h->scal, SC_BB, RED_STORE, s), "reduce");
+    hip_check(launch_reduce(nd, h->part, h->scal, SC_BB, s), "reduce");
     if (sp.use_x0) {
       hip_check(launch_perm_in(L0.n, L0.bs, L0.perm_d, h->dir, x_dev, h->x, s), "perm_in");
       hip_check(launch_spmv(A, h->x, h->q, nullptr, s), "spmv");
@@ -974,16 +1015,19 @@ struct SolveRun {
       hip_check(launch_convert<float, double>(N, h->lv[0].x32, h->p, s), "convert");
     else
       hip_check(launch_copy(N, h->z, h->p, s), "copy");
-    dot_rz();
-    hip_check(launch_reduce(nd, h->part, h->scal, SC_RHO, RED_STORE, s), "reduce");
+    if (f32)
+      hip_check(launch_dot(N, h->r, h->lv[0].x32, h->part, s), "dot");
+    else
+      hip_check(launch_dot(N, h->r, h->z, h->part, s), "dot");
+    hip_check(launch_reduce(nd, h->part, h->scal, SC_RZ, s), "reduce");
     copy_scalars();
   }
   void complete_start_b() {
-    const double rho0 = h->scal_h[SC_RHO];
+    const double rho0 = h->scal_h[SC_RZ];
     if (!(rho0 > 0.0) || !std::isfinite(rho0)) {
       // r = b - A x0 may already be zero (exact x0); otherwise the preconditioner is not SPD
       hip_check(launch_dot(N, h->r, h->r, h->part, s), "dot");
-      hip_check(launch_reduce(nd, h->part, h->scal, SC_RR, RED_STORE, s), "reduce");
+      hip_check(launch_reduce(nd, h->part, h->scal, SC_RR, s), "reduce");
       fetch_scalars(h, s);
       if (h->scal_h[SC_RR] != 0.0) fail(EAMG_ERR_BREAKDOWN, "r.z <= 0 at the start (preconditioner not SPD)");
       converged = true;
@@ -991,44 +1035,46 @@ struct SolveRun {
     }
   }
   // first iteration (p = z already set)
-  void enqueue_start_c() {
-    const Level &L0 = h->lv[0];
-    const SolveMat &A = L0.Am;
-    timed(h, "spmv", tname("k_spmv", L0.bs, L0.bs), spmv_bytes(), s,
-          [&] { return launch_spmv(A, h->p, h->q, h->part, s); });
-    timed(h, "reduce", "k_reduce", 8.0 * ns, s,
-          [&] { return launch_reduce(ns, h->part, h->scal, SC_PQ, RED_ALPHA, s); });
-    update_xr();
-    timed(h, "reduce", "k_reduce", 8.0 * nd, s,
-          [&] { return launch_reduce(nd, h->part, h->scal, SC_RR, RED_STORE, s); });
-    copy_scalars();
-  }
+  void enqueue_start_c() { pcg_step(h, f32, s); }
 
+  // Without an x0 the three phases are enqueued together, one wait for all: whatever the checks
+  // find, the later phases only touch the hierarchy's own vectors, and r = b is not zero when r.z
+  // fails.  (With an x0 that solves the system already, the first iteration would divide zero by zero.)
   void start(const double *b_dev, const double *x_dev) {
     enqueue_start_a(b_dev, x_dev);
-    wait();
-    complete_start_a();
-    if (!active_start) return;
+    if (sp.use_x0) {
+      wait();
+      complete_start_a();
+      if (!active_start) return;
+    }
     enqueue_start_b();
-    wait();
-    complete_start_b();
-    if (!active_start) return;
+    if (sp.use_x0) {
+      wait();
+      complete_start_b();
+      if (!active_start) return;
+    }
     enqueue_start_c();
     wait();
+    if (!sp.use_x0) {
+      complete_start_a();
+      if (!active_start) return;
+      complete_start_b();
+    }
   }
 
-  // The stopping test on the scalars of the last iteration (in h->scal_h); true when another
-  // iteration is due.
+  // The stopping test on the last iteration's record; true when another iteration is due.
   bool next() {
     if (converged) return false;
     ++iters;
-    h->cg_alpha.push_back(h->scal_h[SC_ALPHA]);
-    h->cg_beta.push_back(iters == 1 ? 0.0 : h->scal_h[SC_BETA]);
-    if (h->scal_h[SC_BAD] != 0.0) fail(EAMG_ERR_BREAKDOWN, "p.Ap <= 0 or r.z <= 0 (operator or preconditioner not SPD)");
-    const double rr = h->scal_h[SC_RR];
+    if (!published(iters)) fail(EAMG_ERR_HIP, "an iteration ended without its scalars");
+    const double *rec = record(iters);
+    h->cg_alpha.push_back(rec[SC_ALPHA]);
+    h->cg_beta.push_back(iters == 1 ? 0.0 : rec[SC_BETA]);
+    if (rec[SC_BAD] != 0.0) fail(EAMG_ERR_BREAKDOWN, "p.Ap <= 0 or r.z <= 0 (operator or preconditioner not SPD)");
+    const double rr = rec[SC_RR];
     if (!std::isfinite(rr)) fail(EAMG_ERR_BREAKDOWN, "residual is not finite");
     rel = std::sqrt(rr) / bnorm;
-    if (std::sqrt(rr) <= sp.rtol * bnorm) {
+    if (rec[SC_DONE] != 0.0) {
       converged = true;
       return false;
     }
@@ -1036,21 +1082,34 @@ struct SolveRun {
   }
 
   void eager_iteration() {
-    const Level &L0 = h->lv[0];
-    const SolveMat &A = L0.Am;
     precondition();
-    dot_rz();
-    timed(h, "reduce", "k_reduce", 8.0 * nd, s,
-          [&] { return launch_reduce(nd, h->part, h->scal, SC_RZ, RED_BETA, s); });
-    update_p();
-    timed(h, "spmv", tname("k_spmv", L0.bs, L0.bs), spmv_bytes(), s,
-          [&] { return launch_spmv(A, h->p, h->q, h->part, s); });
-    timed(h, "reduce", "k_reduce", 8.0 * ns, s,
-          [&] { return launch_reduce(ns, h->part, h->scal, SC_PQ, RED_ALPHA, s); });
-    update_xr();
-    timed(h, "reduce", "k_reduce", 8.0 * nd, s,
-          [&] { return launch_reduce(nd, h->part, h->scal, SC_RR, RED_STORE, s); });
-    fetch_scalars(h, s);
+    pcg_direction(h, f32, s);
+    pcg_step(h, f32, s);
+    wait();
+  }
+
+  // The remaining iterations as graph replays.  The next replay is enqueued before the host has seen
+  // the current one's residual (the device stops its own updates once it has converged), so that the
+  // GPU does not wait for the host between iterations (25 to 45 us each): always where a replay too
+  // many costs less than that, else while the residual is so far from the bound that the current
+  // iteration cannot reach it.
+  void replay_iterations(hipGraphExec_t g) {
+    constexpr double kCheap = 1.2e-4, kFar = 100.0;
+    const bool cheap = iteration_seconds(h, f32) < kCheap;
+    int launched = iters;   // iterations enqueued so far
+    try {
+      while (next()) {
+        const int due = iters + 1;
+        const bool ahead = cheap || rel > kFar * sp.rtol;
+        const int want = std::min(sp.max_it, ahead ? due + 1 : due);
+        for (launched = std::max(launched, iters); launched < want; ++launched)
+          hip_check(hipGraphLaunch(g, s), "graph launch");
+        await(due);
+      }
+    } catch (...) {
+      (void)hipStreamSynchronize(s);   // nothing of the solve is left running
+      throw;
+    }
   }
 
   void enqueue_finish(double *x_dev) {
@@ -1058,7 +1117,7 @@ struct SolveRun {
     hip_check(launch_spmv(L0.Am, h->x, h->q, nullptr, s), "spmv");
     hip_check(launch_sub(N, h->bp, h->q, h->z, s), "sub");
     hip_check(launch_dot(N, h->z, h->z, h->part, s), "dot");
-    hip_check(launch_reduce(nd, h->part, h->scal, SC_RR, RED_STORE, s), "reduce");
+    hip_check(launch_reduce(nd, h->part, h->scal, SC_RR, s), "reduce");
     hip_check(launch_perm_out(L0.n, L0.bs, L0.perm_d, h->x, x_dev, s), "perm_out");
     hip_check(hipEventRecord(e1, s), "event");
     copy_scalars();
@@ -1379,8 +1438,15 @@ eamg_status eamg_setup(const eamg_problem *pb, const eamg_setup_params *params, 
     h->part = ar.alloc<double>(size_t(h->part_cap));
     h->scal = ar.alloc<double>(SC_COUNT);
 
-    hip_check(hipHostMalloc(reinterpret_cast<void **>(&h->scal_h), sizeof(double) * SC_COUNT, 0),
+    h->part_rr = ar.alloc<double>(size_t(dot_blocks(N0)));
+
+    hip_check(hipHostMalloc(reinterpret_cast<void **>(&h->scal_h),
+                            sizeof(double) * (SC_COUNT + 1 + size_t(kRing) * kRecord),
+                            hipHostMallocMapped | hipHostMallocCoherent),
               "hipHostMalloc");
+    void *dev_h = nullptr;
+    hip_check(hipHostGetDevicePointer(&dev_h, h->scal_h, 0), "hipHostGetDevicePointer");
+    h->ring_d = static_cast<double *>(dev_h) + SC_COUNT + 1;
     hip_check(hipStreamSynchronize(s), "sync");
     tm.mark("setup: solve vectors");
     for (const auto &ph : phases) {
@@ -1790,14 +1856,10 @@ eamg_status eamg_solve(eamg_hierarchy *h, const double *b_dev, double *x_dev,
     if (!run.converged) {
       const bool graphs = run.sp.precond && !h->prof_on;
       if (graphs && !h->graph_tried[run.f32]) try_build_graph(h, run.f32);
-      while (run.next()) {
-        if (graphs && h->g_iter[run.f32]) {
-          hip_check(hipGraphLaunch(h->g_iter[run.f32], run.s), "graph launch");
-          hip_check(hipStreamSynchronize(run.s), "sync");
-        } else {
-          run.eager_iteration();
-        }
-      }
+      if (graphs && h->g_iter[run.f32])
+        run.replay_iterations(h->g_iter[run.f32]);
+      else
+        while (run.next()) run.eager_iteration();
     }
     run.finish(x_dev);
   });

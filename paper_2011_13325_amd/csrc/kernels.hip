@@ -712,53 +712,95 @@ __global__ __launch_bounds__(kBlock) void k_dot(int64_t n, const double *__restr
   if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
-__global__ __launch_bounds__(kBlock) void k_reduce(int nparts, const double *__restrict__ part,
-                                                  double *scal, int slot, int op) {
-  __shared__ double sh[kBlock];
+// The sum of the partials, on every thread: the same strided sums and tree wherever it is taken.
+__device__ inline double sum_parts(int nparts, const double *__restrict__ part, double *sh) {
   double s = 0.0;
   // unrolled so that the loads are in flight together (the CG SpMV leaves one partial per
   // workgroup: hundreds of thousands on a large level); the sum keeps its order
 #pragma unroll 16
   for (int i = threadIdx.x; i < nparts; i += kBlock) s += part[i];
   const double t = block_sum(s, sh);
-  if (threadIdx.x == 0) {
-    scal[slot] = t;
-    if (op == RED_ALPHA) {
-      if (!(t > 0.0) || !isfinite(t)) scal[SC_BAD] = 1.0;
-      scal[SC_ALPHA] = scal[SC_RHO] / t;
-    } else if (op == RED_BETA) {
-      if (!(t > 0.0) || !isfinite(t)) scal[SC_BAD] = 1.0;
-      scal[SC_BETA] = t / scal[SC_RHO];
-      scal[SC_RHO] = t;
-    }
-  }
+  __syncthreads();
+  return t;
 }
 
-// r32 (optional): the FP32 copy of the new r, the next FP32 V-cycle's right-hand side.
-__global__ __launch_bounds__(kBlock) void k_update_xr(int64_t n, const double *scal, double *x,
-                                                     double *r, const double *__restrict__ p,
-                                                     const double *__restrict__ q, double *part,
+__global__ __launch_bounds__(kBlock) void k_reduce(int nparts, const double *__restrict__ part,
+                                                  double *scal, int slot) {
+  __shared__ double sh[kBlock];
+  const double t = sum_parts(nparts, part, sh);
+  if (threadIdx.x == 0) scal[slot] = t;
+}
+
+// The scalars of an iteration are formed by the kernels that use them: a kernel that only sums a
+// thousand partials costs 2.5 to 4.7 us in the chain of an iteration, the sum inside the next kernel
+// about one.  Every workgroup takes the same sum; workgroup 0 stores the scalars, in slots that no
+// workgroup of the same launch reads.
+__global__ __launch_bounds__(kBlock) void k_update_xr(int64_t n, double *scal, double *__restrict__ x,
+                                                     double *__restrict__ r, const double *__restrict__ p,
+                                                     const double *__restrict__ q,
+                                                     double *__restrict__ part, int npq,
+                                                     const double *__restrict__ pq,
                                                      float *__restrict__ r32) {
   __shared__ double sh[kBlock];
-  const double alpha = scal[SC_ALPHA];
+  const double rz = scal[SC_RZ];
+  const bool done = scal[SC_DONE] != 0.0;
+  const double t = npq > 0 ? sum_parts(npq, pq, sh) : scal[SC_PQ];
+  const double alpha = rz / t;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (!(t > 0.0) || !isfinite(t)) scal[SC_BAD] = 1.0;
+    if (npq > 0) scal[SC_PQ] = t;
+    scal[SC_ALPHA] = alpha;
+    scal[SC_RHO] = rz;
+  }
   double s = 0.0;
   for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += int64_t(gridDim.x) * kBlock) {
-    x[i] = fma(alpha, p[i], x[i]);
-    const double ri = fma(-alpha, q[i], r[i]);
-    r[i] = ri;
-    if (r32) r32[i] = float(ri);
+    double ri = r[i];
+    if (!done) {
+      x[i] = fma(alpha, p[i], x[i]);
+      ri = fma(-alpha, q[i], ri);
+      r[i] = ri;
+      if (r32) r32[i] = float(ri);
+    }
     s = fma(ri, ri, s);
   }
-  const double t = block_sum(s, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = t;
+  const double rr = block_sum(s, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = rr;
 }
 
 template <class TZ>
-__global__ __launch_bounds__(kBlock) void k_update_p(int64_t n, const double *scal,
-                                                    const TZ *__restrict__ z, double *p) {
-  const double beta = scal[SC_BETA];
+__global__ __launch_bounds__(kBlock) void k_update_p(int64_t n, double *scal, const TZ *__restrict__ z,
+                                                    double *__restrict__ p, int nparts,
+                                                    const double *__restrict__ part) {
+  __shared__ double sh[kBlock];
+  const double rho = scal[SC_RHO];
+  const double t = sum_parts(nparts, part, sh);
+  const double beta = t / rho;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (!(t > 0.0) || !isfinite(t)) scal[SC_BAD] = 1.0;
+    scal[SC_RZ] = t;
+    scal[SC_BETA] = beta;
+  }
   for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += int64_t(gridDim.x) * kBlock)
     p[i] = fma(beta, p[i], double(z[i]));
+}
+
+__global__ __launch_bounds__(kBlock) void k_publish(int nparts, const double *__restrict__ part,
+                                                   double *scal, double *ring) {
+  __shared__ double sh[kBlock];
+  const double t = sum_parts(nparts, part, sh);
+  if (threadIdx.x != 0) return;
+  const double it = scal[SC_ITER] + 1.0;
+  scal[SC_RR] = t;
+  scal[SC_ITER] = it;
+  if (sqrt(t) <= scal[SC_RTOL] * sqrt(scal[SC_BB])) scal[SC_DONE] = 1.0;
+  double *rec = ring + (int(it) & (kRing - 1)) * kRecord;
+  for (int i = 0; i < SC_COUNT; ++i) rec[i] = scal[i];
+  __threadfence_system();
+  __hip_atomic_store(rec + kRecord - 1, it, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__global__ void k_init_scal(double rtol, double *scal) {
+  if (threadIdx.x < SC_COUNT) scal[threadIdx.x] = threadIdx.x == SC_RTOL ? rtol : 0.0;
 }
 
 __global__ void k_sub(int64_t n, const double *a, const double *b, double *y) {
@@ -1098,25 +1140,39 @@ hipError_t launch_dot(int64_t n, const double *a, const float *b, double *part, 
   EAMG_LAUNCH_CHECK();
 }
 
-hipError_t launch_reduce(int nparts, const double *part, double *scal, int slot, int op,
-                         hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, s, nparts, part, scal, slot, op);
+hipError_t launch_reduce(int nparts, const double *part, double *scal, int slot, hipStream_t s) {
+  hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, s, nparts, part, scal, slot);
   EAMG_LAUNCH_CHECK();
 }
 
-hipError_t launch_update_xr(int64_t n, const double *scal, double *x, double *r, const double *p,
-                            const double *q, double *part, hipStream_t s, float *r32) {
-  hipLaunchKernelGGL(k_update_xr, dim3(dot_blocks(n)), dim3(kBlock), 0, s, n, scal, x, r, p, q, part, r32);
+hipError_t launch_update_xr(int64_t n, double *scal, double *x, double *r, const double *p,
+                            const double *q, double *part, int npq, const double *pq, hipStream_t s,
+                            float *r32) {
+  if (npq < 0 || npq > kInlineParts || (npq && (!pq || pq == part))) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_update_xr, dim3(dot_blocks(n)), dim3(kBlock), 0, s, n, scal, x, r, p, q, part, npq,
+                     pq, r32);
   EAMG_LAUNCH_CHECK();
 }
 
-hipError_t launch_update_p(int64_t n, const double *scal, const double *z, double *p, hipStream_t s) {
-  hipLaunchKernelGGL(k_update_p<double>, dim3(dot_blocks(n)), dim3(kBlock), 0, s, n, scal, z, p);
+hipError_t launch_update_p(int64_t n, double *scal, const double *z, double *p, int nparts,
+                           const double *part, hipStream_t s) {
+  hipLaunchKernelGGL(k_update_p<double>, dim3(dot_blocks(n)), dim3(kBlock), 0, s, n, scal, z, p, nparts, part);
   EAMG_LAUNCH_CHECK();
 }
 
-hipError_t launch_update_p(int64_t n, const double *scal, const float *z, double *p, hipStream_t s) {
-  hipLaunchKernelGGL(k_update_p<float>, dim3(dot_blocks(n)), dim3(kBlock), 0, s, n, scal, z, p);
+hipError_t launch_update_p(int64_t n, double *scal, const float *z, double *p, int nparts,
+                           const double *part, hipStream_t s) {
+  hipLaunchKernelGGL(k_update_p<float>, dim3(dot_blocks(n)), dim3(kBlock), 0, s, n, scal, z, p, nparts, part);
+  EAMG_LAUNCH_CHECK();
+}
+
+hipError_t launch_publish(int nparts, const double *part, double *scal, double *ring, hipStream_t s) {
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(kBlock), 0, s, nparts, part, scal, ring);
+  EAMG_LAUNCH_CHECK();
+}
+
+hipError_t launch_init_scal(double rtol, double *scal, hipStream_t s) {
+  hipLaunchKernelGGL(k_init_scal, dim3(1), dim3(64), 0, s, rtol, scal);
   EAMG_LAUNCH_CHECK();
 }
 

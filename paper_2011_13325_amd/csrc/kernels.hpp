@@ -154,17 +154,30 @@ int dot_blocks(int64_t n);
 // converted exactly)
 hipError_t launch_dot(int64_t n, const double *a, const double *b, double *part, hipStream_t s);
 hipError_t launch_dot(int64_t n, const double *a, const float *b, double *part, hipStream_t s);
-// Reduce partials into scal[slot]; op selects what else is derived (see kernels.hip).
-enum ReduceOp : int { RED_STORE = 0, RED_ALPHA = 1, RED_BETA = 2 };
-hipError_t launch_reduce(int nparts, const double *part, double *scal, int slot, int op,
-                         hipStream_t s);
-// x += alpha p ; r -= alpha q ; part <- partials of r.r   (alpha = scal[SC_ALPHA]); with r32,
-// also r32 = float(r) (the next FP32 V-cycle's right-hand side)
-hipError_t launch_update_xr(int64_t n, const double *scal, double *x, double *r, const double *p,
-                            const double *q, double *part, hipStream_t s, float *r32 = nullptr);
-// p = z + beta p (beta = scal[SC_BETA]); z in double or float
-hipError_t launch_update_p(int64_t n, const double *scal, const double *z, double *p, hipStream_t s);
-hipError_t launch_update_p(int64_t n, const double *scal, const float *z, double *p, hipStream_t s);
+// Sum of the partials into scal[slot].
+hipError_t launch_reduce(int nparts, const double *part, double *scal, int slot, hipStream_t s);
+// p = z + beta p (z in double or float), beta = r.z / scal[SC_RHO], r.z summed from the partials in
+// `part` by every workgroup alike; also stores SC_RZ and SC_BETA.
+hipError_t launch_update_p(int64_t n, double *scal, const double *z, double *p, int nparts,
+                           const double *part, hipStream_t s);
+hipError_t launch_update_p(int64_t n, double *scal, const float *z, double *p, int nparts,
+                           const double *part, hipStream_t s);
+// x += alpha p ; r -= alpha q ; part <- partials of r.r, alpha = scal[SC_RZ] / p.q, p.q summed from the
+// npq partials in `pq` (npq = 0: scal[SC_PQ]); also stores SC_PQ, SC_ALPHA and SC_RHO = SC_RZ.  With
+// r32, also r32 = float(r) (the next FP32 V-cycle's right-hand side).  Once scal[SC_DONE] is set, x and
+// r stay as they are.
+hipError_t launch_update_xr(int64_t n, double *scal, double *x, double *r, const double *p,
+                            const double *q, double *part, int npq, const double *pq, hipStream_t s,
+                            float *r32 = nullptr);
+// Partial counts up to this many are summed by the kernel that uses the sum.
+constexpr int kInlineParts = 1024;
+// End of an iteration: SC_RR from the partials, SC_ITER + 1, SC_DONE if sqrt(r.r) <= SC_RTOL sqrt(SC_BB),
+// then the scalars published in ring entry SC_ITER mod kRing (host memory; kRecord doubles, the last
+// one, the iteration's number, stored after the others).
+constexpr int kRing = 4, kRecord = 16;
+hipError_t launch_publish(int nparts, const double *part, double *scal, double *ring, hipStream_t s);
+// scal := 0, SC_RTOL = rtol
+hipError_t launch_init_scal(double rtol, double *scal, hipStream_t s);
 // y = a - b
 hipError_t launch_sub(int64_t n, const double *a, const double *b, double *y, hipStream_t s);
 hipError_t launch_copy(int64_t n, const double *a, double *y, hipStream_t s);
@@ -181,7 +194,7 @@ hipError_t launch_fill(int64_t n, double v, double *a, hipStream_t s);
 // Scalar slots on the device.
 enum Scalar : int {
   SC_RHO = 0, SC_PQ = 1, SC_RR = 2, SC_ALPHA = 3, SC_BETA = 4, SC_RZ = 5, SC_BB = 6,
-  SC_BAD = 7, SC_NONFINITE = 8, SC_COUNT = 16
+  SC_BAD = 7, SC_NONFINITE = 8, SC_DONE = 9, SC_RTOL = 10, SC_ITER = 11, SC_COUNT = 15
 };
 
 }  // namespace eamg
