@@ -1184,6 +1184,10 @@ void vcycle_apply(eamg_hierarchy *h, const double *r, double *z, bool f32, hipSt
   vcycle(h, r, z, f32, s);
 }
 
+void vcycle_apply32(eamg_hierarchy *h, hipStream_t s) {
+  vcycle_t<float>(h, 0, h->lv[0].b32, h->lv[0].x32, s);
+}
+
 void vcycle_staged(eamg_hierarchy *h, const double *r_dev, double *z_dev, bool f32, double *rp,
                    double *zp, hipStream_t s) {
   const Level &L0 = h->lv[0];

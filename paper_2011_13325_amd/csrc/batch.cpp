@@ -162,46 +162,62 @@ void pvcycle_t(eamg_hierarchy *h, BatchWork *w, size_t l, const T *b, T *x, hipS
   });
 }
 
-// Z = V(R) for the K columns of the level-0 CG panels.
+// The level-0 panels of the FP32 V-cycle: R's FP32 copy (written with R), and Z.
+float *panel_r32(BatchWork *w) { return vp<float>(w->vb[1][0]); }
+float *panel_z32(BatchWork *w) { return vp<float>(w->vx[1][0]); }
+
+// Z = V(R) for the K columns of the level-0 CG panels: FP32 from panel_r32 to panel_z32, else R to Z.
 void pvcycle(eamg_hierarchy *h, BatchWork *w, bool f32, hipStream_t s) {
-  if (f32) {
-    const int64_t N = level_dofs(h->lv[0]) * w->K;
-    float *b32 = vp<float>(w->vb[1][0]), *x32 = vp<float>(w->vx[1][0]);
-    timed(h, "convert", "k_convert<double, float>", 12.0 * N, s,
-          [&] { return launch_convert<double, float>(N, w->r, b32, s); });
-    pvcycle_t<float>(h, w, 0, b32, x32, s);
-    timed(h, "convert", "k_convert<float, double>", 12.0 * N, s,
-          [&] { return launch_convert<float, double>(N, x32, w->z, s); });
-  } else {
+  if (f32)
+    pvcycle_t<float>(h, w, 0, panel_r32(w), panel_z32(w), s);
+  else
     pvcycle_t<double>(h, w, 0, w->r, w->z, s);
-  }
 }
 
-// One batched PCG iteration after the stopping test (the columns that are still active).
-void penqueue_iteration(eamg_hierarchy *h, BatchWork *w, bool precond, bool f32, hipStream_t s) {
+// part <- R.Z
+void pdot_rz(eamg_hierarchy *h, BatchWork *w, bool f32, hipStream_t s) {
+  const int64_t N = level_dofs(h->lv[0]) * w->K;
+  const int nd = pdot_blocks(N);
+  timed(h, "pdot", "k_pdot", (f32 ? 12.0 : 16.0) * N + 8.0 * nd * w->K, s, [&] {
+    return f32 ? launch_pdot<float>(N, w->K, w->r, panel_z32(w), w->part, s)
+               : launch_pdot<double>(N, w->K, w->r, w->z, w->part, s);
+  });
+}
+
+// Q = A P, alpha, X += alpha P, R -= alpha Q, R.R and the stopping tests.
+void pstep(eamg_hierarchy *h, BatchWork *w, bool f32, hipStream_t s) {
   const Level &L0 = h->lv[0];
   const int K = w->K;
   const int64_t N = level_dofs(L0) * K;
   const int nd = pdot_blocks(N), ns = pspmv_blocks(L0.Am, K);
-  const double vecb = 8.0 * N;
-  if (precond)
-    pvcycle(h, w, f32, s);
-  else
-    hip_check(launch_copy(N, w->r, w->z, s), "copy");
-  timed(h, "pdot", "k_pdot", 2.0 * vecb + 8.0 * nd * K, s,
-        [&] { return launch_pdot(N, K, w->r, w->z, w->part, s); });
-  timed(h, "preduce", "k_preduce", 8.0 * nd * K, s,
-        [&] { return launch_preduce(nd, K, w->part, w->scal, PS_RZ, PRED_BETA, s); });
-  timed(h, "pupdate_p", "k_pupdate_p", 3.0 * vecb, s,
-        [&] { return launch_pupdate_p(N, K, w->scal, w->z, w->p, s); });
   timed(h, "pspmv", tname("k_pspmv", L0.bs), launch_bytes(L0.sh_spmv, LK_SPMV, L0.bs, L0.bs, 8.0, K) + 8.0 * ns * K, s,
         [&] { return launch_pspmv(L0.Am, K, w->p, w->q, w->part, s); });
   timed(h, "preduce", "k_preduce", 8.0 * ns * K, s,
         [&] { return launch_preduce(ns, K, w->part, w->scal, PS_PQ, PRED_ALPHA, s); });
-  timed(h, "pupdate_xr", "k_pupdate_xr", 6.0 * vecb + 8.0 * nd * K, s,
-        [&] { return launch_pupdate_xr(N, K, w->scal, w->x, w->r, w->p, w->q, w->part, s); });
+  timed(h, "pupdate_xr", "k_pupdate_xr", (f32 ? 52.0 : 48.0) * N + 8.0 * nd * K, s, [&] {
+    return launch_pupdate_xr(N, K, w->scal, w->x, w->r, w->p, w->q, w->part, f32 ? panel_r32(w) : nullptr, s);
+  });
   timed(h, "preduce", "k_preduce", 8.0 * nd * K, s,
         [&] { return launch_preduce(nd, K, w->part, w->scal, PS_RR, PRED_RR, s); });
+}
+
+// One batched PCG iteration after the stopping test (the columns that are still active).
+void penqueue_iteration(eamg_hierarchy *h, BatchWork *w, bool precond, bool f32, hipStream_t s) {
+  const int K = w->K;
+  const int64_t N = level_dofs(h->lv[0]) * K;
+  const int nd = pdot_blocks(N);
+  if (precond)
+    pvcycle(h, w, f32, s);
+  else
+    hip_check(launch_copy(N, w->r, w->z, s), "copy");
+  pdot_rz(h, w, f32, s);
+  timed(h, "preduce", "k_preduce", 8.0 * nd * K, s,
+        [&] { return launch_preduce(nd, K, w->part, w->scal, PS_RZ, PRED_BETA, s); });
+  timed(h, "pupdate_p", "k_pupdate_p", (f32 ? 20.0 : 24.0) * N, s, [&] {
+    return f32 ? launch_pupdate_p<float>(N, K, w->scal, panel_z32(w), w->p, s)
+               : launch_pupdate_p<double>(N, K, w->scal, w->z, w->p, s);
+  });
+  pstep(h, w, f32, s);
   hip_check(hipMemcpyAsync(w->scal_h, w->scal, sizeof(double) * PS_COUNT * K, hipMemcpyDeviceToHost, s),
             "copy");
 }
@@ -255,7 +271,7 @@ bool solve_panel(eamg_hierarchy *h, int m, const double *B, int64_t ld, double *
   const Level &L0 = h->lv[0];
   const SolveMat &A = L0.Am;
   const int64_t N = level_dofs(L0) * K;
-  const int nd = pdot_blocks(N), ns = pspmv_blocks(A, K);
+  const int nd = pdot_blocks(N);
   struct Events {
     hipEvent_t a = nullptr, b = nullptr;
     ~Events() {
@@ -270,7 +286,7 @@ bool solve_panel(eamg_hierarchy *h, int m, const double *B, int64_t ld, double *
   hip_check(launch_pinit_scal(K, sp.rtol, sp.max_it, w->scal, s), "pinit");
   hip_check(launch_ppack(L0.n, L0.bs, K, m, L0.perm_d, h->dir, B, ld, w->bp, s), "ppack");
   hip_check(launch_pfinite(N, K, w->bp, w->scal, s), "pfinite");
-  hip_check(launch_pdot(N, K, w->bp, w->bp, w->part, s), "pdot");
+  hip_check(launch_pdot<double>(N, K, w->bp, w->bp, w->part, s), "pdot");
   hip_check(launch_preduce(nd, K, w->part, w->scal, PS_BB, PRED_INIT, s), "preduce");
   if (sp.use_x0) {
     hip_check(launch_ppack(L0.n, L0.bs, K, m, L0.perm_d, h->dir, X, ld, w->x, s), "ppack");
@@ -280,20 +296,21 @@ bool solve_panel(eamg_hierarchy *h, int m, const double *B, int64_t ld, double *
     hip_check(launch_fill(N, 0.0, w->x, s), "fill");
     hip_check(launch_copy(N, w->bp, w->r, s), "copy");
   }
-  hip_check(launch_pdot(N, K, w->r, w->r, w->part, s), "pdot");
+  hip_check(launch_pdot<double>(N, K, w->r, w->r, w->part, s), "pdot");
   hip_check(launch_preduce(nd, K, w->part, w->scal, PS_RR0, PRED_STORE, s), "preduce");
+  if (f32) hip_check(launch_convert<double, float>(N, w->r, panel_r32(w), s), "convert");
   if (precond)
     pvcycle(h, w, f32, s);
   else
     hip_check(launch_copy(N, w->r, w->z, s), "copy");
-  hip_check(launch_copy(N, w->z, w->p, s), "copy");
-  hip_check(launch_pdot(N, K, w->r, w->z, w->part, s), "pdot");
+  if (f32)
+    hip_check(launch_convert<float, double>(N, panel_z32(w), w->p, s), "convert");
+  else
+    hip_check(launch_copy(N, w->z, w->p, s), "copy");
+  pdot_rz(h, w, f32, s);
   hip_check(launch_preduce(nd, K, w->part, w->scal, PS_RHO, PRED_RHO0, s), "preduce");
   // first iteration (p = z), then one graph replay per further iteration
-  hip_check(launch_pspmv(A, K, w->p, w->q, w->part, s), "pspmv");
-  hip_check(launch_preduce(ns, K, w->part, w->scal, PS_PQ, PRED_ALPHA, s), "preduce");
-  hip_check(launch_pupdate_xr(N, K, w->scal, w->x, w->r, w->p, w->q, w->part, s), "pupdate_xr");
-  hip_check(launch_preduce(nd, K, w->part, w->scal, PS_RR, PRED_RR, s), "preduce");
+  pstep(h, w, f32, s);
   pfetch(w, s);
   const bool graphs = precond && !h->prof_on;
   if (graphs && !w->tried[f32]) ptry_graph(h, w, f32);
@@ -310,7 +327,7 @@ bool solve_panel(eamg_hierarchy *h, int m, const double *B, int64_t ld, double *
   // true residuals, x of columns that never started, unpack
   hip_check(launch_pspmv(A, K, w->x, w->q, nullptr, s), "pspmv");
   hip_check(launch_sub(N, w->bp, w->q, w->z, s), "sub");
-  hip_check(launch_pdot(N, K, w->z, w->z, w->part, s), "pdot");
+  hip_check(launch_pdot<double>(N, K, w->z, w->z, w->part, s), "pdot");
   hip_check(launch_preduce(nd, K, w->part, w->scal, PS_RZ, PRED_STORE, s), "preduce");
   hip_check(launch_pzero_unstarted(N, K, w->scal, w->x, s), "pzero");
   hip_check(launch_punpack(L0.n, L0.bs, K, m, L0.perm_d, w->x, X, ld, s), "punpack");

@@ -346,27 +346,47 @@ void check_params(const eamg_hierarchy *F, const eamg_solve_params &sp) {
     fail(EAMG_ERR_INVALID_ARG, "FP32 V-cycle needs every fused hierarchy set up with vcycle_fp32 = 1");
 }
 
+// z = V(r): with the FP32 V-cycle level 0's x32 from b32, r's FP32 copy (written with r), else F->z.
 void fused_precondition(eamg_hierarchy *F, int precond, hipStream_t s) {
   const int64_t N = int64_t(F->lv[0].n) * F->lv[0].bs;
   if (precond == EAMG_PRECOND_NONE)
     hip_check(launch_copy(N, F->r, F->z, s), "copy");
+  else if (precond == EAMG_PRECOND_VCYCLE_FP32)
+    vcycle_apply32(F, s);
   else
-    vcycle_apply(F, F->r, F->z, precond == EAMG_PRECOND_VCYCLE_FP32, s);
+    vcycle_apply(F, F->r, F->z, false, s);
+}
+
+// part <- r.z
+void fused_dot_rz(eamg_hierarchy *F, int precond, hipStream_t s) {
+  const SegTable &T = F->fused->seg;
+  hip_check(precond == EAMG_PRECOND_VCYCLE_FP32 ? launch_sdot<float>(T, F->r, F->lv[0].x32, F->part, s)
+                                                : launch_sdot<double>(T, F->r, F->z, F->part, s),
+            "sdot");
+}
+
+// q = A p, alpha, x += alpha p, r -= alpha q, r.r and the stopping test.
+void fused_step(eamg_hierarchy *F, int precond, hipStream_t s) {
+  const SegTable &T = F->fused->seg;
+  hip_check(launch_spmv(F->lv[0].Am, F->p, F->q, nullptr, s), "spmv");
+  hip_check(launch_sdot<double>(T, F->p, F->q, F->part, s), "sdot");
+  hip_check(launch_sreduce(T, F->part, F->scal, PS_PQ, PRED_ALPHA, s), "sreduce");
+  hip_check(launch_supdate_xr(T, F->scal, F->x, F->r, F->p, F->q, F->part,
+                              precond == EAMG_PRECOND_VCYCLE_FP32 ? F->lv[0].b32 : nullptr, s),
+            "supdate_xr");
+  hip_check(launch_sreduce(T, F->part, F->scal, PS_RR, PRED_RR, s), "sreduce");
 }
 
 // One PCG iteration of every system after its stopping test (inactive systems keep x, r, p).
 void fused_iteration(eamg_hierarchy *F, int precond, hipStream_t s) {
   const SegTable &T = F->fused->seg;
-  const SolveMat &A = F->lv[0].Am;
   fused_precondition(F, precond, s);
-  hip_check(launch_sdot(T, F->r, F->z, F->part, s), "sdot");
+  fused_dot_rz(F, precond, s);
   hip_check(launch_sreduce(T, F->part, F->scal, PS_RZ, PRED_BETA, s), "sreduce");
-  hip_check(launch_supdate_p(T, F->scal, F->z, F->p, s), "supdate_p");
-  hip_check(launch_spmv(A, F->p, F->q, nullptr, s), "spmv");
-  hip_check(launch_sdot(T, F->p, F->q, F->part, s), "sdot");
-  hip_check(launch_sreduce(T, F->part, F->scal, PS_PQ, PRED_ALPHA, s), "sreduce");
-  hip_check(launch_supdate_xr(T, F->scal, F->x, F->r, F->p, F->q, F->part, s), "supdate_xr");
-  hip_check(launch_sreduce(T, F->part, F->scal, PS_RR, PRED_RR, s), "sreduce");
+  hip_check(precond == EAMG_PRECOND_VCYCLE_FP32 ? launch_supdate_p<float>(T, F->scal, F->lv[0].x32, F->p, s)
+                                                : launch_supdate_p<double>(T, F->scal, F->z, F->p, s),
+            "supdate_p");
+  fused_step(F, precond, s);
 }
 
 // Iterations per round: the host reads the systems' active flags once a round (a system that
@@ -585,7 +605,7 @@ eamg_status eamg_solve_fused(eamg_hierarchy *F, const double *const *b_dev, doub
     for (int m = 0; m < nsys; ++m)
       hip_check(launch_scatter_in(I.n0[m], I.bs0, I.map0[m], I.sys[m]->dir, b_dev[m], F->bp, s), "scatter");
     hip_check(launch_sfinite(T, F->bp, F->scal, s), "sfinite");
-    hip_check(launch_sdot(T, F->bp, F->bp, F->part, s), "sdot");
+    hip_check(launch_sdot<double>(T, F->bp, F->bp, F->part, s), "sdot");
     hip_check(launch_sreduce(T, F->part, F->scal, PS_BB, PRED_INIT, s), "sreduce");
     if (sp.use_x0) {
       for (int m = 0; m < nsys; ++m)
@@ -596,17 +616,18 @@ eamg_status eamg_solve_fused(eamg_hierarchy *F, const double *const *b_dev, doub
       hip_check(launch_fill(N, 0.0, F->x, s), "fill");
       hip_check(launch_copy(N, F->bp, F->r, s), "copy");
     }
-    hip_check(launch_sdot(T, F->r, F->r, F->part, s), "sdot");
+    hip_check(launch_sdot<double>(T, F->r, F->r, F->part, s), "sdot");
     hip_check(launch_sreduce(T, F->part, F->scal, PS_RR0, PRED_STORE, s), "sreduce");
+    const bool f32 = pc == EAMG_PRECOND_VCYCLE_FP32;
+    if (f32) hip_check(launch_convert<double, float>(N, F->r, F->lv[0].b32, s), "convert");
     fused_precondition(F, pc, s);
-    hip_check(launch_copy(N, F->z, F->p, s), "copy");
-    hip_check(launch_sdot(T, F->r, F->z, F->part, s), "sdot");
+    if (f32)
+      hip_check(launch_convert<float, double>(N, F->lv[0].x32, F->p, s), "convert");
+    else
+      hip_check(launch_copy(N, F->z, F->p, s), "copy");
+    fused_dot_rz(F, pc, s);
     hip_check(launch_sreduce(T, F->part, F->scal, PS_RHO, PRED_RHO0, s), "sreduce");
-    hip_check(launch_spmv(A, F->p, F->q, nullptr, s), "spmv");
-    hip_check(launch_sdot(T, F->p, F->q, F->part, s), "sdot");
-    hip_check(launch_sreduce(T, F->part, F->scal, PS_PQ, PRED_ALPHA, s), "sreduce");
-    hip_check(launch_supdate_xr(T, F->scal, F->x, F->r, F->p, F->q, F->part, s), "supdate_xr");
-    hip_check(launch_sreduce(T, F->part, F->scal, PS_RR, PRED_RR, s), "sreduce");
+    fused_step(F, pc, s);
     const bool graphs = !F->prof_on;
     if (graphs && !I.tried[pc]) fused_graph(F, pc);
     // rounds of kRound iterations, one graph launch each
@@ -626,7 +647,7 @@ eamg_status eamg_solve_fused(eamg_hierarchy *F, const double *const *b_dev, doub
     // true residuals (slot RZ), then x out
     hip_check(launch_spmv(A, F->x, F->q, nullptr, s), "spmv");
     hip_check(launch_sub(N, F->bp, F->q, F->z, s), "sub");
-    hip_check(launch_sdot(T, F->z, F->z, F->part, s), "sdot");
+    hip_check(launch_sdot<double>(T, F->z, F->z, F->part, s), "sdot");
     hip_check(launch_sreduce(T, F->part, F->scal, PS_RZ, PRED_STORE, s), "sreduce");
     hip_check(hipMemcpyAsync(F->scal_h, F->scal, sizeof(double) * PS_COUNT * nsys,
                              hipMemcpyDeviceToHost, s),

@@ -27,14 +27,16 @@ __device__ inline double block_sum(double v, double *sh) {
   return sh[0];
 }
 
+// b in double, or the FP32 V-cycle's output read as it is
+template <class TB>
 __global__ __launch_bounds__(kFB) void k_sdot(const int64_t *__restrict__ d0,
                                              const int64_t *__restrict__ d1,
                                              const double *__restrict__ a,
-                                             const double *__restrict__ b, double *part) {
+                                             const TB *__restrict__ b, double *part) {
   __shared__ double sh[kFB];
   const int k = blockIdx.x;
   double acc = 0.0;
-  for (int64_t i = d0[k] + threadIdx.x; i < d1[k]; i += kFB) acc = fma(a[i], b[i], acc);
+  for (int64_t i = d0[k] + threadIdx.x; i < d1[k]; i += kFB) acc = fma(a[i], double(b[i]), acc);
   const double t = block_sum(acc, sh);
   if (threadIdx.x == 0) part[k] = t;
 }
@@ -44,7 +46,8 @@ __global__ __launch_bounds__(kFB) void k_supdate_xr(int nsys, const int *__restr
                                                    const int64_t *__restrict__ d1,
                                                    const double *__restrict__ scal, double *x,
                                                    double *r, const double *__restrict__ p,
-                                                   const double *__restrict__ q, double *part) {
+                                                   const double *__restrict__ q, double *part,
+                                                   float *__restrict__ r32) {
   __shared__ double sh[kFB];
   const int k = blockIdx.x;
   const int m = sys[k];
@@ -57,6 +60,7 @@ __global__ __launch_bounds__(kFB) void k_supdate_xr(int nsys, const int *__restr
       x[i] = fma(alpha, p[i], x[i]);
       ri = fma(-alpha, q[i], ri);
       r[i] = ri;
+      if (r32) r32[i] = float(ri);
     }
     acc = fma(ri, ri, acc);
   }
@@ -64,16 +68,17 @@ __global__ __launch_bounds__(kFB) void k_supdate_xr(int nsys, const int *__restr
   if (threadIdx.x == 0) part[k] = t;
 }
 
+template <class TZ>
 __global__ __launch_bounds__(kFB) void k_supdate_p(int nsys, const int *__restrict__ sys,
                                                   const int64_t *__restrict__ d0,
                                                   const int64_t *__restrict__ d1,
                                                   const double *__restrict__ scal,
-                                                  const double *__restrict__ z, double *p) {
+                                                  const TZ *__restrict__ z, double *p) {
   const int k = blockIdx.x;
   const int m = sys[k];
   if (scal[PS_ACTIVE * nsys + m] == 0.0) return;
   const double beta = scal[PS_BETA * nsys + m];
-  for (int64_t i = d0[k] + threadIdx.x; i < d1[k]; i += kFB) p[i] = fma(beta, p[i], z[i]);
+  for (int64_t i = d0[k] + threadIdx.x; i < d1[k]; i += kFB) p[i] = fma(beta, p[i], double(z[i]));
 }
 
 __global__ __launch_bounds__(kFB) void k_sfinite(int nsys, const int *__restrict__ sys,
@@ -91,15 +96,18 @@ __global__ __launch_bounds__(kFB) void k_sfinite(int nsys, const int *__restrict
   if (threadIdx.x == 0 && bad) scal[PS_NONFINITE * nsys + sys[k]] = 1.0;
 }
 
-// One thread per system: its blocks' partials in block order, then the CG bookkeeping of `op`
-// (the same rules as the block-panel reduction, one system per column).
+// One workgroup per system: its blocks' partials (strided sums, then a tree; one thread taking
+// them in turn was 19 us for 16 systems of 2.2 M dofs), then the CG bookkeeping of `op` (the same rules
+// as the block-panel reduction, one system per column).
 __global__ __launch_bounds__(kFB) void k_sreduce(int nsys, const int *__restrict__ bptr,
                                                 const double *__restrict__ part, double *scal,
                                                 int slot, int op) {
-  const int m = int(blockIdx.x) * kFB + int(threadIdx.x);
-  if (m >= nsys) return;
-  double t = 0.0;
-  for (int k = bptr[m]; k < bptr[m + 1]; ++k) t += part[k];
+  __shared__ double sh[kFB];
+  const int m = int(blockIdx.x);
+  double acc = 0.0;
+  for (int k = bptr[m] + int(threadIdx.x); k < bptr[m + 1]; k += kFB) acc += part[k];
+  const double t = block_sum(acc, sh);
+  if (threadIdx.x != 0) return;
   auto at = [&](int sl) -> double & { return scal[sl * nsys + m]; };
   at(slot) = t;
   const bool active = at(PS_ACTIVE) != 0.0;
@@ -190,36 +198,41 @@ __global__ void k_gather_out(int n, int bs, const int *__restrict__ map,
 
 }  // namespace
 
-hipError_t launch_sdot(const SegTable &T, const double *a, const double *b, double *part,
-                       hipStream_t s) {
+template <class TB>
+hipError_t launch_sdot(const SegTable &T, const double *a, const TB *b, double *part, hipStream_t s) {
   if (T.nblk == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_sdot, dim3(T.nblk), dim3(kFB), 0, s, T.d0, T.d1, a, b, part);
+  hipLaunchKernelGGL(k_sdot<TB>, dim3(T.nblk), dim3(kFB), 0, s, T.d0, T.d1, a, b, part);
   return hipGetLastError();
 }
+template hipError_t launch_sdot<double>(const SegTable &, const double *, const double *, double *, hipStream_t);
+template hipError_t launch_sdot<float>(const SegTable &, const double *, const float *, double *, hipStream_t);
 
 hipError_t launch_sreduce(const SegTable &T, const double *part, double *scal, int slot, int op,
                           hipStream_t s) {
   if (T.nsys == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_sreduce, dim3(unsigned(cdiv64f(T.nsys, kFB))), dim3(kFB), 0, s, T.nsys,
+  hipLaunchKernelGGL(k_sreduce, dim3(unsigned(T.nsys)), dim3(kFB), 0, s, T.nsys,
                      T.bptr, part, scal, slot, op);
   return hipGetLastError();
 }
 
 hipError_t launch_supdate_xr(const SegTable &T, const double *scal, double *x, double *r,
-                             const double *p, const double *q, double *part, hipStream_t s) {
+                             const double *p, const double *q, double *part, float *r32,
+                             hipStream_t s) {
   if (T.nblk == 0) return hipSuccess;
   hipLaunchKernelGGL(k_supdate_xr, dim3(T.nblk), dim3(kFB), 0, s, T.nsys, T.sys, T.d0, T.d1, scal,
-                     x, r, p, q, part);
+                     x, r, p, q, part, r32);
   return hipGetLastError();
 }
 
-hipError_t launch_supdate_p(const SegTable &T, const double *scal, const double *z, double *p,
-                            hipStream_t s) {
+template <class TZ>
+hipError_t launch_supdate_p(const SegTable &T, const double *scal, const TZ *z, double *p, hipStream_t s) {
   if (T.nblk == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_supdate_p, dim3(T.nblk), dim3(kFB), 0, s, T.nsys, T.sys, T.d0, T.d1, scal,
+  hipLaunchKernelGGL(k_supdate_p<TZ>, dim3(T.nblk), dim3(kFB), 0, s, T.nsys, T.sys, T.d0, T.d1, scal,
                      z, p);
   return hipGetLastError();
 }
+template hipError_t launch_supdate_p<double>(const SegTable &, const double *, const double *, double *, hipStream_t);
+template hipError_t launch_supdate_p<float>(const SegTable &, const double *, const float *, double *, hipStream_t);
 
 hipError_t launch_sfinite(const SegTable &T, const double *a, double *scal, hipStream_t s) {
   if (T.nblk == 0) return hipSuccess;

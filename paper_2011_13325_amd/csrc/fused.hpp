@@ -29,19 +29,20 @@ struct SegTable {
 // dofs of one block of a segmented launch (a segment is split into blocks of at most this many)
 constexpr int kSegChunk = 2048;
 
-// part[k] <- sum over block k of a.b
-hipError_t launch_sdot(const SegTable &T, const double *a, const double *b, double *part,
-                       hipStream_t s);
-// scal[slot * nsys + m] <- sum of part over system m's blocks, in block order, then the
+// part[k] <- sum over block k of a.b (b in double or float)
+template <class TB>
+hipError_t launch_sdot(const SegTable &T, const double *a, const TB *b, double *part, hipStream_t s);
+// scal[slot * nsys + m] <- sum of part over system m's blocks, in a fixed order, then the
 // per-system bookkeeping of `op` (PanelReduceOp, panel.hpp)
 hipError_t launch_sreduce(const SegTable &T, const double *part, double *scal, int slot, int op,
                           hipStream_t s);
-// active systems: x += ALPHA p ; r -= ALPHA q ; part[k] <- r.r over block k (every system)
+// active systems: x += ALPHA p ; r -= ALPHA q (with r32, also r32 = float(r)) ; part[k] <- r.r over
+// block k (every system)
 hipError_t launch_supdate_xr(const SegTable &T, const double *scal, double *x, double *r,
-                             const double *p, const double *q, double *part, hipStream_t s);
-// active systems: p = z + BETA p
-hipError_t launch_supdate_p(const SegTable &T, const double *scal, const double *z, double *p,
-                            hipStream_t s);
+                             const double *p, const double *q, double *part, float *r32, hipStream_t s);
+// active systems: p = z + BETA p (z in double or float)
+template <class TZ>
+hipError_t launch_supdate_p(const SegTable &T, const double *scal, const TZ *z, double *p, hipStream_t s);
 // NONFINITE of system m = 1 if its segment of a holds a non-finite entry (NONFINITE pre-zeroed)
 hipError_t launch_sfinite(const SegTable &T, const double *a, double *scal, hipStream_t s);
 // every slot zero, then RTOL and MAXIT of every system

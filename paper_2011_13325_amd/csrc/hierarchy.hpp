@@ -270,6 +270,8 @@ void build_sweep_stages(DevArena &ar, Level &L, const Pattern &Ap, const std::ve
 // z = V(r) on level-0 vectors in the hierarchy's solve numbering (FP64, or the FP32 V-cycle
 // with conversions at the boundary).
 void vcycle_apply(eamg_hierarchy *h, const double *r, double *z, bool f32, hipStream_t s);
+// The FP32 V-cycle on level 0's own FP32 vectors: x32 = V(b32).
+void vcycle_apply32(eamg_hierarchy *h, hipStream_t s);
 // Panel launch shapes tuned on the hierarchy for K columns; (time before, after) in ms.
 std::pair<double, double> tune_panels(eamg_hierarchy *h, int K, hipStream_t s);
 // z = V(r) for level-0 vectors in the natural numbering (eamg_vcycle's operation), with the

@@ -424,12 +424,14 @@ __global__ __launch_bounds__(kPB) void k_pspmv(int n_rows, int K, const int *__r
 
 constexpr int kPDotMax = 1024;
 
+// b in double, or the FP32 V-cycle's output read as it is
+template <class TB>
 __global__ __launch_bounds__(kPB) void k_pdot(int64_t n, int K, const double *__restrict__ a,
-                                              const double *__restrict__ b, double *part) {
+                                              const TB *__restrict__ b, double *part) {
   __shared__ double sh[kPB];
   double s = 0.0;
   for (int64_t i = int64_t(blockIdx.x) * kPB + threadIdx.x; i < n; i += int64_t(gridDim.x) * kPB)
-    s = fma(a[i], b[i], s);
+    s = fma(a[i], double(b[i]), s);
   const double t = pcol_sum(s, K, sh);
   if (int(threadIdx.x) < K) part[int64_t(blockIdx.x) * K + threadIdx.x] = t;
 }
@@ -508,7 +510,8 @@ __global__ __launch_bounds__(kPB) void k_preduce(int nparts, int K, const double
 
 __global__ __launch_bounds__(kPB) void k_pupdate_xr(int64_t n, int K, const double *__restrict__ scal,
                                                     double *x, double *r, const double *__restrict__ p,
-                                                    const double *__restrict__ q, double *part) {
+                                                    const double *__restrict__ q, double *part,
+                                                    float *__restrict__ r32) {
   __shared__ double sh[kPB];
   const int k = threadIdx.x & (K - 1);
   const bool active = scal[PS_ACTIVE * K + k] != 0.0;
@@ -520,6 +523,7 @@ __global__ __launch_bounds__(kPB) void k_pupdate_xr(int64_t n, int K, const doub
       x[i] = fma(alpha, p[i], x[i]);
       ri = fma(-alpha, q[i], ri);
       r[i] = ri;
+      if (r32) r32[i] = float(ri);
     }
     s = fma(ri, ri, s);
   }
@@ -527,13 +531,14 @@ __global__ __launch_bounds__(kPB) void k_pupdate_xr(int64_t n, int K, const doub
   if (int(threadIdx.x) < K) part[int64_t(blockIdx.x) * K + threadIdx.x] = t;
 }
 
+template <class TZ>
 __global__ __launch_bounds__(kPB) void k_pupdate_p(int64_t n, int K, const double *__restrict__ scal,
-                                                   const double *__restrict__ z, double *p) {
+                                                   const TZ *__restrict__ z, double *p) {
   const int k = threadIdx.x & (K - 1);
   if (scal[PS_ACTIVE * K + k] == 0.0) return;
   const double beta = scal[PS_BETA * K + k];
   for (int64_t i = int64_t(blockIdx.x) * kPB + threadIdx.x; i < n; i += int64_t(gridDim.x) * kPB)
-    p[i] = fma(beta, p[i], z[i]);
+    p[i] = fma(beta, p[i], double(z[i]));
 }
 
 __global__ void k_pinit_scal(int K, double rtol, double max_it, double *scal) {
@@ -711,10 +716,10 @@ int pdot_blocks(int64_t n) {
   return int(b < kPDotMax ? (b < 1 ? 1 : b) : kPDotMax);
 }
 
-hipError_t launch_pdot(int64_t n, int K, const double *a, const double *b, double *part,
-                       hipStream_t s) {
+template <class TB>
+hipError_t launch_pdot(int64_t n, int K, const double *a, const TB *b, double *part, hipStream_t s) {
   if (!valid_k(K)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_pdot, dim3(pdot_blocks(n)), dim3(kPB), 0, s, n, K, a, b, part);
+  hipLaunchKernelGGL(k_pdot<TB>, dim3(pdot_blocks(n)), dim3(kPB), 0, s, n, K, a, b, part);
   EAMG_PCHECK();
 }
 
@@ -726,16 +731,16 @@ hipError_t launch_preduce(int nparts, int K, const double *part, double *scal, i
 }
 
 hipError_t launch_pupdate_xr(int64_t n, int K, const double *scal, double *x, double *r,
-                             const double *p, const double *q, double *part, hipStream_t s) {
+                             const double *p, const double *q, double *part, float *r32, hipStream_t s) {
   if (!valid_k(K)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_pupdate_xr, dim3(pdot_blocks(n)), dim3(kPB), 0, s, n, K, scal, x, r, p, q, part);
+  hipLaunchKernelGGL(k_pupdate_xr, dim3(pdot_blocks(n)), dim3(kPB), 0, s, n, K, scal, x, r, p, q, part, r32);
   EAMG_PCHECK();
 }
 
-hipError_t launch_pupdate_p(int64_t n, int K, const double *scal, const double *z, double *p,
-                            hipStream_t s) {
+template <class TZ>
+hipError_t launch_pupdate_p(int64_t n, int K, const double *scal, const TZ *z, double *p, hipStream_t s) {
   if (!valid_k(K)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_pupdate_p, dim3(pdot_blocks(n)), dim3(kPB), 0, s, n, K, scal, z, p);
+  hipLaunchKernelGGL(k_pupdate_p<TZ>, dim3(pdot_blocks(n)), dim3(kPB), 0, s, n, K, scal, z, p);
   EAMG_PCHECK();
 }
 
@@ -776,6 +781,10 @@ hipError_t launch_punpack(int n, int bs, int K, int nrhs, const int *perm, const
   EAMG_PCHECK();
 }
 
+template hipError_t launch_pdot<double>(int64_t, int, const double *, const double *, double *, hipStream_t);
+template hipError_t launch_pdot<float>(int64_t, int, const double *, const float *, double *, hipStream_t);
+template hipError_t launch_pupdate_p<double>(int64_t, int, const double *, const double *, double *, hipStream_t);
+template hipError_t launch_pupdate_p<float>(int64_t, int, const double *, const float *, double *, hipStream_t);
 template hipError_t launch_pgs_fwd<double>(const SolveMat &, const double *, int, int, int, const double *, double *, double *, hipStream_t);
 template hipError_t launch_pgs_fwd<float>(const SolveMat &, const float *, int, int, int, const float *, float *, float *, hipStream_t);
 template hipError_t launch_pgs_bwd<double>(const SolveMat &, const double *, int, int, int, const double *, double *, hipStream_t);

@@ -2,12 +2,10 @@
 //
 // A panel holds K right-hand sides of one level interleaved: entry (dof d, column k) of a panel
 // vector lives at v[d * K + k], so the K values of one dof are contiguous.  Every sparse matrix
-// kernel gives one block row to a wavefront: 64 / K sub-teams of K lanes share out the row's
-// blocks, lane k of a sub-team computing column k, and a shuffle reduction adds the sub-teams'
-// sums.  A matrix block is read once per sub-team (its K lanes load the same address) and
-// reused for all K columns; the gathered vector entries are K-wide contiguous loads.  K is a
-// power of two in [1, 64]; lanes of different columns never combine values, so the columns
-// stay independent in every kernel.
+// kernel gives one block row to a team of one or four wavefronts: sub-teams of lanes, each covering
+// the K columns, share out the row's blocks, and the row's sums spread over the team's lanes, which
+// finish the row together (panel.hip).  K is a power of two in [1, 64]; values of different columns
+// are never combined, so the columns stay independent in every kernel.
 //
 // Matrices are the SolveMat block storage of the single-vector path (kernels.hpp), with rows
 // in the level's colour-major order.  All pointers are device pointers; every launcher
@@ -63,17 +61,18 @@ enum PanelReduceOp : int {
   PRED_STORE = 0, PRED_INIT = 1, PRED_RHO0 = 2, PRED_ALPHA = 3, PRED_BETA = 4, PRED_RR = 5
 };
 int pdot_blocks(int64_t n);
-// part[wg * K + k] <- per-column partials of a.b over the n entries
-hipError_t launch_pdot(int64_t n, int K, const double *a, const double *b, double *part,
-                       hipStream_t s);
+// part[wg * K + k] <- per-column partials of a.b over the n entries (b in double or float)
+template <class TB>
+hipError_t launch_pdot(int64_t n, int K, const double *a, const TB *b, double *part, hipStream_t s);
 hipError_t launch_preduce(int nparts, int K, const double *part, double *scal, int slot, int op,
                           hipStream_t s);
-// Active columns: X += ALPHA P ; R -= ALPHA Q ; part <- per-column partials of R.R
+// Active columns: X += ALPHA P ; R -= ALPHA Q (with r32, also r32 = float(R)) ; part <- per-column
+// partials of R.R
 hipError_t launch_pupdate_xr(int64_t n, int K, const double *scal, double *x, double *r,
-                             const double *p, const double *q, double *part, hipStream_t s);
-// Active columns: P = Z + BETA P
-hipError_t launch_pupdate_p(int64_t n, int K, const double *scal, const double *z, double *p,
-                            hipStream_t s);
+                             const double *p, const double *q, double *part, float *r32, hipStream_t s);
+// Active columns: P = Z + BETA P (Z in double or float)
+template <class TZ>
+hipError_t launch_pupdate_p(int64_t n, int K, const double *scal, const TZ *z, double *p, hipStream_t s);
 // Per-column solve state: RTOL, MAXIT, zero everything else.
 hipError_t launch_pinit_scal(int K, double rtol, int max_it, double *scal, hipStream_t s);
 // NONFINITE[k] = 1 if column k of a holds a non-finite entry (NONFINITE pre-zeroed)
