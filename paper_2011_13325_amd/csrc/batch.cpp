@@ -26,6 +26,7 @@ struct BatchWork {
   // V-cycle panels per precision ([0] FP64, [1] FP32) and level: x, b, r
   bool have[2] = {false, false};
   std::vector<void *> vx[2], vb[2], vr[2];
+  std::vector<void *> vu[2];   // right-hand sides of grouped sweep stages (levels that have some)
   hipStream_t cap = nullptr;
   hipGraphExec_t g[2] = {nullptr, nullptr};
   bool tried[2] = {false, false};
@@ -84,6 +85,7 @@ BatchWork *ensure_work(eamg_hierarchy *h, int K, bool f32) {
     w->vx[p].assign(nl, nullptr);
     w->vb[p].assign(nl, nullptr);
     w->vr[p].assign(nl, nullptr);
+    w->vu[p].assign(nl, nullptr);
     for (size_t l = 0; l < nl; ++l) {
       const size_t n = size_t(level_dofs(h->lv[l])) * K * vsz;
       const bool coarsest = l + 1 == nl;
@@ -93,6 +95,7 @@ BatchWork *ensure_work(eamg_hierarchy *h, int K, bool f32) {
         w->vb[p][l] = w->arena.alloc<char>(n);
       }
       if (!coarsest) w->vr[p][l] = w->arena.alloc<char>(n);
+      if (h->lv[l].u) w->vu[p][l] = w->arena.alloc<char>(n);
     }
     w->have[p] = true;
   }
@@ -102,6 +105,60 @@ BatchWork *ensure_work(eamg_hierarchy *h, int K, bool f32) {
 template <class T>
 T *vp(void *v) {
   return static_cast<T *>(v);
+}
+
+// Whether stage k of a panel sweep runs as a group.  A launch costs 4 to 7 us beyond its blocks (more
+// with more columns), a block its values at 3 TB/s and its K columns of the gathered panel at 8 TB/s
+// (64^3, 32 columns, FP32: 10.5 and 22.8 us for colours of 42,000 and 146,000 blocks; 37x29x33, 8 columns,
+// FP64: 22 us for the 130,000 blocks of an S); the group saves its colours' launches but one or two
+// and adds the blocks of S, planned for a single vector.  64^3 x 32 FP32 82.7 -> 70.1 ms.
+bool panel_group(const Level &L, int k, bool fwd, int K, double vs) {
+  if (!L.is_group(k)) return false;
+  const double launch = 4e-6 + 5e-8 * K;
+  const double block = L.bs * L.bs * vs / 3e12 + L.bs * K * vs / 8e12;
+  const double colours = L.cut[size_t(k) + 1] - L.cut[size_t(k)];
+  const double launches = fwd && k == 0 ? 1.0 : 2.0;
+  return launches * launch + (fwd ? L.sh_sf : L.sh_sb)[size_t(k)].blocks * block < colours * launch;
+}
+
+// The group matrix of stage k with its row team: a workgroup per row where its sub-teams find a block
+// each in an average row.
+SolveMat panel_smat(const Level &L, int k, bool fwd) {
+  SolveMat S = fwd ? L.Sf : L.Sb;
+  const LaunchShape &sh = (fwd ? L.sh_sf : L.sh_sb)[size_t(k)];
+  S.n_rows = L.Sf.n_rows;
+  S.panel_waves = sh.blocks >= 16.0 * sh.rows ? 4 : 1;
+  return S;
+}
+
+// Stage k of the panel sweeps of level L (u: the level's vu panel).
+template <class T>
+hipError_t pfwd_stage(const Level &L, const SolveMat &A, const T *Dinv, int k, int K, const T *b, T *x, T *r,
+                      T *u, hipStream_t s) {
+  hipError_t e = hipSuccess;
+  if (panel_group(L, k, true, K, sizeof(T))) {
+    if (k > 0) {
+      e = launch_pgroup_rhs<T>(A, L.lo_end, L.row0(k), L.row1(k), K, b, x, u, s);
+      if (e != hipSuccess) return e;
+    }
+    return launch_pgroup_fwd<T>(A, panel_smat(L, k, true), Dinv, L.row0(k), L.row1(k), K, k > 0 ? u : b, x, r, s);
+  }
+  for (int c = L.cut[size_t(k)]; c < L.cut[size_t(k) + 1] && e == hipSuccess; ++c)
+    e = launch_pgs_fwd<T>(A, Dinv, L.color_ptr[c], L.color_ptr[c + 1], K, b, x, r, s);
+  return e;
+}
+template <class T>
+hipError_t pbwd_stage(const Level &L, const SolveMat &A, const T *Dinv, int k, int K, const T *b, T *x, T *u,
+                      hipStream_t s) {
+  hipError_t e = hipSuccess;
+  if (panel_group(L, k, false, K, sizeof(T))) {
+    e = launch_pgroup_rhs<T>(A, nullptr, L.row0(k), L.row1(k), K, b, x, u, s);
+    if (e != hipSuccess) return e;
+    return launch_pgroup_bwd<T>(panel_smat(L, k, false), Dinv, L.row0(k), L.row1(k), K, u, x, s);
+  }
+  for (int c = L.cut[size_t(k) + 1] - 1; c >= L.cut[size_t(k)] && e == hipSuccess; --c)
+    e = launch_pgs_bwd<T>(A, Dinv, L.color_ptr[c], L.color_ptr[c + 1], K, b, x, s);
+  return e;
 }
 
 template <class T>
@@ -126,16 +183,30 @@ void pvcycle_t(eamg_hierarchy *h, BatchWork *w, size_t l, const T *b, T *x, hipS
   }
   const int bs = L.bs;
   const T *Dinv = bufs<T>(L).Dinv;
-  T *R = vp<T>(w->vr[pi][l]);
+  T *R = vp<T>(w->vr[pi][l]), *U = vp<T>(w->vu[pi][l]);
   double fwd_bytes = 0.0, bwd_bytes = 0.0;
-  for (int c = 0; c < L.ncolors; ++c) {
-    fwd_bytes += launch_bytes(L.sh_fwd[c], LK_GS_FWD, bs, bs, vs, K);
-    bwd_bytes += launch_bytes(L.sh_bwd[c], LK_GS_BWD, bs, bs, vs, K);
+  int fwd_n = 0, bwd_n = 0;
+  for (int k = 0; k < L.stages(); ++k) {
+    if (panel_group(L, k, true, K, vs)) {
+      fwd_bytes += (k > 0 ? launch_bytes(L.sh_rf[k], LK_RESID, bs, bs, vs, K) : 0.0) +
+                   launch_bytes(L.sh_sf[k], LK_GS_FWD, bs, bs, vs, K);
+      fwd_n += k > 0 ? 2 : 1;
+    } else {
+      for (int c = L.cut[k]; c < L.cut[k + 1]; ++c) fwd_bytes += launch_bytes(L.sh_fwd[c], LK_GS_FWD, bs, bs, vs, K);
+      fwd_n += L.cut[k + 1] - L.cut[k];
+    }
+    if (panel_group(L, k, false, K, vs)) {
+      bwd_bytes += launch_bytes(L.sh_rb[k], LK_RESID, bs, bs, vs, K) + launch_bytes(L.sh_sb[k], LK_GS_BWD, bs, bs, vs, K);
+      bwd_n += 2;
+    } else {
+      for (int c = L.cut[k]; c < L.cut[k + 1]; ++c) bwd_bytes += launch_bytes(L.sh_bwd[c], LK_GS_BWD, bs, bs, vs, K);
+      bwd_n += L.cut[k + 1] - L.cut[k];
+    }
   }
   const std::string gs = "k_pgs_color<" + ty + ", " + std::to_string(bs);
-  timed_n(h, "pgs_fwd", lvname(h, l, gs + ", true>"), fwd_bytes, L.ncolors, s, [&] {
-    for (int c = 0; c < L.ncolors; ++c) {
-      const hipError_t e = launch_pgs_fwd<T>(L.Am, Dinv, L.color_ptr[c], L.color_ptr[c + 1], K, b, x, R, s);
+  timed_n(h, "pgs_fwd", lvname(h, l, gs + ", true>"), fwd_bytes, fwd_n, s, [&] {
+    for (int k = 0; k < L.stages(); ++k) {
+      const hipError_t e = pfwd_stage<T>(L, L.Am, Dinv, k, K, b, x, R, U, s);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -153,9 +224,9 @@ void pvcycle_t(eamg_hierarchy *h, BatchWork *w, size_t l, const T *b, T *x, hipS
         launch_bytes(L.sh_P, LK_RECT_ACC, bs, L.kc, vs, K), s,
         [&] { return launch_prect<T>(L.Pm, K, Cx, x, true, s); });
   const SolveMat Mb = L.panel_mat(L.pw_bwd);
-  timed_n(h, "pgs_bwd", lvname(h, l, gs + ", false>"), bwd_bytes, L.ncolors, s, [&] {
-    for (int c = L.ncolors - 1; c >= 0; --c) {
-      const hipError_t e = launch_pgs_bwd<T>(Mb, Dinv, L.color_ptr[c], L.color_ptr[c + 1], K, b, x, s);
+  timed_n(h, "pgs_bwd", lvname(h, l, gs + ", false>"), bwd_bytes, bwd_n, s, [&] {
+    for (int k = L.stages() - 1; k >= 0; --k) {
+      const hipError_t e = pbwd_stage<T>(L, Mb, Dinv, k, K, b, x, U, s);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -488,7 +559,7 @@ std::pair<double, double> tune_panels(eamg_hierarchy *h, int K, hipStream_t s) {
     Level &L = h->lv[l];
     double *b = l == 0 ? w->r : vp<double>(w->vb[0][l]);
     double *x = l == 0 ? w->z : vp<double>(w->vx[0][l]);
-    double *r = vp<double>(w->vr[0][l]);
+    double *r = vp<double>(w->vr[0][l]), *u = vp<double>(w->vu[0][l]);
     double *cb = vp<double>(w->vb[0][l + 1]);
     double *cx = vp<double>(w->vx[0][l + 1]);
     const int64_t nv = level_dofs(L) * K, nc = level_dofs(h->lv[l + 1]) * K;
@@ -497,16 +568,16 @@ std::pair<double, double> tune_panels(eamg_hierarchy *h, int K, hipStream_t s) {
     // forward sweep, residual update and backward sweep tuned apart (each reads a different part
     // of the rows), then the transfers
     auto fwd = [&] {
-      for (int c = 0; c < L.ncolors; ++c)
-        hip_check(launch_pgs_fwd<double>(L.Am, L.Dinv, L.color_ptr[c], L.color_ptr[c + 1], K, b, x, r, s), "pgs");
+      for (int k = 0; k < L.stages(); ++k)
+        hip_check(pfwd_stage<double>(L, L.Am, L.Dinv, k, K, b, x, r, u, s), "pgs");
     };
     auto resid = [&] {
       hip_check(launch_presid_upper<double>(L.panel_mat(L.pw_resid), K, x, r, s), "presid");
     };
     auto bwd = [&] {
       const SolveMat Mb = L.panel_mat(L.pw_bwd);
-      for (int c = L.ncolors - 1; c >= 0; --c)
-        hip_check(launch_pgs_bwd<double>(Mb, L.Dinv, L.color_ptr[c], L.color_ptr[c + 1], K, b, x, s), "pgs");
+      for (int k = L.stages() - 1; k >= 0; --k)
+        hip_check(pbwd_stage<double>(L, Mb, L.Dinv, k, K, b, x, u, s), "pgs");
     };
     auto restrict_ = [&] { hip_check(launch_prect<double>(L.Rm, K, r, cb, false, s), "prect"); };
     auto prolong = [&] { hip_check(launch_prect<double>(L.Pm, K, cx, x, true, s), "prect"); };

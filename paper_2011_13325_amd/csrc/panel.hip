@@ -653,6 +653,68 @@ hipError_t launch_pgs_bwd(const SolveMat &A, const T *Dinv, int r0, int r1, int 
 }
 
 template <class T>
+hipError_t launch_pgroup_rhs(const SolveMat &A, const int *lo_end, int r0, int r1, int K, const T *b,
+                             const T *x, T *u, hipStream_t s) {
+  if (r0 < 0 || r1 > A.n_rows || !valid_k(K)) return hipErrorInvalidValue;
+  if (r1 <= r0) return hipSuccess;
+  const bool f32 = sizeof(T) == 4;
+  const T *val = lo_end ? reinterpret_cast<const T *>(f32 ? (const void *)A.lo_val32 : (const void *)A.lo_val)
+                        : pvals<T>(A);
+  const int *rp = lo_end ? A.lo_rp : A.rp, *re = lo_end ? lo_end : A.rp + 1;
+  const int *col = lo_end ? A.lo_col : A.col;
+  if (!val || !rp) return hipErrorInvalidValue;
+#define EAMG_PRHS(B_)                                                                             \
+  EAMG_PTEAM(W, A, EAMG_PCOLS(C, hipLaunchKernelGGL((k_presid<T, B_, C, W, false>),              \
+                                                    dim3(pteam_grid(r1 - r0, W)), dim3(kPB), 0,  \
+                                                    s, r0, r1, K, rp, re, col, val, x, b, u)))
+  switch (A.br) {
+    case 1: EAMG_PRHS(1); break;
+    case 3: EAMG_PRHS(3); break;
+    case 6: EAMG_PRHS(6); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef EAMG_PRHS
+  EAMG_PCHECK();
+}
+
+namespace {
+template <class T, bool FWD>
+hipError_t launch_pgroup(const SolveMat &S, const T *dval, const T *Dinv, int r0, int r1, int K,
+                         const T *u, T *x, T *r, hipStream_t s) {
+  if (r0 < 0 || r1 > S.n_rows || !valid_k(K)) return hipErrorInvalidValue;
+  if (r1 <= r0) return hipSuccess;
+  const T *val = pvals<T>(S);
+  if (!val || !S.rp || (FWD && !dval)) return hipErrorInvalidValue;
+#define EAMG_PGRP(B_)                                                                               \
+  EAMG_PTEAM(W, S, EAMG_PCOLS(C, hipLaunchKernelGGL((k_pgs_color<T, B_, FWD, C, W>),               \
+                                                    dim3(pteam_grid(r1 - r0, W)), dim3(kPB), 0, s, \
+                                                    r0, r1, K, S.rp, S.col, val, dval, Dinv, u, u, \
+                                                    x, r)))
+  switch (S.br) {
+    case 1: EAMG_PGRP(1); break;
+    case 3: EAMG_PGRP(3); break;
+    case 6: EAMG_PGRP(6); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef EAMG_PGRP
+  EAMG_PCHECK();
+}
+}  // namespace
+
+template <class T>
+hipError_t launch_pgroup_fwd(const SolveMat &A, const SolveMat &S, const T *Dinv, int r0, int r1, int K,
+                             const T *u, T *x, T *r, hipStream_t s) {
+  const T *dval = reinterpret_cast<const T *>(sizeof(T) == 4 ? (const void *)A.dg_val32 : (const void *)A.dg_val);
+  return launch_pgroup<T, true>(S, dval, Dinv, r0, r1, K, u, x, r, s);
+}
+
+template <class T>
+hipError_t launch_pgroup_bwd(const SolveMat &S, const T *Dinv, int r0, int r1, int K, const T *u, T *x,
+                             hipStream_t s) {
+  return launch_pgroup<T, false>(S, nullptr, Dinv, r0, r1, K, u, x, nullptr, s);
+}
+
+template <class T>
 hipError_t launch_presid_upper(const SolveMat &A, int K, const T *x, T *r, hipStream_t s) {
   if (A.n_rows == 0) return hipSuccess;
   const T *val = reinterpret_cast<const T *>(sizeof(T) == 4 ? (const void *)A.up_val32 : (const void *)A.up_val);
@@ -781,6 +843,12 @@ hipError_t launch_punpack(int n, int bs, int K, int nrhs, const int *perm, const
   EAMG_PCHECK();
 }
 
+template hipError_t launch_pgroup_rhs<double>(const SolveMat &, const int *, int, int, int, const double *, const double *, double *, hipStream_t);
+template hipError_t launch_pgroup_fwd<double>(const SolveMat &, const SolveMat &, const double *, int, int, int, const double *, double *, double *, hipStream_t);
+template hipError_t launch_pgroup_bwd<double>(const SolveMat &, const double *, int, int, int, const double *, double *, hipStream_t);
+template hipError_t launch_pgroup_rhs<float>(const SolveMat &, const int *, int, int, int, const float *, const float *, float *, hipStream_t);
+template hipError_t launch_pgroup_fwd<float>(const SolveMat &, const SolveMat &, const float *, int, int, int, const float *, float *, float *, hipStream_t);
+template hipError_t launch_pgroup_bwd<float>(const SolveMat &, const float *, int, int, int, const float *, float *, hipStream_t);
 template hipError_t launch_pdot<double>(int64_t, int, const double *, const double *, double *, hipStream_t);
 template hipError_t launch_pdot<float>(int64_t, int, const double *, const float *, double *, hipStream_t);
 template hipError_t launch_pupdate_p<double>(int64_t, int, const double *, const double *, double *, hipStream_t);

@@ -29,6 +29,19 @@ hipError_t launch_pgs_fwd(const SolveMat &A, const T *Dinv, int r0, int r1, int 
 template <class T>
 hipError_t launch_pgs_bwd(const SolveMat &A, const T *Dinv, int r0, int r1, int K, const T *b, T *x,
                           hipStream_t s);
+// Grouped sweep stages (SweepPlan, structure.hpp; as launch_group_rhs / _fwd / _bwd of kernels.hpp):
+//   U_i = B_i - (couplings outside the group) X; forward lo_end holds the ends of those left of the
+//   diagonal, backward (null) the whole row counts;
+//   T_i = U_i - sum_j S_ij U_j; forward X_i = Dinv_i T_i, R_i = T_i - A_ii X_i; backward X_i += Dinv_i T_i.
+template <class T>
+hipError_t launch_pgroup_rhs(const SolveMat &A, const int *lo_end, int r0, int r1, int K, const T *b,
+                             const T *x, T *u, hipStream_t s);
+template <class T>
+hipError_t launch_pgroup_fwd(const SolveMat &A, const SolveMat &S, const T *Dinv, int r0, int r1, int K,
+                             const T *u, T *x, T *r, hipStream_t s);
+template <class T>
+hipError_t launch_pgroup_bwd(const SolveMat &S, const T *Dinv, int r0, int r1, int K, const T *u, T *x,
+                             hipStream_t s);
 // R_i -= sum_{j > i} A_ij X_j on all rows.
 template <class T>
 hipError_t launch_presid_upper(const SolveMat &A, int K, const T *x, T *r, hipStream_t s);
