@@ -607,7 +607,7 @@ hipError_t resid_update(const Level &L, const T *x, T *r, hipStream_t s) {
   return hipSuccess;
 }
 
-// Stage k of the forward and of the backward sweep of level L.
+// Stage k of the forward and of the backward sweep of level L (rz: see launch_group_bwd).
 template <class T>
 hipError_t fwd_stage(Level &L, int k, const T *b, T *x, T *r, hipStream_t s) {
   const LevelBufs<T> B = bufs<T>(L);
@@ -624,7 +624,8 @@ hipError_t fwd_stage(Level &L, int k, const T *b, T *x, T *r, hipStream_t s) {
   return launch_group_fwd<T>(A, S, B.Dinv, L.row0(k), L.row1(k), u, x, r, s);
 }
 template <class T>
-hipError_t bwd_stage(Level &L, int k, const T *b, T *x, hipStream_t s) {
+hipError_t bwd_stage(Level &L, int k, const T *b, T *x, hipStream_t s, const double *cg_r = nullptr,
+                     double *rz = nullptr) {
   const LevelBufs<T> B = bufs<T>(L);
   const SolveMat A = L.bwd_mat(k);
   if (!L.is_group(k)) return launch_gs_bwd<T>(A, B.Dinv, L.row0(k), L.row1(k), b, x, s);
@@ -632,7 +633,7 @@ hipError_t bwd_stage(Level &L, int k, const T *b, T *x, hipStream_t s) {
   if (e != hipSuccess) return e;
   SolveMat S = L.Sb;
   S.group = L.gs_b[size_t(k)];
-  return launch_group_bwd<T>(S, B.Dinv, L.row0(k), L.row1(k), B.u, x, s);
+  return launch_group_bwd<T>(S, B.Dinv, L.row0(k), L.row1(k), B.u, x, s, cg_r, rz);
 }
 
 // Launches and algorithmic bytes (values of vs bytes) of stage k.
@@ -681,8 +682,20 @@ void dense_sets<float>(eamg_hierarchy *h, size_t l, const float *b, float *x, hi
     });
 }
 
+// Partials of the CG's r.z that the V-cycle's last launch leaves: where it covers all rows of level 0
+// (the level is one group), else 0.
+int rz_parts(const eamg_hierarchy *h) {
+  const Level &L = h->lv[0];
+  if (h->fused || h->lv.size() < 2 || L.stages() != 1 || !L.is_group(0)) return 0;
+  SolveMat S = L.Sb;
+  S.group = L.gs_b[0];
+  const int nb = group_blocks(S, L.row0(0), L.row1(0));
+  return nb <= kInlineParts ? nb : 0;
+}
+
+// rz (level 0 with rz_parts): partials of h->r . x
 template <class T>
-void vcycle_t(eamg_hierarchy *h, size_t l, const T *b, T *x, hipStream_t s) {
+void vcycle_t(eamg_hierarchy *h, size_t l, const T *b, T *x, hipStream_t s, double *rz = nullptr) {
   Level &L = h->lv[l];
   const bool f32 = sizeof(T) == 4;
   const std::string ty = type_name<T>();
@@ -757,12 +770,12 @@ void vcycle_t(eamg_hierarchy *h, size_t l, const T *b, T *x, hipStream_t s) {
     for (int k = ns - 1; k >= 0; --k)
       timed_n(h, "gs_bwd", lvname(h, l, "c" + std::to_string(L.cut[size_t(k)]) + " " + gs + ", false>"),
               stage_bytes(L, k, false, vs), stage_launches(L, k, false), s,
-              [&] { return bwd_stage<T>(L, k, b, x, s); });
+              [&] { return bwd_stage<T>(L, k, b, x, s, h->r, rz); });
     return;
   }
   timed_n(h, "gs_bwd", lvname(h, l, gs + ", false>"), bwd_bytes, bwd_n, s, [&] {
     for (int k = ns - 1; k >= 0; --k) {
-      const hipError_t e = bwd_stage<T>(L, k, b, x, s);
+      const hipError_t e = bwd_stage<T>(L, k, b, x, s, h->r, rz);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -784,55 +797,70 @@ void vcycle(eamg_hierarchy *h, const double *r, double *z, bool f32, hipStream_t
   }
 }
 
-// The second half of a PCG iteration, p set: q = A p, alpha, x += alpha p, r -= alpha q, r.r, and the
-// scalars published to the host.
-void pcg_step(eamg_hierarchy *h, bool f32, hipStream_t s) {
+// The second half of a PCG iteration: q = A p, alpha, x += alpha p, r -= alpha q, r.r, and the scalars
+// published to the host.  nrz = 0: p is set, its product is formed here; else p = z + beta p first,
+// beta from the nrz partials of r.z in part_rr, inside the product where the hierarchy has a second
+// direction vector (pn).
+void pcg_step(eamg_hierarchy *h, bool f32, int nrz, hipStream_t s) {
   const Level &L0 = h->lv[0];
   const SolveMat &A = L0.Am;
   const int64_t N = int64_t(L0.n) * L0.bs;
-  const double vecb = 8.0 * N;
+  const double vecb = 8.0 * N, zb = f32 ? 4.0 * N : vecb;
   const int nd = dot_blocks(N), ns = spmv_blocks(A);
   if (nd > h->part_cap || ns > h->part_cap) fail(EAMG_ERR_INVALID_ARG, "partial-sum buffer too small");
-  timed(h, "spmv", tname("k_spmv", L0.bs, L0.bs), launch_bytes(L0.sh_spmv, LK_SPMV, L0.bs, L0.bs, 8.0, 1) + 8.0 * ns,
-        s, [&] { return launch_spmv(A, h->p, h->q, h->part, s); });
+  const double spmv_b = launch_bytes(L0.sh_spmv, LK_SPMV, L0.bs, L0.bs, 8.0, 1) + 8.0 * ns;
+  const bool dir = nrz && h->pn;
+  if (dir) {
+    timed(h, "spmv_dir", "k_spmv_dir<" + std::to_string(L0.bs) + (f32 ? ", float>" : ", double>"), spmv_b + vecb + zb, s, [&] {
+      return f32 ? launch_spmv_dir(A, h->scal, L0.x32, h->p, h->pn, h->q, nrz, h->part_rr, h->part, s)
+                 : launch_spmv_dir(A, h->scal, h->z, h->p, h->pn, h->q, nrz, h->part_rr, h->part, s);
+    });
+  } else {
+    if (nrz)
+      timed(h, "update_p", f32 ? "k_update_p<float>" : "k_update_p", 2.0 * vecb + zb, s, [&] {
+        return f32 ? launch_update_p(N, h->scal, L0.x32, h->p, nrz, h->part_rr, s)
+                   : launch_update_p(N, h->scal, h->z, h->p, nrz, h->part_rr, s);
+      });
+    timed(h, "spmv", tname("k_spmv", L0.bs, L0.bs), spmv_b, s,
+          [&] { return launch_spmv(A, h->p, h->q, h->part, s); });
+  }
   const bool inl = ns <= kInlineParts;
   if (!inl)
     timed(h, "reduce", "k_reduce", 8.0 * ns, s, [&] { return launch_reduce(ns, h->part, h->scal, SC_PQ, s); });
-  timed(h, "update_xr", "k_update_xr", 6.0 * vecb + (f32 ? 4.0 * N : 0.0) + 8.0 * nd, s, [&] {
-    return launch_update_xr(N, h->scal, h->x, h->r, h->p, h->q, h->part_rr, inl ? ns : 0, inl ? h->part : nullptr, s,
-                            f32 ? h->lv[0].b32 : nullptr);
+  const bool one = N <= kOneBlock;
+  timed(h, "update_xr", "k_update_xr", (dir ? 7.0 : 6.0) * vecb + (f32 ? 4.0 * N : 0.0) + 8.0 * nd, s, [&] {
+    return launch_update_xr(N, h->scal, h->x, h->r, dir ? h->pn : h->p, h->q, h->part_rr, inl ? ns : 0,
+                            inl ? h->part : nullptr, s, f32 ? h->lv[0].b32 : nullptr, dir ? h->p : nullptr,
+                            one ? h->ring_d : nullptr);
   });
-  timed(h, "publish", "k_publish", 8.0 * nd, s,
-        [&] { return launch_publish(nd, h->part_rr, h->scal, h->ring_d, s); });
+  if (!one)
+    timed(h, "publish", "k_publish", 8.0 * nd, s,
+          [&] { return launch_publish(nd, h->part_rr, h->scal, h->ring_d, s); });
 }
 
-// p = z + beta p, z the V-cycle's output (FP32: level 0's x32, else h->z).
-void pcg_direction(eamg_hierarchy *h, bool f32, hipStream_t s) {
+// Partials of r.z in part_rr; returns their number.
+int pcg_dot(eamg_hierarchy *h, bool f32, hipStream_t s) {
   const Level &L0 = h->lv[0];
   const int64_t N = int64_t(L0.n) * L0.bs;
-  const double vecb = 8.0 * N;
   const int nd = dot_blocks(N);
-  if (f32) {
-    timed(h, "dot", "k_dot<float>", vecb + 4.0 * N + 8.0 * nd, s,
-          [&] { return launch_dot(N, h->r, L0.x32, h->part, s); });
-    timed(h, "update_p", "k_update_p<float>", 2.0 * vecb + 4.0 * N, s,
-          [&] { return launch_update_p(N, h->scal, L0.x32, h->p, nd, h->part, s); });
-  } else {
-    timed(h, "dot", "k_dot", 2.0 * vecb + 8.0 * nd, s, [&] { return launch_dot(N, h->r, h->z, h->part, s); });
-    timed(h, "update_p", "k_update_p", 3.0 * vecb, s,
-          [&] { return launch_update_p(N, h->scal, h->z, h->p, nd, h->part, s); });
-  }
+  timed(h, "dot", f32 ? "k_dot<float>" : "k_dot", 8.0 * N + (f32 ? 4.0 : 8.0) * N + 8.0 * nd, s, [&] {
+    return f32 ? launch_dot(N, h->r, L0.x32, h->part_rr, s) : launch_dot(N, h->r, h->z, h->part_rr, s);
+  });
+  return nd;
 }
 
-// One PCG iteration after the stopping test.  With the FP32 V-cycle, it reads r's FP32 copy (written
-// with r by the previous update) and its output z is read in FP32 by the dot product and the p update.
+// One PCG iteration after the stopping test: z = V(r) (FP32: from r's FP32 copy, written with r by the
+// previous update, into level 0's x32), the partials of r.z, and the step.
 void enqueue_iteration(eamg_hierarchy *h, bool f32, hipStream_t s) {
+  const Level &L0 = h->lv[0];
+  int nrz = rz_parts(h);
+  double *rz = nrz ? h->part_rr : nullptr;
   if (f32)
-    vcycle_t<float>(h, 0, h->lv[0].b32, h->lv[0].x32, s);
+    vcycle_t<float>(h, 0, L0.b32, L0.x32, s, rz);
   else
-    vcycle(h, h->r, h->z, false, s);
-  pcg_direction(h, f32, s);
-  pcg_step(h, f32, s);
+    vcycle_t<double>(h, 0, h->r, h->z, s, rz);
+  if (!nrz) nrz = pcg_dot(h, f32, s);
+  pcg_step(h, f32, nrz, s);
 }
 
 // Estimated time of one iteration: its launches in a chain plus its bytes at the HBM rate.
@@ -989,20 +1017,15 @@ struct SolveRun {
     h->cg_beta.clear();
     hip_check(hipEventRecord(e0, s), "event");
     for (int k = 0; k < kRing; ++k) h->scal_h[SC_COUNT + 1 + size_t(k) * kRecord + kRecord - 1] = 0.0;
-    hip_check(launch_init_scal(sp.rtol, h->scal, s), "init");
-    hip_check(launch_perm_in(L0.n, L0.bs, L0.perm_d, h->dir, b_dev, h->bp, s), "perm_in");
-    hip_check(launch_finite_check(N, h->bp, h->scal, SC_NONFINITE, s), "finite");
-    hip_check(launch_dot(N, h->bp, h->bp, h->part, s), "dot");
-    hip_check(launch_reduce(nd, h->part, h->scal, SC_BB, s), "reduce");
+    hip_check(launch_start(N, L0.bs, L0.perm_d, h->dir, b_dev, h->bp, sp.use_x0 ? nullptr : h->x, h->r, r32(),
+                           sp.rtol, h->part, h->part_rr, h->scal, s),
+              "start");
     if (sp.use_x0) {
       hip_check(launch_perm_in(L0.n, L0.bs, L0.perm_d, h->dir, x_dev, h->x, s), "perm_in");
       hip_check(launch_spmv(A, h->x, h->q, nullptr, s), "spmv");
       hip_check(launch_sub(N, h->bp, h->q, h->r, s), "sub");
-    } else {
-      hip_check(launch_fill(N, 0.0, h->x, s), "fill");
-      hip_check(launch_copy(N, h->bp, h->r, s), "copy");
+      if (f32) hip_check(launch_convert<double, float>(N, h->r, r32(), s), "convert");
     }
-    if (f32) hip_check(launch_convert<double, float>(N, h->r, r32(), s), "convert");
     copy_scalars();
   }
   void complete_start_a() {
@@ -1017,13 +1040,9 @@ struct SolveRun {
   void enqueue_start_b() {
     precondition();
     if (f32)
-      hip_check(launch_convert<float, double>(N, h->lv[0].x32, h->p, s), "convert");
+      hip_check(launch_start_p(N, h->lv[0].x32, h->r, h->p, h->part, s), "start p");
     else
-      hip_check(launch_copy(N, h->z, h->p, s), "copy");
-    if (f32)
-      hip_check(launch_dot(N, h->r, h->lv[0].x32, h->part, s), "dot");
-    else
-      hip_check(launch_dot(N, h->r, h->z, h->part, s), "dot");
+      hip_check(launch_start_p(N, h->z, h->r, h->p, h->part, s), "start p");
     hip_check(launch_reduce(nd, h->part, h->scal, SC_RZ, s), "reduce");
     copy_scalars();
   }
@@ -1040,7 +1059,7 @@ struct SolveRun {
     }
   }
   // first iteration (p = z already set)
-  void enqueue_start_c() { pcg_step(h, f32, s); }
+  void enqueue_start_c() { pcg_step(h, f32, 0, s); }
 
   // Without an x0 the three phases are enqueued together, one wait for all: whatever the checks
   // find, the later phases only touch the hierarchy's own vectors, and r = b is not zero when r.z
@@ -1087,9 +1106,12 @@ struct SolveRun {
   }
 
   void eager_iteration() {
-    precondition();
-    pcg_direction(h, f32, s);
-    pcg_step(h, f32, s);
+    if (sp.precond) {
+      enqueue_iteration(h, f32, s);
+    } else {
+      precondition();
+      pcg_step(h, f32, pcg_dot(h, f32, s), s);
+    }
     wait();
   }
 
@@ -1120,10 +1142,8 @@ struct SolveRun {
   void enqueue_finish(double *x_dev) {
     const Level &L0 = h->lv[0];
     hip_check(launch_spmv(L0.Am, h->x, h->q, nullptr, s), "spmv");
-    hip_check(launch_sub(N, h->bp, h->q, h->z, s), "sub");
-    hip_check(launch_dot(N, h->z, h->z, h->part, s), "dot");
+    hip_check(launch_finish(N, L0.bs, L0.perm_d, h->x, h->bp, h->q, x_dev, h->part, s), "finish");
     hip_check(launch_reduce(nd, h->part, h->scal, SC_RR, s), "reduce");
-    hip_check(launch_perm_out(L0.n, L0.bs, L0.perm_d, h->x, x_dev, s), "perm_out");
     hip_check(hipEventRecord(e1, s), "event");
     copy_scalars();
   }
@@ -1447,7 +1467,8 @@ eamg_status eamg_setup(const eamg_problem *pb, const eamg_setup_params *params, 
     h->part = ar.alloc<double>(size_t(h->part_cap));
     h->scal = ar.alloc<double>(SC_COUNT);
 
-    h->part_rr = ar.alloc<double>(size_t(dot_blocks(N0)));
+    h->part_rr = ar.alloc<double>(size_t(std::max(dot_blocks(N0), kInlineParts)));
+    if (N0 <= kDirEntries) h->pn = ar.alloc<double>(size_t(N0));
 
     hip_check(hipHostMalloc(reinterpret_cast<void **>(&h->scal_h),
                             sizeof(double) * (SC_COUNT + 1 + size_t(kRing) * kRecord),

@@ -315,7 +315,8 @@ struct eamg_hierarchy {
   uint8_t *dir = nullptr;     // level-0 Dirichlet mask (natural)
   double *x = nullptr, *r = nullptr, *z = nullptr, *p = nullptr, *q = nullptr, *bp = nullptr;
   double *part = nullptr, *scal = nullptr;
-  double *part_rr = nullptr;  // partials of r.r (written while p.q's are read)
+  double *part_rr = nullptr;  // partials of r.r, then of r.z (written while p.q's are read)
+  double *pn = nullptr;       // second direction vector (launch_spmv_dir), or null
   int part_cap = 0;   // entries of part: the largest partial-sum count any launch shape can need
   double *scal_h = nullptr;   // pinned; single systems: the scalars, then the ring of records
   double *ring_d = nullptr;   // the ring as the device sees it

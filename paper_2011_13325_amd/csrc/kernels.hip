@@ -373,11 +373,10 @@ __device__ inline void gather_block(const T *x, int64_t c, T (&xv)[BC]) {
   }
 }
 
-// acc[r] += sum over blocks p in [p0, p1) (strided by G) of A_p x_col(p)
-template <class T, int BR, int BC>
-__device__ inline void row_accumulate(int p0, int p1, int lane, int G, const int *__restrict__ col,
-                                      const T *__restrict__ val, int64_t nnz, const T *x,
-                                      T (&acc)[BR]) {
+// acc[r] += sum over blocks p in [p0, p1) (strided by G) of A_p x_col(p), x_c read by load(c, out)
+template <class T, int BR, int BC, class F>
+__device__ inline void row_accumulate_of(int p0, int p1, int lane, int G, const int *__restrict__ col,
+                                         const T *__restrict__ val, T (&acc)[BR], F &&load) {
   for (int p = p0 + lane; p < p1; p += G) {
     const int64_t c = col[p];
     T v[BR * BC];
@@ -386,12 +385,19 @@ __device__ inline void row_accumulate(int p0, int p1, int lane, int G, const int
     // every value load is issued before the gathers of x, which wait for the column index
     __builtin_amdgcn_sched_barrier(0);
     T xv[BC];
-    gather_block<T, BC>(x, c, xv);
+    load(c, xv);
 #pragma unroll
     for (int r = 0; r < BR; ++r)
 #pragma unroll
       for (int cc = 0; cc < BC; ++cc) acc[r] = fma(v[r * BC + cc], xv[cc], acc[r]);
   }
+}
+template <class T, int BR, int BC>
+__device__ inline void row_accumulate(int p0, int p1, int lane, int G, const int *__restrict__ col,
+                                      const T *__restrict__ val, int64_t nnz, const T *x,
+                                      T (&acc)[BR]) {
+  row_accumulate_of<T, BR, BC>(p0, p1, lane, G, col, val, acc,
+                               [x](int64_t c, T (&xv)[BC]) { gather_block<T, BC>(x, c, xv); });
 }
 
 template <int BR, int BC>
@@ -442,8 +448,9 @@ __device__ inline T pick(const T (&v)[B], int i) {
 // colour writes x_i, so the prefetched x_i[q] is the value the gathers see.
 // y: the vector the blocks multiply, x itself for a colour.  For a group of colours b and
 // y are both its right-hand side u and (rp, col, val) the group's matrix S (SweepPlan).
+// Returns the lane's component of the new x_i (lanes < B of a valid row).
 template <class T, int B, bool FWD, int W>
-__device__ inline void gs_row(int row, bool valid, int lane, int G, const int *__restrict__ rp,
+__device__ inline T gs_row(int row, bool valid, int lane, int G, const int *__restrict__ rp,
                               const int *__restrict__ col, const T *__restrict__ val, int64_t nnz,
                               const T *__restrict__ dval, int64_t nd, const T *__restrict__ Dinv,
                               const T *__restrict__ b, const T *y, T *x, T *r, T *sh) {
@@ -498,8 +505,10 @@ __device__ inline void gs_row(int row, bool valid, int lane, int G, const int *_
       r[int64_t(row) * B + lane] = rq;
     }
   } else {
-    if (own) x[int64_t(row) * B + lane] = xo + xq;
+    xq = xo + xq;
+    if (own) x[int64_t(row) * B + lane] = xq;
   }
+  return xq;
 }
 
 // r_i = b_i - sum over the blocks [rp[i], re[i]) of A_ij x_j for one row (b may be r).
@@ -562,18 +571,29 @@ __global__ __launch_bounds__(kBlock) void k_group_rhs(int r0, int r1, int G, con
   resid_row<T, B, W>(row, row < r1, lane, G, rp, re, col, val, nnz, x, b, u, sh);
 }
 
-template <class T, int B, bool FWD, int W>
+//
+// rz (backward): the workgroup's part of the CG's r.z over its rows, z the new x, in rz[workgroup]
+// (the sweep's last launch, of a level that is one group).
+template <class T, int B, bool FWD, int W, bool RZ>
 __global__ __launch_bounds__(kBlock) void k_gs_group(int r0, int r1, int G, const int *__restrict__ rp,
                                                     const int *__restrict__ col,
                                                     const T *__restrict__ val, int64_t nnz,
                                                     const T *__restrict__ dval, int64_t nd,
                                                     const T *__restrict__ Dinv,
                                                     const T *__restrict__ u, T *__restrict__ x,
-                                                    T *__restrict__ r) {
+                                                    T *__restrict__ r, const double *__restrict__ cg_r,
+                                                    double *__restrict__ rz) {
   __shared__ T sh[W > 1 ? (kBlock / 64) * B : 1];
   const int lane = threadIdx.x & (G - 1);
   const int row = r0 + xcd_block() * (kBlock / G) + threadIdx.x / G;
-  gs_row<T, B, FWD, W>(row, row < r1, lane, G, rp, col, val, nnz, dval, nd, Dinv, u, u, x, r, sh);
+  const bool own = RZ && row < r1 && lane < B;
+  const double rq = own ? cg_r[int64_t(row) * B + lane] : 0.0;
+  const T z = gs_row<T, B, FWD, W>(row, row < r1, lane, G, rp, col, val, nnz, dval, nd, Dinv, u, u, x, r, sh);
+  if (RZ) {
+    __shared__ double shd[kBlock];
+    const double t = block_sum(own ? rq * double(z) : 0.0, shd);
+    if (threadIdx.x == 0) rz[blockIdx.x] = t;
+  }
 }
 
 // One row of S per workgroup (launch_group_fill); thread e owns entry e, e + 256, ... of the row.
@@ -731,6 +751,18 @@ __global__ __launch_bounds__(kBlock) void k_reduce(int nparts, const double *__r
   if (threadIdx.x == 0) scal[slot] = t;
 }
 
+// End of an iteration, one thread: t = r.r (see launch_publish).
+__device__ inline void publish(double t, double *scal, double *ring) {
+  const double it = scal[SC_ITER] + 1.0;
+  scal[SC_RR] = t;
+  scal[SC_ITER] = it;
+  if (sqrt(t) <= scal[SC_RTOL] * sqrt(scal[SC_BB])) scal[SC_DONE] = 1.0;
+  double *rec = ring + (int(it) & (kRing - 1)) * kRecord;
+  for (int i = 0; i < SC_COUNT; ++i) rec[i] = scal[i];
+  __threadfence_system();
+  __hip_atomic_store(rec + kRecord - 1, it, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The scalars of an iteration are formed by the kernels that use them: a kernel that only sums a
 // thousand partials costs 2.5 to 4.7 us in the chain of an iteration, the sum inside the next kernel
 // about one.  Every workgroup takes the same sum; workgroup 0 stores the scalars, in slots that no
@@ -740,7 +772,8 @@ __global__ __launch_bounds__(kBlock) void k_update_xr(int64_t n, double *scal, d
                                                      const double *__restrict__ q,
                                                      double *__restrict__ part, int npq,
                                                      const double *__restrict__ pq,
-                                                     float *__restrict__ r32) {
+                                                     float *__restrict__ r32, double *__restrict__ pold,
+                                                     double *ring) {
   __shared__ double sh[kBlock];
   const double rz = scal[SC_RZ];
   const bool done = scal[SC_DONE] != 0.0;
@@ -755,8 +788,10 @@ __global__ __launch_bounds__(kBlock) void k_update_xr(int64_t n, double *scal, d
   double s = 0.0;
   for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += int64_t(gridDim.x) * kBlock) {
     double ri = r[i];
+    const double pi = p[i];
+    if (pold) pold[i] = pi;
     if (!done) {
-      x[i] = fma(alpha, p[i], x[i]);
+      x[i] = fma(alpha, pi, x[i]);
       ri = fma(-alpha, q[i], ri);
       r[i] = ri;
       if (r32) r32[i] = float(ri);
@@ -764,7 +799,11 @@ __global__ __launch_bounds__(kBlock) void k_update_xr(int64_t n, double *scal, d
     s = fma(ri, ri, s);
   }
   const double rr = block_sum(s, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = rr;
+  if (threadIdx.x != 0) return;
+  if (ring)
+    publish(rr, scal, ring);
+  else
+    part[blockIdx.x] = rr;
 }
 
 template <class TZ>
@@ -788,19 +827,147 @@ __global__ __launch_bounds__(kBlock) void k_publish(int nparts, const double *__
                                                    double *scal, double *ring) {
   __shared__ double sh[kBlock];
   const double t = sum_parts(nparts, part, sh);
-  if (threadIdx.x != 0) return;
-  const double it = scal[SC_ITER] + 1.0;
-  scal[SC_RR] = t;
-  scal[SC_ITER] = it;
-  if (sqrt(t) <= scal[SC_RTOL] * sqrt(scal[SC_BB])) scal[SC_DONE] = 1.0;
-  double *rec = ring + (int(it) & (kRing - 1)) * kRecord;
-  for (int i = 0; i < SC_COUNT; ++i) rec[i] = scal[i];
-  __threadfence_system();
-  __hip_atomic_store(rec + kRecord - 1, it, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (threadIdx.x == 0) publish(t, scal, ring);
 }
 
-__global__ void k_init_scal(double rtol, double *scal) {
-  if (threadIdx.x < SC_COUNT) scal[threadIdx.x] = threadIdx.x == SC_RTOL ? rtol : 0.0;
+// p' = z + beta p, formed where the rows gather it, and q = A p': the p update's launch and its pass
+// over the vectors, for a second gather per block.  p' goes to pn (other rows still gather p), and
+// the x and r update copies it back.
+template <int B, class TZ>
+__global__ __launch_bounds__(kBlock) void k_spmv_dir(int n_rows, int G, const int *__restrict__ rp,
+                                                    const int *__restrict__ col,
+                                                    const double *__restrict__ val,
+                                                    const TZ *__restrict__ z, const double *__restrict__ p,
+                                                    double *__restrict__ pn, double *__restrict__ q,
+                                                    double *scal, int nparts,
+                                                    const double *__restrict__ rz, double *__restrict__ part) {
+  __shared__ double sh[kBlock];
+  const int lane = threadIdx.x & (G - 1);
+  const int wg = xcd_block();
+  const int row = wg * (kBlock / G) + threadIdx.x / G;
+  int p0 = 0, p1 = 0;
+  if (row < n_rows) {
+    p0 = rp[row];
+    p1 = rp[row + 1];
+  }
+  const double rho = scal[SC_RHO];
+  const double t = sum_parts(nparts, rz, sh);
+  const double beta = t / rho;
+  if (wg == 0 && threadIdx.x == 0) {
+    if (!(t > 0.0) || !isfinite(t)) scal[SC_BAD] = 1.0;
+    scal[SC_RZ] = t;
+    scal[SC_BETA] = beta;
+  }
+  const auto load = [&](int64_t c, double (&xv)[B]) {
+    TZ zv[B];
+    double pv[B];
+    gather_block<TZ, B>(z, c, zv);
+    gather_block<double, B>(p, c, pv);
+#pragma unroll
+    for (int e = 0; e < B; ++e) xv[e] = fma(beta, pv[e], double(zv[e]));
+  };
+  double acc[B];
+#pragma unroll
+  for (int r = 0; r < B; ++r) acc[r] = 0.0;
+  row_accumulate_of<double, B, B>(p0, p1, lane, G, col, val, acc, load);
+  group_reduce<double, B>(acc, G);
+  double d = 0.0;
+  if (row < n_rows && lane == 0) {
+    double pi[B];
+    load(row, pi);
+#pragma unroll
+    for (int r = 0; r < B; ++r) {
+      const int64_t i = int64_t(row) * B + r;
+      q[i] = acc[r];
+      pn[i] = pi[r];
+      d += pi[r] * acc[r];
+    }
+  }
+  const double s = block_sum(d, sh);
+  if (threadIdx.x == 0) part[wg] = s;
+}
+
+// Start of a solve, one pass over the vectors: bp = the right-hand side in solve order (Dirichlet
+// zeroed), with x also x = 0, r = bp and (r32) its FP32 copy; part <- partials of bp.bp, bad <-
+// whether a workgroup's entries are not all finite.  Launches bound the small solves: with the end's
+// k_finish and r.z taken by the last sweep launch, a solve of 1,029 dofs takes 530 us instead of 561
+// (ten passes of their own before and after the iterations), one of 14,739 dofs 2.04 ms instead of 2.08.
+__global__ __launch_bounds__(kBlock) void k_start(int64_t n, int bs, const int *__restrict__ perm,
+                                                 const uint8_t *__restrict__ mask,
+                                                 const double *__restrict__ b, double *__restrict__ bp,
+                                                 double *__restrict__ x, double *__restrict__ r,
+                                                 float *__restrict__ r32, double *__restrict__ part,
+                                                 double *__restrict__ bad) {
+  __shared__ double sh[kBlock];
+  double s = 0.0;
+  int wrong = 0;
+  for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += int64_t(gridDim.x) * kBlock) {
+    const int64_t row = i / bs;
+    const int o = perm[row];
+    const double v = (mask && mask[o]) ? 0.0 : b[int64_t(o) * bs + (i - row * bs)];
+    bp[i] = v;
+    if (x) {
+      x[i] = 0.0;
+      r[i] = v;
+      if (r32) r32[i] = float(v);
+    }
+    s = fma(v, v, s);
+    wrong |= !isfinite(v);
+  }
+  wrong = __syncthreads_or(wrong);
+  const double t = block_sum(s, sh);
+  if (threadIdx.x != 0) return;
+  part[blockIdx.x] = t;
+  bad[blockIdx.x] = wrong ? 1.0 : 0.0;
+}
+
+// The scalars of a new solve: SC_RTOL, SC_BB and SC_NONFINITE from the start's partials, else 0.
+__global__ __launch_bounds__(kBlock) void k_start_scal(int nparts, const double *__restrict__ part,
+                                                      const double *__restrict__ bad, double rtol,
+                                                      double *__restrict__ scal) {
+  __shared__ double sh[kBlock];
+  int wrong = 0;
+  for (int i = threadIdx.x; i < nparts; i += kBlock) wrong |= bad[i] != 0.0;
+  wrong = __syncthreads_or(wrong);
+  const double t = sum_parts(nparts, part, sh);
+  if (threadIdx.x < SC_COUNT)
+    scal[threadIdx.x] = threadIdx.x == SC_RTOL ? rtol
+                        : threadIdx.x == SC_BB ? t
+                        : threadIdx.x == SC_NONFINITE ? (wrong ? 1.0 : 0.0)
+                                                      : 0.0;
+}
+
+// p = z, part <- partials of r.z
+template <class TZ>
+__global__ __launch_bounds__(kBlock) void k_start_p(int64_t n, const TZ *__restrict__ z,
+                                                   const double *__restrict__ r, double *__restrict__ p,
+                                                   double *__restrict__ part) {
+  __shared__ double sh[kBlock];
+  double s = 0.0;
+  for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += int64_t(gridDim.x) * kBlock) {
+    const double zi = double(z[i]);
+    p[i] = zi;
+    s = fma(r[i], zi, s);
+  }
+  const double t = block_sum(s, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = t;
+}
+
+// End of a solve: out = x in natural order, part <- partials of |b - q|^2 (q = A x)
+__global__ __launch_bounds__(kBlock) void k_finish(int64_t n, int bs, const int *__restrict__ perm,
+                                                  const double *__restrict__ x, const double *__restrict__ b,
+                                                  const double *__restrict__ q, double *__restrict__ out,
+                                                  double *__restrict__ part) {
+  __shared__ double sh[kBlock];
+  double s = 0.0;
+  for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += int64_t(gridDim.x) * kBlock) {
+    const int64_t row = i / bs;
+    out[int64_t(perm[row]) * bs + (i - row * bs)] = x[i];
+    const double d = b[i] - q[i];
+    s = fma(d, d, s);
+  }
+  const double t = block_sum(s, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
 __global__ void k_sub(int64_t n, const double *a, const double *b, double *y) {
@@ -834,11 +1001,6 @@ __global__ void k_perm_out(int n, int bs, const int *perm, const double *in, dou
   const int64_t r = gid / bs;
   const int c = int(gid % bs);
   out[int64_t(perm[r]) * bs + c] = in[gid];
-}
-
-__global__ void k_finite_check(int64_t n, const double *a, double *scal, int slot) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n && !isfinite(a[i])) scal[slot] = 1.0;
 }
 
 int groups_for(int G) { return kBlock / G; }
@@ -1026,21 +1188,23 @@ hipError_t launch_group_rhs(const SolveMat &A, const int *lo_end, int r0, int r1
   EAMG_LAUNCH_CHECK();
 }
 
+int group_blocks(const SolveMat &S, int r0, int r1) { return int(cdiv64(r1 - r0, groups_for(S.group))); }
+
 namespace {
-template <class T, bool FWD>
+template <class T, bool FWD, bool RZ>
 hipError_t launch_group(const SolveMat &S, const T *dg, const T *Dinv, int r0, int r1, const T *u, T *x,
-                        T *r, hipStream_t s) {
+                        T *r, const double *cg_r, double *rz, hipStream_t s) {
   if (r0 < 0 || r1 > S.n_rows) return hipErrorInvalidValue;
   if (r1 <= r0) return hipSuccess;
   const T *val = solve_vals<T>(S);
   if (!val || !S.rp || (FWD && !dg)) return hipErrorInvalidValue;
   const int G = S.group;
-  const dim3 grid(cdiv64(r1 - r0, groups_for(G)));
+  const dim3 grid(group_blocks(S, r0, r1));
   const int64_t nd = S.n_rows;
   switch (S.br) {
-    case 1: EAMG_GS_W(W_, hipLaunchKernelGGL((k_gs_group<T, 1, FWD, W_>), grid, dim3(kBlock), 0, s, r0, r1, G, S.rp, S.col, val, S.nnz, dg, nd, Dinv, u, x, r)); break;
-    case 3: EAMG_GS_W(W_, hipLaunchKernelGGL((k_gs_group<T, 3, FWD, W_>), grid, dim3(kBlock), 0, s, r0, r1, G, S.rp, S.col, val, S.nnz, dg, nd, Dinv, u, x, r)); break;
-    case 6: EAMG_GS_W(W_, hipLaunchKernelGGL((k_gs_group<T, 6, FWD, W_>), grid, dim3(kBlock), 0, s, r0, r1, G, S.rp, S.col, val, S.nnz, dg, nd, Dinv, u, x, r)); break;
+    case 1: EAMG_GS_W(W_, hipLaunchKernelGGL((k_gs_group<T, 1, FWD, W_, RZ>), grid, dim3(kBlock), 0, s, r0, r1, G, S.rp, S.col, val, S.nnz, dg, nd, Dinv, u, x, r, cg_r, rz)); break;
+    case 3: EAMG_GS_W(W_, hipLaunchKernelGGL((k_gs_group<T, 3, FWD, W_, RZ>), grid, dim3(kBlock), 0, s, r0, r1, G, S.rp, S.col, val, S.nnz, dg, nd, Dinv, u, x, r, cg_r, rz)); break;
+    case 6: EAMG_GS_W(W_, hipLaunchKernelGGL((k_gs_group<T, 6, FWD, W_, RZ>), grid, dim3(kBlock), 0, s, r0, r1, G, S.rp, S.col, val, S.nnz, dg, nd, Dinv, u, x, r, cg_r, rz)); break;
     default: return hipErrorInvalidValue;
   }
   EAMG_LAUNCH_CHECK();
@@ -1051,13 +1215,14 @@ template <class T>
 hipError_t launch_group_fwd(const SolveMat &A, const SolveMat &S, const T *Dinv, int r0, int r1,
                             const T *u, T *x, T *r, hipStream_t s) {
   const T *dg = sizeof(T) == 4 ? reinterpret_cast<const T *>(A.dg_val32) : reinterpret_cast<const T *>(A.dg_val);
-  return launch_group<T, true>(S, dg, Dinv, r0, r1, u, x, r, s);
+  return launch_group<T, true, false>(S, dg, Dinv, r0, r1, u, x, r, nullptr, nullptr, s);
 }
 
 template <class T>
 hipError_t launch_group_bwd(const SolveMat &S, const T *Dinv, int r0, int r1, const T *u, T *x,
-                            hipStream_t s) {
-  return launch_group<T, false>(S, nullptr, Dinv, r0, r1, u, x, nullptr, s);
+                            hipStream_t s, const double *cg_r, double *rz) {
+  if (rz) return launch_group<T, false, true>(S, nullptr, Dinv, r0, r1, u, x, nullptr, cg_r, rz, s);
+  return launch_group<T, false, false>(S, nullptr, Dinv, r0, r1, u, x, nullptr, nullptr, nullptr, s);
 }
 
 hipError_t launch_group_fill(int nrows, const int *rows, int bs, const int *q0, const int *q1,
@@ -1118,8 +1283,8 @@ template hipError_t launch_group_rhs<double>(const SolveMat &, const int *, int,
 template hipError_t launch_group_rhs<float>(const SolveMat &, const int *, int, int, const float *, const float *, float *, hipStream_t);
 template hipError_t launch_group_fwd<double>(const SolveMat &, const SolveMat &, const double *, int, int, const double *, double *, double *, hipStream_t);
 template hipError_t launch_group_fwd<float>(const SolveMat &, const SolveMat &, const float *, int, int, const float *, float *, float *, hipStream_t);
-template hipError_t launch_group_bwd<double>(const SolveMat &, const double *, int, int, const double *, double *, hipStream_t);
-template hipError_t launch_group_bwd<float>(const SolveMat &, const float *, int, int, const float *, float *, hipStream_t);
+template hipError_t launch_group_bwd<double>(const SolveMat &, const double *, int, int, const double *, double *, hipStream_t, const double *, double *);
+template hipError_t launch_group_bwd<float>(const SolveMat &, const float *, int, int, const float *, float *, hipStream_t, const double *, double *);
 template hipError_t launch_rect<double>(const SolveMat &, const double *, double *, bool, hipStream_t);
 template hipError_t launch_rect<float>(const SolveMat &, const float *, float *, bool, hipStream_t);
 template hipError_t launch_convert<double, float>(int64_t, const double *, float *, hipStream_t);
@@ -1147,10 +1312,10 @@ hipError_t launch_reduce(int nparts, const double *part, double *scal, int slot,
 
 hipError_t launch_update_xr(int64_t n, double *scal, double *x, double *r, const double *p,
                             const double *q, double *part, int npq, const double *pq, hipStream_t s,
-                            float *r32) {
+                            float *r32, double *pold, double *ring) {
   if (npq < 0 || npq > kInlineParts || (npq && (!pq || pq == part))) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_update_xr, dim3(dot_blocks(n)), dim3(kBlock), 0, s, n, scal, x, r, p, q, part, npq,
-                     pq, r32);
+  hipLaunchKernelGGL(k_update_xr, dim3(ring ? 1 : dot_blocks(n)), dim3(kBlock), 0, s, n, scal, x, r, p, q, part,
+                     npq, pq, r32, pold, ring);
   EAMG_LAUNCH_CHECK();
 }
 
@@ -1171,8 +1336,44 @@ hipError_t launch_publish(int nparts, const double *part, double *scal, double *
   EAMG_LAUNCH_CHECK();
 }
 
-hipError_t launch_init_scal(double rtol, double *scal, hipStream_t s) {
-  hipLaunchKernelGGL(k_init_scal, dim3(1), dim3(64), 0, s, rtol, scal);
+template <class TZ>
+hipError_t launch_spmv_dir(const SolveMat &A, double *scal, const TZ *z, const double *p, double *pn, double *q,
+                           int nparts, const double *rz, double *part, hipStream_t s) {
+  if (A.n_rows == 0) return hipSuccess;
+  if (A.br != A.bc || !pn || pn == p || rz == part || nparts < 1 || nparts > kInlineParts) return hipErrorInvalidValue;
+  const int G = spmv_group(A);
+  const dim3 grid(spmv_blocks(A));
+  switch (A.br) {
+    case 1: hipLaunchKernelGGL((k_spmv_dir<1, TZ>), grid, dim3(kBlock), 0, s, A.n_rows, G, A.rp, A.col, A.val, z, p, pn, q, scal, nparts, rz, part); break;
+    case 3: hipLaunchKernelGGL((k_spmv_dir<3, TZ>), grid, dim3(kBlock), 0, s, A.n_rows, G, A.rp, A.col, A.val, z, p, pn, q, scal, nparts, rz, part); break;
+    case 6: hipLaunchKernelGGL((k_spmv_dir<6, TZ>), grid, dim3(kBlock), 0, s, A.n_rows, G, A.rp, A.col, A.val, z, p, pn, q, scal, nparts, rz, part); break;
+    default: return hipErrorInvalidValue;
+  }
+  EAMG_LAUNCH_CHECK();
+}
+template hipError_t launch_spmv_dir<double>(const SolveMat &, double *, const double *, const double *, double *, double *, int, const double *, double *, hipStream_t);
+template hipError_t launch_spmv_dir<float>(const SolveMat &, double *, const float *, const double *, double *, double *, int, const double *, double *, hipStream_t);
+
+hipError_t launch_start(int64_t n, int bs, const int *perm, const uint8_t *mask, const double *b, double *bp,
+                        double *x, double *r, float *r32, double rtol, double *part, double *bad, double *scal,
+                        hipStream_t s) {
+  const int nd = dot_blocks(n);
+  hipLaunchKernelGGL(k_start, dim3(nd), dim3(kBlock), 0, s, n, bs, perm, mask, b, bp, x, r, r32, part, bad);
+  hipLaunchKernelGGL(k_start_scal, dim3(1), dim3(kBlock), 0, s, nd, part, bad, rtol, scal);
+  EAMG_LAUNCH_CHECK();
+}
+
+template <class TZ>
+hipError_t launch_start_p(int64_t n, const TZ *z, const double *r, double *p, double *part, hipStream_t s) {
+  hipLaunchKernelGGL(k_start_p<TZ>, dim3(dot_blocks(n)), dim3(kBlock), 0, s, n, z, r, p, part);
+  EAMG_LAUNCH_CHECK();
+}
+template hipError_t launch_start_p<double>(int64_t, const double *, const double *, double *, double *, hipStream_t);
+template hipError_t launch_start_p<float>(int64_t, const float *, const double *, double *, double *, hipStream_t);
+
+hipError_t launch_finish(int64_t n, int bs, const int *perm, const double *x, const double *b, const double *q,
+                         double *out, double *part, hipStream_t s) {
+  hipLaunchKernelGGL(k_finish, dim3(dot_blocks(n)), dim3(kBlock), 0, s, n, bs, perm, x, b, q, out, part);
   EAMG_LAUNCH_CHECK();
 }
 
@@ -1207,12 +1408,6 @@ hipError_t launch_perm_out(int n, int bs, const int *perm, const double *in, dou
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_perm_out, dim3(cdiv64(int64_t(n) * bs, 256)), dim3(256), 0, s, n, bs, perm,
                      in, out);
-  EAMG_LAUNCH_CHECK();
-}
-
-hipError_t launch_finite_check(int64_t n, const double *a, double *scal, int slot, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_finite_check, dim3(cdiv64(n, 256)), dim3(256), 0, s, n, a, scal, slot);
   EAMG_LAUNCH_CHECK();
 }
 

@@ -131,7 +131,10 @@ hipError_t launch_group_fwd(const SolveMat &A, const SolveMat &S, const T *Dinv,
                             const T *u, T *x, T *r, hipStream_t s);
 template <class T>
 hipError_t launch_group_bwd(const SolveMat &S, const T *Dinv, int r0, int r1, const T *u, T *x,
-                            hipStream_t s);
+                            hipStream_t s, const double *cg_r = nullptr, double *rz = nullptr);
+// Workgroups of a group's launch over rows [r0, r1), and with rz (launch_group_bwd) its partials of
+// the CG's r.z there: cg_r times the new x.
+int group_blocks(const SolveMat &S, int r0, int r1);
 // One rank of the group matrices, row rows[k] (k < nrows) each: its couplings inside the group
 // are the positions [q0[i], q1[i]) of A (col, val, natural FP64 blocks in the solve numbering), and
 //   S_ik = sum over those q, j = col[q], of A_q Dinv_j ([j == k] I - S_jk).
@@ -165,10 +168,22 @@ hipError_t launch_update_p(int64_t n, double *scal, const float *z, double *p, i
 // x += alpha p ; r -= alpha q ; part <- partials of r.r, alpha = scal[SC_RZ] / p.q, p.q summed from the
 // npq partials in `pq` (npq = 0: scal[SC_PQ]); also stores SC_PQ, SC_ALPHA and SC_RHO = SC_RZ.  With
 // r32, also r32 = float(r) (the next FP32 V-cycle's right-hand side).  Once scal[SC_DONE] is set, x and
-// r stay as they are.
+// r stay as they are.  With pold, pold = p (launch_spmv_dir's direction).  With ring, one workgroup
+// does all of it and publishes (launch_publish), without partials: up to kOneBlock entries, from where
+// the launch that publishes is cheaper than one workgroup's longer loop (elasticity cubes: 375 dofs
+// 102.2 -> 97.6 us a solve, 1,029 dofs 530 -> 518, 3,993 dofs 854, not 865).
+constexpr int64_t kOneBlock = 1536;
 hipError_t launch_update_xr(int64_t n, double *scal, double *x, double *r, const double *p,
                             const double *q, double *part, int npq, const double *pq, hipStream_t s,
-                            float *r32 = nullptr);
+                            float *r32 = nullptr, double *pold = nullptr, double *ring = nullptr);
+// p' = z + beta p in pn and q = A p', beta as in launch_update_p (from the nparts partials in rz);
+// part <- partials of p'.q.  For up to kDirEntries entries, where the p update's launch costs more than
+// the rows' second gather (solves of elasticity cubes of 1,029 dofs 530 -> 523 us, 3,993 dofs 854 ->
+// 811, 14,739 dofs 2,039 -> 2,021, 41,472 dofs 4,505 -> 4,487; scalar 262,000 dofs 7.66 ms, not 7.87).
+constexpr int64_t kDirEntries = 1 << 16;
+template <class TZ>
+hipError_t launch_spmv_dir(const SolveMat &A, double *scal, const TZ *z, const double *p, double *pn, double *q,
+                           int nparts, const double *rz, double *part, hipStream_t s);
 // Partial counts up to this many are summed by the kernel that uses the sum.
 constexpr int kInlineParts = 1024;
 // End of an iteration: SC_RR from the partials, SC_ITER + 1, SC_DONE if sqrt(r.r) <= SC_RTOL sqrt(SC_BB),
@@ -176,8 +191,18 @@ constexpr int kInlineParts = 1024;
 // one, the iteration's number, stored after the others).
 constexpr int kRing = 4, kRecord = 16;
 hipError_t launch_publish(int nparts, const double *part, double *scal, double *ring, hipStream_t s);
-// scal := 0, SC_RTOL = rtol
-hipError_t launch_init_scal(double rtol, double *scal, hipStream_t s);
+// Start of a solve: bp = the right-hand side b in solve order (as launch_perm_in); with x also x = 0,
+// r = bp and (r32) its FP32 copy; scal := 0 but SC_RTOL, SC_BB = bp.bp and SC_NONFINITE = whether an
+// entry of bp is not finite.  part, bad: dot_blocks(n) entries each.
+hipError_t launch_start(int64_t n, int bs, const int *perm, const uint8_t *mask, const double *b, double *bp,
+                        double *x, double *r, float *r32, double rtol, double *part, double *bad, double *scal,
+                        hipStream_t s);
+// p = z; part <- partials of r.z
+template <class TZ>
+hipError_t launch_start_p(int64_t n, const TZ *z, const double *r, double *p, double *part, hipStream_t s);
+// End of a solve: out = x in natural order; part <- partials of |b - q|^2
+hipError_t launch_finish(int64_t n, int bs, const int *perm, const double *x, const double *b, const double *q,
+                         double *out, double *part, hipStream_t s);
 // y = a - b
 hipError_t launch_sub(int64_t n, const double *a, const double *b, double *y, hipStream_t s);
 hipError_t launch_copy(int64_t n, const double *a, double *y, hipStream_t s);
@@ -187,8 +212,6 @@ hipError_t launch_perm_in(int n, int bs, const int *perm, const uint8_t *mask, c
 // out[perm[r]*bs+c] = in[r*bs+c]   (colour-major -> natural)
 hipError_t launch_perm_out(int n, int bs, const int *perm, const double *in, double *out,
                            hipStream_t s);
-// flag non-finite entries: scal[slot] = 1 if any a[i] is not finite (scal[slot] pre-zeroed)
-hipError_t launch_finite_check(int64_t n, const double *a, double *scal, int slot, hipStream_t s);
 hipError_t launch_fill(int64_t n, double v, double *a, hipStream_t s);
 
 // Scalar slots on the device.
