@@ -461,7 +461,9 @@ struct WideLevel {
 // x = V_l(b) for K columns on level l (b.p == nullptr: columns j0 .. j0 + K - 1 of the identity,
 // and x is zero on entry).  The forward sweep of an identity right-hand side stays at or below
 // the diagonal, so each colour takes only the columns that reach its rows; r is zeroed for the
-// rest.
+// rest.  The result's columns beyond the diagonal are its rows (V is symmetric), so the backward
+// sweep leaves them too: a row needs the later rows' new values, theirs reach at least as far, and
+// the earlier rows' old ones, which are complete.  x ends up valid on and below the diagonal only.
 void wide_vcycle(eamg_hierarchy *h, std::vector<WideLevel> &w, size_t l, WidePanel b, int j0, WidePanel x,
                  int K, hipStream_t s) {
   Level &L = h->lv[l];
@@ -470,20 +472,26 @@ void wide_vcycle(eamg_hierarchy *h, std::vector<WideLevel> &w, size_t l, WidePan
     return;
   }
   const WidePanel r = w[l].r;
+  // columns of the launch that reach rows before r1
+  const auto reach = [&](int r1) {
+    if (b.p) return K;
+    const int64_t d = int64_t(r1) * L.bs - j0;
+    return int(std::max<int64_t>(0, std::min<int64_t>(K, (d + 1) / 2 * 2)));
+  };
   if (!b.p) hip_check(launch_fill(level_dofs(L) * r.ld, 0.0, r.p, s), "fill");
   for (int c = 0; c < L.ncolors; ++c) {
     const int r0 = L.color_ptr[c], r1 = L.color_ptr[c + 1];
-    const int64_t reach = int64_t(r1) * L.bs - j0;
-    const int Kc = b.p ? K : int(std::max<int64_t>(0, std::min<int64_t>(K, (reach + 1) / 2 * 2)));
-    hip_check(launch_wide_fwd(L.Am, L.Dinv, r0, r1, Kc, b, j0, x, r, s), "wide fwd");
+    hip_check(launch_wide_fwd(L.Am, L.Dinv, r0, r1, reach(r1), b, j0, x, r, s), "wide fwd");
   }
   hip_check(launch_wide_resid(L.Am, K, x, r, s), "wide resid");
   WideLevel &C = w[l + 1];
   hip_check(launch_wide_rect(L.Rm, K, r, C.b, false, s), "wide restrict");
   wide_vcycle(h, w, l + 1, C.b, 0, C.x, K, s);
   hip_check(launch_wide_rect(L.Pm, K, C.x, x, true, s), "wide prolong");
-  for (int c = L.ncolors - 1; c >= 0; --c)
-    hip_check(launch_wide_bwd(L.Am, L.Dinv, L.color_ptr[c], L.color_ptr[c + 1], K, b, j0, x, s), "wide bwd");
+  for (int c = L.ncolors - 1; c >= 0; --c) {
+    const int r0 = L.color_ptr[c], r1 = L.color_ptr[c + 1];
+    hip_check(launch_wide_bwd(L.Am, L.Dinv, r0, r1, reach(r1), b, j0, x, s), "wide bwd");
+  }
 }
 
 }  // namespace
@@ -536,10 +544,10 @@ void build_dense_tail(eamg_hierarchy *h, size_t t, hipStream_t s) {
   const DenseTail d = make_dense_tail(h, t, full, s);
   h->nT = d.n;
   h->tailS = h->arena.alloc<double>(sym_entries(d.n));
-  hip_check(launch_pack_sym<double>(d.n, d.ld, d.T, h->tailS, s), "pack tail");
+  hip_check(launch_pack_lower<double>(d.n, d.ld, d.T, h->tailS, s), "pack tail");
   if (h->prm.vcycle_fp32 && h->prm.dense_tail_fp32) {
     h->tailS32 = h->arena.alloc<float>(sym_entries(d.n));
-    hip_check(launch_pack_sym<float>(d.n, d.ld, d.T, h->tailS32, s), "pack tail f32");
+    hip_check(launch_pack_lower<float>(d.n, d.ld, d.T, h->tailS32, s), "pack tail f32");
   }
   h->tailW = h->arena.alloc<double>(sym_work_doubles(d.n));
   hip_check(hipStreamSynchronize(s), "sync");

@@ -62,6 +62,9 @@ inline size_t sym_work_doubles(int n) { return size_t(sym_blocks(n)) * sym_block
 // leading dimension ld (a multiple of kSymTile).
 template <class TM>
 hipError_t launch_pack_sym(int n, int ld, const double *D, TM *S, hipStream_t s);
+// The same for a symmetric D of which only the entries on and below the diagonal are valid.
+template <class TM>
+hipError_t launch_pack_lower(int n, int ld, const double *D, TM *S, hipStream_t s);
 
 // y = S x for the packed symmetric S (TM values; FP64 accumulation; x, y of length n; TV double
 // with TM double, float with either).  Two launches: one workgroup per stored tile writes its

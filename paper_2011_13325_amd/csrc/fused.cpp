@@ -267,11 +267,11 @@ void build_fused_level(eamg_hierarchy *F, const std::vector<eamg_hierarchy *> &h
       // built for the fused hierarchy
       if (own.n != n) fail(EAMG_ERR_INVALID_ARG, "dense tail size mismatch");
       double *P = ar.alloc<double>(sym_entries(n));
-      hip_check(launch_pack_sym<double>(n, own.ld, own.T, P, s), "pack tail");
+      hip_check(launch_pack_lower<double>(n, own.ld, own.T, P, s), "pack tail");
       S = P;
       if (f32 && F->prm.dense_tail_fp32) {
         float *P32 = ar.alloc<float>(sym_entries(n));
-        hip_check(launch_pack_sym<float>(n, own.ld, own.T, P32, s), "pack tail f32");
+        hip_check(launch_pack_lower<float>(n, own.ld, own.T, P32, s), "pack tail f32");
         S32 = P32;
       }
     } else if (H->tail_level == l && H->tailS) {

@@ -9,7 +9,8 @@
 // with three or four wavefronts per SIMD in flight on levels of fifty rows per colour.  Against
 // 64-column panels (a row team summing lane parts, one panel after another: 9 to 13 us for each of
 // 2 x colours x n / 64 launches) the tail of a 21^3 cube with inclusions (15,200 dofs on its
-// first level) takes 49 ms instead of 475 ms, and the whole setup and solve 276 ms instead of 667.
+// first level) takes 49 ms instead of 475 ms, and with the backward sweep on the columns up to the
+// diagonal 44.
 #include "wide.hpp"
 
 namespace eamg {
