@@ -30,96 +30,134 @@ __device__ inline int xcd_block() {
   return x * q + min(x, rem) + (b >> 3);
 }
 
-// ---- small dense helpers (one thread) ----------------------------------------------------
+// ---- small dense helpers (one thread; every size a constant, so that the arrays are registers) ---
 
-__device__ inline void dev_skew_q(const double *t, int k, double *Q) {
-  for (int i = 0; i < k * k; ++i) Q[i] = 0.0;
-  for (int i = 0; i < k; ++i) Q[i * k + i] = 1.0;
-  if (k == 6) {
-    // upper right block Skew(t): Skew(t) r = t x r
-    Q[0 * 6 + 4] = -t[2];
-    Q[0 * 6 + 5] = t[1];
-    Q[1 * 6 + 3] = t[2];
-    Q[1 * 6 + 5] = -t[0];
-    Q[2 * 6 + 3] = -t[1];
-    Q[2 * 6 + 4] = t[0];
+// X := X Q(t), Q(t) = [I Skew(t); 0 I] (K = 6; Skew(t) r = t x r) or 1 (K = 1); X is R x K.
+template <int R, int K>
+__device__ __forceinline__ void mul_q(double (&X)[R * K], const double (&t)[3]) {
+  if constexpr (K == 6) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const double a = X[r * 6], b = X[r * 6 + 1], c = X[r * 6 + 2];
+      X[r * 6 + 3] += b * t[2] - c * t[1];
+      X[r * 6 + 4] += c * t[0] - a * t[2];
+      X[r * 6 + 5] += a * t[1] - b * t[0];
+    }
   }
 }
-
-// C (m x p) = A (m x n) * B (n x p)
-__device__ inline void dev_mm(int m, int n, int p, const double *A, const double *B, double *C) {
-  for (int i = 0; i < m; ++i)
-    for (int j = 0; j < p; ++j) {
-      double s = 0.0;
-      for (int l = 0; l < n; ++l) s += A[i * n + l] * B[l * p + j];
-      C[i * p + j] = s;
+// X := Q(t)^T X
+template <int K>
+__device__ __forceinline__ void tmul_q(double (&X)[K * K], const double (&t)[3]) {
+  if constexpr (K == 6) {
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+      const double a = X[j], b = X[6 + j], c = X[12 + j];
+      X[18 + j] += b * t[2] - c * t[1];
+      X[24 + j] += c * t[0] - a * t[2];
+      X[30 + j] += a * t[1] - b * t[0];
     }
+  }
 }
-
-// C (m x p) = A^T * B with A (n x m)
-__device__ inline void dev_tmm(int m, int n, int p, const double *A, const double *B, double *C) {
-  for (int i = 0; i < m; ++i)
-    for (int j = 0; j < p; ++j) {
-      double s = 0.0;
-      for (int l = 0; l < n; ++l) s += A[l * m + i] * B[l * p + j];
-      C[i * p + j] = s;
+// out (R x P) = A (R x N, the first R rows of a matrix with rows of N) B (N x P)
+template <int R, int N, int P>
+__device__ __forceinline__ void mul_rows(const double *A, const double (&B)[N * P], double (&out)[R * P]) {
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+      double v = 0.0;
+#pragma unroll
+      for (int l = 0; l < N; ++l) v += A[i * N + l] * B[l * P + j];
+      out[i * P + j] = v;
     }
 }
 
 // Symmetric pseudo-inverse by cyclic Jacobi; eigenvalues <= tau * max(lambda_max, 0) dropped.
-__device__ void dev_pinv(int n, const double *X, double *P, double tau) {
-  double A[36], V[36], w[6];
+template <int N>
+__device__ __forceinline__ void dev_pinv(const double (&X)[N * N], double (&P)[N * N], double tau) {
+  double A[N * N], V[N * N];
   double fro2 = 0.0;
-  for (int i = 0; i < n; ++i)
-    for (int j = 0; j < n; ++j) {
-      A[i * n + j] = 0.5 * (X[i * n + j] + X[j * n + i]);
-      V[i * n + j] = i == j ? 1.0 : 0.0;
-      fro2 += A[i * n + j] * A[i * n + j];
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      A[i * N + j] = 0.5 * (X[i * N + j] + X[j * N + i]);
+      V[i * N + j] = i == j ? 1.0 : 0.0;
+      fro2 += A[i * N + j] * A[i * N + j];
     }
   for (int sweep = 0; sweep < 60; ++sweep) {
     double off = 0.0;
-    for (int p = 0; p < n; ++p)
-      for (int q = p + 1; q < n; ++q) off += A[p * n + q] * A[p * n + q];
+#pragma unroll
+    for (int p = 0; p < N; ++p)
+#pragma unroll
+      for (int q = p + 1; q < N; ++q) off += A[p * N + q] * A[p * N + q];
     if (off <= 1e-40 * fro2 || off == 0.0) break;
-    for (int p = 0; p < n; ++p)
-      for (int q = p + 1; q < n; ++q) {
-        const double apq = A[p * n + q];
+#pragma unroll
+    for (int p = 0; p < N; ++p)
+#pragma unroll
+      for (int q = p + 1; q < N; ++q) {
+        const double apq = A[p * N + q];
         if (apq == 0.0) continue;
-        const double theta = (A[q * n + q] - A[p * n + p]) / (2.0 * apq);
+        const double theta = (A[q * N + q] - A[p * N + p]) / (2.0 * apq);
         const double t = (theta >= 0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
         const double cs = 1.0 / sqrt(t * t + 1.0), sn = t * cs;
-        for (int k = 0; k < n; ++k) {
-          const double akp = A[k * n + p], akq = A[k * n + q];
-          A[k * n + p] = cs * akp - sn * akq;
-          A[k * n + q] = sn * akp + cs * akq;
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+          const double akp = A[k * N + p], akq = A[k * N + q];
+          A[k * N + p] = cs * akp - sn * akq;
+          A[k * N + q] = sn * akp + cs * akq;
         }
-        for (int k = 0; k < n; ++k) {
-          const double apk = A[p * n + k], aqk = A[q * n + k];
-          A[p * n + k] = cs * apk - sn * aqk;
-          A[q * n + k] = sn * apk + cs * aqk;
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+          const double apk = A[p * N + k], aqk = A[q * N + k];
+          A[p * N + k] = cs * apk - sn * aqk;
+          A[q * N + k] = sn * apk + cs * aqk;
         }
-        A[p * n + q] = 0.0;
-        A[q * n + p] = 0.0;
-        for (int k = 0; k < n; ++k) {
-          const double vkp = V[k * n + p], vkq = V[k * n + q];
-          V[k * n + p] = cs * vkp - sn * vkq;
-          V[k * n + q] = sn * vkp + cs * vkq;
+        A[p * N + q] = 0.0;
+        A[q * N + p] = 0.0;
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+          const double vkp = V[k * N + p], vkq = V[k * N + q];
+          V[k * N + p] = cs * vkp - sn * vkq;
+          V[k * N + q] = sn * vkp + cs * vkq;
         }
       }
   }
   double lmax = A[0];
-  for (int i = 0; i < n; ++i) {
-    w[i] = A[i * n + i];
-    lmax = w[i] > lmax ? w[i] : lmax;
-  }
-  for (int i = 0; i < n * n; ++i) P[i] = 0.0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) lmax = A[i * N + i] > lmax ? A[i * N + i] : lmax;
+#pragma unroll
+  for (int i = 0; i < N * N; ++i) P[i] = 0.0;
   if (!(lmax > 0.0)) return;
-  for (int k = 0; k < n; ++k) {
-    if (!(w[k] > tau * lmax)) continue;
-    const double inv = 1.0 / w[k];
-    for (int i = 0; i < n; ++i)
-      for (int j = 0; j < n; ++j) P[i * n + j] += V[i * n + k] * inv * V[j * n + k];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const double wk = A[k * N + k];
+    if (!(wk > tau * lmax)) continue;
+    const double inv = 1.0 / wk;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int j = 0; j < N; ++j) P[i * N + j] += V[i * N + k] * inv * V[j * N + k];
   }
+}
+
+template <int N>
+__device__ __forceinline__ void load_block(const double *src, double (&dst)[N]) {
+#pragma unroll
+  for (int e = 0; e < N; ++e) dst[e] = src[e];
+}
+
+// Block (i, i) of a matrix in rows [rp[i], rp[i + 1]), zero if it has none.
+template <int B>
+__device__ __forceinline__ void diagonal_block(int i, const int64_t *rp, const int *col, const double *val,
+                                               double (&out)[B * B]) {
+#pragma unroll
+  for (int e = 0; e < B * B; ++e) out[e] = 0.0;
+  for (int64_t p = rp[i]; p < rp[i + 1]; ++p)
+    if (col[p] == i) {
+      load_block<B * B>(val + p * (B * B), out);
+      break;
+    }
 }
 
 // ---- setup kernels --------------------------------------------------------------------------
@@ -137,117 +175,115 @@ __global__ void k_dirichlet(int n, int bs, const int64_t *rp, const int *col, do
   }
 }
 
-__global__ void k_diag_pinv(int n, int bs, const int64_t *rp, const int *col, const double *val,
-                            double *Dinv, double tau) {
+template <int B>
+__global__ __launch_bounds__(64) void k_diag_pinv(int n, const int64_t *rp, const int *col, const double *val,
+                                                 double *Dinv, double tau) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const int bsz = bs * bs;
-  double blk[36], P[36];
-  for (int e = 0; e < bsz; ++e) blk[e] = 0.0;
-  for (int64_t p = rp[i]; p < rp[i + 1]; ++p)
-    if (col[p] == i) {
-      for (int e = 0; e < bsz; ++e) blk[e] = val[p * bsz + e];
-      break;
-    }
-  dev_pinv(bs, blk, P, tau);
-  for (int e = 0; e < bsz; ++e) Dinv[int64_t(i) * bsz + e] = P[e];
+  double blk[B * B], P[B * B];
+  diagonal_block<B>(i, rp, col, val, blk);
+  dev_pinv<B>(blk, P, tau);
+#pragma unroll
+  for (int e = 0; e < B * B; ++e) Dinv[int64_t(i) * (B * B) + e] = P[e];
 }
 
-// Tentative block P_iJ = Q^{J->i} restricted to its first bs rows (bs x k).
-__device__ inline void dev_tentative(int k, int bs, const double *xf, const double *xcJ, double *out) {
-  double t[3] = {xf[0] - xcJ[0], xf[1] - xcJ[1], xf[2] - xcJ[2]};
-  double Q[36];
-  dev_skew_q(t, k, Q);
-  for (int e = 0; e < bs * k; ++e) out[e] = Q[e];
-}
-
-// One fine row of the auxiliary smoothed prolongation (Def. def:aux_sp).
-__global__ void k_ps_numeric(PsArgs a) {
+// One fine row of the auxiliary smoothed prolongation (Def. def:aux_sp), one thread.  Bound: the chain
+// of a row (its pseudo-inverse, then a congruence per neighbour); the blocks' sizes are constants and
+// the transformations Q are applied as the cross products they are, so that a row's blocks stay in
+// registers: PSUS for the 9,261 rows of a cube with inclusions and its three coarse levels, 13.0 ms
+// with arrays in scratch memory.
+template <int K, int BS>
+__global__ __launch_bounds__(64) void k_ps_numeric(PsArgs a) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
   const int type = a.type[i];
   if (type == 2) return;  // dropped row: no entries
-  const int k = a.k, bs = a.bs, Ji = a.agg[i];
+  const int Ji = a.agg[i];
   const double *xi = a.x + 3 * int64_t(i);
-  double Dp[36], acc[36], tmp[36], T[36];
   if (type == 0) {
-    // real-matrix row: P_i - omega pinv(A_ii) sum_j A_ij P_j
-    double Aii[36];
-    for (int e = 0; e < bs * bs; ++e) Aii[e] = 0.0;
-    for (int64_t p = a.Arp[i]; p < a.Arp[i + 1]; ++p)
-      if (a.Acol[p] == i) {
-        for (int e = 0; e < bs * bs; ++e) Aii[e] = a.Aval[p * bs * bs + e];
-        break;
-      }
-    dev_pinv(bs, Aii, Dp, a.tau);
+    // real-matrix row: P_i - omega pinv(A_ii) sum_j A_ij P_j, P_j the first BS rows of Q^{J->j}
+    double Dp[BS * BS];
+    {
+      double Aii[BS * BS];
+      diagonal_block<BS>(i, a.Arp, a.Acol, a.Aval, Aii);
+      dev_pinv<BS>(Aii, Dp, a.tau);
+    }
     for (int64_t q = a.Prp[i]; q < a.Prp[i + 1]; ++q) {
       const int J = a.Pcol[q];
-      for (int e = 0; e < bs * k; ++e) acc[e] = 0.0;
+      const double *xJ = a.xc + 3 * int64_t(J);
+      double acc[BS * K], X[BS * K];
+#pragma unroll
+      for (int e = 0; e < BS * K; ++e) acc[e] = 0.0;
       for (int64_t p = a.Arp[i]; p < a.Arp[i + 1]; ++p) {
         const int j = a.Acol[p];
         if (a.agg[j] != J) continue;
-        dev_tentative(k, bs, a.x + 3 * int64_t(j), a.xc + 3 * int64_t(J), T);
-        dev_mm(bs, bs, k, a.Aval + p * bs * bs, T, tmp);
-        for (int e = 0; e < bs * k; ++e) acc[e] += tmp[e];
+        const double *xj = a.x + 3 * int64_t(j);
+        const double t[3] = {xj[0] - xJ[0], xj[1] - xJ[1], xj[2] - xJ[2]};
+#pragma unroll
+        for (int r = 0; r < BS; ++r)
+#pragma unroll
+          for (int c = 0; c < K; ++c) X[r * K + c] = c < BS ? a.Aval[p * (BS * BS) + r * BS + c] : 0.0;
+        mul_q<BS, K>(X, t);
+#pragma unroll
+        for (int e = 0; e < BS * K; ++e) acc[e] += X[e];
       }
-      dev_mm(bs, bs, k, Dp, acc, tmp);
-      double *out = a.Pval + q * bs * k;
-      if (J == Ji) {
-        dev_tentative(k, bs, xi, a.xc + 3 * int64_t(J), T);
-        for (int e = 0; e < bs * k; ++e) out[e] = T[e] - a.omega * tmp[e];
-      } else {
-        for (int e = 0; e < bs * k; ++e) out[e] = -a.omega * tmp[e];
-      }
+      mul_rows<BS, BS, K>(Dp, acc, X);
+      double *out = a.Pval + q * (BS * K);
+      double T[BS * K];
+#pragma unroll
+      for (int e = 0; e < BS * K; ++e) T[e] = J == Ji && e / K == e % K ? 1.0 : 0.0;
+      const double t[3] = {xi[0] - xJ[0], xi[1] - xJ[1], xi[2] - xJ[2]};
+      mul_q<BS, K>(T, t);
+#pragma unroll
+      for (int e = 0; e < BS * K; ++e) out[e] = T[e] - a.omega * X[e];
     }
     return;
   }
   // edge-matrix row: P_i - omega pinv(Dhat0_ii) (Dhat0_ii P_i + sum_{l in F} Ahat0_il P_l)
-  double Dh[36], Qa[36], Qb[36], Ee[36];
-  for (int e = 0; e < k * k; ++e) Dh[e] = 0.0;
+  constexpr int KK = K * K;
+  double Dh[KK], Dp[KK], X[KK];
+#pragma unroll
+  for (int e = 0; e < KK; ++e) Dh[e] = 0.0;
   for (int64_t f = a.Fptr[i]; f < a.Fptr[i + 1]; ++f) {
     const double *xl = a.x + 3 * int64_t(a.Fvtx[f]);
     const double th[3] = {0.5 * (xl[0] - xi[0]), 0.5 * (xl[1] - xi[1]), 0.5 * (xl[2] - xi[2])};
-    dev_skew_q(th, k, Qa);  // Q^{il}
-    const double *Ef = a.E + int64_t(a.Fedge[f]) * k * k;
-    dev_tmm(k, k, k, Qa, Ef, tmp);
-    dev_mm(k, k, k, tmp, Qa, Ee);
-    for (int e = 0; e < k * k; ++e) Dh[e] += Ee[e];
+    load_block<KK>(a.E + int64_t(a.Fedge[f]) * KK, X);
+    tmul_q<K>(X, th);
+    mul_q<K, K>(X, th);   // Q^{il,T} E Q^{il}
+#pragma unroll
+    for (int e = 0; e < KK; ++e) Dh[e] += X[e];
   }
-  dev_pinv(k, Dh, Dp, a.tau);
-  double Pi[36];
-  {
-    const double *xJ = a.xc + 3 * int64_t(Ji);
-    const double t[3] = {xi[0] - xJ[0], xi[1] - xJ[1], xi[2] - xJ[2]};
-    dev_skew_q(t, k, Pi);  // Q^{J->i}, full k x k
-  }
+  dev_pinv<K>(Dh, Dp, a.tau);
   for (int64_t q = a.Prp[i]; q < a.Prp[i + 1]; ++q) {
     const int J = a.Pcol[q];
-    if (J == Ji)
-      dev_mm(k, k, k, Dh, Pi, acc);
-    else
-      for (int e = 0; e < k * k; ++e) acc[e] = 0.0;
+    const double *xJ = a.xc + 3 * int64_t(J);
+    const double ti[3] = {xi[0] - xJ[0], xi[1] - xJ[1], xi[2] - xJ[2]};
+    double acc[KK];
+#pragma unroll
+    for (int e = 0; e < KK; ++e) acc[e] = J == Ji ? Dh[e] : 0.0;
+    mul_q<K, K>(acc, ti);   // Dhat0_ii Q^{J->i}
     for (int64_t f = a.Fptr[i]; f < a.Fptr[i + 1]; ++f) {
       const int l = a.Fvtx[f];
       if (a.agg[l] != J) continue;
       const double *xl = a.x + 3 * int64_t(l);
       const double th[3] = {0.5 * (xl[0] - xi[0]), 0.5 * (xl[1] - xi[1]), 0.5 * (xl[2] - xi[2])};
       const double mh[3] = {-th[0], -th[1], -th[2]};
-      dev_skew_q(th, k, Qa);  // Q^{il}
-      dev_skew_q(mh, k, Qb);  // Q^{li}
-      const double *Ef = a.E + int64_t(a.Fedge[f]) * k * k;
-      dev_tmm(k, k, k, Qa, Ef, tmp);
-      dev_mm(k, k, k, tmp, Qb, Ee);  // Q^{il,T} E Q^{li}
-      const double *xJ = a.xc + 3 * int64_t(J);
       const double t[3] = {xl[0] - xJ[0], xl[1] - xJ[1], xl[2] - xJ[2]};
-      dev_skew_q(t, k, T);   // Q^{J->l}
-      dev_mm(k, k, k, Ee, T, tmp);
-      for (int e = 0; e < k * k; ++e) acc[e] -= tmp[e];
+      load_block<KK>(a.E + int64_t(a.Fedge[f]) * KK, X);
+      tmul_q<K>(X, th);
+      mul_q<K, K>(X, mh);   // Q^{il,T} E Q^{li}
+      mul_q<K, K>(X, t);    // ... Q^{J->l}
+#pragma unroll
+      for (int e = 0; e < KK; ++e) acc[e] -= X[e];
     }
-    dev_mm(k, k, k, Dp, acc, tmp);
-    double *out = a.Pval + q * bs * k;
-    for (int r = 0; r < bs; ++r)
-      for (int c = 0; c < k; ++c)
-        out[r * k + c] = (J == Ji ? Pi[r * k + c] : 0.0) - a.omega * tmp[r * k + c];
+    double R[BS * K], T[BS * K];
+    mul_rows<BS, K, K>(Dp, acc, R);
+#pragma unroll
+    for (int e = 0; e < BS * K; ++e) T[e] = J == Ji && e / K == e % K ? 1.0 : 0.0;
+    mul_q<BS, K>(T, ti);
+    double *out = a.Pval + q * (BS * K);
+#pragma unroll
+    for (int e = 0; e < BS * K; ++e) out[e] = T[e] - a.omega * R[e];
   }
 }
 
@@ -1021,13 +1057,27 @@ hipError_t launch_dirichlet(int n, int bs, const int64_t *rp, const int *col, do
 hipError_t launch_diag_pinv(int n, int bs, const int64_t *rp, const int *col, const double *val,
                             double *Dinv, double tau, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_diag_pinv, dim3(cdiv64(n, 64)), dim3(64), 0, s, n, bs, rp, col, val, Dinv, tau);
+  const dim3 grid(cdiv64(n, 64));
+  switch (bs) {
+    case 1: hipLaunchKernelGGL(k_diag_pinv<1>, grid, dim3(64), 0, s, n, rp, col, val, Dinv, tau); break;
+    case 3: hipLaunchKernelGGL(k_diag_pinv<3>, grid, dim3(64), 0, s, n, rp, col, val, Dinv, tau); break;
+    case 6: hipLaunchKernelGGL(k_diag_pinv<6>, grid, dim3(64), 0, s, n, rp, col, val, Dinv, tau); break;
+    default: return hipErrorInvalidValue;
+  }
   EAMG_LAUNCH_CHECK();
 }
 
 hipError_t launch_ps_numeric(const PsArgs &a, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_ps_numeric, dim3(cdiv64(a.n, 64)), dim3(64), 0, s, a);
+  const dim3 grid(cdiv64(a.n, 64));
+  if (a.k == 6 && a.bs == 3)
+    hipLaunchKernelGGL((k_ps_numeric<6, 3>), grid, dim3(64), 0, s, a);
+  else if (a.k == 6 && a.bs == 6)
+    hipLaunchKernelGGL((k_ps_numeric<6, 6>), grid, dim3(64), 0, s, a);
+  else if (a.k == 1 && a.bs == 1)
+    hipLaunchKernelGGL((k_ps_numeric<1, 1>), grid, dim3(64), 0, s, a);
+  else
+    return hipErrorInvalidValue;
   EAMG_LAUNCH_CHECK();
 }
 
