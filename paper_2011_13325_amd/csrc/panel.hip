@@ -58,6 +58,13 @@ inline unsigned chunk_grid(unsigned wgs) { return (wgs + 8 * kChunkWg - 1) / (8 
 // contiguous run of memory), and the column index of a sub-team's next block is
 // fetched one step ahead, so a step waits for one round of gathers only.
 //
+// The lanes of a sub-team need the same block.  Q neighbours among them (all blocks of 6x6, 3x6 and 6x3
+// entries; Q = 2 or 4, see share_log2) load 1/Q of it each and hand the values round by DPP: the loads
+// of a block's entries, 9 of the 15 vector loads of a 6x6 block in FP32, drop to 3, and their registers
+// with them.  64^3 x 32 FP32 69.9 -> 65.3 ms, 37x29x33 x 7 FP64 13.6 -> 12.8 ms.  Bound then: the x
+// panels from L2 (level 1's backward colours gather 14 TB/s); more wavefronts per SIMD (five for four)
+// change nothing.
+//
 // The row's BR K sums then spread over the lanes: halving exchanges across the sub-teams of a
 // wavefront (each lane ends with its share of the values, 21 shuffles for 6 x 4 values over eight
 // sub-teams where a butterfly takes 72), the wavefronts' shares meeting in LDS in wavefront order.
@@ -90,9 +97,15 @@ __device__ inline PVec<T, C> pload(const T *p) {
   return out;
 }
 
+// Columns per lane C, and how many consecutive lanes Q share a block's values (pteam_sums):
+// CQ = C + kQuad log2(Q).
+constexpr int kQuad = 16;
+
 // Where a thread sits in a row team of 64 W lanes for K columns, C per lane.
-template <int C, int W>
+template <int CQ, int W>
 struct PTeam {
+  static constexpr int C = CQ % kQuad;
+
   int row_in_wg;   // which of the kPB / (64 W) rows of the workgroup
   int t;           // lane within the row team
   int lg;          // log2(K / C)
@@ -141,12 +154,37 @@ __device__ __forceinline__ void pbutterfly(T (&v)[M], int off) {
     for (int k = 0; k < N; ++k) v[k] += __shfl_xor(v[k], off, kWave);
 }
 
+// The value that lane q of this lane's group of Q (2 or 4) consecutive lanes holds in v.
+template <int Q, int q>
+__device__ __forceinline__ int shared_bits(int v) {
+  constexpr int perm = Q == 4 ? q * 0x55 : (q ? 0xf5 : 0xa0);   // quad_perm: q q q q, or q q q+2 q+2
+  return __builtin_amdgcn_mov_dpp(v, perm, 0xf, 0xf, true);
+}
+template <int Q>
+__device__ __forceinline__ int shared_bits(int v, int q) {
+  if constexpr (Q == 2) return q == 0 ? shared_bits<2, 0>(v) : shared_bits<2, 1>(v);
+  return q == 0 ? shared_bits<4, 0>(v) : q == 1 ? shared_bits<4, 1>(v) : q == 2 ? shared_bits<4, 2>(v) : shared_bits<4, 3>(v);
+}
+template <int Q>
+__device__ __forceinline__ float shared_value(float v, int q) {
+  return __int_as_float(shared_bits<Q>(__float_as_int(v), q));
+}
+template <int Q>
+__device__ __forceinline__ double shared_value(double v, int q) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = unsigned(shared_bits<Q>(int(b & 0xffffffffLL), q));
+  const int hi = shared_bits<Q>(int(b >> 32), q);
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | lo);
+}
+
 // The row's sums over blocks p in [p0, p1) of M_p X_col(p), by wavefront: entry (r, column k) of
 // wavefront w's share at red[(w BR + r) K + k], visible to the team on return.
-template <class T, int BR, int BC, int C, int W>
-__device__ inline void pteam_sums(int p0, int p1, int K, const PTeam<C, W> &tm,
+template <class T, int BR, int BC, int CQ, int W>
+__device__ inline void pteam_sums(int p0, int p1, int K, const PTeam<CQ, W> &tm,
                                   const int *__restrict__ col, const T *__restrict__ val,
                                   const T *__restrict__ x, T *red) {
+  constexpr int C = CQ % kQuad;
+  constexpr int Q = 1 << (CQ / kQuad), per = BR * BC / Q;   // lanes that share a block, values each loads
   constexpr int NV = BR * C;
   T acc[NV];
 #pragma unroll
@@ -157,21 +195,30 @@ __device__ inline void pteam_sums(int p0, int p1, int K, const PTeam<C, W> &tm,
     const int64_t c = cn;
     const int pn = p + tm.S;
     cn = pn < p1 ? col[pn] : 0;
-    T a[BR * BC];
+    T a[per];
+    const T *mine = val + int64_t(p) * (BR * BC) + (Q > 1 ? (tm.g & (Q - 1)) * per : 0);
 #pragma unroll
-    for (int e = 0; e < BR * BC; ++e) a[e] = val[int64_t(p) * (BR * BC) + e];
+    for (int e = 0; e < per; ++e) a[e] = mine[e];
     PVec<T, C> xv[BC];
 #pragma unroll
     for (int cc = 0; cc < BC; ++cc) xv[cc] = pload<T, C>(x + (c * BC + cc) * K + tm.g * C);
     // the whole block and its gathers in flight together (64^3 x 32 FP32 86.1 -> 84.6 ms, 37x29x33 x 7
-    // FP64 17.8 -> 17.0 ms); a further block ahead only costs registers (FP32 90.4 ms)
+    // FP64 17.8 -> 17.0 ms); a further block ahead only costs registers (68.0 ms, not 65.3)
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int r = 0; r < BR; ++r)
 #pragma unroll
       for (int cc = 0; cc < BC; ++cc)
 #pragma unroll
-        for (int i = 0; i < C; ++i) acc[r * C + i] = fma(a[r * BC + cc], xv[cc].v[i], acc[r * C + i]);
+        for (int i = 0; i < C; ++i) {
+          const int e = r * BC + cc;
+          T m;
+          if constexpr (Q > 1)
+            m = shared_value<Q>(a[e % per], e / per);
+          else
+            m = a[e];
+          acc[r * C + i] = fma(m, xv[cc].v[i], acc[r * C + i]);
+        }
   }
   // K <= 64: a wavefront has at least four sub-teams
   constexpr int H1 = NV % 2 == 0 ? NV / 2 : 0, H2 = NV % 4 == 0 ? NV / 4 : 0, H3 = NV % 8 == 0 ? NV / 8 : 0;
@@ -603,12 +650,20 @@ inline int pwaves(const SolveMat &M, int K) {
 
 inline unsigned pteam_grid(int rows, int W) { return pgrid(rows, kPB / (kWave * W)); }
 
-#define EAMG_PCOLS(C_, ...)                                     \
-  switch (pcols(K)) {                                           \
-    case 1: { constexpr int C_ = 1; __VA_ARGS__; } break;       \
-    case 2: { constexpr int C_ = 2; __VA_ARGS__; } break;       \
-    default: { constexpr int C_ = 4; __VA_ARGS__; } break;      \
+// SHARE_: log2 of the lanes that may share a block (0: none); a sub-team has K / 4 of them
+#define EAMG_PCOLS_Q(C_, SHARE_, ...)                                                          \
+  switch (pcols(K)) {                                                                          \
+    case 1: { constexpr int C_ = 1; __VA_ARGS__; } break;                                      \
+    case 2: { constexpr int C_ = 2; __VA_ARGS__; } break;                                      \
+    default:                                                                                   \
+      if (K >= 16) { constexpr int C_ = 4 + kQuad * (SHARE_); __VA_ARGS__; }                   \
+      else if (K >= 8) { constexpr int C_ = 4 + kQuad * ((SHARE_) ? 1 : 0); __VA_ARGS__; }     \
+      else { constexpr int C_ = 4; __VA_ARGS__; }                                              \
+      break;                                                                                   \
   }
+#define EAMG_PCOLS(C_, ...) EAMG_PCOLS_Q(C_, 0, __VA_ARGS__)
+// 9 entries a lane: 36 over four lanes, 18 over two; blocks of 1 or 9 stay whole.
+constexpr int share_log2(int br, int bc) { return br * bc == 36 ? 2 : br * bc == 18 ? 1 : 0; }
 #define EAMG_PTEAM(W_, M_, ...)                                 \
   if (pwaves(M_, K) == 4) { constexpr int W_ = 4; __VA_ARGS__; } \
   else { constexpr int W_ = 1; __VA_ARGS__; }
@@ -626,7 +681,7 @@ hipError_t launch_pgs(const SolveMat &A, const T *Dinv, int r0, int r1, int K, c
   const int *col = FWD ? A.lo_col : A.col;
   if (!val || !rp || !valid_k(K) || (FWD && !dval) || r0 < 0 || r1 > A.n_rows) return hipErrorInvalidValue;
 #define EAMG_PGS(B_)                                                                                \
-  EAMG_PTEAM(W, A, EAMG_PCOLS(C, hipLaunchKernelGGL((k_pgs_color<T, B_, FWD, C, W>),               \
+  EAMG_PTEAM(W, A, EAMG_PCOLS_Q(C, share_log2(B_, B_), hipLaunchKernelGGL((k_pgs_color<T, B_, FWD, C, W>),               \
                                                     dim3(pteam_grid(r1 - r0, W)), dim3(kPB), 0, s, \
                                                     r0, r1, K, rp, col, val, dval, Dinv, b, x, x,  \
                                                     r)))
@@ -664,7 +719,7 @@ hipError_t launch_pgroup_rhs(const SolveMat &A, const int *lo_end, int r0, int r
   const int *col = lo_end ? A.lo_col : A.col;
   if (!val || !rp) return hipErrorInvalidValue;
 #define EAMG_PRHS(B_)                                                                             \
-  EAMG_PTEAM(W, A, EAMG_PCOLS(C, hipLaunchKernelGGL((k_presid<T, B_, C, W, false>),              \
+  EAMG_PTEAM(W, A, EAMG_PCOLS_Q(C, share_log2(B_, B_), hipLaunchKernelGGL((k_presid<T, B_, C, W, false>),              \
                                                     dim3(pteam_grid(r1 - r0, W)), dim3(kPB), 0,  \
                                                     s, r0, r1, K, rp, re, col, val, x, b, u)))
   switch (A.br) {
@@ -686,7 +741,7 @@ hipError_t launch_pgroup(const SolveMat &S, const T *dval, const T *Dinv, int r0
   const T *val = pvals<T>(S);
   if (!val || !S.rp || (FWD && !dval)) return hipErrorInvalidValue;
 #define EAMG_PGRP(B_)                                                                               \
-  EAMG_PTEAM(W, S, EAMG_PCOLS(C, hipLaunchKernelGGL((k_pgs_color<T, B_, FWD, C, W>),               \
+  EAMG_PTEAM(W, S, EAMG_PCOLS_Q(C, share_log2(B_, B_), hipLaunchKernelGGL((k_pgs_color<T, B_, FWD, C, W>),               \
                                                     dim3(pteam_grid(r1 - r0, W)), dim3(kPB), 0, s, \
                                                     r0, r1, K, S.rp, S.col, val, dval, Dinv, u, u, \
                                                     x, r)))
@@ -720,7 +775,7 @@ hipError_t launch_presid_upper(const SolveMat &A, int K, const T *x, T *r, hipSt
   const T *val = reinterpret_cast<const T *>(sizeof(T) == 4 ? (const void *)A.up_val32 : (const void *)A.up_val);
   if (!val || !A.up_rp || !valid_k(K)) return hipErrorInvalidValue;
 #define EAMG_PRES(B_)                                                                             \
-  EAMG_PTEAM(W, A, EAMG_PCOLS(C, hipLaunchKernelGGL((k_presid<T, B_, C, W, true>),               \
+  EAMG_PTEAM(W, A, EAMG_PCOLS_Q(C, share_log2(B_, B_), hipLaunchKernelGGL((k_presid<T, B_, C, W, true>),               \
                                                     dim3(chunk_grid(pteam_grid(A.n_rows, W))),   \
                                                     dim3(kPB), 0, s, 0, A.n_rows, K, A.up_rp,    \
                                                     A.up_rp + 1, A.up_col, val, x, r, r)))
@@ -741,7 +796,7 @@ hipError_t launch_prect(const SolveMat &M, int K, const T *x, T *y, bool accumul
   if (!val || !valid_k(K)) return hipErrorInvalidValue;
   const int accf = accumulate ? 1 : 0;
 #define EAMG_PRECT(BR_, BC_)                                                                      \
-  EAMG_PTEAM(W, M, EAMG_PCOLS(C, hipLaunchKernelGGL((k_prect<T, BR_, BC_, C, W>),                \
+  EAMG_PTEAM(W, M, EAMG_PCOLS_Q(C, share_log2(BR_, BC_), hipLaunchKernelGGL((k_prect<T, BR_, BC_, C, W>),                \
                                                     dim3(chunk_grid(pteam_grid(M.n_rows, W))),   \
                                                     dim3(kPB), 0, s, M.n_rows, K, M.rp, M.col,   \
                                                     val, x, y, accf)))
