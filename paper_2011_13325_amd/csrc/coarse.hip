@@ -514,7 +514,8 @@ __global__ __launch_bounds__(kThreads) void k_dense_panel_sum(int64_t nk, int S,
 // each output's parts in ascending order, so the result is reproducible.
 // Bound: the stored half of the matrix from HBM.  Reading the whole matrix row by row (16 rows 100 KB
 // apart per wavefront) took 473 us for 13,416 dofs and 8 columns (3.0 TB/s of twice the bytes); now
-// 236 us and 26 us for the sums.
+// 210 us and 26 us for the sums (236 with batches of four sub-blocks loaded, then multiplied; two such
+// batches spill).
 constexpr int kSymCols = 16;
 
 inline int sym_run_len(int nb) {
@@ -533,7 +534,7 @@ __global__ __launch_bounds__(256, 2) void k_dense_panel_sym(int n, int nb, int R
                                                          const T *__restrict__ X, double *__restrict__ P,
                                                          double *__restrict__ Q) {
   constexpr int kPad = kSymCols;   // columns held, zero past Kc
-  constexpr int kBatch = 4;
+  constexpr int kBatch = 2;
   __shared__ double xi[kSymTile * kPad];
   // block row and first tile of this run
   int i = 0, g = int(blockIdx.x);
@@ -553,46 +554,51 @@ __global__ __launch_bounds__(256, 2) void k_dense_panel_sym(int n, int nb, int R
 #pragma unroll
   for (int rg = 0; rg < 8; ++rg) yi[rg] = dbl4{0.0, 0.0, 0.0, 0.0};
   const size_t tile0 = size_t(i) * nb - size_t(i) * (i - 1) / 2 - i;   // packed index of (i, j) is tile0 + j
-  auto tile = [&](int j, auto offdiag) {
-    constexpr bool off = decltype(offdiag)::value;
+  // A tile is two strips of 16 columns, a strip four batches of kBatch sub-blocks, both operand layouts;
+  // the next batch is loaded while the matrix cores work on this one (x_j with a strip's first).
+  struct Batch {
+    dbl4 a[kBatch];
+    double bt[kBatch][4];
+  };
+  auto load = [&](Batch &B, double (&xj)[4], int j, auto batch) {
+    constexpr int cs = decltype(batch)::value / 4, r0 = decltype(batch)::value % 4 * kBatch;
+    const int cb = 32 * w + 16 * cs;            // the sub-blocks' first column
     const double *Tl = S + (tile0 + j) * (kSymTile * kSymTile);
-#pragma unroll
-    for (int cs = 0; cs < 2; ++cs) {
-      const int cb = 32 * w + 16 * cs;            // the sub-blocks' first column
-      double xj[4];
+    if constexpr (r0 == 0)
 #pragma unroll
       for (int st = 0; st < 4; ++st) {
         const int d = j * kSymTile + cb + 4 * hi + st;
         const double v = double(X[size_t(min(d, n - 1)) * K + c0 + min(lo, Kc - 1)]);
         xj[st] = (d < n && lo < Kc) ? v : 0.0;
       }
-      dbl4 yj = dbl4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int r0 = 0; r0 < 8; r0 += kBatch) {
-        // kBatch sub-blocks in flight, both operand layouts
-        dbl4 a[kBatch];
-        double bt[kBatch][4];
+    for (int q = 0; q < kBatch; ++q) {
+      const double *sb = Tl + size_t(16 * (r0 + q)) * kSymTile + cb;
+      B.a[q] = *reinterpret_cast<const dbl4 *>(sb + size_t(lo) * kSymTile + 4 * hi);
 #pragma unroll
-        for (int q = 0; q < kBatch; ++q) {
-          const double *sb = Tl + size_t(16 * (r0 + q)) * kSymTile + cb;
-          a[q] = *reinterpret_cast<const dbl4 *>(sb + size_t(lo) * kSymTile + 4 * hi);
-          if constexpr (off)
+      for (int st = 0; st < 4; ++st) B.bt[q][st] = sb[size_t(4 * hi + st) * kSymTile + lo];
+    }
+  };
+  dbl4 yj;
+  auto apply = [&](const Batch &B, const double (&xj)[4], int j, auto batch) {
+    constexpr int cs = decltype(batch)::value / 4, r0 = decltype(batch)::value % 4 * kBatch;
+    const int cb = 32 * w + 16 * cs;
+    if constexpr (r0 == 0) yj = dbl4{0.0, 0.0, 0.0, 0.0};
+    const bool off = j != i;   // the diagonal tile's transpose is itself
 #pragma unroll
-            for (int st = 0; st < 4; ++st) bt[q][st] = sb[size_t(4 * hi + st) * kSymTile + lo];
-        }
-        __builtin_amdgcn_sched_barrier(0);
+    for (int q = 0; q < kBatch; ++q) {
+      const int rg = r0 + q;
 #pragma unroll
-        for (int q = 0; q < kBatch; ++q) {
-          const int rg = r0 + q;
+      for (int st = 0; st < 4; ++st)
+        yi[rg] = __builtin_amdgcn_mfma_f64_16x16x4f64(B.a[q][st], xj[st], yi[rg], 0, 0, 0);
+    }
+    if (off) {
 #pragma unroll
-          for (int st = 0; st < 4; ++st) {
-            yi[rg] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q][st], xj[st], yi[rg], 0, 0, 0);
-            if constexpr (off)
-              yj = __builtin_amdgcn_mfma_f64_16x16x4f64(bt[q][st], xi[(16 * rg + 4 * hi + st) * kPad + lo], yj, 0, 0, 0);
-          }
-        }
-      }
-      if constexpr (off) {
+      for (int q = 0; q < kBatch; ++q)
+#pragma unroll
+        for (int st = 0; st < 4; ++st)
+          yj = __builtin_amdgcn_mfma_f64_16x16x4f64(B.bt[q][st], xi[(16 * (r0 + q) + 4 * hi + st) * kPad + lo], yj, 0, 0, 0);
+      if constexpr (r0 == 6) {
         double *q = Q + (tile0 + j) * (size_t(kSymTile) * Kc);
 #pragma unroll
         for (int v = 0; v < 4; ++v)
@@ -600,12 +606,27 @@ __global__ __launch_bounds__(256, 2) void k_dense_panel_sym(int n, int nb, int R
       }
     }
   };
-  int j = j0;
-  if (j == i) {
-    tile(j, std::false_type{});
-    ++j;
+  Batch u, v;
+  double xa[4], xb[4];
+  using std::integral_constant;
+  const auto step = [&](int j, auto batch) {
+    constexpr int q = decltype(batch)::value, nq = (q + 1) % 8;
+    const int jn = q == 7 ? j + 1 : j;
+    if (jn < j1) load(nq % 2 ? v : u, nq / 4 ? xb : xa, jn, integral_constant<int, nq>{});
+    __builtin_amdgcn_sched_barrier(0);
+    apply(q % 2 ? v : u, q / 4 ? xb : xa, j, batch);
+  };
+  load(u, xa, j0, integral_constant<int, 0>{});
+  for (int j = j0; j < j1; ++j) {
+    step(j, integral_constant<int, 0>{});
+    step(j, integral_constant<int, 1>{});
+    step(j, integral_constant<int, 2>{});
+    step(j, integral_constant<int, 3>{});
+    step(j, integral_constant<int, 4>{});
+    step(j, integral_constant<int, 5>{});
+    step(j, integral_constant<int, 6>{});
+    step(j, integral_constant<int, 7>{});
   }
-  for (; j < j1; ++j) tile(j, std::true_type{});
   // y_i: the wavefronts' sums in wavefront order, through the x_i buffer
   for (int s = 0; s < 4; ++s) {
     __syncthreads();
