@@ -228,13 +228,13 @@ __global__ __launch_bounds__(kThreads) void k_dense_gemv(int n, int ld, const do
 // Tile (i, j) of the upper block triangle from its packed index t (row by row: tile (i, j) has
 // index i * nb - i * (i - 1) / 2 + j - i).  Uniform over the workgroup.
 __device__ inline void sym_tile_of(int t, int nb, int &i, int &j) {
-  int r = t, a = 0;
-  while (r >= nb - a) {
-    r -= nb - a;
-    ++a;
-  }
+  const auto first = [nb](int a) { return a * nb - a * (a - 1) / 2; };   // of block row a
+  const double m = 2.0 * nb + 1.0;
+  int a = max(0, min(nb - 1, int(0.5 * (m - sqrt(m * m - 8.0 * t)))));
+  while (first(a) > t) --a;
+  while (a + 1 < nb && first(a + 1) <= t) ++a;
   i = a;
-  j = a + r;
+  j = a + (t - first(a));
 }
 
 // S (packed, TM) := the upper tiles of (D + D^T) / 2 for the first n rows and columns of D
@@ -361,20 +361,39 @@ __device__ __forceinline__ void symv_tile(int n, int nb, int t, const TM *__rest
   }
 }
 
-// Row i of y from the partial sums W of its matrix: sum over q of W[i / 128][q][i % 128], q
-// ascending.
-__device__ inline double symv_row_sum(int nb, int i, const double *__restrict__ W) {
-  const double *w = W + size_t(i / kSymTile) * nb * kSymTile + i % kSymTile;
+// Sums of a hundred partial blocks per output: a workgroup takes 256 / NS outputs, each of its NS slices
+// every NS-th term (four in flight), and the slices meet in LDS in slice order.  A thread per output
+// walked through all of them, a chain of loads on a few dozen workgroups: with 88 blocks of 128 outputs
+// 12.1 us, now 4.8 (panel of 13,416 rows and 8 columns: 26 and 14).  Returns the sum of term(0) ..
+// term(count - 1) on slice 0 (threadIdx.x < 256 / NS).
+template <int NS, class F>
+__device__ __forceinline__ double sliced_sum(int count, F &&term) {
+  constexpr int outs = 256 / NS;
+  __shared__ double sh[NS][outs];
+  const int o = int(threadIdx.x) % outs, sl = int(threadIdx.x) / outs;
   double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-  int q = 0;
-  for (; q + 4 <= nb; q += 4) {
-    a0 += w[size_t(q) * kSymTile];
-    a1 += w[size_t(q + 1) * kSymTile];
-    a2 += w[size_t(q + 2) * kSymTile];
-    a3 += w[size_t(q + 3) * kSymTile];
+  int q = sl;
+  for (; q + 3 * NS < count; q += 4 * NS) {
+    const double t0 = term(q), t1 = term(q + NS), t2 = term(q + 2 * NS), t3 = term(q + 3 * NS);
+    a0 += t0;
+    a1 += t1;
+    a2 += t2;
+    a3 += t3;
   }
-  for (; q < nb; ++q) a0 += w[size_t(q) * kSymTile];
-  return (a0 + a1) + (a2 + a3);
+  for (; q < count; q += NS) a0 += term(q);
+  sh[sl][o] = (a0 + a1) + (a2 + a3);
+  __syncthreads();
+  double v = sh[0][o];
+#pragma unroll
+  for (int k = 1; k < NS; ++k) v += sh[k][o];
+  return v;
+}
+constexpr int kSumSlices = 8, kSumOuts = 256 / kSumSlices;
+
+// Row i of y from the partial sums W of its matrix: sum over q of W[i / 128][q][i % 128] (i < 0: none).
+__device__ __forceinline__ double symv_row_sum(int nb, int i, const double *__restrict__ W) {
+  const double *w = W + size_t(max(i, 0) / kSymTile) * nb * kSymTile + max(i, 0) % kSymTile;
+  return sliced_sum<kSumSlices>(i < 0 ? 0 : nb, [w](int q) { return w[size_t(q) * kSymTile]; });
 }
 
 template <class TM, class TV>
@@ -385,10 +404,11 @@ __global__ __launch_bounds__(256) void k_dense_symv(int n, int nb, const TM *__r
 }
 
 template <class TV>
-__global__ void k_dense_symv_sum(int n, int nb, const double *__restrict__ W, TV *__restrict__ y) {
-  const int g = int(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (g >= n) return;
-  y[g] = TV(symv_row_sum(nb, g, W));
+__global__ __launch_bounds__(256) void k_dense_symv_sum(int n, int nb, const double *__restrict__ W,
+                                                       TV *__restrict__ y) {
+  const int g = int(blockIdx.x) * kSumOuts + int(threadIdx.x) % kSumOuts;
+  const double v = symv_row_sum(nb, g < n ? g : -1, W);
+  if (threadIdx.x < kSumOuts && g < n) y[g] = TV(v);
 }
 
 // The last part whose first tile (by_tile) or first row is at most t.
@@ -417,15 +437,16 @@ __global__ __launch_bounds__(256) void k_dense_symv_multi(int nparts, const SymP
 }
 
 template <class TV>
-__global__ void k_dense_symv_sum_multi(int nparts, const SymPart *__restrict__ parts, int rows,
-                                       const double *__restrict__ active, const double *__restrict__ W,
-                                       TV *__restrict__ y) {
-  const int g = int(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (g >= rows) return;
-  const SymPart P = parts[sym_part_of(nparts, parts, g, false)];
-  if (active && active[P.sys] == 0.0) return;
+__global__ __launch_bounds__(256) void k_dense_symv_sum_multi(int nparts, const SymPart *__restrict__ parts,
+                                                             int rows, const double *__restrict__ active,
+                                                             const double *__restrict__ W,
+                                                             TV *__restrict__ y) {
+  const int g = int(blockIdx.x) * kSumOuts + int(threadIdx.x) % kSumOuts;
+  const SymPart P = parts[sym_part_of(nparts, parts, min(g, rows - 1), false)];
+  const bool on = g < rows && !(active && active[P.sys] == 0.0);
   const int i = g - P.row0;
-  y[P.off + i] = TV(symv_row_sum(P.nb, i, W + P.woff));
+  const double v = symv_row_sum(P.nb, on ? i : -1, W + P.woff);
+  if (threadIdx.x < kSumOuts && on) y[P.off + i] = TV(v);
 }
 
 // Y = D X for a panel of K columns on the matrix cores (v_mfma_f64_16x16x4): a dense FP64
@@ -514,22 +535,24 @@ __global__ __launch_bounds__(kThreads) void k_dense_panel_sum(int64_t nk, int S,
 // each output's parts in ascending order, so the result is reproducible.
 // Bound: the stored half of the matrix from HBM.  Reading the whole matrix row by row (16 rows 100 KB
 // apart per wavefront) took 473 us for 13,416 dofs and 8 columns (3.0 TB/s of twice the bytes); now
-// 210 us and 26 us for the sums (236 with batches of four sub-blocks loaded, then multiplied; two such
+// 207 us and 14 us for the sums (236 with batches of four sub-blocks loaded, then multiplied; two such
 // batches spill).
 constexpr int kSymCols = 16;
 
-inline int sym_run_len(int nb) {
-  const int64_t r = sym_tiles(nb) / 2048;   // about two thousand workgroups
-  return int(r < 1 ? 1 : (r > 8 ? 8 : r));
+// log2 of a run's tiles: about two thousand workgroups
+inline int sym_run_log2(int nb) {
+  int lr = 0;
+  while (lr < 3 && (sym_tiles(nb) >> (lr + 1)) >= 2048) ++lr;
+  return lr;
 }
-inline int64_t sym_runs(int nb, int R) {
-  int64_t t = 0;
-  for (int i = 0; i < nb; ++i) t += (nb - i + R - 1) / R;
-  return t;
+// Runs of block rows of m, m - 1, .., 1 tiles.
+__host__ __device__ inline int sym_runs(int m, int lr) {
+  const int R = 1 << lr, q = m >> lr;
+  return R * (q * (q + 1) / 2) + (m & (R - 1)) * (q + 1);
 }
 
 template <class T>
-__global__ __launch_bounds__(256, 2) void k_dense_panel_sym(int n, int nb, int R, int K, int c0, int Kc,
+__global__ __launch_bounds__(256, 2) void k_dense_panel_sym(int n, int nb, int lr, int K, int c0, int Kc,
                                                          const double *__restrict__ S,
                                                          const T *__restrict__ X, double *__restrict__ P,
                                                          double *__restrict__ Q) {
@@ -537,12 +560,16 @@ __global__ __launch_bounds__(256, 2) void k_dense_panel_sym(int n, int nb, int R
   constexpr int kBatch = 2;
   __shared__ double xi[kSymTile * kPad];
   // block row and first tile of this run
-  int i = 0, g = int(blockIdx.x);
-  for (int c = (nb + R - 1) / R; g >= c; c = (nb - i + R - 1) / R) {
-    g -= c;
-    ++i;
+  const int all = sym_runs(nb, lr), run = int(blockIdx.x);
+  int i = 0;
+  for (int hi = nb - 1; i < hi;) {
+    const int mid = (i + hi + 1) >> 1;
+    if (all - sym_runs(nb - mid, lr) <= run)
+      i = mid;
+    else
+      hi = mid - 1;
   }
-  const int j0 = i + g * R, j1 = min(nb, j0 + R);
+  const int j0 = i + ((run - (all - sym_runs(nb - i, lr))) << lr), j1 = min(nb, j0 + (1 << lr));
   for (int e = threadIdx.x; e < kSymTile * kPad; e += 256) {
     const int d = i * kSymTile + e / kPad, c = e % kPad;
     xi[e] = (d < n && c < Kc) ? double(X[size_t(d) * K + c0 + c]) : 0.0;
@@ -644,33 +671,25 @@ __global__ __launch_bounds__(256, 2) void k_dense_panel_sym(int n, int nb, int R
   for (int e = threadIdx.x; e < kSymTile * Kc; e += 256) p[e] = xi[size_t(e / Kc) * kPad + e % Kc];
 }
 
-// Entry (d, c) of Y: its block row's runs, then the mirrored tiles (i, block row), i ascending.
+// Entry (d, c) of Y: its block row's runs, then the mirrored tiles (i, block row).
+constexpr int kPanelSumSlices = 8, kPanelSumOuts = 256 / kPanelSumSlices;
 template <class T>
-__global__ __launch_bounds__(kThreads) void k_dense_panel_sym_sum(int n, int nb, int R, int K, int c0,
+__global__ __launch_bounds__(256) void k_dense_panel_sym_sum(int n, int nb, int lr, int K, int c0,
                                                                   int Kc, const double *__restrict__ P,
                                                                   const double *__restrict__ Q,
                                                                   T *__restrict__ Y) {
-  const int64_t e = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-  if (e >= int64_t(n) * Kc) return;
-  const int d = int(e / Kc), c = int(e % Kc);
+  const int64_t e = int64_t(blockIdx.x) * kPanelSumOuts + int(threadIdx.x) % kPanelSumOuts;
+  const bool on = e < int64_t(n) * Kc;
+  const int d = on ? int(e / Kc) : 0, c = on ? int(e % Kc) : 0;
   const int b = d / kSymTile;
   const size_t at = size_t(d % kSymTile) * Kc + c, len = size_t(kSymTile) * Kc;
-  int g0 = 0;
-  for (int i = 0; i < b; ++i) g0 += (nb - i + R - 1) / R;
-  const int runs = (nb - b + R - 1) / R;
-  double v = 0.0;
-  for (int g = 0; g < runs; ++g) v += P[size_t(g0 + g) * len + at];
-  double u0 = 0.0, u1 = 0.0, u2 = 0.0, u3 = 0.0;
-  int i = 0;
-  auto tile = [&](int a) { return size_t(a) * nb - size_t(a) * (a - 1) / 2 + (b - a); };
-  for (; i + 4 <= b; i += 4) {
-    u0 += Q[tile(i) * len + at];
-    u1 += Q[tile(i + 1) * len + at];
-    u2 += Q[tile(i + 2) * len + at];
-    u3 += Q[tile(i + 3) * len + at];
-  }
-  for (; i < b; ++i) u0 += Q[tile(i) * len + at];
-  Y[size_t(d) * K + c0 + c] = T(v + ((u0 + u1) + (u2 + u3)));
+  const int g0 = sym_runs(nb, lr) - sym_runs(nb - b, lr), runs = (nb - b + (1 << lr) - 1) >> lr;
+  const double v = sliced_sum<kPanelSumSlices>(on ? runs + b : 0, [&](int q) {
+    if (q < runs) return P[size_t(g0 + q) * len + at];
+    const size_t a = size_t(q - runs);
+    return Q[(a * nb - a * (a - 1) / 2 + (b - a)) * len + at];
+  });
+  if (int(threadIdx.x) < kPanelSumOuts && on) Y[size_t(d) * K + c0 + c] = T(v);
 }
 
 }  // namespace
@@ -742,7 +761,7 @@ hipError_t launch_dense_panel(int n, int ld, int K, const double *D, const T *X,
 
 size_t sym_panel_work_doubles(int n, int K) {
   const int nb = sym_blocks(n);
-  return size_t(sym_runs(nb, sym_run_len(nb)) + sym_tiles(nb)) * kSymTile * (K < kSymCols ? K : kSymCols);
+  return size_t(sym_runs(nb, sym_run_log2(nb)) + sym_tiles(nb)) * kSymTile * (K < kSymCols ? K : kSymCols);
 }
 
 template <class T>
@@ -750,13 +769,13 @@ hipError_t launch_dense_panel_sym(int n, int K, const double *S, const T *X, T *
                                   hipStream_t s) {
   if (n == 0) return hipSuccess;
   if (!S || !work || K < 1 || K > 64 || (K & (K - 1))) return hipErrorInvalidValue;
-  const int nb = sym_blocks(n), R = sym_run_len(nb), Kc = K < kSymCols ? K : kSymCols;
-  const unsigned runs = unsigned(sym_runs(nb, R));
+  const int nb = sym_blocks(n), lr = sym_run_log2(nb), Kc = K < kSymCols ? K : kSymCols;
+  const unsigned runs = unsigned(sym_runs(nb, lr));
   double *P = work, *Q = work + size_t(runs) * kSymTile * Kc;
   for (int c0 = 0; c0 < K; c0 += Kc) {
-    hipLaunchKernelGGL(k_dense_panel_sym<T>, dim3(runs), dim3(256), 0, s, n, nb, R, K, c0, Kc, S, X, P, Q);
-    hipLaunchKernelGGL(k_dense_panel_sym_sum<T>, dim3(cdiv(int64_t(n) * Kc, kThreads)), dim3(kThreads), 0, s, n,
-                       nb, R, K, c0, Kc, P, Q, Y);
+    hipLaunchKernelGGL(k_dense_panel_sym<T>, dim3(runs), dim3(256), 0, s, n, nb, lr, K, c0, Kc, S, X, P, Q);
+    hipLaunchKernelGGL(k_dense_panel_sym_sum<T>, dim3(cdiv(int64_t(n) * Kc, kPanelSumOuts)), dim3(256), 0, s, n,
+                       nb, lr, K, c0, Kc, P, Q, Y);
   }
   return hipGetLastError();
 }
@@ -787,7 +806,7 @@ hipError_t launch_dense_symv(int n, const TM *S, const TV *x, TV *y, double *W, 
   if (!S || !W) return hipErrorInvalidValue;
   const int nb = sym_blocks(n);
   hipLaunchKernelGGL((k_dense_symv<TM, TV>), dim3(unsigned(sym_tiles(nb))), dim3(256), 0, s, n, nb, S, x, W);
-  hipLaunchKernelGGL(k_dense_symv_sum<TV>, dim3(cdiv(n, kThreads)), dim3(kThreads), 0, s, n, nb, W, y);
+  hipLaunchKernelGGL(k_dense_symv_sum<TV>, dim3(cdiv(n, kSumOuts)), dim3(256), 0, s, n, nb, W, y);
   return hipGetLastError();
 }
 
@@ -798,8 +817,8 @@ hipError_t launch_dense_symv_multi(int nparts, const SymPart *parts, int tiles, 
   if (!parts || !W || tiles < 1) return hipErrorInvalidValue;
   hipLaunchKernelGGL((k_dense_symv_multi<TM, TV>), dim3(unsigned(tiles)), dim3(256), 0, s, nparts, parts,
                      active, x, W);
-  hipLaunchKernelGGL(k_dense_symv_sum_multi<TV>, dim3(cdiv(rows, kThreads)), dim3(kThreads), 0, s, nparts,
-                     parts, rows, active, W, y);
+  hipLaunchKernelGGL(k_dense_symv_sum_multi<TV>, dim3(cdiv(rows, kSumOuts)), dim3(256), 0, s, nparts, parts, rows,
+                     active, W, y);
   return hipGetLastError();
 }
 
