@@ -208,6 +208,15 @@ SolveMat make_solve_mat(DevArena &ar, const Pattern &Pp, const std::vector<int64
   // long rows of a square level matrix: one row per workgroup, so that a row is one round of
   // loads (at most one block per lane) instead of a loop over its blocks
   if (diag_out && M.n_rows > 0 && double(M.nnz) / M.n_rows > kWideRowBlocks) M.group = kBlock;
+  // scalar rows: a workgroup of one entry per lane reads little for its dispatch (12 to 25 us per 15,000
+  // workgroups), so where a whole-level launch has more than the chip's slots need, a lane takes up to
+  // four entries.  Solves of scalar boxes of 263,055 rows 7.68 -> 6.75 ms, 884,736 rows 19.5 -> 16.5; of
+  // 4,913 rows always 668, not 729 us; 3x3 and 6x6 blocks (64^3) 38.3, not 38.8 ms.
+  constexpr double kLaneEntries = 4.0, kWgSlots = 4096.0;
+  if (br * bc == 1)
+    while (M.group > (diag_out ? 8 : 4) && M.n_rows * double(M.group) / kBlock > kWgSlots &&
+           kLaneEntries * (M.group / 2) >= double(M.nnz) / M.n_rows)
+      M.group /= 2;
   M.rp = ar.upload(to_i32(Pp.rp), s);
   M.col = ar.upload(Pp.col, s);
   int64_t *src_d = ar.upload(src, s);
