@@ -591,9 +591,9 @@ __global__ __launch_bounds__(kBlock) void k_gs_color(int r0, int r1, int G, cons
 // dependent steps (dispatch, row offsets, blocks, gathers, reduction, store) of 3.3 to 5 us that its
 // bytes hardly add to, and a sweep is 20 to 70 such launches.  A group runs any number of colours
 // in two: u = b - (couplings outside the group) x over all its rows, then its colours' recursion
-// multiplied out, t = u - S u.  Sweeps of the library's defaults (no dense tail), start to now: 17^3
-// FP64 solve 9.22 -> 2.25 ms (1536 colour launches -> 132 group launches), Poisson 65x57x71 15.1 ->
-// 7.9 ms; with the tail 64^3 FP32 25.9 -> 19.6 ms, FP64 35.9 -> 29.3 ms, 128^3 FP32 155 -> 143 ms.
+// multiplied out, t = u - S u.  Solves with groups against one launch per colour, without a dense tail:
+// 17^3 FP64 9.22 -> 2.25 ms (1536 colour launches -> 132 group launches), Poisson 65x57x71 15.1 -> 7.9
+// ms; with the tail 64^3 FP32 25.9 -> 19.6 ms, FP64 35.9 -> 29.3 ms, 128^3 FP32 155 -> 143 ms.
 template <class T, int B, int W>
 __global__ __launch_bounds__(kBlock) void k_group_rhs(int r0, int r1, int G, const int *__restrict__ rp,
                                                      const int *__restrict__ re,
