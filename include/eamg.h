@@ -130,7 +130,7 @@ typedef struct {
  *                     applied as one dense product per V-cycle (an FP64 matrix with FP64
  *                     accumulation, in either V-cycle precision unless dense_tail_fp32).  The
  *                     operator is symmetric, so the product reads only the 128 x 128 tiles of
- *                     its upper block triangle, symmetrized.  The hierarchy, and the V-cycle as
+ *                     its upper block triangle.  The hierarchy, and the V-cycle as
  *                     an operator, are those of the sparse path; only the rounding differs.  No
  *                     tail when that level is the coarsest or no level qualifies.  Memory: about
  *                     0.5 ld^2 doubles (the upper tiles; + 0.5 ld^2 floats with dense_tail_fp32),
