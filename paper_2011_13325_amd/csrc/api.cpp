@@ -22,6 +22,7 @@
 #include "hierarchy.hpp"
 #include "kernels.hpp"
 #include "structure.hpp"
+#include "wait.hpp"
 
 namespace eamg {
 
@@ -1000,18 +1001,15 @@ struct SolveRun {
     return b;
   }
   // Wait for it in host memory: the stream itself may already hold the next iteration.  The stream is
-  // asked now and then, so that an error there ends the wait.
+  // asked now and then, so that an error there, or its end without the record, ends the wait.
   void await(int k) const {
-    for (int spins = 0;; ++spins) {
-      if (published(k)) return;
-      if (spins % 4096 == 4095) {
-        const hipError_t e = hipStreamQuery(s);
-        if (e == hipErrorNotReady) continue;
-        hip_check(e, "iteration");
-        if (published(k)) return;
-        fail(EAMG_ERR_HIP, "an iteration ended without its scalars");
-      }
-    }
+    const auto busy = [&] {
+      const hipError_t e = hipStreamQuery(s);
+      if (e != hipErrorNotReady) hip_check(e, "iteration");
+      return e == hipErrorNotReady;
+    };
+    if (!poll_until([&] { return published(k); }, busy))
+      fail(EAMG_ERR_HIP, "an iteration ended without its scalars");
   }
 
   // start() in phases: each enqueue_* ends with the scalars copied to the host, each complete_*

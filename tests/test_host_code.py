@@ -1,0 +1,61 @@
+"""Host parts of the library on their own (CPU): small C++ programs over its headers and sources."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2011_13325_amd import build as B
+
+
+def _run(tmp_path, source, *sources, timeout=120):
+    cxx = shutil.which("g++") or B._hipcc()
+    src, exe = tmp_path / "t.cpp", tmp_path / "t"
+    src.write_text(source)
+    subprocess.run([cxx, "-O2", "-ftrapv", "-std=c++17", "-pthread", f"-I{B.CSRC}", str(src),
+                    *[os.path.join(B.CSRC, f) for f in sources], "-o", str(exe)],
+                   check=True, capture_output=True, timeout=300)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=timeout)
+    assert r.returncode == 0, (r.returncode, r.stdout[-2000:], r.stderr[-2000:])
+    return r.stdout
+
+
+POLL = r"""
+#include "wait.hpp"
+#include <cstdint>
+#include <cstdio>
+#include <stdexcept>
+using namespace eamg;
+struct NoRest { void operator()() const {} };
+#define CHECK(c) do { if (!(c)) { std::printf("line %d: " #c "\n", __LINE__); return 1; } } while (0)
+int main() {
+  volatile int64_t polls = 0;
+  int64_t asked = 0;
+  auto poll = [&](int64_t ready_at, int64_t busy_for) {
+    polls = asked = 0;
+    return poll_until([&] { return (polls = polls + 1) > ready_at; },
+                      [&] { return ++asked < busy_for; }, NoRest());
+  };
+  const int64_t never = INT64_MAX;
+  CHECK(poll(0, never) && polls == 1 && asked == 0);
+  CHECK(poll(kPolls - 1, never) && asked == 0);
+  CHECK(poll(kPolls, never) && asked == 1);
+  CHECK(poll(5 * kPolls + 3, never) && asked == 5);
+  // nothing left to wait for: one last look
+  CHECK(!poll(never, 3) && asked == 3 && polls == 3 * kPolls + 1);
+  CHECK(poll(3 * kPolls, 3) && asked == 3);
+  // a wait of more polls than an int counts is asked about as often as a short one
+  const int64_t many = (int64_t(1) << 31) / kPolls + 1000;
+  CHECK(!poll(never, many) && asked == many && polls == many * kPolls + 1);
+  try {
+    poll_until([] { return false; }, []() -> bool { throw std::runtime_error("x"); });
+    CHECK(false);
+  } catch (const std::runtime_error &) {
+  }
+  return 0;
+}
+"""
+
+
+def test_a_wait_of_any_length_keeps_asking_whether_to_go_on(tmp_path):
+    _run(tmp_path, POLL)
