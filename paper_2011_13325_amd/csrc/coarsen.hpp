@@ -17,7 +17,9 @@
 #include <cstdio>
 #include <cstdlib>
 #include <atomic>
+#include <exception>
 #include <functional>
+#include <system_error>
 #include <thread>
 #include <utility>
 #include <vector>
@@ -68,7 +70,9 @@ struct PhaseTimer {
   }
 };
 
-// Parallel loop with dynamic chunks, for iterations of uneven cost.
+// Parallel loop with dynamic chunks, for iterations of uneven cost.  An exception of f (its lists
+// may not fit in memory) ends the loop and is thrown to the caller once every thread is done; a thread
+// that cannot be started leaves its share to the others.
 template <class F>
 void parallel_for_dynamic(int64_t n, F &&f, int64_t chunk = 64) {
   unsigned nt = std::thread::hardware_concurrency();
@@ -78,13 +82,26 @@ void parallel_for_dynamic(int64_t n, F &&f, int64_t chunk = 64) {
     return;
   }
   std::atomic<int64_t> next{0};
-  std::vector<std::thread> th;
-  for (unsigned t = 0; t < nt; ++t)
-    th.emplace_back([&] {
+  std::atomic<bool> failed{false};
+  std::exception_ptr error;
+  auto work = [&] {
+    try {
       for (int64_t lo = next.fetch_add(chunk); lo < n; lo = next.fetch_add(chunk))
         for (int64_t i = lo; i < std::min(n, lo + chunk); ++i) f(i);
-    });
+    } catch (...) {
+      if (!failed.exchange(true)) error = std::current_exception();
+      next = n;
+    }
+  };
+  std::vector<std::thread> th;
+  th.reserve(nt);
+  try {
+    for (unsigned t = 1; t < nt; ++t) th.emplace_back(work);
+  } catch (const std::system_error &) {
+  }
+  work();
   for (auto &x : th) x.join();
+  if (error) std::rethrow_exception(error);
 }
 
 // Features of the candidate pairs of one matching pass (kPairFeatures per pair), for the

@@ -1,6 +1,5 @@
 """Host parts of the library on their own (CPU): small C++ programs over its headers and sources."""
 import os
-import shutil
 import subprocess
 
 import pytest
@@ -9,7 +8,10 @@ from paper_2011_13325_amd import build as B
 
 
 def _run(tmp_path, source, *sources, timeout=120):
-    cxx = shutil.which("g++") or B._hipcc()
+    try:
+        cxx = B._hipcc()
+    except RuntimeError:
+        pytest.skip("hipcc not found")
     src, exe = tmp_path / "t.cpp", tmp_path / "t"
     src.write_text(source)
     subprocess.run([cxx, "-O2", "-ftrapv", "-std=c++17", "-pthread", f"-I{B.CSRC}", str(src),
@@ -59,3 +61,33 @@ int main() {
 
 def test_a_wait_of_any_length_keeps_asking_whether_to_go_on(tmp_path):
     _run(tmp_path, POLL)
+
+
+LOOP = r"""
+#include "coarsen.hpp"
+#include <new>
+using namespace eamg;
+#define CHECK(c) do { if (!(c)) { std::printf("line %d: " #c "\n", __LINE__); return 1; } } while (0)
+int main() {
+  for (int64_t n : {int64_t(0), int64_t(1), int64_t(7), int64_t(200), int64_t(100000)})
+    for (int64_t chunk : {int64_t(1), int64_t(64)}) {
+      std::vector<int> seen(size_t(n), 0);
+      parallel_for_dynamic(n, [&](int64_t i) { ++seen[size_t(i)]; }, chunk);
+      for (int v : seen) CHECK(v == 1);
+    }
+  for (int64_t bad : {int64_t(0), int64_t(777), int64_t(99999)}) {
+    bool caught = false;
+    try {
+      parallel_for_dynamic(100000, [&](int64_t i) { if (i >= bad) throw std::bad_alloc(); }, 1);
+    } catch (const std::bad_alloc &) {
+      caught = true;
+    }
+    CHECK(caught);
+  }
+  return 0;
+}
+"""
+
+
+def test_a_failed_allocation_in_a_parallel_loop_reaches_the_caller(tmp_path):
+    _run(tmp_path, LOOP)
