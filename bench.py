@@ -207,8 +207,8 @@ def _per_level(E, hier, b, x, precond, stream):
 
 
 def _per_colour(E, hier, b, x, precond, stream):
-    """Time and algorithmic bytes of every colour launch of the sweeps (one profiled solve with
-    events around each colour launch, which adds their own dispatch to every launch)."""
+    """Time and algorithmic bytes of every colour launch, and of every group of colours, of the sweeps
+    (one profiled solve with events around each, which adds their own dispatch to every launch)."""
     import re
     E.eamg_profile_enable(hier.h, 3)
     hier.solve(b, x, precond=precond, stream=stream)
@@ -216,10 +216,10 @@ def _per_colour(E, hier, b, x, precond, stream):
     E.eamg_profile_enable(hier.h, False)
     out = []
     for k in ks:
-        m = re.match(r"L(\d+) c(\d+) k_gs_color<\w+, (\d+), (true|false)>", k["name"])
+        m = re.match(r"L(\d+) c(\d+)(?:-(\d+))? k_gs_color<\w+, (\d+), (true|false)>", k["name"])
         if m:
-            out.append({"level": int(m.group(1)), "sweep": "fwd" if m.group(4) == "true" else "bwd",
-                        "colour": int(m.group(2)),
+            out.append({"level": int(m.group(1)), "sweep": "fwd" if m.group(5) == "true" else "bwd",
+                        "colour": int(m.group(2)), "last_colour": int(m.group(3) or m.group(2)),
                         "us_per_launch": round(k["total_ms"] / k["launches"] * 1e3, 2),
                         "MB_per_launch": round(k["bytes"] / k["launches"] / 1e6, 4)})
     out.sort(key=lambda r: (r["level"], r["sweep"], r["colour"]))

@@ -487,9 +487,13 @@ eamg_status eamg_dense_tail(const eamg_hierarchy *h, int32_t *level, int32_t *do
  * per launch) are recorded.  eamg_profile_read synchronizes the device, aggregates the records
  * by kernel name (the template instance, e.g. "k_gs_color<double, 6, false>"), sorts them by
  * total time, copies up to max_entries of them into out, stores the number of kernels in
- * *n_out and clears the records.  on: 0 off, 1 per kernel, 2 per kernel and level (V-cycle
- * names prefixed "L<level> "), 3 as 2 with every colour launch of the single-vector sweeps
- * timed on its own (names "L<level> c<colour> ...").  Enabling resets the records.
+ * *n_out and clears the records.  Colours of a sweep that run as groups (two launches for any number
+ * of colours, k_group_rhs and k_gs_group) are records of their own, under the name of the colour
+ * launches they take the place of with " grouped" appended; their bytes are what the colours
+ * need, without the groups' matrices.  on: 0 off, 1 per kernel, 2 per kernel and level (V-cycle
+ * names prefixed "L<level> "), 3 as 2 with every colour launch and every group of the
+ * single-vector sweeps timed on its own (names "L<level> c<colour> ...", "L<level> c<first>-<last>
+ * ... grouped").  Enabling resets the records.
  */
 typedef struct {
   char name[48];

@@ -356,46 +356,23 @@ void build_sweep_stages(DevArena &ar, Level &L, const Pattern &Ap, const std::ve
   tp.mark("layout: sweep plan");
   const int ns = int(pl.cut.size()) - 1, bs = L.bs;
   L.cut = pl.cut;
-  for (auto *v : {&L.sh_rf, &L.sh_rb, &L.sh_sf, &L.sh_sb}) v->assign(size_t(ns), LaunchShape());
-  L.gs_f.assign(size_t(ns), 0);
-  L.gs_b.assign(size_t(ns), 0);
+  L.gs_blocks.assign(size_t(ns), 0);
+  L.gs_team.assign(size_t(ns), 0);
   if (!pl.grouped()) return;
   std::vector<int64_t> unused;
   const Pattern Sb = transpose_pattern(pl.S, unused);
-  // lanes per row of each group's S, and what its launches stream
-  std::vector<int> mark(size_t(L.n), -1);
-  int stamp = 0;
-  auto shape = [&](int k, const Pattern &M, auto &&lo, auto &&hi) {
-    LaunchShape sh;
-    sh.rows = L.row1(k) - L.row0(k);
-    ++stamp;
-    for (int i = L.row0(k); i < L.row1(k); ++i) {
-      const int64_t a = lo(i), b = hi(i);
-      sh.blocks += double(b - a);
-      for (int64_t q = a; q < b; ++q)
-        if (mark[size_t(M.col[size_t(q)])] != stamp) {
-          mark[size_t(M.col[size_t(q)])] = stamp;
-          sh.uniq += 1.0;
-        }
-    }
-    return sh;
-  };
-  // Blocks past the team are a second dependent load, and a group's rows differ in length (its first
-  // colour has none, its last the most), so rows of 3x3 and 6x6 blocks get a team for twice the
-  // average; of scalars the average, where idle lanes cost more than the second load (each against
-  // the other: 64^3 solves FP64 29.25 -> 28.04 ms, FP32 18.92 -> 18.15; Poisson 65x57x71 7.68, not 7.81).
-  auto lanes = [bs](const LaunchShape &sh) {
-    const double want = (bs == 1 ? 1.0 : 2.0) * sh.blocks;
-    return want > kWideRowBlocks * sh.rows ? kBlock : std::max(8, pick_group(int64_t(want), int(sh.rows)));
-  };
+  // Lanes per row of each group's S (S^T has the same blocks in the group's rows).  Blocks past the team
+  // are a second dependent load, and a group's rows differ in length (its first colour has none, its
+  // last the most), so rows of 3x3 and 6x6 blocks get a team for twice the average; of scalars the
+  // average, where idle lanes cost more than the second load (each against the other: 64^3 solves FP64
+  // 29.25 -> 28.04 ms, FP32 18.92 -> 18.15; Poisson 65x57x71 7.68, not 7.81).
   for (int k = 0; k < ns; ++k) {
     if (!L.is_group(k)) continue;
-    L.sh_rf[size_t(k)] = shape(k, Ap, [&](int i) { return Ap.rp[size_t(i)]; }, [&](int i) { return pl.pre[size_t(i)]; });
-    L.sh_rb[size_t(k)] = shape(k, Ap, [&](int i) { return Ap.rp[size_t(i)]; }, [&](int i) { return Ap.rp[size_t(i) + 1]; });
-    L.sh_sf[size_t(k)] = shape(k, pl.S, [&](int i) { return pl.S.rp[size_t(i)]; }, [&](int i) { return pl.S.rp[size_t(i) + 1]; });
-    L.sh_sb[size_t(k)] = shape(k, Sb, [&](int i) { return Sb.rp[size_t(i)]; }, [&](int i) { return Sb.rp[size_t(i) + 1]; });
-    L.gs_f[size_t(k)] = lanes(L.sh_sf[size_t(k)]);
-    L.gs_b[size_t(k)] = lanes(L.sh_sb[size_t(k)]);
+    const int rows = L.row1(k) - L.row0(k);
+    const int64_t blocks = pl.S.rp[size_t(L.row1(k))] - pl.S.rp[size_t(L.row0(k))];
+    const double want = (bs == 1 ? 1.0 : 2.0) * double(blocks);
+    L.gs_blocks[size_t(k)] = blocks;
+    L.gs_team[size_t(k)] = want > kWideRowBlocks * rows ? kBlock : std::max(8, pick_group(int64_t(want), rows));
   }
   // positions of the rows' couplings inside their groups, in the whole matrix and in its lower part
   std::vector<int> right(size_t(L.n)), lo_end(size_t(L.n));
@@ -630,7 +607,7 @@ hipError_t fwd_stage(Level &L, int k, const T *b, T *x, T *r, hipStream_t s) {
     u = B.u;
   }
   SolveMat S = L.Sf;
-  S.group = L.gs_f[size_t(k)];
+  S.group = L.gs_team[size_t(k)];
   return launch_group_fwd<T>(A, S, B.Dinv, L.row0(k), L.row1(k), u, x, r, s);
 }
 template <class T>
@@ -642,22 +619,11 @@ hipError_t bwd_stage(Level &L, int k, const T *b, T *x, hipStream_t s, const dou
   const hipError_t e = launch_group_rhs<T>(A, nullptr, L.row0(k), L.row1(k), b, x, B.u, s);
   if (e != hipSuccess) return e;
   SolveMat S = L.Sb;
-  S.group = L.gs_b[size_t(k)];
+  S.group = L.gs_team[size_t(k)];
   return launch_group_bwd<T>(S, B.Dinv, L.row0(k), L.row1(k), B.u, x, s, cg_r, rz);
 }
 
-// Launches and algorithmic bytes (values of vs bytes) of stage k.
 int stage_launches(const Level &L, int k, bool fwd) { return !L.is_group(k) || (fwd && k == 0) ? 1 : 2; }
-double stage_bytes(const Level &L, int k, bool fwd, double vs) {
-  const int bs = L.bs;
-  const LaunchKind kind = fwd ? LK_GS_FWD : LK_GS_BWD;
-  if (!L.is_group(k)) {
-    const int c = L.cut[size_t(k)];
-    return launch_bytes((fwd ? L.sh_fwd : L.sh_bwd)[size_t(c)], kind, bs, bs, vs, 1);
-  }
-  const double rhs = launch_bytes((fwd ? L.sh_rf : L.sh_rb)[size_t(k)], LK_RESID, bs, bs, vs, 1);
-  return (fwd && k == 0 ? 0.0 : rhs) + launch_bytes((fwd ? L.sh_sf : L.sh_sb)[size_t(k)], kind, bs, bs, vs, 1);
-}
 
 // Algorithmic bytes of one dense-tail apply: the packed upper tiles (FP32 or FP64), both passes
 // over the partial sums, and x and y.
@@ -698,7 +664,7 @@ int rz_parts(const eamg_hierarchy *h) {
   const Level &L = h->lv[0];
   if (h->fused || h->lv.size() < 2 || L.stages() != 1 || !L.is_group(0)) return 0;
   SolveMat S = L.Sb;
-  S.group = L.gs_b[0];
+  S.group = L.gs_team[0];
   const int nb = group_blocks(S, L.row0(0), L.row1(0));
   return nb <= kInlineParts ? nb : 0;
 }
@@ -738,32 +704,10 @@ void vcycle_t(eamg_hierarchy *h, size_t l, const T *b, T *x, hipStream_t s, doub
   const LevelBufs<T> B = bufs<T>(L);
   const int bs = L.bs;
   const double vs = sizeof(T);
-  const int ns = L.stages();
-  double fwd_bytes = 0.0, bwd_bytes = 0.0;
-  int fwd_n = 0, bwd_n = 0;
-  for (int k = 0; k < ns; ++k) {
-    fwd_bytes += stage_bytes(L, k, true, vs);
-    bwd_bytes += stage_bytes(L, k, false, vs);
-    fwd_n += stage_launches(L, k, true);
-    bwd_n += stage_launches(L, k, false);
-  }
-  const std::string gs = "k_gs_color<" + ty + ", " + std::to_string(bs);
-  // the stages of a sweep are back-to-back launches: one profiler record (events per launch would
-  // add their own dispatch to every launch)
-  if (h->prof_colours) {
-    for (int k = 0; k < ns; ++k)
-      timed_n(h, "gs_fwd", lvname(h, l, "c" + std::to_string(L.cut[size_t(k)]) + " " + gs + ", true>"),
-              stage_bytes(L, k, true, vs), stage_launches(L, k, true), s,
-              [&] { return fwd_stage<T>(L, k, b, x, B.r, s); });
-  } else {
-    timed_n(h, "gs_fwd", lvname(h, l, gs + ", true>"), fwd_bytes, fwd_n, s, [&] {
-      for (int k = 0; k < ns; ++k) {
-        const hipError_t e = fwd_stage<T>(L, k, b, x, B.r, s);
-        if (e != hipSuccess) return e;
-      }
-      return hipSuccess;
-    });
-  }
+  const auto grouped = [&L](int k) { return L.is_group(k); };
+  sweep<T>(h, l, true, "k_gs_color", 1, h->prof_colours, grouped,
+           [&L](int k) { return stage_launches(L, k, true); },
+           [&](int k) { return fwd_stage<T>(L, k, b, x, B.r, s); }, s);
   const int nres = L.resid_cut.empty() ? 1 : int(L.resid_cut.size()) - 1;
   timed_n(h, "resid_upper", lvname(h, l, "k_resid_upper<" + ty + ", " + std::to_string(bs) + ">"),
           launch_bytes(L.sh_resid, LK_RESID, bs, bs, vs, 1), nres, s, [&] {
@@ -776,20 +720,9 @@ void vcycle_t(eamg_hierarchy *h, size_t l, const T *b, T *x, hipStream_t s, doub
   vcycle_t<T>(h, l + 1, CB.b, CB.x, s);
   timed(h, "prolong", lvname(h, l, "k_rect<" + ty + ", " + std::to_string(bs) + ", " + std::to_string(L.kc) + ">"),
         launch_bytes(L.sh_P, LK_RECT_ACC, bs, L.kc, vs, 1), s, [&] { return launch_rect<T>(L.Pm, CB.x, x, true, s); });
-  if (h->prof_colours) {
-    for (int k = ns - 1; k >= 0; --k)
-      timed_n(h, "gs_bwd", lvname(h, l, "c" + std::to_string(L.cut[size_t(k)]) + " " + gs + ", false>"),
-              stage_bytes(L, k, false, vs), stage_launches(L, k, false), s,
-              [&] { return bwd_stage<T>(L, k, b, x, s, h->r, rz); });
-    return;
-  }
-  timed_n(h, "gs_bwd", lvname(h, l, gs + ", false>"), bwd_bytes, bwd_n, s, [&] {
-    for (int k = ns - 1; k >= 0; --k) {
-      const hipError_t e = bwd_stage<T>(L, k, b, x, s, h->r, rz);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  });
+  sweep<T>(h, l, false, "k_gs_color", 1, h->prof_colours, grouped,
+           [&L](int k) { return stage_launches(L, k, false); },
+           [&](int k) { return bwd_stage<T>(L, k, b, x, s, h->r, rz); }, s);
 }
 
 // z = V(r) on colour-major level-0 vectors: FP64, or FP32 with conversions at the boundary.
@@ -890,7 +823,8 @@ double iteration_seconds(const eamg_hierarchy *h, bool f32) {
              launch_bytes(L.sh_P, LK_RECT_ACC, L.bs, L.kc, vs, 1);
     for (int k = 0; k < L.stages(); ++k) {
       launches += stage_launches(L, k, true) + stage_launches(L, k, false);
-      bytes += stage_bytes(L, k, true, vs) + stage_bytes(L, k, false, vs);
+      bytes += stage_bytes(L, k, true, vs, 1) + stage_bytes(L, k, false, vs, 1) +
+               2.0 * double(L.gs_blocks[size_t(k)]) * (L.bs * L.bs * vs + 4.0);
     }
   }
   return launches * 3.5e-6 + bytes / 4.5e12;
@@ -1616,8 +1550,7 @@ eamg_status eamg_autotune(eamg_hierarchy *h, int32_t panel_width, void *stream, 
         L.Am.group = g;
         L.Am.group_bwd = 0;
         L.group_resid = 0;
-        L.gs_f.assign(L.gs_f.size(), g);
-        L.gs_b.assign(L.gs_b.size(), g);
+        L.gs_team.assign(L.gs_team.size(), g);
         continue;
       }
       // forward sweep, residual update and backward sweep: lanes per row chosen apart
@@ -1997,7 +1930,7 @@ eamg_status eamg_traffic_model(const eamg_hierarchy *h, int32_t precision, doubl
       }
       const double vs = f32 ? 4.0 : 8.0;
       const int bs = L.bs;
-      for (int k = 0; k < L.stages(); ++k) v += stage_bytes(L, k, true, vs) + stage_bytes(L, k, false, vs);
+      for (int k = 0; k < L.stages(); ++k) v += stage_bytes(L, k, true, vs, 1) + stage_bytes(L, k, false, vs, 1);
       v += launch_bytes(L.sh_resid, LK_RESID, bs, bs, vs, 1) +
            launch_bytes(L.sh_R, LK_RECT, L.kc, bs, vs, 1) +
            launch_bytes(L.sh_P, LK_RECT_ACC, bs, L.kc, vs, 1);

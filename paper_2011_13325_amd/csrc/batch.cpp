@@ -118,16 +118,14 @@ bool panel_group(const Level &L, int k, bool fwd, int K, double vs) {
   const double block = L.bs * L.bs * vs / 3e12 + L.bs * K * vs / 8e12;
   const double colours = L.cut[size_t(k) + 1] - L.cut[size_t(k)];
   const double launches = fwd && k == 0 ? 1.0 : 2.0;
-  return launches * launch + (fwd ? L.sh_sf : L.sh_sb)[size_t(k)].blocks * block < colours * launch;
+  return launches * launch + double(L.gs_blocks[size_t(k)]) * block < colours * launch;
 }
 
 // The group matrix of stage k with its row team: a workgroup per row where its sub-teams find a block
 // each in an average row.
 SolveMat panel_smat(const Level &L, int k, bool fwd) {
   SolveMat S = fwd ? L.Sf : L.Sb;
-  const LaunchShape &sh = (fwd ? L.sh_sf : L.sh_sb)[size_t(k)];
-  S.n_rows = L.Sf.n_rows;
-  S.panel_waves = sh.blocks >= 16.0 * sh.rows ? 4 : 1;
+  S.panel_waves = double(L.gs_blocks[size_t(k)]) >= 16.0 * (L.row1(k) - L.row0(k)) ? 4 : 1;
   return S;
 }
 
@@ -184,33 +182,12 @@ void pvcycle_t(eamg_hierarchy *h, BatchWork *w, size_t l, const T *b, T *x, hipS
   const int bs = L.bs;
   const T *Dinv = bufs<T>(L).Dinv;
   T *R = vp<T>(w->vr[pi][l]), *U = vp<T>(w->vu[pi][l]);
-  double fwd_bytes = 0.0, bwd_bytes = 0.0;
-  int fwd_n = 0, bwd_n = 0;
-  for (int k = 0; k < L.stages(); ++k) {
-    if (panel_group(L, k, true, K, vs)) {
-      fwd_bytes += (k > 0 ? launch_bytes(L.sh_rf[k], LK_RESID, bs, bs, vs, K) : 0.0) +
-                   launch_bytes(L.sh_sf[k], LK_GS_FWD, bs, bs, vs, K);
-      fwd_n += k > 0 ? 2 : 1;
-    } else {
-      for (int c = L.cut[k]; c < L.cut[k + 1]; ++c) fwd_bytes += launch_bytes(L.sh_fwd[c], LK_GS_FWD, bs, bs, vs, K);
-      fwd_n += L.cut[k + 1] - L.cut[k];
-    }
-    if (panel_group(L, k, false, K, vs)) {
-      bwd_bytes += launch_bytes(L.sh_rb[k], LK_RESID, bs, bs, vs, K) + launch_bytes(L.sh_sb[k], LK_GS_BWD, bs, bs, vs, K);
-      bwd_n += 2;
-    } else {
-      for (int c = L.cut[k]; c < L.cut[k + 1]; ++c) bwd_bytes += launch_bytes(L.sh_bwd[c], LK_GS_BWD, bs, bs, vs, K);
-      bwd_n += L.cut[k + 1] - L.cut[k];
-    }
-  }
-  const std::string gs = "k_pgs_color<" + ty + ", " + std::to_string(bs);
-  timed_n(h, "pgs_fwd", lvname(h, l, gs + ", true>"), fwd_bytes, fwd_n, s, [&] {
-    for (int k = 0; k < L.stages(); ++k) {
-      const hipError_t e = pfwd_stage<T>(L, L.Am, Dinv, k, K, b, x, R, U, s);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  });
+  const auto run = [&](bool fwd, auto &&stage) {
+    const auto grouped = [&](int k) { return panel_group(L, k, fwd, K, vs); };
+    const auto launches = [&](int k) { return !grouped(k) ? L.cut[size_t(k) + 1] - L.cut[size_t(k)] : fwd && k == 0 ? 1 : 2; };
+    sweep<T>(h, l, fwd, "k_pgs_color", K, false, grouped, launches, stage, s);
+  };
+  run(true, [&](int k) { return pfwd_stage<T>(L, L.Am, Dinv, k, K, b, x, R, U, s); });
   timed(h, "presid_upper", lvname(h, l, "k_presid_upper<" + ty + ", " + std::to_string(bs) + ">"),
         launch_bytes(L.sh_resid, LK_RESID, bs, bs, vs, K), s,
         [&] { return launch_presid_upper<T>(L.panel_mat(L.pw_resid), K, x, R, s); });
@@ -224,13 +201,7 @@ void pvcycle_t(eamg_hierarchy *h, BatchWork *w, size_t l, const T *b, T *x, hipS
         launch_bytes(L.sh_P, LK_RECT_ACC, bs, L.kc, vs, K), s,
         [&] { return launch_prect<T>(L.Pm, K, Cx, x, true, s); });
   const SolveMat Mb = L.panel_mat(L.pw_bwd);
-  timed_n(h, "pgs_bwd", lvname(h, l, gs + ", false>"), bwd_bytes, bwd_n, s, [&] {
-    for (int k = L.stages() - 1; k >= 0; --k) {
-      const hipError_t e = pbwd_stage<T>(L, Mb, Dinv, k, K, b, x, U, s);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  });
+  run(false, [&](int k) { return pbwd_stage<T>(L, Mb, Dinv, k, K, b, x, U, s); });
 }
 
 // The level-0 panels of the FP32 V-cycle: R's FP32 copy (written with R), and Z.

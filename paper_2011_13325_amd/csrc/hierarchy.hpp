@@ -166,8 +166,8 @@ struct Level {
   const int *lo_end = nullptr;
   double *u = nullptr;
   float *u32 = nullptr;
-  std::vector<int> gs_f, gs_b;               // per stage: lanes per row of S
-  std::vector<LaunchShape> sh_rf, sh_rb, sh_sf, sh_sb;   // per stage: group launches
+  std::vector<int> gs_team;                  // per stage: lanes per row of S
+  std::vector<int64_t> gs_blocks;            // per stage: blocks of S
   int stages() const { return cut.empty() ? 0 : int(cut.size()) - 1; }
   bool is_group(int k) const { return cut[size_t(k) + 1] > cut[size_t(k)] + 1; }
   int row0(int k) const { return color_ptr[size_t(cut[size_t(k)])]; }
@@ -395,6 +395,51 @@ void timed(eamg_hierarchy *h, const char *what, const std::string &name, double 
 // Profiler name of a V-cycle launch on level l.
 inline std::string lvname(const eamg_hierarchy *h, size_t l, const std::string &name) {
   return h->prof_levels ? "L" + std::to_string(l) + " " + name : name;
+}
+
+// Algorithmic bytes of stage k of a sweep (values of vs bytes, K right-hand sides): what its colours need,
+// also where they run as a group, whose S is the plan's choice.
+inline double stage_bytes(const Level &L, int k, bool fwd, double vs, int K) {
+  double bytes = 0.0;
+  for (int c = L.cut[size_t(k)]; c < L.cut[size_t(k) + 1]; ++c)
+    bytes += launch_bytes((fwd ? L.sh_fwd : L.sh_bwd)[size_t(c)], fwd ? LK_GS_FWD : LK_GS_BWD, L.bs, L.bs, vs, K);
+  return bytes;
+}
+
+// One sweep of level l: stage(k) enqueues stage k, launches(k) launches; grouped(k) says whether they are a
+// group's.  While profiling, a record for every run of colours and for every run of groups (name + "
+// grouped"): events around every launch would add their own dispatch to it.  each: one per stage.
+template <class T, class G, class N, class F>
+void sweep(eamg_hierarchy *h, size_t l, bool fwd, const char *kernel, int K, bool each, G &&grouped,
+           N &&launches, F &&stage, hipStream_t s) {
+  const Level &L = h->lv[l];
+  const int ns = L.stages();
+  const auto at = [&](int t) { return fwd ? t : ns - 1 - t; };
+  const auto run = [&](int t0, int t1) {
+    hipError_t e = hipSuccess;
+    for (int t = t0; t < t1 && e == hipSuccess; ++t) e = stage(at(t));
+    return e;
+  };
+  if (!h->prof_on) {
+    hip_check(run(0, ns), kernel);
+    return;
+  }
+  for (int t0 = 0, t1; t0 < ns; t0 = t1) {
+    const bool group = grouped(at(t0));
+    double bytes = 0.0;
+    int n = 0;
+    for (t1 = t0; t1 < ns && grouped(at(t1)) == group && (t1 == t0 || !each); ++t1) {
+      bytes += stage_bytes(L, at(t1), fwd, sizeof(T), K);
+      n += launches(at(t1));
+    }
+    std::string name = std::string(kernel) + "<" + type_name<T>() + ", " + std::to_string(L.bs) +
+                       (fwd ? ", true>" : ", false>") + (group ? " grouped" : "");
+    if (each) {
+      const int c0 = L.cut[size_t(at(t0))], c1 = L.cut[size_t(at(t0)) + 1] - 1;
+      name = "c" + std::to_string(c0) + (group ? "-" + std::to_string(c1) : "") + " " + name;
+    }
+    timed_n(h, kernel, lvname(h, l, name), bytes, n, s, [&] { return run(t0, t1); });
+  }
 }
 
 inline std::string tname(const char *base, int a) { return std::string(base) + "<" + std::to_string(a) + ">"; }
