@@ -349,18 +349,13 @@ void level_shapes(Level &L, const Pattern &Ap, const std::vector<int> &dg) {
   }, 1);
 }
 
-void build_sweep_stages(DevArena &ar, Level &L, const Pattern &Ap, const std::vector<int> &dg, bool f32,
-                        hipStream_t s) {
-  PhaseTimer tp;
-  const SweepPlan pl = plan_sweeps(Ap, dg, L.color_ptr, L.ncolors, L.bs);
-  tp.mark("layout: sweep plan");
+void build_sweep_stages(DevArena &ar, Level &L, const SweepStages &st, bool f32, hipStream_t s) {
+  const SweepPlan &pl = st.plan;
   const int ns = int(pl.cut.size()) - 1, bs = L.bs;
   L.cut = pl.cut;
   L.gs_blocks.assign(size_t(ns), 0);
   L.gs_team.assign(size_t(ns), 0);
   if (!pl.grouped()) return;
-  std::vector<int64_t> unused;
-  const Pattern Sb = transpose_pattern(pl.S, unused);
   // Lanes per row of each group's S (S^T has the same blocks in the group's rows).  Blocks past the team
   // are a second dependent load, and a group's rows differ in length (its first colour has none, its
   // last the most), so rows of 3x3 and 6x6 blocks get a team for twice the average; of scalars the
@@ -374,51 +369,41 @@ void build_sweep_stages(DevArena &ar, Level &L, const Pattern &Ap, const std::ve
     L.gs_blocks[size_t(k)] = blocks;
     L.gs_team[size_t(k)] = want > kWideRowBlocks * rows ? kBlock : std::max(8, pick_group(int64_t(want), rows));
   }
-  // positions of the rows' couplings inside their groups, in the whole matrix and in its lower part
-  std::vector<int> right(size_t(L.n)), lo_end(size_t(L.n));
-  int64_t lo = 0;
-  for (int i = 0; i < L.n; ++i) {
-    right[size_t(i)] = dg[size_t(i)] + 1;
-    lo_end[size_t(i)] = int(lo + (pl.pre[size_t(i)] - Ap.rp[size_t(i)]));
-    lo += dg[size_t(i)] - Ap.rp[size_t(i)];
-  }
-  L.lo_end = ar.upload(lo_end, s);
-  int *pre_d = ar.upload(pl.pre, s), *post_d = ar.upload(pl.post, s), *right_d = ar.upload(right, s);
-  std::vector<int> order, rank_ptr(size_t(pl.max_rank) + 2, 0);
-  for (int r : pl.rank)
-    if (r >= 0) ++rank_ptr[size_t(r) + 1];
-  for (int r = 0; r <= pl.max_rank; ++r) rank_ptr[size_t(r) + 1] += rank_ptr[size_t(r)];
-  order.resize(size_t(rank_ptr.back()));
-  std::vector<int> fill(rank_ptr.begin(), rank_ptr.end() - 1);
-  for (int i = 0; i < L.n; ++i)
-    if (pl.rank[size_t(i)] >= 0) order[size_t(fill[size_t(pl.rank[size_t(i)])]++)] = i;
-  int *order_d = ar.upload(order, s);
-  auto matrix = [&](const Pattern &P, bool fwd) {
+  L.lo_end = ar.upload(st.lo_end, s);
+  int *pre_d = ar.upload(pl.pre, s), *post_d = ar.upload(pl.post, s), *right_d = ar.upload(st.right, s);
+  int *order_d = ar.upload(st.order, s);
+  int64_t longest = 0;
+  auto matrix = [&](const Pattern &P, double *&v) {
     SolveMat M;
     M.n_rows = M.n_cols = L.n;
     M.br = M.bc = bs;
     M.nnz = P.nnz();
     M.rp = ar.upload(to_i32(P.rp), s);
     M.col = ar.upload(P.col, s);
-    double *v = ar.alloc<double>(size_t(M.nnz) * bs * bs);
-    // the rows of a rank need those of every rank nearer their group's first (last) colour
-    for (int t = 0; t <= pl.max_rank; ++t) {
-      const int r = fwd ? t : pl.max_rank - t;
-      hip_check(launch_group_fill(rank_ptr[size_t(r) + 1] - rank_ptr[size_t(r)], order_d + rank_ptr[size_t(r)], bs,
-                                  fwd ? pre_d : right_d, fwd ? L.Am.diag : post_d, L.Am.col, L.Am.val,
-                                  L.Dinv, M.rp, M.col, v, s),
-                "group fill");
-    }
-    M.val = v;
-    if (f32) {
-      float *v32 = ar.alloc<float>(size_t(M.nnz) * bs * bs);
-      hip_check(launch_convert<double, float>(M.nnz * bs * bs, v, v32, s), "convert");
-      M.val32 = v32;
-    }
+    M.val = v = ar.alloc<double>(size_t(M.nnz) * bs * bs);
+    for (int i = 0; i < L.n; ++i) longest = std::max(longest, P.rp[size_t(i) + 1] - P.rp[size_t(i)]);
     return M;
   };
-  L.Sf = matrix(pl.S, true);
-  L.Sb = matrix(Sb, false);
+  double *vf = nullptr, *vb = nullptr;
+  L.Sf = matrix(pl.S, vf);
+  L.Sb = matrix(st.Sb, vb);
+  // the rows of a rank need those of every rank nearer their group's first (last) colour
+  for (int t = 0; t <= pl.max_rank; ++t) {
+    const auto rank = [&](int r, const SolveMat &M, const int *q0, const int *q1, double *v) {
+      const int a = st.rank_ptr[size_t(r)];
+      return GroupRank{order_d + a, st.rank_ptr[size_t(r) + 1] - a, q0, q1, M.rp, M.col, v};
+    };
+    hip_check(launch_group_fill(rank(t, L.Sf, pre_d, L.Am.diag, vf),
+                                rank(pl.max_rank - t, L.Sb, right_d, post_d, vb), int(longest), bs, L.Am.col,
+                                L.Am.val, L.Dinv, s),
+              "group fill");
+  }
+  if (f32)
+    for (SolveMat *M : {&L.Sf, &L.Sb}) {
+      float *v32 = ar.alloc<float>(size_t(M->nnz) * bs * bs);
+      hip_check(launch_convert<double, float>(M->nnz * bs * bs, M->val, v32, s), "convert");
+      M->val32 = v32;
+    }
   L.u = ar.alloc<double>(size_t(L.n) * bs);
   if (f32) L.u32 = ar.alloc<float>(size_t(L.n) * bs);
   hip_check(hipStreamSynchronize(s), "sync");
@@ -430,44 +415,46 @@ namespace {
 static_assert(std::is_nothrow_move_constructible<Level>::value,
               "levels must move without copying their patterns");
 
+// Whether level l, of `dofs`, is small enough for the dense V-cycle tail: if it is, so are all below it.
+bool tail_sized(const eamg_setup_params &prm, size_t l, int64_t dofs) {
+  return prm.dense_tail_dofs > 0 && l >= 1 && dofs <= prm.dense_tail_dofs;
+}
 // Level the dense V-cycle tail starts on, 0 if there is none.
 size_t tail_start(const eamg_hierarchy *h) {
-  if (h->prm.dense_tail_dofs > 0)
-    for (size_t l = 1; l + 1 < h->lv.size(); ++l)
-      if (int64_t(h->lv[l].n) * h->lv[l].bs <= h->prm.dense_tail_dofs) return l;
+  for (size_t l = 1; l + 1 < h->lv.size(); ++l)
+    if (tail_sized(h->prm, l, int64_t(h->lv[l].n) * h->lv[l].bs)) return l;
   return 0;
 }
 
-void build_level_layout(eamg_hierarchy *h, size_t l, hipStream_t s) {
+// c: the level's colouring and what follows from it (not read on the coarsest level; its pattern is
+// taken over).
+void build_level_layout(eamg_hierarchy *h, size_t l, Smoothing &c, hipStream_t s) {
   Level &L = h->lv[l];
   DevArena &ar = h->arena;
   const bool coarsest = (l + 1 == h->lv.size());
   const int bs = L.bs;
+  PhaseTimer tl;
   // colour-major numbering (identity on the coarsest level, which has no smoother)
-  L.perm.resize(size_t(L.n));
-  L.inv.resize(size_t(L.n));
+  std::vector<int64_t> src;
+  Pattern Ap;
   if (coarsest) {
+    L.perm.resize(size_t(L.n));
+    L.inv.resize(size_t(L.n));
     for (int i = 0; i < L.n; ++i) L.perm[i] = L.inv[i] = i;
     L.ncolors = 0;
     L.color.assign(size_t(L.n), -1);
     L.color_ptr = {0, L.n};
+    Ap = permute_pattern(L.A, L.perm, L.inv, src);
   } else {
-    if (L.color.size() != size_t(L.n)) {
-      PhaseTimer tc;
-      L.color = greedy_coloring(L.A, L.ncolors);
-      tc.mark("layout: colouring");
-    }
-    L.color_ptr.assign(size_t(L.ncolors) + 1, 0);
-    for (int c : L.color) L.color_ptr[c + 1]++;
-    for (int c = 0; c < L.ncolors; ++c) L.color_ptr[c + 1] += L.color_ptr[c];
-    std::vector<int> fill(L.color_ptr.begin(), L.color_ptr.end() - 1);
-    for (int i = 0; i < L.n; ++i) L.perm[fill[L.color[i]]++] = i;
-    for (int r = 0; r < L.n; ++r) L.inv[L.perm[r]] = r;
+    L.color = std::move(c.color);
+    L.ncolors = c.ncolors;
+    L.color_ptr = std::move(c.order.ptr);
+    L.perm = std::move(c.order.perm);
+    L.inv = std::move(c.order.inv);
+    Ap = std::move(c.Ap);
+    src = std::move(c.src);
   }
-  PhaseTimer tl;
   L.perm_d = ar.upload(L.perm, s);
-  std::vector<int64_t> src;
-  const Pattern Ap = permute_pattern(L.A, L.perm, L.inv, src);
   tl.mark("layout: permute");
   std::vector<int> dg;
   const bool f32 = h->prm.vcycle_fp32 != 0;
@@ -504,9 +491,8 @@ void build_level_layout(eamg_hierarchy *h, size_t l, hipStream_t s) {
   }
   hip_check(hipStreamSynchronize(s), "sync");
   ar.release(Dn);
-  // no sweeps below the dense tail's first level
-  const size_t t = tail_start(h);
-  if (t == 0 || l < t) build_sweep_stages(ar, L, Ap, dg, f32, s);
+  // no sweeps on and below the dense tail's first level
+  if (!c.stages.plan.cut.empty()) build_sweep_stages(ar, L, c.stages, f32, s);
   tl.mark("layout: sweep stages");
   // transfers: fine rows colour-major, coarse columns in the coarse level's colour-major order
   const Level &C = h->lv[l + 1];
@@ -1263,27 +1249,19 @@ eamg_status eamg_setup(const eamg_problem *pb, const eamg_setup_params *params, 
         gnn_logits(net, dg, s, z);
       };
     }
-    // The smoother's colouring of a level depends on its pattern only: it runs on a thread of its
-    // own beside the matching of that level and of the levels below.  The thread reads the
-    // pattern's buffers, which stay in place while the levels move (nothrow moves).
-    struct Colouring {
-      std::vector<int> color;
-      int ncolors = 0;
-    };
-    std::vector<std::future<Colouring>> colourings;
+    // The smoother's colouring of a level and the stages of its sweeps depend on its pattern only:
+    // they are found on a thread of their own beside the matching of that level and of the levels
+    // below.  The thread reads the level's pattern, which stays in place.
+    h->lv.reserve(size_t(prm.max_levels));
+    std::vector<std::future<Smoothing>> smoothing;
     while (true) {
       const size_t l = h->lv.size() - 1;
       {
         const Level &L = h->lv[l];
         if (int64_t(L.bs) * L.n < prm.coarsest_max_dofs || int(h->lv.size()) >= prm.max_levels) break;
-        const int nr = L.A.n_rows;
-        const int64_t *rp = L.A.rp.data();
-        const int *cl = L.A.col.data();
-        colourings.push_back(std::async(std::launch::async, [nr, rp, cl] {
-          Colouring c;
-          c.color = greedy_coloring(nr, rp, cl, c.ncolors);
-          return c;
-        }));
+        const bool sweeps = !tail_sized(prm, l, int64_t(L.bs) * L.n);
+        smoothing.push_back(std::async(std::launch::async,
+                                       [&A = L.A, bs = L.bs, sweeps] { return plan_smoothing(A, bs, sweeps); }));
       }
       tm.mark("setup: level upload");
       MatchResult mr = successive_matching(aux, l == 0 ? vd : std::vector<char>(), mp);
@@ -1380,13 +1358,13 @@ eamg_status eamg_setup(const eamg_problem *pb, const eamg_setup_params *params, 
     }
     coarsest_factor(h.get(), s);
     tm.mark("setup: coarsest factor");
-    for (size_t l = 0; l < colourings.size(); ++l) {
-      Colouring c = colourings[l].get();
-      h->lv[l].color = std::move(c.color);
-      h->lv[l].ncolors = c.ncolors;
-    }
+    std::vector<Smoothing> smooth(h->lv.size());
+    for (size_t l = 0; l < smoothing.size(); ++l) smooth[l] = smoothing[l].get();
     tm.mark("setup: colouring (wait)");
-    for (size_t l = h->lv.size(); l-- > 0;) build_level_layout(h.get(), l, s);
+    for (size_t l = h->lv.size(); l-- > 0;) {
+      build_level_layout(h.get(), l, smooth[l], s);
+      smooth[l] = Smoothing();
+    }
     tm.mark("setup: solve layout");
     if (prm.dense_tail_dofs > 0) {
       if (const size_t t = tail_start(h.get())) build_dense_tail(h.get(), t, s);

@@ -17,6 +17,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <future>
 #include <memory>
 #include <string>
 #include <vector>
@@ -162,7 +163,9 @@ void build_fused_level(eamg_hierarchy *F, const std::vector<eamg_hierarchy *> &h
   const Pattern Ap = permute_pattern(Acat, perm, inv, src);
   std::vector<int> dg;
   L.Am = make_solve_mat(ar, Ap, src, bs, bs, vcat, s, &dg, false, f32);
+  std::future<SweepStages> sweeps;   // beside the rest of the level's layout
   if (o.n_smooth > 0) {
+    sweeps = std::async(std::launch::async, [&] { return prepare_sweeps(Ap, dg, L.color_ptr, L.ncolors, bs); });
     attach_split_parts(ar, Ap, src, dg, bs, vcat, s, f32, L.Am);
     level_shapes(L, Ap, dg);
   } else {
@@ -194,7 +197,7 @@ void build_fused_level(eamg_hierarchy *F, const std::vector<eamg_hierarchy *> &h
       L.Dinv32 = ar.alloc<float>(size_t(o.n_smooth) * bs * bs);
       hip_check(launch_convert(int64_t(o.n_smooth) * bs * bs, L.Dinv, L.Dinv32, s), "convert");
     }
-    build_sweep_stages(ar, L, Ap, dg, f32, s);
+    build_sweep_stages(ar, L, sweeps.get(), f32, s);
     // transfers: P of the smoothed systems, rows in the fused order of level l, columns in the
     // fused order of level l + 1
     const FusedOrder &oc = ord[size_t(l) + 1];

@@ -263,10 +263,9 @@ LaunchShape range_shape(const Pattern &Ap, const std::vector<int> &dg, int r0, i
 LaunchShape matrix_shape(const Pattern &M);
 // Launch shapes of a smoothed level (colours, residual update over smooth_rows(), SpMV).
 void level_shapes(Level &L, const Pattern &Ap, const std::vector<int> &dg);
-// Sweep stages of a smoothed level whose matrix and D^+ are in place (Ap, dg: its colour-major pattern
-// and diagonal positions): the plan, the group matrices and u.
-void build_sweep_stages(DevArena &ar, Level &L, const Pattern &Ap, const std::vector<int> &dg, bool f32,
-                        hipStream_t s);
+// Sweep stages of a smoothed level whose matrix and D^+ are in place: the plan taken over, the group
+// matrices and u built.
+void build_sweep_stages(DevArena &ar, Level &L, const SweepStages &st, bool f32, hipStream_t s);
 // z = V(r) on level-0 vectors in the hierarchy's solve numbering (FP64, or the FP32 V-cycle
 // with conversions at the boundary).
 void vcycle_apply(eamg_hierarchy *h, const double *r, double *z, bool f32, hipStream_t s);

@@ -632,61 +632,89 @@ __global__ __launch_bounds__(kBlock) void k_gs_group(int r0, int r1, int G, cons
   }
 }
 
-// One row of S per workgroup (launch_group_fill); thread e owns entry e, e + 256, ... of the row.
-// The products A_q Dinv_j of kFillChunk couplings at a time sit in LDS.  Setup only.
-constexpr int kFillChunk = 32;
+// 256 entries of a row of S per workgroup (launch_group_fill), one per thread.  The products A_q Dinv_j of
+// FillSize::chunk couplings at a time sit in LDS.  Setup only.  Bound: the chain of ranks, each waiting for the
+// one before, and in it the searches of S_jk's position in row j, dependent loads through L2; FillSize::ahead
+// couplings are searched for at once, the forward and the backward matrix fill beside each other, and a
+// row's entries are shared out over workgroups.  A scalar level of 895 rows in one group of 59 colours
+// (S of 361,684 entries) took 38 ms with one workgroup a row, one search after the other and the
+// matrices in turn, 6 ms now (the level's stages with uploads and allocations).
 template <int B>
-__global__ __launch_bounds__(kBlock) void k_group_fill(const int *__restrict__ rows,
-                                                      const int *__restrict__ q0,
-                                                      const int *__restrict__ q1,
-                                                      const int *__restrict__ col,
+struct FillSize {
+  static constexpr int chunk = B == 1 ? 256 : B == 3 ? 64 : 32, ahead = B == 6 ? 4 : 8;
+};
+template <int B>
+__global__ __launch_bounds__(kBlock) void k_group_fill(GroupRank fwd, GroupRank bwd, const int *__restrict__ col,
                                                       const double *__restrict__ val,
-                                                      const double *__restrict__ Dinv,
-                                                      const int *__restrict__ Srp,
-                                                      const int *__restrict__ Scol, double *Sval) {
-  constexpr int BB = B * B;
-  __shared__ double P[kFillChunk * BB];
-  __shared__ int J[kFillChunk];
-  const int i = rows[blockIdx.x];
-  const int a = q0[i], b = q1[i], s0 = Srp[i], s1 = Srp[i + 1];
-  for (int e0 = s0; e0 < s1; e0 += kBlock) {
-    const int e = e0 + int(threadIdx.x);
-    const int k = e < s1 ? Scol[e] : -1;
-    double acc[BB];
+                                                      const double *__restrict__ Dinv) {
+  constexpr int BB = B * B, kChunk = FillSize<B>::chunk, kAhead = FillSize<B>::ahead;
+  static_assert(kChunk % kAhead == 0, "a batch stays inside a chunk");
+  __shared__ double P[kChunk * BB];
+  __shared__ int J[kChunk], J0[kChunk], J1[kChunk];
+  const GroupRank g = blockIdx.z ? bwd : fwd;
+  if (int(blockIdx.x) >= g.nrows) return;
+  const int i = g.rows[blockIdx.x];
+  const int s0 = g.rp[i] + int(blockIdx.y) * kBlock, s1 = g.rp[i + 1];
+  if (s0 >= s1) return;
+  const int a = g.q0[i], b = g.q1[i];
+  const int e = s0 + int(threadIdx.x);
+  const int k = e < s1 ? g.col[e] : -1;
+  double acc[BB];
 #pragma unroll
-    for (int v = 0; v < BB; ++v) acc[v] = 0.0;
-    for (int qa = a; qa < b; qa += kFillChunk) {
-      const int m = min(kFillChunk, b - qa);
-      __syncthreads();
-      for (int t = threadIdx.x; t < m * BB; t += kBlock) {
-        const int q = t / BB, r = (t % BB) / B, c = t % B;
-        const int j = col[qa + q];
-        double v = 0.0;
-        for (int l = 0; l < B; ++l) v = fma(val[int64_t(qa + q) * BB + r * B + l], Dinv[int64_t(j) * BB + l * B + c], v);
-        P[t] = v;
-        if (r == 0 && c == 0) J[q] = j;
+  for (int v = 0; v < BB; ++v) acc[v] = 0.0;
+  for (int qa = a; qa < b; qa += kChunk) {
+    const int m = min(kChunk, b - qa);
+    __syncthreads();
+    for (int t = threadIdx.x; t < m * BB; t += kBlock) {
+      const int q = t / BB, r = (t % BB) / B, c = t % B;
+      const int j = col[qa + q];
+      double v = 0.0;
+#pragma unroll
+      for (int l = 0; l < B; ++l) v = fma(val[int64_t(qa + q) * BB + r * B + l], Dinv[int64_t(j) * BB + l * B + c], v);
+      P[t] = v;
+      if (r == 0 && c == 0) {
+        J[q] = j;
+        J0[q] = g.rp[j];
+        J1[q] = g.rp[j + 1];
       }
-      __syncthreads();
+    }
+    __syncthreads();
+    for (int qb = 0; qb < m; qb += kAhead) {
+      // lo[u]: the first entry of row j at a column >= k
+      int lo[kAhead], hi[kAhead], longest = 0;
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int q = min(qb + u, m - 1);
+        lo[u] = J0[q];
+        hi[u] = J1[q];
+        longest = max(longest, hi[u] - lo[u]);
+      }
+      for (; longest > 0; longest >>= 1)
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          const int mid = (lo[u] + hi[u]) >> 1;
+          const bool in = lo[u] < hi[u];
+          const bool less = g.col[in ? mid : s0] < k;
+          hi[u] = in && !less ? mid : hi[u];
+          lo[u] = in && less ? mid + 1 : lo[u];
+        }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int q = min(qb + u, m - 1), at = lo[u];
+        hi[u] = at < J1[q] && g.col[at < J1[q] ? at : s0] == k ? at : -1;
+      }
       if (k < 0) continue;
-      for (int q = 0; q < m; ++q) {
-        const int j = J[q];
-        const double *Pq = P + q * BB;
-        if (j == k) {
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        if (qb + u >= m) break;
+        const double *Pq = P + (qb + u) * BB;
+        if (J[qb + u] == k) {
 #pragma unroll
           for (int v = 0; v < BB; ++v) acc[v] += Pq[v];
           continue;
         }
-        int lo = Srp[j], hi = Srp[j + 1];
-        const int end = hi;
-        while (lo < hi) {
-          const int mid = (lo + hi) >> 1;
-          if (Scol[mid] < k)
-            lo = mid + 1;
-          else
-            hi = mid;
-        }
-        if (lo == end || Scol[lo] != k) continue;
-        const double *Sj = Sval + int64_t(lo) * BB;
+        if (hi[u] < 0) continue;
+        const double *Sj = g.val + int64_t(hi[u]) * BB;
 #pragma unroll
         for (int l = 0; l < B; ++l) {
           double sj[B];
@@ -699,10 +727,10 @@ __global__ __launch_bounds__(kBlock) void k_group_fill(const int *__restrict__ r
         }
       }
     }
-    if (k >= 0)
-#pragma unroll
-      for (int v = 0; v < BB; ++v) Sval[int64_t(e) * BB + v] = acc[v];
   }
+  if (k >= 0)
+#pragma unroll
+    for (int v = 0; v < BB; ++v) g.val[int64_t(e) * BB + v] = acc[v];
 }
 
 template <class T, int B, int W>
@@ -1275,15 +1303,15 @@ hipError_t launch_group_bwd(const SolveMat &S, const T *Dinv, int r0, int r1, co
   return launch_group<T, false, false>(S, nullptr, Dinv, r0, r1, u, x, nullptr, nullptr, nullptr, s);
 }
 
-hipError_t launch_group_fill(int nrows, const int *rows, int bs, const int *q0, const int *q1,
-                             const int *col, const double *val, const double *Dinv, const int *Srp,
-                             const int *Scol, double *Sval, hipStream_t s) {
-  if (nrows == 0) return hipSuccess;
-  const dim3 grid(static_cast<unsigned>(nrows));
+hipError_t launch_group_fill(const GroupRank &fwd, const GroupRank &bwd, int longest, int bs, const int *col,
+                             const double *val, const double *Dinv, hipStream_t s) {
+  const int nrows = fwd.nrows > bwd.nrows ? fwd.nrows : bwd.nrows;
+  if (nrows == 0 || longest == 0) return hipSuccess;
+  const dim3 grid(static_cast<unsigned>(nrows), static_cast<unsigned>(cdiv64(longest, kBlock)), 2);
   switch (bs) {
-    case 1: hipLaunchKernelGGL(k_group_fill<1>, grid, dim3(kBlock), 0, s, rows, q0, q1, col, val, Dinv, Srp, Scol, Sval); break;
-    case 3: hipLaunchKernelGGL(k_group_fill<3>, grid, dim3(kBlock), 0, s, rows, q0, q1, col, val, Dinv, Srp, Scol, Sval); break;
-    case 6: hipLaunchKernelGGL(k_group_fill<6>, grid, dim3(kBlock), 0, s, rows, q0, q1, col, val, Dinv, Srp, Scol, Sval); break;
+    case 1: hipLaunchKernelGGL(k_group_fill<1>, grid, dim3(kBlock), 0, s, fwd, bwd, col, val, Dinv); break;
+    case 3: hipLaunchKernelGGL(k_group_fill<3>, grid, dim3(kBlock), 0, s, fwd, bwd, col, val, Dinv); break;
+    case 6: hipLaunchKernelGGL(k_group_fill<6>, grid, dim3(kBlock), 0, s, fwd, bwd, col, val, Dinv); break;
     default: return hipErrorInvalidValue;
   }
   EAMG_LAUNCH_CHECK();

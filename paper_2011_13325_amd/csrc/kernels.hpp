@@ -135,12 +135,20 @@ hipError_t launch_group_bwd(const SolveMat &S, const T *Dinv, int r0, int r1, co
 // Workgroups of a group's launch over rows [r0, r1), and with rz (launch_group_bwd) its partials of
 // the CG's r.z there: cg_r times the new x.
 int group_blocks(const SolveMat &S, int r0, int r1);
-// One rank of the group matrices, row rows[k] (k < nrows) each: its couplings inside the group
-// are the positions [q0[i], q1[i]) of A (col, val, natural FP64 blocks in the solve numbering), and
-//   S_ik = sum over those q, j = col[q], of A_q Dinv_j ([j == k] I - S_jk).
-hipError_t launch_group_fill(int nrows, const int *rows, int bs, const int *q0, const int *q1,
-                             const int *col, const double *val, const double *Dinv, const int *Srp,
-                             const int *Scol, double *Sval, hipStream_t s);
+// One rank of a group matrix, rows[0 .. nrows): row i's couplings inside the group are the positions
+// [q0[i], q1[i]) of A (col, val, FP64 blocks in the solve numbering), and
+//   S_ik = sum over those q, j = col[q], of A_q Dinv_j ([j == k] I - S_jk)
+// for the row's columns k in S (rp, col of `longest` entries at most; val is written).
+struct GroupRank {
+  const int *rows;
+  int nrows;
+  const int *q0, *q1;
+  const int *rp, *col;
+  double *val;
+};
+// A rank of the forward and one of the backward matrix.
+hipError_t launch_group_fill(const GroupRank &fwd, const GroupRank &bwd, int longest, int bs, const int *col,
+                             const double *val, const double *Dinv, hipStream_t s);
 // y = M x (rectangular, overwrite) or y += M x (accumulate = true).
 template <class T>
 hipError_t launch_rect(const SolveMat &M, const T *x, T *y, bool accumulate, hipStream_t s);

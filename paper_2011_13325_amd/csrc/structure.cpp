@@ -4,6 +4,7 @@
 #include <functional>
 #include <map>
 #include <queue>
+#include <utility>
 
 namespace eamg {
 
@@ -326,23 +327,36 @@ SweepPlan plan_sweeps(const Pattern &Ap, const std::vector<int> &dg, const std::
       const bool many = direct * (1.0 + nnz / double(a - r0)) > 3e5;
       const int chunk = many ? 32 : b - a, nch = (b - a + chunk - 1) / std::max(1, chunk);
       parallel_for_dynamic(nch, [&](int64_t ch) {
-        std::vector<char> seen(size_t(a - r0), 0);
+        std::vector<uint64_t> seen(size_t(a - r0 + 63) / 64, 0);
+        const auto visit = [&](int j) {   // whether j is new
+          uint64_t &w = seen[size_t(j - r0) >> 6];
+          const uint64_t bit = uint64_t(1) << ((j - r0) & 63);
+          const bool fresh = !(w & bit);
+          w |= bit;
+          return fresh;
+        };
         for (int i = a + int(ch) * chunk; i < std::min(b, a + int(ch + 1) * chunk); ++i) {
           std::vector<int> &R = rows[size_t(i)];
           R.clear();
-          auto add = [&](int j) {
-            if (!seen[size_t(j - r0)]) {
-              seen[size_t(j - r0)] = 1;
-              R.push_back(j);
-            }
-          };
-          for (int q = first_at(i, r0); q < dg[size_t(i)]; ++q) {
+          // the rows' sets are closed under their chains: those of a row already reached are in,
+          // and the later colours, first here, reach the most
+          for (int q = dg[size_t(i)] - 1, q0 = first_at(i, r0); q >= q0; --q) {
             const int j = Ap.col[size_t(q)];
-            add(j);
-            for (int k : rows[size_t(j)]) add(k);
+            if (!visit(j)) continue;
+            R.push_back(j);
+            for (int k : rows[size_t(j)])
+              if (visit(k)) R.push_back(k);
           }
-          for (int j : R) seen[size_t(j - r0)] = 0;
-          std::sort(R.begin(), R.end());
+          // ascending: from the marks, or sorted where there are few
+          if (seen.size() < 16 * R.size()) {
+            size_t m = 0;
+            for (size_t w = 0; w < seen.size(); ++w)
+              for (uint64_t v = std::exchange(seen[w], 0); v; v &= v - 1)
+                R[m++] = r0 + int(w * 64) + __builtin_ctzll(v);
+          } else {
+            for (int j : R) seen[size_t(j - r0) >> 6] = 0;
+            std::sort(R.begin(), R.end());
+          }
         }
       }, 1);
       double add = 0.0;
@@ -371,6 +385,71 @@ SweepPlan plan_sweeps(const Pattern &Ap, const std::vector<int> &dg, const std::
   for (int i = 0; i < n; ++i)
     if (pl.rank[size_t(i)] > 0) pl.S.col.insert(pl.S.col.end(), rows[size_t(i)].begin(), rows[size_t(i)].end());
   return pl;
+}
+
+ColourOrder colour_order(const std::vector<int> &color, int ncolors) {
+  ColourOrder o;
+  const size_t n = color.size();
+  o.ptr.assign(size_t(ncolors) + 1, 0);
+  for (int c : color) o.ptr[size_t(c) + 1]++;
+  for (int c = 0; c < ncolors; ++c) o.ptr[size_t(c) + 1] += o.ptr[size_t(c)];
+  o.perm.resize(n);
+  o.inv.resize(n);
+  std::vector<int> fill(o.ptr.begin(), o.ptr.end() - 1);
+  for (size_t i = 0; i < n; ++i) o.perm[size_t(fill[size_t(color[i])]++)] = int(i);
+  for (size_t r = 0; r < n; ++r) o.inv[size_t(o.perm[r])] = int(r);
+  return o;
+}
+
+SweepStages prepare_sweeps(const Pattern &Ap, const std::vector<int> &dg, const std::vector<int> &color_ptr,
+                           int ncolors, int bs) {
+  SweepStages st;
+  st.plan = plan_sweeps(Ap, dg, color_ptr, ncolors, bs);
+  const SweepPlan &pl = st.plan;
+  if (!pl.grouped()) return st;
+  const int n = Ap.n_rows;
+  st.Sb.n_rows = st.Sb.n_cols = n;
+  st.Sb.rp.assign(size_t(n) + 1, 0);
+  for (int c : pl.S.col) ++st.Sb.rp[size_t(c) + 1];
+  for (int i = 0; i < n; ++i) st.Sb.rp[size_t(i) + 1] += st.Sb.rp[size_t(i)];
+  st.Sb.col.resize(pl.S.col.size());
+  std::vector<int64_t> next(st.Sb.rp.begin(), st.Sb.rp.end() - 1);
+  const int *col = pl.S.col.data();
+  for (int i = 0; i < n; ++i)
+    for (int64_t q = pl.S.rp[size_t(i)], q1 = pl.S.rp[size_t(i) + 1]; q < q1; ++q)
+      st.Sb.col[size_t(next[size_t(col[q])]++)] = i;
+  st.lo_end.resize(size_t(n));
+  st.right.resize(size_t(n));
+  int64_t lo = 0;
+  for (int i = 0; i < n; ++i) {
+    st.right[size_t(i)] = dg[size_t(i)] + 1;
+    st.lo_end[size_t(i)] = int(lo + (pl.pre[size_t(i)] - Ap.rp[size_t(i)]));
+    lo += dg[size_t(i)] - Ap.rp[size_t(i)];
+  }
+  st.rank_ptr.assign(size_t(pl.max_rank) + 2, 0);
+  for (int r : pl.rank)
+    if (r >= 0) ++st.rank_ptr[size_t(r) + 1];
+  for (int r = 0; r <= pl.max_rank; ++r) st.rank_ptr[size_t(r) + 1] += st.rank_ptr[size_t(r)];
+  st.order.resize(size_t(st.rank_ptr.back()));
+  std::vector<int> fill(st.rank_ptr.begin(), st.rank_ptr.end() - 1);
+  for (int i = 0; i < n; ++i)
+    if (pl.rank[size_t(i)] >= 0) st.order[size_t(fill[size_t(pl.rank[size_t(i)])]++)] = i;
+  return st;
+}
+
+Smoothing plan_smoothing(const Pattern &A, int bs, bool sweeps) {
+  Smoothing c;
+  c.color = greedy_coloring(A, c.ncolors);
+  c.order = colour_order(c.color, c.ncolors);
+  c.Ap = permute_pattern(A, c.order.perm, c.order.inv, c.src);
+  if (!sweeps) return c;
+  const Pattern &P = c.Ap;
+  std::vector<int> dg(size_t(P.n_rows));
+  for (int i = 0; i < P.n_rows; ++i)
+    dg[size_t(i)] = int(std::lower_bound(P.col.begin() + P.rp[size_t(i)], P.col.begin() + P.rp[size_t(i) + 1], i) -
+                        P.col.begin());
+  c.stages = prepare_sweeps(P, dg, c.order.ptr, c.ncolors, bs);
+  return c;
 }
 
 }  // namespace eamg

@@ -77,6 +77,37 @@ struct SweepPlan {
 SweepPlan plan_sweeps(const Pattern &Ap, const std::vector<int> &dg, const std::vector<int> &color_ptr,
                       int ncolors, int bs);
 
+// Colour-major numbering: colour c holds the rows [ptr[c], ptr[c + 1]), row r is natural row perm[r],
+// inv its inverse; ascending natural rows within a colour.
+struct ColourOrder {
+  std::vector<int> ptr, perm, inv;
+};
+ColourOrder colour_order(const std::vector<int> &color, int ncolors);
+
+// A plan and what its group matrices are built from on the device.
+struct SweepStages {
+  SweepPlan plan;
+  Pattern Sb;                     // the backward matrix's pattern
+  std::vector<int> lo_end;        // per row: end of [row start, plan.pre) among the blocks left of the diagonal
+  std::vector<int> right;         // per row: first position right of the diagonal
+  std::vector<int> order, rank_ptr;   // rows of rank r: order[rank_ptr[r]] .. order[rank_ptr[r + 1] - 1]
+};
+// Arguments as plan_sweeps.
+SweepStages prepare_sweeps(const Pattern &Ap, const std::vector<int> &dg, const std::vector<int> &color_ptr,
+                           int ncolors, int bs);
+
+// A smoothed level's colouring and what follows from it on the host.
+struct Smoothing {
+  std::vector<int> color;
+  int ncolors = 0;
+  ColourOrder order;
+  Pattern Ap;                  // colour-major pattern
+  std::vector<int64_t> src;    // its positions in the natural pattern
+  SweepStages stages;          // if asked for
+};
+// A: the level's natural pattern (structurally symmetric, with every diagonal block).
+Smoothing plan_smoothing(const Pattern &A, int bs, bool sweeps);
+
 // Rows permuted by the fine permutation, columns renumbered by the coarse one (re-sorted).
 Pattern permute_rect(const Pattern &P, const std::vector<int> &perm_rows,
                      const std::vector<int> &inv_cols, std::vector<int64_t> &src);
