@@ -349,13 +349,18 @@ void level_shapes(Level &L, const Pattern &Ap, const std::vector<int> &dg) {
   }, 1);
 }
 
-void build_sweep_stages(DevArena &ar, Level &L, const SweepStages &st, bool f32, hipStream_t s) {
+namespace {
+
+// The group matrices and u of a plan that has groups.
+void build_groups(DevArena &ar, Level &L, const SweepStages &st, bool f32, hipStream_t s) {
   const SweepPlan &pl = st.plan;
   const int ns = int(pl.cut.size()) - 1, bs = L.bs;
-  L.cut = pl.cut;
-  L.gs_blocks.assign(size_t(ns), 0);
-  L.gs_team.assign(size_t(ns), 0);
-  if (!pl.grouped()) return;
+  double left = HUGE_VAL;
+  if (const char *e = std::getenv("EAMG_GROUP_MB")) left = std::atof(e) * 1e6;
+  const auto room = [&](size_t bytes) {
+    left -= double(bytes);
+    if (left < 0.0) fail(EAMG_ERR_OOM, "sweep groups: out of device memory");
+  };
   // Lanes per row of each group's S (S^T has the same blocks in the group's rows).  Blocks past the team
   // are a second dependent load, and a group's rows differ in length (its first colour has none, its
   // last the most), so rows of 3x3 and 6x6 blocks get a team for twice the average; of scalars the
@@ -380,6 +385,7 @@ void build_sweep_stages(DevArena &ar, Level &L, const SweepStages &st, bool f32,
     M.nnz = P.nnz();
     M.rp = ar.upload(to_i32(P.rp), s);
     M.col = ar.upload(P.col, s);
+    room(size_t(M.nnz) * bs * bs * sizeof(double));
     M.val = v = ar.alloc<double>(size_t(M.nnz) * bs * bs);
     for (int i = 0; i < L.n; ++i) longest = std::max(longest, P.rp[size_t(i) + 1] - P.rp[size_t(i)]);
     return M;
@@ -400,6 +406,7 @@ void build_sweep_stages(DevArena &ar, Level &L, const SweepStages &st, bool f32,
   }
   if (f32)
     for (SolveMat *M : {&L.Sf, &L.Sb}) {
+      room(size_t(M->nnz) * bs * bs * sizeof(float));
       float *v32 = ar.alloc<float>(size_t(M->nnz) * bs * bs);
       hip_check(launch_convert<double, float>(M->nnz * bs * bs, M->val, v32, s), "convert");
       M->val32 = v32;
@@ -408,6 +415,34 @@ void build_sweep_stages(DevArena &ar, Level &L, const SweepStages &st, bool f32,
   if (f32) L.u32 = ar.alloc<float>(size_t(L.n) * bs);
   hip_check(hipStreamSynchronize(s), "sync");
   for (int *p : {pre_d, post_d, right_d, order_d}) ar.release(p);
+}
+
+}  // namespace
+
+void build_sweep_stages(DevArena &ar, Level &L, const SweepStages &st, bool f32, hipStream_t s) {
+  const auto plain = [&L](int stages) {
+    L.gs_blocks.assign(size_t(stages), 0);
+    L.gs_team.assign(size_t(stages), 0);
+    L.Sf = L.Sb = SolveMat();
+    L.lo_end = nullptr;
+    L.u = nullptr;
+    L.u32 = nullptr;
+  };
+  L.cut = st.plan.cut;
+  plain(L.stages());
+  if (!st.plan.grouped()) return;
+  DevArena own;
+  try {
+    build_groups(own, L, st, f32, s);
+    ar.adopt(own);
+  } catch (const Failure &e) {
+    if (e.code != EAMG_ERR_OOM) throw;
+    (void)hipGetLastError();
+    hip_check(hipStreamSynchronize(s), "sync");   // launches that read `own`
+    L.cut.resize(size_t(L.ncolors) + 1);
+    for (int c = 0; c <= L.ncolors; ++c) L.cut[size_t(c)] = c;
+    plain(L.ncolors);
+  }
 }
 
 namespace {
@@ -491,9 +526,6 @@ void build_level_layout(eamg_hierarchy *h, size_t l, Smoothing &c, hipStream_t s
   }
   hip_check(hipStreamSynchronize(s), "sync");
   ar.release(Dn);
-  // no sweeps on and below the dense tail's first level
-  if (!c.stages.plan.cut.empty()) build_sweep_stages(ar, L, c.stages, f32, s);
-  tl.mark("layout: sweep stages");
   // transfers: fine rows colour-major, coarse columns in the coarse level's colour-major order
   const Level &C = h->lv[l + 1];
   std::vector<int64_t> srcP;
@@ -1361,10 +1393,7 @@ eamg_status eamg_setup(const eamg_problem *pb, const eamg_setup_params *params, 
     std::vector<Smoothing> smooth(h->lv.size());
     for (size_t l = 0; l < smoothing.size(); ++l) smooth[l] = smoothing[l].get();
     tm.mark("setup: colouring (wait)");
-    for (size_t l = h->lv.size(); l-- > 0;) {
-      build_level_layout(h.get(), l, smooth[l], s);
-      smooth[l] = Smoothing();
-    }
+    for (size_t l = h->lv.size(); l-- > 0;) build_level_layout(h.get(), l, smooth[l], s);
     tm.mark("setup: solve layout");
     if (prm.dense_tail_dofs > 0) {
       if (const size_t t = tail_start(h.get())) build_dense_tail(h.get(), t, s);
@@ -1398,6 +1427,11 @@ eamg_status eamg_setup(const eamg_problem *pb, const eamg_setup_params *params, 
     h->ring_d = static_cast<double *>(dev_h) + SC_COUNT + 1;
     hip_check(hipStreamSynchronize(s), "sync");
     tm.mark("setup: solve vectors");
+    // none on and below the dense tail's first level
+    for (size_t l = 0; l < h->lv.size(); ++l)
+      if (!smooth[l].stages.plan.cut.empty())
+        build_sweep_stages(ar, h->lv[l], smooth[l].stages, prm.vcycle_fp32 != 0, s);
+    tm.mark("setup: sweep groups");
     for (const auto &ph : phases) {
       auto it = std::find_if(h->setup_phases.begin(), h->setup_phases.end(),
                              [&](const std::pair<std::string, double> &q) { return q.first == ph.first; });
@@ -1949,7 +1983,7 @@ eamg_status eamg_setup_phases(const eamg_hierarchy *h, int32_t max_entries, eamg
     // where each phase runs: 0 host, 1 device, 2 host-to-device copies
     auto where = [](const std::string &name) {
       if (name.find("upload") != std::string::npos) return 2;
-      for (const char *d : {"Dirichlet", "numeric", "coarsest factor", "dense tail", "solve vectors"})
+      for (const char *d : {"Dirichlet", "numeric", "coarsest factor", "dense tail", "solve vectors", "sweep groups"})
         if (name.find(d) != std::string::npos) return 1;
       return 0;
     };

@@ -119,7 +119,8 @@ double *concat_device(DevArena &ar, const std::vector<std::pair<const double *, 
   return d;
 }
 
-void build_fused_level(eamg_hierarchy *F, const std::vector<eamg_hierarchy *> &hs,
+// Returns the level's sweep stages (build_sweep_stages).
+SweepStages build_fused_level(eamg_hierarchy *F, const std::vector<eamg_hierarchy *> &hs,
                        const std::vector<int> &depth, const std::vector<FusedOrder> &ord, int l,
                        hipStream_t s) {
   const int nsys = int(hs.size());
@@ -197,7 +198,6 @@ void build_fused_level(eamg_hierarchy *F, const std::vector<eamg_hierarchy *> &h
       L.Dinv32 = ar.alloc<float>(size_t(o.n_smooth) * bs * bs);
       hip_check(launch_convert(int64_t(o.n_smooth) * bs * bs, L.Dinv, L.Dinv32, s), "convert");
     }
-    build_sweep_stages(ar, L, sweeps.get(), f32, s);
     // transfers: P of the smoothed systems, rows in the fused order of level l, columns in the
     // fused order of level l + 1
     const FusedOrder &oc = ord[size_t(l) + 1];
@@ -338,6 +338,7 @@ void build_fused_level(eamg_hierarchy *F, const std::vector<eamg_hierarchy *> &h
     L.b32 = ar.alloc<float>(nv);
     L.x32 = ar.alloc<float>(nv);
   }
+  return sweeps.valid() ? sweeps.get() : SweepStages();
 }
 
 void check_params(const eamg_hierarchy *F, const eamg_solve_params &sp) {
@@ -508,7 +509,8 @@ eamg_status eamg_fuse(int32_t nsys, eamg_hierarchy *const *hs, int32_t dense_tai
           F->fused->own[size_t(m)] =
               make_dense_tail(H, size_t(d), F->arena, s);
       }
-    for (int l = 0; l < U; ++l) build_fused_level(F.get(), sys, F->fused->depth, ord, l, s);
+    std::vector<SweepStages> stages;
+    for (int l = 0; l < U; ++l) stages.push_back(build_fused_level(F.get(), sys, F->fused->depth, ord, l, s));
     // packed by now
     for (DenseTail &d : F->fused->own) {
       F->arena.release(d.T);
@@ -562,6 +564,9 @@ eamg_status eamg_fuse(int32_t nsys, eamg_hierarchy *const *hs, int32_t dense_tai
     hip_check(hipHostMalloc(reinterpret_cast<void **>(&F->scal_h), sizeof(double) * PS_COUNT * nsys,
                             hipHostMallocDefault),
               "hipHostMalloc");
+    for (int l = 0; l < U; ++l)
+      if (F->lv[size_t(l)].n_smooth > 0)
+        build_sweep_stages(F->arena, F->lv[size_t(l)], stages[size_t(l)], F->prm.vcycle_fp32 != 0, s);
     hip_check(hipStreamSynchronize(s), "sync");
     *out = F.release();
   });

@@ -65,6 +65,11 @@ struct DevArena {
       ptrs.erase(it);
     }
   }
+  // Take over the allocations of another arena.
+  void adopt(DevArena &o) {
+    ptrs.insert(ptrs.end(), o.ptrs.begin(), o.ptrs.end());
+    o.ptrs.clear();
+  }
   ~DevArena() {
     for (void *p : ptrs) (void)hipFree(p);
   }
@@ -264,7 +269,9 @@ LaunchShape matrix_shape(const Pattern &M);
 // Launch shapes of a smoothed level (colours, residual update over smooth_rows(), SpMV).
 void level_shapes(Level &L, const Pattern &Ap, const std::vector<int> &dg);
 // Sweep stages of a smoothed level whose matrix and D^+ are in place: the plan taken over, the group
-// matrices and u built.
+// matrices and u built in `ar`.  Called once everything else that a hierarchy needs is allocated: where
+// the memory does not hold the groups, every colour of the level stays a stage of its own.
+// EAMG_GROUP_MB sets the memory of a level's groups, in megabytes (for tests; 0: no groups).
 void build_sweep_stages(DevArena &ar, Level &L, const SweepStages &st, bool f32, hipStream_t s);
 // z = V(r) on level-0 vectors in the hierarchy's solve numbering (FP64, or the FP32 V-cycle
 // with conversions at the boundary).
