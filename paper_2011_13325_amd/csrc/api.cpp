@@ -1427,8 +1427,9 @@ eamg_status eamg_setup(const eamg_problem *pb, const eamg_setup_params *params, 
     h->ring_d = static_cast<double *>(dev_h) + SC_COUNT + 1;
     hip_check(hipStreamSynchronize(s), "sync");
     tm.mark("setup: solve vectors");
-    // none on and below the dense tail's first level
-    for (size_t l = 0; l < h->lv.size(); ++l)
+    // none on and below the dense tail's first level, nor on the coarsest (planned too where the coarsening
+    // stalled on it)
+    for (size_t l = 0; l + 1 < h->lv.size(); ++l)
       if (!smooth[l].stages.plan.cut.empty())
         build_sweep_stages(ar, h->lv[l], smooth[l].stages, prm.vcycle_fp32 != 0, s);
     tm.mark("setup: sweep groups");

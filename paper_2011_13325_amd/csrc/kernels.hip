@@ -1307,6 +1307,9 @@ hipError_t launch_group_fill(const GroupRank &fwd, const GroupRank &bwd, int lon
                              const double *val, const double *Dinv, hipStream_t s) {
   const int nrows = fwd.nrows > bwd.nrows ? fwd.nrows : bwd.nrows;
   if (nrows == 0 || longest == 0) return hipSuccess;
+  for (const GroupRank *g : {&fwd, &bwd})
+    if (!g->rows || !g->q0 || !g->q1 || !g->rp || !g->col || !g->val) return hipErrorInvalidValue;
+  if (!col || !val || !Dinv) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(nrows), static_cast<unsigned>(cdiv64(longest, kBlock)), 2);
   switch (bs) {
     case 1: hipLaunchKernelGGL(k_group_fill<1>, grid, dim3(kBlock), 0, s, fwd, bwd, col, val, Dinv); break;

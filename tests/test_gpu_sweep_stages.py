@@ -101,3 +101,16 @@ def test_setup_without_memory_for_groups_runs_colour_by_colour(name, monkeypatch
             assert float((x - x0).norm() / x0.norm()) <= tol
     for h in (f, f0, full, none, part):
         h.close()
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_coarsest_level_the_coarsening_stalled_on_has_no_sweeps(name, monkeypatch):
+    # a bound no level reaches: the last level was planned for sweeps before its matching found nothing
+    p = make_problem(**CASES[name])
+    h = _hierarchy(p, monkeypatch, coarsest_max_dofs=1)
+    ref = _hierarchy(p, monkeypatch, 0, coarsest_max_dofs=1)
+    levels = h.stats()["n_levels"]
+    assert sorted(_stages(p, h)[0]) == list(range(levels - 1))
+    _compare(p, h, ref)
+    h.close()
+    ref.close()
