@@ -355,12 +355,7 @@ namespace {
 void build_groups(DevArena &ar, Level &L, const SweepStages &st, bool f32, hipStream_t s) {
   const SweepPlan &pl = st.plan;
   const int ns = int(pl.cut.size()) - 1, bs = L.bs;
-  double left = HUGE_VAL;
-  if (const char *e = std::getenv("EAMG_GROUP_MB")) left = std::atof(e) * 1e6;
-  const auto room = [&](size_t bytes) {
-    left -= double(bytes);
-    if (left < 0.0) fail(EAMG_ERR_OOM, "sweep groups: out of device memory");
-  };
+  GroupRoom room;
   // Lanes per row of each group's S (S^T has the same blocks in the group's rows).  Blocks past the team
   // are a second dependent load, and a group's rows differ in length (its first colour has none, its
   // last the most), so rows of 3x3 and 6x6 blocks get a team for twice the average; of scalars the
@@ -385,7 +380,7 @@ void build_groups(DevArena &ar, Level &L, const SweepStages &st, bool f32, hipSt
     M.nnz = P.nnz();
     M.rp = ar.upload(to_i32(P.rp), s);
     M.col = ar.upload(P.col, s);
-    room(size_t(M.nnz) * bs * bs * sizeof(double));
+    room.take(size_t(M.nnz) * bs * bs * sizeof(double));
     M.val = v = ar.alloc<double>(size_t(M.nnz) * bs * bs);
     for (int i = 0; i < L.n; ++i) longest = std::max(longest, P.rp[size_t(i) + 1] - P.rp[size_t(i)]);
     return M;
@@ -406,7 +401,7 @@ void build_groups(DevArena &ar, Level &L, const SweepStages &st, bool f32, hipSt
   }
   if (f32)
     for (SolveMat *M : {&L.Sf, &L.Sb}) {
-      room(size_t(M->nnz) * bs * bs * sizeof(float));
+      room.take(size_t(M->nnz) * bs * bs * sizeof(float));
       float *v32 = ar.alloc<float>(size_t(M->nnz) * bs * bs);
       hip_check(launch_convert<double, float>(M->nnz * bs * bs, M->val, v32, s), "convert");
       M->val32 = v32;

@@ -26,7 +26,9 @@ struct BatchWork {
   // V-cycle panels per precision ([0] FP64, [1] FP32) and level: x, b, r
   bool have[2] = {false, false};
   std::vector<void *> vx[2], vb[2], vr[2];
-  std::vector<void *> vu[2];   // right-hand sides of grouped sweep stages (levels that have some)
+  // right-hand sides of grouped sweep stages: levels that have some, if the memory holds them (else their
+  // colours run one by one)
+  std::vector<void *> vu[2];
   hipStream_t cap = nullptr;
   hipGraphExec_t g[2] = {nullptr, nullptr};
   bool tried[2] = {false, false};
@@ -95,7 +97,17 @@ BatchWork *ensure_work(eamg_hierarchy *h, int K, bool f32) {
         w->vb[p][l] = w->arena.alloc<char>(n);
       }
       if (!coarsest) w->vr[p][l] = w->arena.alloc<char>(n);
-      if (h->lv[l].u) w->vu[p][l] = w->arena.alloc<char>(n);
+    }
+    for (size_t l = 0; l < nl; ++l) {
+      if (!h->lv[l].u) continue;
+      const size_t n = size_t(level_dofs(h->lv[l])) * K * vsz;
+      try {
+        GroupRoom().take(n);
+        w->vu[p][l] = w->arena.alloc<char>(n);
+      } catch (const Failure &e) {
+        if (e.code != EAMG_ERR_OOM) throw;
+        (void)hipGetLastError();
+      }
     }
     w->have[p] = true;
   }
@@ -107,13 +119,13 @@ T *vp(void *v) {
   return static_cast<T *>(v);
 }
 
-// Whether stage k of a panel sweep runs as a group.  A launch costs 4 to 7 us beyond its blocks (more
+// Whether stage k of a panel sweep runs as a group (u: the level's vu panel).  A launch costs 4 to 7 us beyond its blocks (more
 // with more columns), a block its values at 3 TB/s and its K columns of the gathered panel at 8 TB/s
 // (64^3, 32 columns, FP32: 10.5 and 22.8 us for colours of 42,000 and 146,000 blocks; 37x29x33, 8 columns,
 // FP64: 22 us for the 130,000 blocks of an S); the group saves its colours' launches but one or two
 // and adds the blocks of S, planned for a single vector.  64^3 x 32 FP32 82.7 -> 70.1 ms.
-bool panel_group(const Level &L, int k, bool fwd, int K, double vs) {
-  if (!L.is_group(k)) return false;
+bool panel_group(const Level &L, const void *u, int k, bool fwd, int K, double vs) {
+  if (!u || !L.is_group(k)) return false;
   const double launch = 4e-6 + 5e-8 * K;
   const double block = L.bs * L.bs * vs / 3e12 + L.bs * K * vs / 8e12;
   const double colours = L.cut[size_t(k) + 1] - L.cut[size_t(k)];
@@ -134,7 +146,7 @@ template <class T>
 hipError_t pfwd_stage(const Level &L, const SolveMat &A, const T *Dinv, int k, int K, const T *b, T *x, T *r,
                       T *u, hipStream_t s) {
   hipError_t e = hipSuccess;
-  if (panel_group(L, k, true, K, sizeof(T))) {
+  if (panel_group(L, u, k, true, K, sizeof(T))) {
     if (k > 0) {
       e = launch_pgroup_rhs<T>(A, L.lo_end, L.row0(k), L.row1(k), K, b, x, u, s);
       if (e != hipSuccess) return e;
@@ -149,7 +161,7 @@ template <class T>
 hipError_t pbwd_stage(const Level &L, const SolveMat &A, const T *Dinv, int k, int K, const T *b, T *x, T *u,
                       hipStream_t s) {
   hipError_t e = hipSuccess;
-  if (panel_group(L, k, false, K, sizeof(T))) {
+  if (panel_group(L, u, k, false, K, sizeof(T))) {
     e = launch_pgroup_rhs<T>(A, nullptr, L.row0(k), L.row1(k), K, b, x, u, s);
     if (e != hipSuccess) return e;
     return launch_pgroup_bwd<T>(panel_smat(L, k, false), Dinv, L.row0(k), L.row1(k), K, u, x, s);
@@ -183,7 +195,7 @@ void pvcycle_t(eamg_hierarchy *h, BatchWork *w, size_t l, const T *b, T *x, hipS
   const T *Dinv = bufs<T>(L).Dinv;
   T *R = vp<T>(w->vr[pi][l]), *U = vp<T>(w->vu[pi][l]);
   const auto run = [&](bool fwd, auto &&stage) {
-    const auto grouped = [&](int k) { return panel_group(L, k, fwd, K, vs); };
+    const auto grouped = [&](int k) { return panel_group(L, U, k, fwd, K, vs); };
     const auto launches = [&](int k) { return !grouped(k) ? L.cut[size_t(k) + 1] - L.cut[size_t(k)] : fwd && k == 0 ? 1 : 2; };
     sweep<T>(h, l, fwd, "k_pgs_color", K, false, grouped, launches, stage, s);
   };

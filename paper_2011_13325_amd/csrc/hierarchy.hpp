@@ -5,7 +5,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
+#include <cstdlib>
 #include <new>
 #include <string>
 #include <utility>
@@ -268,10 +270,21 @@ LaunchShape range_shape(const Pattern &Ap, const std::vector<int> &dg, int r0, i
 LaunchShape matrix_shape(const Pattern &M);
 // Launch shapes of a smoothed level (colours, residual update over smooth_rows(), SpMV).
 void level_shapes(Level &L, const Pattern &Ap, const std::vector<int> &dg);
+// Device memory that the sweep groups of a level may take: whatever is free, or EAMG_GROUP_MB megabytes
+// (for tests; 0: none).
+struct GroupRoom {
+  double left = HUGE_VAL;
+  GroupRoom() {
+    if (const char *e = std::getenv("EAMG_GROUP_MB")) left = std::atof(e) * 1e6;
+  }
+  void take(size_t bytes) {
+    left -= double(bytes);
+    if (left < 0.0) fail(EAMG_ERR_OOM, "sweep groups: out of device memory");
+  }
+};
 // Sweep stages of a smoothed level whose matrix and D^+ are in place: the plan taken over, the group
 // matrices and u built in `ar`.  Called once everything else that a hierarchy needs is allocated: where
 // the memory does not hold the groups, every colour of the level stays a stage of its own.
-// EAMG_GROUP_MB sets the memory of a level's groups, in megabytes (for tests; 0: no groups).
 void build_sweep_stages(DevArena &ar, Level &L, const SweepStages &st, bool f32, hipStream_t s);
 // z = V(r) on level-0 vectors in the hierarchy's solve numbering (FP64, or the FP32 V-cycle
 // with conversions at the boundary).

@@ -114,3 +114,29 @@ def test_coarsest_level_the_coarsening_stalled_on_has_no_sweeps(name, monkeypatc
     _compare(p, h, ref)
     h.close()
     ref.close()
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_panels_without_memory_for_groups_run_colour_by_colour(name, monkeypatch):
+    p = make_problem(**CASES[name])
+    h, ref = _hierarchy(p, monkeypatch), _hierarchy(p, monkeypatch)
+    B = _rhs(p, 5, 7)
+    for prec, tol in ((F64, 1e-11), (F32, 1e-5)):
+        kw = dict(rtol=0.0, max_it=2, precond=prec)
+        names = {}
+        for key, hier in (("groups", ref), ("none", h)):
+            if key == "none":
+                monkeypatch.setenv("EAMG_GROUP_MB", "0")
+            X = hier.solve_batch(B, **kw)[0]
+            monkeypatch.delenv("EAMG_GROUP_MB", raising=False)
+            E.eamg_profile_enable(hier.h, True)
+            assert torch.equal(hier.solve_batch(B, **kw)[0], X)
+            names[key] = [k["name"] for k in E.eamg_profile_read(hier.h)]
+            E.eamg_profile_enable(hier.h, False)
+            if key == "groups":
+                X0 = X
+        assert any(n.endswith(" grouped") for n in names["groups"]), names
+        assert not any(n.endswith(" grouped") for n in names["none"]), names
+        assert float(((X - X0).norm(dim=1) / X0.norm(dim=1)).max()) <= tol
+    h.close()
+    ref.close()
