@@ -539,18 +539,6 @@ __global__ __launch_bounds__(kThreads) void k_dense_panel_sum(int64_t nk, int S,
 // batches spill).
 constexpr int kSymCols = 16;
 
-// log2 of a run's tiles: about two thousand workgroups
-inline int sym_run_log2(int nb) {
-  int lr = 0;
-  while (lr < 3 && (sym_tiles(nb) >> (lr + 1)) >= 2048) ++lr;
-  return lr;
-}
-// Runs of block rows of m, m - 1, .., 1 tiles.
-__host__ __device__ inline int sym_runs(int m, int lr) {
-  const int R = 1 << lr, q = m >> lr;
-  return R * (q * (q + 1) / 2) + (m & (R - 1)) * (q + 1);
-}
-
 template <class T>
 __global__ __launch_bounds__(256, 2) void k_dense_panel_sym(int n, int nb, int lr, int K, int c0, int Kc,
                                                          const double *__restrict__ S,
@@ -559,17 +547,8 @@ __global__ __launch_bounds__(256, 2) void k_dense_panel_sym(int n, int nb, int l
   constexpr int kPad = kSymCols;   // columns held, zero past Kc
   constexpr int kBatch = 2;
   __shared__ double xi[kSymTile * kPad];
-  // block row and first tile of this run
-  const int all = sym_runs(nb, lr), run = int(blockIdx.x);
-  int i = 0;
-  for (int hi = nb - 1; i < hi;) {
-    const int mid = (i + hi + 1) >> 1;
-    if (all - sym_runs(nb - mid, lr) <= run)
-      i = mid;
-    else
-      hi = mid - 1;
-  }
-  const int j0 = i + ((run - (all - sym_runs(nb - i, lr))) << lr), j1 = min(nb, j0 + (1 << lr));
+  const SymRun at = sym_run(nb, lr, int(blockIdx.x));
+  const int i = at.i, j0 = at.j0, j1 = at.j1;
   for (int e = threadIdx.x; e < kSymTile * kPad; e += 256) {
     const int d = i * kSymTile + e / kPad, c = e % kPad;
     xi[e] = (d < n && c < Kc) ? double(X[size_t(d) * K + c0 + c]) : 0.0;
@@ -683,7 +662,7 @@ __global__ __launch_bounds__(256) void k_dense_panel_sym_sum(int n, int nb, int 
   const int d = on ? int(e / Kc) : 0, c = on ? int(e % Kc) : 0;
   const int b = d / kSymTile;
   const size_t at = size_t(d % kSymTile) * Kc + c, len = size_t(kSymTile) * Kc;
-  const int g0 = sym_runs(nb, lr) - sym_runs(nb - b, lr), runs = (nb - b + (1 << lr) - 1) >> lr;
+  const int g0 = sym_first_run(nb, lr, b), runs = sym_first_run(nb, lr, b + 1) - g0;
   const double v = sliced_sum<kPanelSumSlices>(on ? runs + b : 0, [&](int q) {
     if (q < runs) return P[size_t(g0 + q) * len + at];
     const size_t a = size_t(q - runs);

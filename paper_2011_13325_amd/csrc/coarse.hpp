@@ -55,6 +55,37 @@ constexpr int kSymTile = 128;
 inline int sym_blocks(int n) { return (n + kSymTile - 1) / kSymTile; }
 inline int64_t sym_tiles(int nb) { return int64_t(nb) * (nb + 1) / 2; }
 inline size_t sym_entries(int n) { return size_t(sym_tiles(sym_blocks(n))) * kSymTile * kSymTile; }
+// Runs of tiles, the workgroups of launch_dense_panel_sym: up to 1 << lr consecutive tiles of one block row
+// each, numbered row by row.
+// log2 of a run's tiles: about two thousand workgroups
+inline int sym_run_log2(int nb) {
+  int lr = 0;
+  while (lr < 3 && (sym_tiles(nb) >> (lr + 1)) >= 2048) ++lr;
+  return lr;
+}
+// Runs of block rows of m, m - 1, .., 1 tiles.
+__host__ __device__ inline int sym_runs(int m, int lr) {
+  const int R = 1 << lr, q = m >> lr;
+  return R * (q * (q + 1) / 2) + (m & (R - 1)) * (q + 1);
+}
+// The first run of block row b (b = nb: the number of runs).
+__host__ __device__ inline int sym_first_run(int nb, int lr, int b) { return sym_runs(nb, lr) - sym_runs(nb - b, lr); }
+// Run `run`: tiles (i, j0) .. (i, j1 - 1).
+struct SymRun {
+  int i, j0, j1;
+};
+__host__ __device__ inline SymRun sym_run(int nb, int lr, int run) {
+  int i = 0;
+  for (int hi = nb - 1; i < hi;) {
+    const int mid = (i + hi + 1) >> 1;
+    if (sym_first_run(nb, lr, mid) <= run)
+      i = mid;
+    else
+      hi = mid - 1;
+  }
+  const int j0 = i + ((run - sym_first_run(nb, lr, i)) << lr), j1 = j0 + (1 << lr);
+  return {i, j0, j1 < nb ? j1 : nb};
+}
 // Workspace of launch_dense_symv: nb * nb partial blocks of kSymTile doubles.
 inline size_t sym_work_doubles(int n) { return size_t(sym_blocks(n)) * sym_blocks(n) * kSymTile; }
 

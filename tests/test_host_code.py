@@ -91,3 +91,43 @@ int main() {
 
 def test_a_failed_allocation_in_a_parallel_loop_reaches_the_caller(tmp_path):
     _run(tmp_path, LOOP)
+
+
+RUNS = r"""
+#include "coarse.hpp"
+#include <cstdio>
+#include <vector>
+using namespace eamg;
+#define CHECK(c) do { if (!(c)) { std::printf("nb %d lr %d line %d: " #c "\n", nb, lr, __LINE__); return 1; } } while (0)
+int main() {
+  int seen_lr[4] = {0, 0, 0, 0};
+  for (int nb = 1; nb <= 128; ++nb) {   // a tail has up to 16,384 dofs
+    ++seen_lr[sym_run_log2(nb)];
+    for (int lr = 0; lr <= 3; ++lr) {
+      const int runs = sym_first_run(nb, lr, nb);
+      std::vector<int> owner(size_t(nb) * nb, -1);
+      int last_i = 0;
+      for (int run = 0; run < runs; ++run) {
+        const SymRun r = sym_run(nb, lr, run);
+        CHECK(r.i >= last_i && r.i < nb && r.j0 >= r.i && r.j1 > r.j0 && r.j1 <= nb && r.j1 - r.j0 <= 1 << lr);
+        CHECK(r.i == last_i || run == sym_first_run(nb, lr, r.i));
+        last_i = r.i;
+        for (int j = r.j0; j < r.j1; ++j) {
+          CHECK(owner[size_t(r.i) * nb + j] < 0);
+          owner[size_t(r.i) * nb + j] = run;
+        }
+        CHECK(r.j1 - r.j0 == 1 << lr || r.j1 == nb);
+      }
+      for (int i = 0; i < nb; ++i)
+        for (int j = 0; j < nb; ++j) CHECK((owner[size_t(i) * nb + j] >= 0) == (j >= i));
+    }
+  }
+  const int nb = 0, lr = 0;
+  CHECK(seen_lr[0] == 90 && seen_lr[1] == 37 && seen_lr[2] == 1);
+  return 0;
+}
+"""
+
+
+def test_runs_of_the_packed_panel_product_cover_every_tile_once(tmp_path):
+    _run(tmp_path, RUNS)
