@@ -491,6 +491,8 @@ DenseTail make_dense_tail(eamg_hierarchy *h, size_t t, DevArena &out, hipStream_
   const int ld = dense_ld(n);
   double *T = out.alloc<double>(size_t(ld) * ld);
   int K = std::min(ld, kWideCols);
+  // EAMG_WIDE_COLS: the columns of a pass, as if the memory held no more (for tests)
+  if (const char *e = std::getenv("EAMG_WIDE_COLS")) K = std::min(ld, std::max(2, (std::atoi(e) + 1) / 2 * 2));
   std::unique_ptr<DevArena> work;
   std::vector<WideLevel> w(h->lv.size());
   for (;; K = (K / 2 + 1) / 2 * 2) {
