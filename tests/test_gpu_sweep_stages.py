@@ -17,6 +17,15 @@ CASES = {
     "poisson": dict(n=33, ny=29, nz=31, kind="poisson", clamp="all"),
     "elasticity": dict(n=13, ny=12, nz=14, nu=0.3),
 }
+# layouts of the levels, by block size: one group, several groups, groups beside single colours
+LAYOUTS = {
+    "poisson": (CASES["poisson"], {(1, "one"), (1, "several")}),
+    "poisson_flat": (dict(n=64, ny=5, nz=3, kind="poisson"), {(1, "one")}),
+    "elasticity": (dict(n=24, ny=19, nz=21, nu=0.3), {(3, "one"), (6, "one"), (6, "several")}),
+    "elasticity_beside": (dict(n=30, ny=29, nz=31, nu=0.3), {(3, "beside"), (6, "one"), (6, "several")}),
+    # singular (pseudo-inverted) diagonal blocks
+    "inclusions": (dict(n=16, inclusions=5, geometry_seed=3), {(3, "one"), (6, "one"), (6, "several")}),
+}
 STAGE = re.compile(r"L(\d+) c(\d+)(?:-(\d+))? k_gs_color<double, (\d), true>( grouped)?$")
 F64, F32 = E.EAMG_PRECOND_VCYCLE, E.EAMG_PRECOND_VCYCLE_FP32
 
@@ -67,6 +76,42 @@ def _compare(p, h, ref, seed=5, rhs=9):
         errs.append(float((z - z0).norm() / z0.norm()))
         print(f"    {errs}", flush=True)
         assert max(errs) <= tol, (prec, errs)
+
+
+def _layouts(stages, bs):
+    out = set()
+    for l, v in stages.items():
+        groups = sum(c1 > c0 for c0, c1 in v)
+        if groups:
+            out.add((bs[l], "one" if len(v) == 1 else "several" if groups == len(v) else "beside"))
+    return out
+
+
+@pytest.mark.parametrize("name", list(LAYOUTS))
+def test_groups_equal_single_colours(name, monkeypatch):
+    mesh, want = LAYOUTS[name]
+    p = make_problem(**mesh)
+    h, ref = (_hierarchy(p, monkeypatch, mb, coarsest_max_dofs=60) for mb in (None, 0))
+    stages, bs = _stages(p, h)
+    print(f"\n[{name}] {stages}", flush=True)
+    assert want <= _layouts(stages, bs) and not _groups(_stages(p, ref)[0])
+    _compare(p, h, ref)
+    h.close()
+    ref.close()
+
+
+@pytest.mark.parametrize("group", [8, 16, 32, 64, 128, 256])
+@pytest.mark.parametrize("name", ["poisson", "elasticity"])
+def test_groups_with_every_row_team_equal_single_colours(name, group, monkeypatch):
+    p = make_problem(**LAYOUTS[name][0])
+    h, ref = (_hierarchy(p, monkeypatch, mb) for mb in (None, 0))
+    monkeypatch.setenv("EAMG_FORCE_GROUP", str(group))
+    E.eamg_autotune(h.h, 0)
+    monkeypatch.delenv("EAMG_FORCE_GROUP")
+    assert _groups(_stages(p, h)[0])
+    _compare(p, h, ref)
+    h.close()
+    ref.close()
 
 
 @pytest.mark.parametrize("name", list(CASES))
