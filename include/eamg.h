@@ -101,6 +101,12 @@ typedef struct {
  *  vcycle_fp32        0: FP64 V-cycle only (default).  1: also keep FP32 copies of the V-cycle
  *                     matrices (A_l, P_s, R, D^+) and FP32 level vectors, so that solves and
  *                     V-cycles may ask for EAMG_PRECOND_VCYCLE_FP32 (about +50% V-cycle memory).
+ *                     Either way the sweeps of levels with few rows per colour run groups of
+ *                     colours, whose matrices (forward and backward, FP64 and with vcycle_fp32
+ *                     FP32) take memory of their own: a 128^3 elasticity hierarchy 1.16 of 79 GB
+ *                     with both precisions and a dense tail, 64^3 0.73 of 10.3 GB, a scalar 90^3
+ *                     one without a tail 0.27 of 2.1 GB.  They are built last; a level whose
+ *                     groups do not fit in the device's memory runs its colours one by one.
  *  gnn, gnn_skip      learned walk (NULL / 0: the exact walk, default).  With a network (see
  *                     eamg_gnn_*) and gnn_skip in (0, 1): in every matching pass the candidate
  *                     pairs are scored once on the GPU; the walk passes over candidates whose
@@ -117,9 +123,8 @@ typedef struct {
  *                     example (figures fig:2dc_rob / fig:2dc_norob); for comparisons only.
  *  gpu_criteria       1: the matching walks hand the pairs whose criteria they need to GPU
  *                     kernels in batches (mu_b per pair, mu_g per union of up to four vertices;
- *                     bit-identical to the host code, so the same hierarchy; default); batches
- *                     too small to gain from a launch (under 4096 pairs, 128 unions) stay on host
- *                     threads.  2: every batch on the GPU.  0: host threads only.
+ *                     bit-identical to the host code, so the same hierarchy; default); small
+ *                     batches (under 4096 pairs, 128 unions) stay on host threads.  2: every batch on the GPU.  0: host threads only.
  *  dense_tail_dofs    0: every level below the finest runs its own sweeps, residual and
  *                     transfers in the V-cycle (default).  > 0 (at most 16384): the V-cycle on
  *                     the first level l >= 1 with bs_l * n_l <= dense_tail_dofs and on every level

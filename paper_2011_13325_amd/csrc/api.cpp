@@ -1159,8 +1159,8 @@ struct MultiStreams {
 
 }  // namespace
 
-void vcycle_apply(eamg_hierarchy *h, const double *r, double *z, bool f32, hipStream_t s) {
-  vcycle(h, r, z, f32, s);
+void vcycle_apply(eamg_hierarchy *h, const double *r, double *z, hipStream_t s) {
+  vcycle(h, r, z, false, s);
 }
 
 void vcycle_apply32(eamg_hierarchy *h, hipStream_t s) {

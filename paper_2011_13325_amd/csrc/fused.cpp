@@ -358,7 +358,7 @@ void fused_precondition(eamg_hierarchy *F, int precond, hipStream_t s) {
   else if (precond == EAMG_PRECOND_VCYCLE_FP32)
     vcycle_apply32(F, s);
   else
-    vcycle_apply(F, F->r, F->z, false, s);
+    vcycle_apply(F, F->r, F->z, s);
 }
 
 // part <- r.z

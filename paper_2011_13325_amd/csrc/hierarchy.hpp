@@ -286,9 +286,8 @@ struct GroupRoom {
 // matrices and u built in `ar`.  Called once everything else that a hierarchy needs is allocated: where
 // the memory does not hold the groups, every colour of the level stays a stage of its own.
 void build_sweep_stages(DevArena &ar, Level &L, const SweepStages &st, bool f32, hipStream_t s);
-// z = V(r) on level-0 vectors in the hierarchy's solve numbering (FP64, or the FP32 V-cycle
-// with conversions at the boundary).
-void vcycle_apply(eamg_hierarchy *h, const double *r, double *z, bool f32, hipStream_t s);
+// z = V(r) on level-0 vectors in the hierarchy's solve numbering, the FP64 V-cycle.
+void vcycle_apply(eamg_hierarchy *h, const double *r, double *z, hipStream_t s);
 // The FP32 V-cycle on level 0's own FP32 vectors: x32 = V(b32).
 void vcycle_apply32(eamg_hierarchy *h, hipStream_t s);
 // Panel launch shapes tuned on the hierarchy for K columns; (time before, after) in ms.

@@ -607,7 +607,7 @@ __global__ __launch_bounds__(kBlock) void k_group_rhs(int r0, int r1, int G, con
   resid_row<T, B, W>(row, row < r1, lane, G, rp, re, col, val, nnz, x, b, u, sh);
 }
 
-//
+// The second launch: t = u - S u, x and (forward) r; u = launch_group_rhs's, or b for the first group.
 // rz (backward): the workgroup's part of the CG's r.z over its rows, z the new x, in rz[workgroup]
 // (the sweep's last launch, of a level that is one group).
 template <class T, int B, bool FWD, int W, bool RZ>
